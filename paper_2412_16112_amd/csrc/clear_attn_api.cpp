@@ -179,6 +179,31 @@ static void choose_text_splits(long long N, int BH, int n_tq_tiles, int num_cus,
     *n_splits = (int)((N + keys - 1) / keys);
 }
 
+// Launch shape of the fp32 kernel.  A workgroup is four waves of 16 queries, all on one 8 x 8 patch of queries (64 text
+// queries); with `groups` = 2 or 4 waves on every 16 queries a patch of 4 x 8 or 4 x 4 (32 or 16 text queries) walks its
+// keys in a half or a quarter of the steps, at two or four times the staging traffic per pair.  So: as many waves per
+// patch as it takes to have two workgroups for every CU.  Text-query
+// rows: key ranges of 1 024 and more, about the length of an image query's walk, so that no text workgroup is the
+// last one running by far; shorter ones, down to 256, where that leaves CUs without work.
+static void choose_f32_shape(long long NV, int BH, int num_cus, FwdParams* p)
+{
+    const long long image = (long long)BH * p->n_q_tiles_launch * 4;
+    auto text_units = [&](int groups) { return (long long)BH * ((p->n_text * groups + 63) / 64); };
+    p->f32_groups = 1;
+    while (p->f32_groups < 4 && image * p->f32_groups + text_units(p->f32_groups) < 2LL * num_cus) p->f32_groups *= 2;
+    const int groups = p->f32_groups;
+    p->n_tq_tiles = (p->n_text * groups + 63) / 64;
+    if (p->n_text == 0) return;
+    long long splits = NV / 1024;
+    const long long idle = 2LL * num_cus - image * groups;
+    if (idle > 0) splits = std::max(splits, std::min(NV / (256 * groups), idle / text_units(groups)));
+    splits = std::max(1LL, std::min<long long>(splits, max_text_splits(NV)));
+    long long keys = (NV + splits - 1) / splits;
+    keys = ((keys + kKeyTileKeys - 1) / kKeyTileKeys) * kKeyTileKeys;
+    p->split_keys = (int)keys;
+    p->n_splits = (int)((NV + keys - 1) / keys);
+}
+
 // Builds the tile lists of a gridH x gridW raster for the kernels of (head_dim, dtype, mask) and copies them to the
 // current device.  Returns CLEAR_OK, or an error code with *why set (the caller releases `t`).
 static int build_tile_tables(int gridH, int gridW, int head_dim, int r, int dtype, int mask_kind, int shift, TileTables* t, std::string* why)
@@ -517,7 +542,7 @@ int clear_attn_reserve(clear_attn_ctx* ctx, int BH)
 static bool launches_together(const clear_attn_ctx* ctx, const FwdParams& p)
 {
     const long long image_wgs = (long long)p.B * p.H * p.n_classes * p.n_q_tiles_launch;
-    return ctx->dtype == CLEAR_BF16 && p.n_text > 0 && image_wgs <= 64LL * ctx->num_cus;
+    return ctx->dtype == CLEAR_F32 || (p.n_text > 0 && image_wgs <= 64LL * ctx->num_cus);
 }
 
 // Tile lists of the context's grid moved down by y_shift rows (row bands; see prepare_forward), built on first use.
@@ -668,10 +693,13 @@ static int prepare_forward(clear_attn_ctx* ctx, const void* Q, const void* K, co
         p.band_o = band->text_o;
         p.band_lse = band->text_lse;
     }
+    if (ctx->dtype == CLEAR_F32) choose_f32_shape(p.NV, BH, ctx->num_cus, &p);
     if (n_text > 0) {
-        const int per_block = ctx->dtype == CLEAR_BF16 ? bf16_text_queries_per_block() : f32_text_queries_per_block();
-        p.n_tq_tiles = (n_text + per_block - 1) / per_block;
-        choose_text_splits(p.NV, BH, p.n_tq_tiles, ctx->num_cus, launches_together(ctx, p), &p.n_splits, &p.split_keys);
+        if (ctx->dtype == CLEAR_BF16) {
+            const int per_block = bf16_text_queries_per_block();
+            p.n_tq_tiles = (n_text + per_block - 1) / per_block;
+            choose_text_splits(p.NV, BH, p.n_tq_tiles, ctx->num_cus, launches_together(ctx, p), &p.n_splits, &p.split_keys);
+        }
         if (noalloc) {
             // partial outputs, then (maximum, denominator) pairs, both inside the static scratch array
             const size_t rows = (size_t)BH * p.n_splits * n_text;

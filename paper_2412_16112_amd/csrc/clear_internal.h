@@ -20,7 +20,7 @@ constexpr int kBf16NWY = CLEAR_NWY, kBf16NWX = 2;    // workgroup = (4 NWY) x 16
 constexpr int kBf16QTileH = kBf16NWY * kWaveQH, kBf16QTileW = kBf16NWX * kWaveQW;
 constexpr int kTextQueriesPerWave = 32;
 
-// fp32 accuracy path: one thread per query, 16 x 16 queries per workgroup, same key tiles.
+// fp32 path: 16 x 16 query tiles in the schedule (the workgroups take parts of them), same key tiles.
 constexpr int kF32QTileH = 16, kF32QTileW = 16;
 
 struct Schedule {
@@ -43,7 +43,7 @@ unsigned long long mask_count(int n_text, int gridH, int gridW, int r, int mask_
 unsigned long long executed_pairs_bf16(const Schedule& s, int n_text, int text_split_keys);
 // The same for a strided context (s: the schedule of the class sub-grid; gridH, gridW: the real grid).
 unsigned long long executed_pairs_bf16_strided(const Schedule& s, int n_text, int gridH, int gridW, int stride, int layer);
-// Pairs visited by the fp32 path (it tests every slot of every staged tile).
+// Pairs the fp32 path multiplies: 4 x 4 query patches against the cells of 16 keys they reach.
 unsigned long long executed_pairs_f32(const Schedule& s, int n_text);
 
 // Where element (b, h, n, c) of a [B, H, N, head_dim] tensor lives: base + b * sb + h * sh + n * sn + c (in
@@ -101,6 +101,7 @@ struct FwdParams {
     const float* rope_y;  // [gridH][head_dim/2][2] (cos, sin) per row, or null: no rotation
     const float* rope_x;  // [gridW][head_dim/2][2] (cos, sin) per column
     float norm_eps;
+    int f32_groups;  // fp32 kernel: waves per 16-query patch (1, 2 or 4 of a workgroup's 4)
 };
 
 // Launchers (kernels_bf16.hip, kernels_f32.hip).  Each returns the first HIP error met.

@@ -1,215 +1,367 @@
-// fp32 accuracy path of the CLEAR local-attention forward pass (head_dim 64): plain vector-ALU
-// arithmetic, one thread per query, exact online softmax (Eq. 1) over the keys the mask of Eq. 3
-// admits.  It walks the same tile schedule as the MFMA path (text keys, then the listed 8 x 8 image
-// key tiles), stages each 64-key tile in LDS, and tests every (query, key) pair against the mask.
-// Text-query rows run the same loop over a contiguous key range, split along the keys and merged.
+// fp32 path of the CLEAR local-attention forward pass (head_dim 64): fp32 matrix instructions (products and sums in
+// fp32), exact online softmax (Eq. 1) over the keys the mask of Eq. 3 admits, on the tile schedule of the bf16 path.
+//
+// As in the bf16 kernels everything is computed transposed, so that a lane owns one query: S^T = K Q^T and O^T += V^T P^T
+// on v_mfma_f32_16x16x4_f32.  A wave owns a 4 x 4 patch of queries (or 16 text queries), four lanes per query, and
+// takes the keys in cells of 16 (4 x 4 image tokens, or 16 consecutive ones), of which it skips those out of its
+// reach: 16 rather than 32 on a side because this path is bound by the fp32 matrix rate (1/16 of the bf16 one, so
+// that operand reads from LDS and the vector work of the softmax hide behind it), and the smaller the patch and the
+// cell, the fewer masked pairs are multiplied (r = 16: 1 150 keys per query for 793 admitted ones, 1 440 with 32).
+//
+// A workgroup is four waves and walks the text keys, then the image tiles of its schedule row that its own
+// queries reach, staged in LDS half a tile at a time and double-buffered.  The waves hold 4, 2 or 1 patches (`groups` = 1,
+// 2, 4 waves per patch): with several waves per patch each takes a share of every tile's cells and the partial softmax sums are joined
+// in LDS at the end, which gives small problems as many workgroups as the chip has CUs and shorter key walks.
+// A 38-head 64 x 64 grid with 333 text tokens, r = 16: 2.98 -> 0.71 ms
+// (74 TFLOP/s of admitted pairs, 110 where nothing is masked; a large fp32 matrix product reaches 154); one head of 16 x 16
+// tokens with 8 text tokens 0.43 ms -> 12 us.  (Before: vector arithmetic, a thread per query, the whole list of every
+// 16 x 16 tile.  A single 32 KB stage per workgroup: 0.73 ms; two whole-tile stages, two workgroups per CU: 1.17 ms.)
 #include <hip/hip_runtime.h>
 
+#include <cfloat>
+
+#include "bf16_common.h"
 #include "block_class.h"
 #include "clear_internal.h"
 
 namespace clear {
 namespace {
 
-constexpr int D = 64;
-constexpr int TILE_KEYS = kKeyTileKeys;
-constexpr int NT = kF32QTileH * kF32QTileW;  // 256 threads, one query each
+constexpr int HD = 64;                     // head_dim
+constexpr int kWaves = 4;
+constexpr int kCell = 16;  // keys per cell, queries per wave
 
-template <bool TEXTQ>
-__global__ void __launch_bounds__(NT) clear_fwd_f32_kernel(const FwdParams p)
+// LDS rows are 256 bytes, one sweep over the banks, 16-byte chunks permuted: logical chunk c of row k sits in slot
+// c ^ (k & 15).  The 16 rows of a K read (one chunk each) and the 4 rows x 64 bytes of a V read then use all banks once.
+__device__ __forceinline__ int f32_swz(int row) { return row & 15; }
+
+// 16 bytes per lane from global memory into LDS at lds_addr + 16 * lane (see load_to_lds_16B; 64-bit addresses, as a head
+// of an fp32 context may exceed 4 GB).
+__device__ __forceinline__ void load_to_lds_16B_far(const void* src, unsigned lds_addr)
 {
-    __shared__ float4 ldsK[TILE_KEYS * D / 4];
-    __shared__ float4 ldsV[TILE_KEYS * D / 4];
-
-    const int tid = threadIdx.x;
-    int bh, qt, split = 0;
-    {
-        const int vid = blockIdx.x;
-        if (TEXTQ) {
-            split = vid % p.n_splits;
-            const int t = vid / p.n_splits;
-            qt = t % p.n_tq_tiles;
-            bh = t / p.n_tq_tiles;
-        } else {
-            qt = p.qt_begin + vid % p.n_q_tiles_launch;
-            bh = vid / p.n_q_tiles_launch;
-        }
-    }
-    const long long head_off = (long long)bh * p.N * D;
-    const float* const Qh = (const float*)p.Q + head_off;
-    const float4* const Kh = (const float4*)((const float*)p.K + head_off);
-    const float4* const Vh = (const float4*)((const float*)p.V + head_off);
-
-    int qy = 0, qx = 0;
-    long long q_token;
-    bool q_valid;
-    if (TEXTQ) {
-        q_token = (long long)qt * NT + tid;
-        q_valid = q_token < p.n_text;
-        if (!q_valid) q_token = p.n_text - 1;
-    } else {
-        qy = (qt / p.n_qtx) * kF32QTileH + tid / kF32QTileW;
-        qx = (qt % p.n_qtx) * kF32QTileW + tid % kF32QTileW;
-        q_valid = qy < p.gridH && qx < p.gridW && qy >= p.own_y0 && qy < p.own_y1;  // (row-band mode: owned rows only)
-        q_token = (long long)p.n_text + (long long)imin(qy, p.gridH - 1) * p.gridW + imin(qx, p.gridW - 1);
-    }
-
-    float q[D], o[D];
-#pragma unroll
-    for (int c4 = 0; c4 < D / 4; ++c4) {
-        const float4 v = *(const float4*)(Qh + q_token * D + 4 * c4);
-        q[4 * c4] = v.x; q[4 * c4 + 1] = v.y; q[4 * c4 + 2] = v.z; q[4 * c4 + 3] = v.w;
-    }
-#pragma unroll
-    for (int c = 0; c < D; ++c) o[c] = 0.f;
-    float m = -INFINITY, l = 0.f;
-    const float sc = p.scale_log2e;
-
-    int n_stages, n_lin_stages, csr_begin = 0;
-    long long lin_begin = 0, lin_limit = 0;
-    if (TEXTQ) {
-        lin_begin = (long long)split * p.split_keys;
-        lin_limit = lin_begin + p.split_keys < p.NV ? lin_begin + p.split_keys : p.NV;
-        n_lin_stages = (int)((lin_limit - lin_begin + TILE_KEYS - 1) / TILE_KEYS);
-        n_stages = n_lin_stages;
-    } else {
-        lin_limit = p.n_text;
-        n_lin_stages = (p.n_text + TILE_KEYS - 1) / TILE_KEYS;
-        csr_begin = p.row_ptr[qt];
-        n_stages = n_lin_stages + (p.row_ptr[qt + 1] - csr_begin);
-    }
-
-    for (int st = 0; st < n_stages; ++st) {
-        const bool linear = st < n_lin_stages;
-        long long a, b;  // linear: first token, limit; image: tile origin (row, col)
-        if (linear) {
-            a = lin_begin + (long long)st * TILE_KEYS;
-            b = lin_limit;
-        } else {
-            const int packed = p.col_idx[csr_begin + st - n_lin_stages];  // tile origin, row << 16 | col
-            a = packed >> 16;
-            b = packed & 0xffff;
-        }
-        __syncthreads();  // previous tile fully consumed
-        for (int ch = tid; ch < TILE_KEYS * D / 4; ch += NT) {
-            const int slot = ch / (D / 4), cc = ch % (D / 4);
-            long long token;
-            if (linear) {
-                token = a + slot;
-                if (token > b - 1) token = b - 1;
-                if (TEXTQ && token >= p.vkeys_text) token += p.vshift;  // position in the key list -> token
-            } else {
-                const int ky = imin((int)a + slot / kKeyTileW, p.gridH - 1);
-                const int kx = imin((int)b + slot % kKeyTileW, p.gridW - 1);
-                token = (long long)p.n_text + (long long)ky * p.gridW + kx;
-            }
-            ldsK[ch] = Kh[token * (D / 4) + cc];
-            ldsV[ch] = Vh[token * (D / 4) + cc];
-        }
-        __syncthreads();
-
-        for (int slot = 0; slot < TILE_KEYS; ++slot) {
-            bool ok;
-            if (linear) {
-                ok = a + slot < b;
-            } else {
-                const int ky = (int)a + slot / kKeyTileW, kx = (int)b + slot % kKeyTileW;
-                const int dy = ky - qy, dx = kx - qx;
-                const MaskSpec spec = {p.mask_kind, p.mask_r, p.mask_shift};
-                ok = !TEXTQ && ky < p.gridH && kx < p.gridW && (p.mask_kind == kMaskDisc ? dx * dx + dy * dy < p.r2 : mask_admits(spec, qy, qx, ky, kx));
-            }
-            if (!ok) continue;
-            float s = 0.f;
-#pragma unroll
-            for (int c4 = 0; c4 < D / 4; ++c4) {
-                const float4 kv = ldsK[slot * (D / 4) + c4];  // same address in every lane: LDS broadcast
-                s = __builtin_fmaf(q[4 * c4], kv.x, s);
-                s = __builtin_fmaf(q[4 * c4 + 1], kv.y, s);
-                s = __builtin_fmaf(q[4 * c4 + 2], kv.z, s);
-                s = __builtin_fmaf(q[4 * c4 + 3], kv.w, s);
-            }
-            if (s > m) {  // re-base on the new maximum
-                const float alpha = exp2f((m - s) * sc);
-                l *= alpha;
-#pragma unroll
-                for (int c = 0; c < D; ++c) o[c] *= alpha;
-                m = s;
-            }
-            const float pr = exp2f((s - m) * sc);
-            l += pr;
-#pragma unroll
-            for (int c4 = 0; c4 < D / 4; ++c4) {
-                const float4 vv = ldsV[slot * (D / 4) + c4];
-                o[4 * c4] = __builtin_fmaf(pr, vv.x, o[4 * c4]);
-                o[4 * c4 + 1] = __builtin_fmaf(pr, vv.y, o[4 * c4 + 1]);
-                o[4 * c4 + 2] = __builtin_fmaf(pr, vv.z, o[4 * c4 + 2]);
-                o[4 * c4 + 3] = __builtin_fmaf(pr, vv.w, o[4 * c4 + 3]);
-            }
-        }
-    }
-
-    if (!q_valid) return;
-    if (TEXTQ) {
-        const long long row = ((long long)bh * p.n_splits + split) * p.n_text + q_token;
-        float* wo = p.ws_o + row * D;
-#pragma unroll
-        for (int c4 = 0; c4 < D / 4; ++c4) *(float4*)(wo + 4 * c4) = make_float4(o[4 * c4], o[4 * c4 + 1], o[4 * c4 + 2], o[4 * c4 + 3]);
-        p.ws_ml[row * 2] = m;
-        p.ws_ml[row * 2 + 1] = l;
-    } else {
-        const float inv = 1.0f / l;
-        if (p.lse) p.lse[(long long)bh * p.N + q_token] = logf(l) + m * p.scale_log2e * 0.6931471805599453f;
-        float* orow = (float*)p.O + head_off + q_token * D;
-#pragma unroll
-        for (int c4 = 0; c4 < D / 4; ++c4)
-            *(float4*)(orow + 4 * c4) = make_float4(o[4 * c4] * inv, o[4 * c4 + 1] * inv, o[4 * c4 + 2] * inv, o[4 * c4 + 3] * inv);
-    }
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(src) : "memory", "m0");
 }
 
-// Log-sum-exp combination of the key-split partial results of the text-query rows.
-__global__ void __launch_bounds__(D) clear_text_merge_f32_kernel(const FwdParams p)
+// max / sum over the four lanes that share a query (lanes l, l ^ 16, l ^ 32, l ^ 48)
+__device__ __forceinline__ float quad_max(float x)
 {
-    const int row = blockIdx.x;
-    const int bh = row / p.n_text, q = row % p.n_text;
-    const int ch = threadIdx.x;
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return wave_pair_max(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
+}
+__device__ __forceinline__ float quad_sum(float x)
+{
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return wave_pair_sum(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+}
+
+typedef __attribute__((address_space(3))) const f32x4* lds_f32x4_ptr;
+typedef __attribute__((address_space(3))) const float* lds_f32_ptr;
+
+// DISC: the mask of Eq. 3 (its element test is a few instructions); otherwise whichever mask p.mask_kind names.
+// CELLS: key cells per stage; half a tile (2, 32 KB of LDS for two stages: five workgroups per CU) unless four waves share a patch.
+template <bool DISC, int CELLS>
+__global__ void __launch_bounds__(kWaves * 64, CELLS == 2 ? 5 : 2) clear_fwd_f32_kernel(const FwdParams p, const int n_image)
+{
+    constexpr int STAGE_KEYS = CELLS * kCell, HALF_BYTES = STAGE_KEYS * HD * 4;
+    constexpr int PARTS = TILE_KEYS / STAGE_KEYS, PART_H = kKeyTileH / PARTS;  // stages per key tile; rows of an image tile in one
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * 2 * HALF_BYTES];  // [stage buffer][K | V]
+    const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
+    const int lane = threadIdx.x & 63, qi = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int groups = p.f32_groups, patches = kWaves / groups;
+    const int patch = wave / groups, group = wave % groups;
+
+    // ---- workgroup -> (batch*head, query tile); image-query workgroups first, each XCD a contiguous range of either kind
+    const bool textq = (int)blockIdx.x >= n_image;
+    int vid;
+    {
+        const int bid = textq ? (int)blockIdx.x - n_image : (int)blockIdx.x, nblk = textq ? (int)gridDim.x - n_image : n_image;
+        const int xcd = bid & 7, idx = bid >> 3, q = nblk >> 3, rem = nblk & 7;
+        vid = xcd * q + imin(xcd, rem) + idx;
+    }
+    int bh, qt = 0, split = 0;
+    int ty0 = 0, tx0 = 0, th = 0, tw = 0;  // image: the rectangle of queries of this workgroup
+    int qy = 0, qx = 0, wy0 = 0, wx0 = 0;
+    long long q_token;
+    bool q_valid, wave_has_queries;
+    if (textq) {
+        split = vid % p.n_splits;
+        const int t = vid / p.n_splits;
+        bh = t / p.n_tq_tiles;
+        const int q0 = (t % p.n_tq_tiles) * (patches * kCell) + patch * kCell;
+        q_token = q0 + qi;
+        q_valid = q_token < p.n_text;
+        wave_has_queries = q0 < p.n_text;
+        if (!q_valid) q_token = p.n_text - 1;
+    } else {
+        // 16 x 16 query tiles of the schedule, cut into 8 x 8, 4 x 8 or 4 x 4 ones
+        th = groups == 1 ? 8 : 4;
+        tw = groups == 4 ? 4 : 8;
+        const int sx = kF32QTileW / tw, subs = (kF32QTileH / th) * sx;
+        const int sub = vid % subs, t = vid / subs;
+        qt = p.qt_begin + t % p.n_q_tiles_launch;
+        bh = t / p.n_q_tiles_launch;
+        ty0 = (qt / p.n_qtx) * kF32QTileH + (sub / sx) * th;
+        tx0 = (qt % p.n_qtx) * kF32QTileW + (sub % sx) * tw;
+        if (ty0 >= p.gridH || tx0 >= p.gridW || ty0 >= p.own_y1 || ty0 + th <= p.own_y0) return;  // no query here
+        wy0 = ty0 + 4 * (patch >> 1);
+        wx0 = tx0 + 4 * (patch & 1);
+        qy = wy0 + (qi >> 2);
+        qx = wx0 + (qi & 3);
+        q_valid = qy < p.gridH && qx < p.gridW && qy >= p.own_y0 && qy < p.own_y1;  // (row-band mode: owned rows only)
+        wave_has_queries = wy0 < p.gridH && wx0 < p.gridW;
+        q_token = (long long)p.n_text + (long long)imin(qy, p.gridH - 1) * p.gridW + imin(qx, p.gridW - 1);
+    }
+    const long long head_off = (long long)bh * p.N * HD;
+    const float* const Kh = (const float*)p.K + head_off;
+    const float* const Vh = (const float*)p.V + head_off;
+
+    // ---- stage list: the key range in stages of STAGE_KEYS tokens, then (image) the parts of the schedule row's tiles that
+    // this workgroup reaches
+    int n_lin, n_stages, csr_begin = 0;
+    long long lin_begin = 0, lin_limit;
+    const const_int_ptr row_ptr = (const_int_ptr)p.row_ptr, col_idx = (const_int_ptr)p.col_idx;
+    if (textq) {
+        lin_begin = (long long)split * p.split_keys;
+        lin_limit = lin_begin + p.split_keys < p.NV ? lin_begin + p.split_keys : p.NV;
+        n_stages = n_lin = (int)((lin_limit - lin_begin + STAGE_KEYS - 1) / STAGE_KEYS);
+    } else {
+        lin_limit = p.n_text;
+        n_lin = (p.n_text + STAGE_KEYS - 1) / STAGE_KEYS;
+        csr_begin = row_ptr[qt];
+        n_stages = n_lin + (row_ptr[qt + 1] - csr_begin) * PARTS;
+    }
+    const MaskSpec spec = {DISC ? (int)kMaskDisc : p.mask_kind, p.mask_r, p.mask_shift};
+    struct Stage {
+        int i;     // index in the list; n_stages: the end
+        int a, b;  // image: origin (row, col)
+    };
+    auto next_stage = [&](int i) {  // the first stage at or after i that holds a key for this workgroup
+        Stage t = {i, 0, 0};
+        for (; t.i < n_stages; ++t.i) {
+            if (t.i < n_lin) break;
+            const int e = t.i - n_lin, packed = col_idx[csr_begin + e / PARTS];
+            t.a = (packed >> 16) + PART_H * (e % PARTS);
+            t.b = packed & 0xffff;
+            if (classify_image_block_spec(spec, ty0, tx0, th, tw, t.a, t.b, PART_H, kKeyTileW, p.gridH, p.gridW) != kBlockSkip) break;
+        }
+        return t;
+    };
+    // LDS row 16 c + i of a stage is key i of cell c: linear stages in token order, image stages as rows of two 4 x 4 cells
+    auto issue_stage = [&](const Stage& t, int buf) {
+        const unsigned dst = lds_base + (unsigned)buf * (2 * HALF_BYTES);
+#pragma unroll
+        for (int n = 0; n < STAGE_KEYS / 4 / kWaves; ++n) {
+            const int ii = wave * (STAGE_KEYS / 4 / kWaves) + n;  // 1 KB = 4 rows per load instruction
+            const int row = 4 * ii + g;
+            long long token;
+            if (t.i < n_lin) {
+                token = lin_begin + (long long)t.i * STAGE_KEYS + row;
+                token = token < lin_limit ? token : lin_limit - 1;
+                if (textq && token >= p.vkeys_text) token += p.vshift;  // position in the key list -> token
+            } else {
+                const int c = row >> 4, i = row & 15;
+                const int ky = imin(t.a + 4 * (c >> 1) + (i >> 2), p.gridH - 1), kx = imin(t.b + 4 * (c & 1) + (i & 3), p.gridW - 1);
+                token = (long long)p.n_text + (long long)ky * p.gridW + kx;
+            }
+            const long long off = token * HD + 4 * (qi ^ f32_swz(row));
+            load_to_lds_16B_far(Kh + off, dst + ii * 1024);
+            load_to_lds_16B_far(Vh + off, dst + HALF_BYTES + ii * 1024);
+        }
+    };
+
+    Stage cur = next_stage(0);
+    if (cur.i < n_stages) issue_stage(cur, 0);
+
+    // Q as B operand: contraction step 4 j + t takes channel 4 (4 j + g) + t from lane group g
+    f32x4 qf[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) qf[j] = *(const f32x4*)((const float*)p.Q + head_off + q_token * HD + 4 * (4 * j + g));
+
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 o[4] = {zero, zero, zero, zero};  // channel 16 cb + 4 g + reg of this lane's query
+    float m = -FLT_MAX, l = 0.f;            // running maximum (finite, so that no difference below is inf - inf); this lane's share of the sum
+    const float sc = p.scale_log2e;
+    // LDS addresses in cell 0 of stage buffer 0 (the other cells follow through the instructions' immediate offsets): chunk
+    // 4 j + g of K row qi; channel 16 cb + qi of V row 4 g + t
+    unsigned k_addr[4], v_addr[4][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) k_addr[j] = lds_base + (unsigned)(qi * 256 + (((4 * j + g) ^ f32_swz(qi)) << 4));
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb)
+            v_addr[t][cb] = lds_base + (unsigned)(HALF_BYTES + (4 * g + t) * 256 + (((4 * cb + (qi >> 2)) ^ f32_swz(4 * g + t)) << 4) + (qi & 3) * 4);
+
+    auto run_stage = [&](auto buf_tag) __attribute__((always_inline)) {
+        constexpr int buf = decltype(buf_tag)::value;
+        wait_vmcnt<0>();
+        __syncthreads();  // the stage has landed, and everyone has left the other buffer
+        const Stage nxt = next_stage(cur.i + 1);
+        if (nxt.i < n_stages) issue_stage(nxt, buf ^ 1);
+        const bool linear = cur.i < n_lin;
+        const long long lin_left = lin_limit - lin_begin - (long long)cur.i * STAGE_KEYS;  // keys of the range from this stage on
+        const int left = lin_left < STAGE_KEYS ? (int)lin_left : STAGE_KEYS;
+        const bool cut = cur.a + PART_H > p.gridH || cur.b + kKeyTileW > p.gridW;
+        auto run_cell = [&](auto c_tag) __attribute__((always_inline)) {
+            constexpr int c = decltype(c_tag)::value;
+            if ((c & (groups - 1)) != group || !wave_has_queries) return;
+            const int ky0 = cur.a + 4 * (c >> 1), kx0 = cur.b + 4 * (c & 1);
+            const int cls = linear ? classify_linear_block(c * kCell, kCell, left)
+                                   : classify_image_block_spec(spec, wy0, wx0, 4, 4, ky0, kx0, 4, 4, p.gridH, p.gridW);
+            if (cls == kBlockSkip) return;
+            constexpr unsigned at = buf * 2 * HALF_BYTES + c * kCell * 256;
+            f32x4 k4[4], s = zero;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) k4[j] = *(lds_f32x4_ptr)(size_t)(k_addr[j] + at);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) s = __builtin_amdgcn_mfma_f32_16x16x4f32(k4[j][t], qf[j][t], s, 0, 0, 0);
+            // register t of lane group g is key 4 g + t of the cell
+            if (cls == kBlockPartial) {
+                if (linear) {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) s[t] = c * kCell + 4 * g + t < left ? s[t] : -INFINITY;
+                } else if (DISC) {
+                    const int dy = ky0 + g - qy, dx0 = kx0 - qx;
+                    const int lim = p.r2 - __mul24(dy, dy);  // dx^2 has to stay below this
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) s[t] = __mul24(dx0 + t, dx0 + t) < lim ? s[t] : -INFINITY;
+                } else {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) s[t] = mask_admits(spec, qy, qx, ky0 + g, kx0 + t) ? s[t] : -INFINITY;
+                }
+                if (cut && !linear) {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) s[t] = ky0 + g < p.gridH && kx0 + t < p.gridW ? s[t] : -INFINITY;
+                }
+            }
+            const float mx = quad_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
+            if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {  // some query of the wave has a new maximum
+                const float m_new = fmaxf(m, mx), alpha = __builtin_amdgcn_exp2f((m - m_new) * sc);
+                m = m_new;
+                l *= alpha;
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) o[cb] *= alpha;
+            }
+            f32x4 pr;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) pr[t] = __builtin_amdgcn_exp2f((s[t] - m) * sc);
+            l += (pr[0] + pr[1]) + (pr[2] + pr[3]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb)
+                    o[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(*(lds_f32_ptr)(size_t)(v_addr[t][cb] + at), pr[t], o[cb], 0, 0, 0);
+        };
+        static_for<CELLS>(run_cell);
+        cur = nxt;
+    };
+    while (cur.i < n_stages) {
+        run_stage(std::integral_constant<int, 0>{});
+        if (cur.i >= n_stages) break;
+        run_stage(std::integral_constant<int, 1>{});
+    }
+
+    l = quad_sum(l);
+    if (groups > 1) {
+        // join the partial sums of the waves that share a patch: wave by wave in LDS, 18 floats per lane
+        __syncthreads();
+        float* const mine = (float*)smem + wave * (18 * 64) + lane;
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) mine[(4 * cb + t) * 64] = o[cb][t];
+        mine[16 * 64] = m;
+        mine[17 * 64] = l;
+        __syncthreads();
+        if (group != 0) return;
+        for (int k = 1; k < groups; ++k) {
+            const float* const other = mine + k * (18 * 64);
+            const float mo = other[16 * 64], m_new = fmaxf(m, mo);
+            const float wa = __builtin_amdgcn_exp2f((m - m_new) * sc), wb = __builtin_amdgcn_exp2f((mo - m_new) * sc);
+            m = m_new;
+            l = l * wa + other[17 * 64] * wb;
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) o[cb][t] = o[cb][t] * wa + other[(4 * cb + t) * 64] * wb;
+        }
+    }
+    if (!q_valid) return;
+    if (textq && p.n_splits > 1) {
+        const long long row = ((long long)bh * p.n_splits + split) * p.n_text + q_token;
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) *(f32x4*)(p.ws_o + row * HD + 16 * cb + 4 * g) = o[cb];
+        if (g == 0) {
+            p.ws_ml[row * 2] = m;
+            p.ws_ml[row * 2 + 1] = l;
+        }
+        return;
+    }
+    const float inv = 1.0f / l, lse = logf(l) + m * sc * 0.6931471805599453f;
+    float* orow = (float*)p.O + head_off + q_token * HD;
+    float* lse_out = p.lse ? p.lse + (long long)bh * p.N + q_token : nullptr;
+    if (textq && p.band_o) {
+        orow = p.band_o + ((long long)bh * p.n_text + q_token) * HD;
+        lse_out = p.band_lse + (long long)bh * p.n_text + q_token;
+    }
+    if (lse_out && g == 0) *lse_out = lse;
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) *(f32x4*)(orow + 16 * cb + 4 * g) = o[cb] * inv;
+}
+
+// Log-sum-exp combination of the key-split partial results of the text-query rows: 16 lanes per row, 4 channels each.
+__global__ void __launch_bounds__(256) clear_text_merge_f32_kernel(const FwdParams p)
+{
+    const long long row = (long long)blockIdx.x * 16 + threadIdx.x / 16;
+    if (row >= (long long)p.B * p.H * p.n_text) return;
+    const int bh = (int)(row / p.n_text), q = (int)(row % p.n_text);
+    const int ch = 4 * (threadIdx.x % 16);
     float m = -INFINITY;
     for (int s = 0; s < p.n_splits; ++s) m = fmaxf(m, p.ws_ml[(((long long)bh * p.n_splits + s) * p.n_text + q) * 2]);
-    float num = 0.f, den = 0.f;
+    f32x4 num = {0.f, 0.f, 0.f, 0.f};
+    float den = 0.f;
     for (int s = 0; s < p.n_splits; ++s) {
         const long long r = ((long long)bh * p.n_splits + s) * p.n_text + q;
-        const float w = exp2f((p.ws_ml[r * 2] - m) * p.scale_log2e);
+        const float w = __builtin_amdgcn_exp2f((p.ws_ml[r * 2] - m) * p.scale_log2e);
         den += w * p.ws_ml[r * 2 + 1];
-        num += w * p.ws_o[r * D + ch];
+        num += w * *(const f32x4*)(p.ws_o + r * HD + ch);
     }
-    if (p.band_o) {
-        p.band_o[(long long)row * D + ch] = num / den;
-        if (ch == 0) p.band_lse[row] = logf(den) + m * p.scale_log2e * 0.6931471805599453f;
-    } else {
-        ((float*)p.O)[((long long)bh * p.N + q) * D + ch] = num / den;
-        if (p.lse && ch == 0) p.lse[(long long)bh * p.N + q] = logf(den) + m * p.scale_log2e * 0.6931471805599453f;
+    const float lse = logf(den) + m * p.scale_log2e * 0.6931471805599453f;
+    float* out = p.band_o ? p.band_o + row * HD : (float*)p.O + ((long long)bh * p.N + q) * HD;
+    *(f32x4*)(out + ch) = num / den;
+    if (ch == 0) {
+        if (p.band_o)
+            p.band_lse[row] = lse;
+        else if (p.lse)
+            p.lse[(long long)bh * p.N + q] = lse;
     }
 }
 
 }  // namespace
 
-int f32_text_queries_per_block() { return NT; }
+int f32_text_queries_per_block() { return kWaves * kCell; }
 
 hipError_t launch_f32_d64(const FwdParams& p, hipStream_t stream, int phase)
 {
     const int BH = p.B * p.H;
     hipError_t e = hipSuccess;
-    if (phase == kPhaseAll || phase == kPhaseImage) {
-        hipLaunchKernelGGL(clear_fwd_f32_kernel<false>, dim3(BH * p.n_q_tiles_launch), dim3(NT), 0, stream, p);
+    const bool all = phase == kPhaseAll || phase == kPhaseImageAndTextQuery;
+    const int subs = 4 * p.f32_groups;  // workgroups per 16 x 16 query tile
+    const int n_image = all || phase == kPhaseImage ? BH * p.n_q_tiles_launch * subs : 0;
+    const int n_text = p.n_text > 0 && (all || phase == kPhaseTextQuery) ? BH * p.n_tq_tiles * p.n_splits : 0;
+    if (n_image + n_text > 0) {
+        const bool disc = p.mask_kind == kMaskDisc, wide = p.f32_groups == 4;
+        auto kern = disc ? (wide ? clear_fwd_f32_kernel<true, 4> : clear_fwd_f32_kernel<true, 2>)
+                         : (wide ? clear_fwd_f32_kernel<false, 4> : clear_fwd_f32_kernel<false, 2>);
+        hipLaunchKernelGGL(kern, dim3(n_image + n_text), dim3(kWaves * 64), 0, stream, p, n_image);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (p.n_text > 0 && (phase == kPhaseAll || phase == kPhaseTextQuery)) {
-        hipLaunchKernelGGL(clear_fwd_f32_kernel<true>, dim3(BH * p.n_tq_tiles * p.n_splits), dim3(NT), 0, stream, p);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (p.n_text > 0 && (phase == kPhaseAll || phase == kPhaseTextMerge)) {
-        hipLaunchKernelGGL(clear_text_merge_f32_kernel, dim3(BH * p.n_text), dim3(D), 0, stream, p);
+    if (p.n_text > 0 && p.n_splits > 1 && (phase == kPhaseAll || phase == kPhaseTextMerge)) {
+        hipLaunchKernelGGL(clear_text_merge_f32_kernel, dim3((unsigned)(((long long)BH * p.n_text + 15) / 16)), dim3(256), 0, stream, p);
         e = hipGetLastError();
     }
     return e;

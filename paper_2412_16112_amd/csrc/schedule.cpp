@@ -257,12 +257,21 @@ unsigned long long executed_pairs_bf16_strided(const Schedule& s, int n_text, in
 unsigned long long executed_pairs_f32(const Schedule& s, int n_text)
 {
     const long long N = (long long)n_text + (long long)s.gridH * s.gridW;
-    const unsigned long long n_text_tiles = (unsigned long long)ceil_div(n_text, kKeyTileKeys);
-    unsigned long long pairs = 0;
+    const MaskSpec spec = {s.mask_kind, s.r, s.mask_shift};
+    constexpr int kSide = 4, kCell = kSide * kSide;  // 4 x 4 query patches against cells of 16 keys
+    const unsigned long long text_cells = (unsigned long long)ceil_div(n_text, kCell);
+    unsigned long long cells = text_cells * (unsigned long long)((N + kCell - 1) / kCell);  // text queries meet every cell of [0, N)
     for (size_t qt = 0; qt + 1 < s.row_ptr.size(); ++qt)
-        pairs += (n_text_tiles + (unsigned long long)(s.row_ptr[qt + 1] - s.row_ptr[qt])) * kKeyTileKeys * (unsigned long long)(s.qth * s.qtw);
-    pairs += (unsigned long long)n_text * (unsigned long long)(((N + kKeyTileKeys - 1) / kKeyTileKeys) * kKeyTileKeys);
-    return pairs;
+        for (int y0 = (int)(qt / s.n_qtx) * s.qth, ye = imin(y0 + s.qth, s.gridH); y0 < ye; y0 += kSide)
+            for (int x0 = (int)(qt % s.n_qtx) * s.qtw, xe = imin(x0 + s.qtw, s.gridW); x0 < xe; x0 += kSide) {
+                cells += text_cells;
+                for (int e = s.row_ptr[qt]; e < s.row_ptr[qt + 1]; ++e)
+                    for (int c = 0; c < kKeyTileKeys / kCell; ++c) {
+                        const int ky0 = (s.col_idx[e] / s.n_ktx) * s.kth + kSide * (c >> 1), kx0 = (s.col_idx[e] % s.n_ktx) * s.ktw + kSide * (c & 1);
+                        cells += classify_image_block_spec(spec, y0, x0, kSide, kSide, ky0, kx0, kSide, kSide, s.gridH, s.gridW) != kBlockSkip;
+                    }
+            }
+    return cells * kCell * kCell;
 }
 
 }  // namespace clear
