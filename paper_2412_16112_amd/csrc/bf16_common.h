@@ -206,6 +206,7 @@ __host__ __device__ constexpr int mask_code_of(int mask_kind)
 // completion the tile prefetch waits on.
 typedef const __attribute__((address_space(4))) int* const_int_ptr;
 typedef const __attribute__((address_space(4))) unsigned long long* const_u64_ptr;
+typedef const __attribute__((address_space(4))) unsigned* const_u32_ptr;
 
 struct MaskArgs {
     int a, b;  // linear: first token of the tile, token limit; image: tile origin (row, col)

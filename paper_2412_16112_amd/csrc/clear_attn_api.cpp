@@ -18,26 +18,58 @@
 
 using namespace clear;
 
+// Tables that go to the device together, in one allocation and one copy.
+class TablePack {
+  public:
+    template <typename T>
+    size_t add(const std::vector<T>& v)
+    {
+        const size_t at = (bytes_.size() + 255) & ~(size_t)255;
+        bytes_.resize(at + std::max<size_t>(v.size(), 1) * sizeof(T));
+        if (!v.empty()) memcpy(bytes_.data() + at, v.data(), v.size() * sizeof(T));
+        return at;
+    }
+    hipError_t upload(unsigned char** device) const
+    {
+        hipError_t e = hipMalloc((void**)device, bytes_.size());
+        return e == hipSuccess ? hipMemcpy(*device, bytes_.data(), bytes_.size(), hipMemcpyHostToDevice) : e;
+    }
+
+  private:
+    std::vector<unsigned char> bytes_;
+};
+
+// What the bf16 forward kernels follow, for one number of waves per query patch (1, 2, 4: query tiles of 16, 8, 4 rows).
+struct ForwardTables {
+    int qth = 0, n_qty = 0, n_qtx = 0;
+    double stages = 0, steps = 0;  // of a query tile, on average: stages, blocks per wave
+    int* d_row_ptr = nullptr;
+    int* d_col_idx = nullptr;
+    unsigned* d_words = nullptr;
+    unsigned* d_ptr = nullptr;
+    unsigned text_words[3] = {};
+};
+
 // Tile lists of one raster and their copies on the device.
 struct TileTables {
     Schedule sched;
+    ForwardTables fwd[3];        // bf16: 1, 2, 4 waves per patch (the latter two only for small grids)
+    unsigned char* forward = nullptr;  // all of their tables, and
+    unsigned long long* d_block_masks = nullptr;
+    int* d_qt_order = nullptr;         // the order in which a head's query tiles are dealt to the workgroups (may be null)
+    // fp32 kernel, and the bf16 backward kernels (built with the backward workspace)
+    unsigned char* lists = nullptr;  // all of the below
     int* d_row_ptr = nullptr;
     int* d_col_idx = nullptr;   // kernel order: tiles inside the grid first, border tiles last
     int* d_n_plain = nullptr;
-    int* d_qt_order = nullptr;   // bf16: the order in which a head's query tiles are dealt to the workgroups (see build_tile_tables)
     unsigned long long* d_mask_tbl = nullptr;
     int* d_wave_desc = nullptr;  // per listed key tile and wave: mask-table entries of its blocks (bf16, with d_mask_tbl)
     int mask_ry = 0, mask_rx = 0;
     void release()
     {
-        if (d_row_ptr) (void)hipFree(d_row_ptr);
-        if (d_col_idx) (void)hipFree(d_col_idx);
-        if (d_n_plain) (void)hipFree(d_n_plain);
-        if (d_qt_order) (void)hipFree(d_qt_order);
-        if (d_mask_tbl) (void)hipFree(d_mask_tbl);
-        if (d_wave_desc) (void)hipFree(d_wave_desc);
-        d_row_ptr = d_col_idx = d_n_plain = d_qt_order = d_wave_desc = nullptr;
-        d_mask_tbl = nullptr;
+        if (forward) (void)hipFree(forward);
+        if (lists) (void)hipFree(lists);
+        forward = lists = nullptr;
     }
 };
 
@@ -62,6 +94,13 @@ struct clear_attn_ctx {
     // keys after the prologue (clear_attn_forward_prologue), grown on demand
     int kpro_BH = 0;
     void* d_kpro = nullptr;        // [B*H][N][head_dim] bf16
+    struct ShapeOf {               // the launch shape of the last bf16 forward call and what it was chosen for
+        int BH = 0, own_y0 = 0, own_y1 = 0;
+        long long NV = 0;
+        const TileTables* tables = nullptr;
+        int groups = 1, tq_groups = 1, n_splits = 1, split_keys = 0;
+        bool text_first = false;
+    } shape_of;
     void* scratch = nullptr;       // this device's copy of the static scratch array (clear_attn_forward_noalloc)
     std::string err;
 };
@@ -179,6 +218,8 @@ static void choose_text_splits(long long N, int BH, int n_tq_tiles, int num_cus,
     *n_splits = (int)((N + keys - 1) / keys);
 }
 
+constexpr size_t kGroupsMaxTiles = 64;
+
 // Launch shape of the fp32 kernel.  A workgroup is four waves of 16 queries, all on one 8 x 8 patch of queries (64 text
 // queries); with `groups` = 2 or 4 waves on every 16 queries a patch of 4 x 8 or 4 x 4 (32 or 16 text queries) walks its
 // keys in a half or a quarter of the steps, at two or four times the staging traffic per pair.  So: as many waves per
@@ -204,9 +245,160 @@ static void choose_f32_shape(long long NV, int BH, int num_cus, FwdParams* p)
     p->n_splits = (int)((NV + keys - 1) / keys);
 }
 
+// Kernel-side tile lists of a schedule: per query tile, the origins (row << 16 | col) of its key tiles, those inside the
+// grid (the first cutH rows, cutW columns) first, border tiles last; n_plain: how many lie inside.
+static void order_key_tiles(const Schedule& sc, int cutH, int cutW, std::vector<int>* k_col_out, std::vector<int>* n_plain_out)
+{
+    std::vector<int>&k_col = *k_col_out, &n_plain = *n_plain_out;
+    k_col.assign(sc.col_idx.size(), 0);
+    n_plain.assign(sc.row_ptr.size() - 1, 0);
+    auto cut = [&](int id) {
+        const int ty = id / sc.n_ktx, tx = id % sc.n_ktx;
+        return (ty + 1) * sc.kth > cutH || (tx + 1) * sc.ktw > cutW;
+    };
+    auto origin = [&](int id) { return ((id / sc.n_ktx) * sc.kth) << 16 | ((id % sc.n_ktx) * sc.ktw); };
+    std::vector<int> plain, used;
+    for (size_t qt = 0; qt + 1 < sc.row_ptr.size(); ++qt) {
+        // Tiles inside the grid, reordered so that each stage (two consecutive tiles) holds a tile and its
+        // point mirror through the centre of the query tile: what one wave's disc misses of the pair,
+        // the wave sharing its SIMD tends to reach, which evens out the work between barriers.
+        plain.clear();
+        for (int e = sc.row_ptr[qt]; e < sc.row_ptr[qt + 1]; ++e)
+            if (!cut(sc.col_idx[e])) plain.push_back(sc.col_idx[e]);
+        used.assign(plain.size(), 0);
+        const int qy0 = (int)(qt / sc.n_qtx) * sc.qth, qx0 = (int)(qt % sc.n_qtx) * sc.qtw;
+        int w = sc.row_ptr[qt];
+        std::vector<int> single;
+        for (size_t i = 0; i < plain.size(); ++i) {
+            if (used[i]) continue;
+            used[i] = 1;
+            const int ky = (plain[i] / sc.n_ktx) * sc.kth, kx = (plain[i] % sc.n_ktx) * sc.ktw;
+            const int my = 2 * qy0 + sc.qth - sc.kth - ky, mx = 2 * qx0 + sc.qtw - sc.ktw - kx;
+            int partner = -1;
+            if (my >= 0 && mx >= 0 && my % sc.kth == 0 && mx % sc.ktw == 0) {
+                const int mid = (my / sc.kth) * sc.n_ktx + mx / sc.ktw;
+                for (size_t j = i + 1; j < plain.size(); ++j)
+                    if (!used[j] && plain[j] == mid) { partner = (int)j; break; }
+            }
+            if (partner >= 0) {
+                used[partner] = 1;
+                k_col[w++] = origin(plain[i]);
+                k_col[w++] = origin(plain[partner]);
+            } else {
+                single.push_back(plain[i]);
+            }
+        }
+        for (int id : single) k_col[w++] = origin(id);
+        n_plain[qt] = w - sc.row_ptr[qt];
+        for (int e = sc.row_ptr[qt]; e < sc.row_ptr[qt + 1]; ++e)
+            if (cut(sc.col_idx[e])) k_col[w++] = origin(sc.col_idx[e]);
+    }
+}
+
+// Tables of the bf16 forward kernels on the current device: one wave per query patch and, where the query tiles of one head do not fill the chip
+// by themselves, several (see choose_forward_shape); order: may be empty.
+static hipError_t build_forward_tables(int n_text, int head_dim, int stride, int gridH, int gridW, const std::vector<int>& order, TileTables* t)
+{
+    const Schedule& sched = t->sched;
+    const int n = stride == 1 && sched.row_ptr.size() - 1 <= kGroupsMaxTiles ? 3 : 1;
+    Schedule sub[3];
+    QueryTilePatterns pat[3];
+    std::vector<int> col_idx[3];
+    std::vector<ProgramInput> in(n);
+    for (int i = 0; i < n; ++i) {
+        if (i > 0) build_schedule(sched.gridH, sched.gridW, sched.r, sched.qth >> i, sched.qtw, sched.kth, sched.ktw, &sub[i], sched.mask_kind, sched.mask_shift);
+        const Schedule& s = i > 0 ? sub[i] : sched;
+        pat[i] = query_tile_patterns(s);
+        order_forward_tiles(s, pat[i], &col_idx[i]);
+        in[i] = {&s, &pat[i], &col_idx[i], 1 << i};
+    }
+    std::vector<BlockPrograms> prog;
+    std::vector<unsigned long long> masks;
+    build_block_programs(in, n_text, head_dim, stride, gridH, gridW, &prog, &masks);
+    TablePack pack;
+    size_t at[3][4] = {};
+    for (int i = 0; i < n; ++i) {
+        const Schedule& s = *in[i].sched;
+        ForwardTables& f = t->fwd[i];
+        f.qth = s.qth;
+        f.n_qty = s.n_qty;
+        f.n_qtx = s.n_qtx;
+        f.stages = prog[i].mean_stages;
+        f.steps = prog[i].mean_steps;
+        std::copy(prog[i].text_words, prog[i].text_words + 3, f.text_words);
+        at[i][0] = pack.add(s.row_ptr);
+        at[i][1] = pack.add(col_idx[i]);
+        at[i][2] = pack.add(prog[i].words);
+        at[i][3] = pack.add(prog[i].ptr);
+    }
+    const size_t masks_at = pack.add(masks);
+    const size_t order_at = order.empty() ? 0 : pack.add(order);
+    const hipError_t e = pack.upload(&t->forward);
+    if (e != hipSuccess) return e;
+    for (int i = 0; i < n; ++i) {
+        ForwardTables& f = t->fwd[i];
+        f.d_row_ptr = (int*)(t->forward + at[i][0]);
+        f.d_col_idx = (int*)(t->forward + at[i][1]);
+        f.d_words = (unsigned*)(t->forward + at[i][2]);
+        f.d_ptr = (unsigned*)(t->forward + at[i][3]);
+    }
+    t->d_block_masks = (unsigned long long*)(t->forward + masks_at);
+    t->d_qt_order = order.empty() ? nullptr : (int*)(t->forward + order_at);
+    return hipSuccess;
+}
+
+// Tile lists of the fp32 kernel and of the bf16 backward kernels, and what the latter mask with, on the current device.
+static hipError_t build_lists(int gridH, int gridW, int r, int dtype, int mask_kind, int shift, TileTables* t)
+{
+    const bool strided = mask_kind == CLEAR_MASK_STRIDED;
+    // (strided: tiles count as inside the grid only if they are so for the smallest class, extents rounded down)
+    const int cutH = strided ? gridH / r : gridH, cutW = strided ? gridW / r : gridW;
+    std::vector<int> k_col, n_plain;
+    order_key_tiles(t->sched, cutH, cutW, &k_col, &n_plain);
+    std::vector<unsigned long long> mask_tbl;
+    if (dtype == CLEAR_BF16 && (mask_kind == CLEAR_MASK_DISC || mask_kind == CLEAR_MASK_SQUARE)) {
+        // (masks that depend on the offset between the tokens alone; Swin windows take the arithmetic element mask)
+        // relative block offsets that a non-empty (patch, block) pair can have
+        t->mask_ry = std::min((r + 2) / 4, (gridH + 3) / 4);
+        t->mask_rx = std::min((r + 6) / 8, (gridW + 7) / 8);
+        const size_t entries = (size_t)(2 * t->mask_ry + 1) * (2 * t->mask_rx + 1) + 2;
+        if (entries * 128 <= (64u << 20)) {  // beyond 64 MB the kernels fall back to arithmetic masks
+            build_bf16_mask_table(r, t->mask_ry, t->mask_rx, mask_kind, &mask_tbl);
+        }
+    }
+    if (dtype == CLEAR_BF16 && mask_kind == CLEAR_MASK_SWIN && r % 8 == 0 && shift % 8 == 0) {
+        // Windows whose edges fall on multiples of 8: a 4 x 8 query patch and a 4 x 8 key block each lie in one
+        // window, so inside the grid a block is either wholly admitted or out of reach.  The table then only
+        // needs its all-ones and all-zeros entries (the entry for offset (0, 0) in front of them is never used).
+        t->mask_ry = t->mask_rx = 0;
+        build_bf16_mask_table(r, 0, 0, mask_kind, &mask_tbl);
+    }
+    std::vector<int> wave_desc;
+    if (!mask_tbl.empty()) {
+        // mask-table entries reach 16-bit indices only up to 65535; beyond that (r in the thousands) the kernels use arithmetic masks
+        const size_t entries = mask_tbl.size() / 16;
+        if (entries <= 0xffff && k_col.size() * (size_t)(kBf16NWY * kBf16NWX) * sizeof(int) <= ((size_t)256 << 20)) {
+            build_wave_descriptors(t->sched, k_col, n_plain, t->mask_ry, t->mask_rx, &wave_desc);
+        } else {
+            mask_tbl.clear();
+        }
+    }
+    TablePack pack;
+    const size_t row_ptr = pack.add(t->sched.row_ptr), col_idx = pack.add(k_col), plain = pack.add(n_plain);
+    const size_t masks = mask_tbl.empty() ? 0 : pack.add(mask_tbl), desc = wave_desc.empty() ? 0 : pack.add(wave_desc);
+    hipError_t e = pack.upload(&t->lists);
+    if (e != hipSuccess) return e;
+    t->d_row_ptr = (int*)(t->lists + row_ptr);
+    t->d_col_idx = (int*)(t->lists + col_idx);
+    t->d_n_plain = (int*)(t->lists + plain);
+    t->d_mask_tbl = mask_tbl.empty() ? nullptr : (unsigned long long*)(t->lists + masks);
+    t->d_wave_desc = wave_desc.empty() ? nullptr : (int*)(t->lists + desc);
+    return hipSuccess;
+}
+
 // Builds the tile lists of a gridH x gridW raster for the kernels of (head_dim, dtype, mask) and copies them to the
 // current device.  Returns CLEAR_OK, or an error code with *why set (the caller releases `t`).
-static int build_tile_tables(int gridH, int gridW, int head_dim, int r, int dtype, int mask_kind, int shift, TileTables* t, std::string* why)
+static int build_tile_tables(int n_text, int gridH, int gridW, int head_dim, int r, int dtype, int mask_kind, int shift, TileTables* t, std::string* why)
 {
     const bool strided = mask_kind == CLEAR_MASK_STRIDED;
     int qth, qtw, kth, ktw;
@@ -215,7 +407,6 @@ static int build_tile_tables(int gridH, int gridW, int head_dim, int r, int dtyp
     // every query tile meets every key tile; tiles count as inside the grid only if they are so for the
     // smallest class (extents rounded down).
     const int schedH = strided ? (gridH + r - 1) / r : gridH, schedW = strided ? (gridW + r - 1) / r : gridW;
-    const int cutH = strided ? gridH / r : gridH, cutW = strided ? gridW / r : gridW;
     if (schedule_pair_bound(schedH, schedW, strided ? schedH + schedW : r, qth, qtw, kth, ktw) > kMaxSchedulePairs) {
         *why = "the tile schedule would exceed 2^28 (query tile, key tile) pairs: r is too close to the size of a grid this large";
         return CLEAR_ERR_UNSUPPORTED;
@@ -229,135 +420,35 @@ static int build_tile_tables(int gridH, int gridW, int head_dim, int r, int dtyp
         *why = "out of host memory building the schedule";
         return CLEAR_ERR_ALLOC;
     }
-    // kernel-side tile lists: per query tile, the origins (row << 16 | col) of its key tiles, those inside the
-    // grid first (mirror pairs adjacent), border tiles last
-    std::vector<int> k_col(t->sched.col_idx.size()), n_plain(t->sched.row_ptr.size() - 1, 0);
-    {
-        const Schedule& sc = t->sched;
-        auto cut = [&](int id) {
-            const int ty = id / sc.n_ktx, tx = id % sc.n_ktx;
-            return (ty + 1) * sc.kth > cutH || (tx + 1) * sc.ktw > cutW;
-        };
-        auto origin = [&](int id) { return ((id / sc.n_ktx) * sc.kth) << 16 | ((id % sc.n_ktx) * sc.ktw); };
-        std::vector<int> plain, used;
-        for (size_t qt = 0; qt + 1 < sc.row_ptr.size(); ++qt) {
-            // Tiles inside the grid, reordered so that each stage (two consecutive tiles) holds a tile and its
-            // point mirror through the centre of the query tile: what one wave's disc misses of the pair,
-            // the wave sharing its SIMD tends to reach, which evens out the work between barriers.
-            plain.clear();
-            for (int e = sc.row_ptr[qt]; e < sc.row_ptr[qt + 1]; ++e)
-                if (!cut(sc.col_idx[e])) plain.push_back(sc.col_idx[e]);
-            used.assign(plain.size(), 0);
-            const int qy0 = (int)(qt / sc.n_qtx) * sc.qth, qx0 = (int)(qt % sc.n_qtx) * sc.qtw;
-            int w = sc.row_ptr[qt];
-            std::vector<int> single;
-            for (size_t i = 0; i < plain.size(); ++i) {
-                if (used[i]) continue;
-                used[i] = 1;
-                const int ky = (plain[i] / sc.n_ktx) * sc.kth, kx = (plain[i] % sc.n_ktx) * sc.ktw;
-                const int my = 2 * qy0 + sc.qth - sc.kth - ky, mx = 2 * qx0 + sc.qtw - sc.ktw - kx;
-                int partner = -1;
-                if (my >= 0 && mx >= 0 && my % sc.kth == 0 && mx % sc.ktw == 0) {
-                    const int mid = (my / sc.kth) * sc.n_ktx + mx / sc.ktw;
-                    for (size_t j = i + 1; j < plain.size(); ++j)
-                        if (!used[j] && plain[j] == mid) { partner = (int)j; break; }
-                }
-                if (partner >= 0) {
-                    used[partner] = 1;
-                    k_col[w++] = origin(plain[i]);
-                    k_col[w++] = origin(plain[partner]);
-                } else {
-                    single.push_back(plain[i]);
-                }
-            }
-            for (int id : single) k_col[w++] = origin(id);
-            n_plain[qt] = w - sc.row_ptr[qt];
-            for (int e = sc.row_ptr[qt]; e < sc.row_ptr[qt + 1]; ++e)
-                if (cut(sc.col_idx[e])) k_col[w++] = origin(sc.col_idx[e]);
-        }
-    }
-    std::vector<unsigned long long> mask_tbl;
-    if (dtype == CLEAR_BF16 && (mask_kind == CLEAR_MASK_DISC || mask_kind == CLEAR_MASK_SQUARE)) {
-        // (masks that depend on the offset between the tokens alone; Swin windows take the arithmetic element mask)
-        // relative block offsets that a non-empty (patch, block) pair can have
-        t->mask_ry = std::min((r + 2) / 4, (gridH + 3) / 4);
-        t->mask_rx = std::min((r + 6) / 8, (gridW + 7) / 8);
-        const size_t entries = (size_t)(2 * t->mask_ry + 1) * (2 * t->mask_rx + 1) + 2;
-        if (entries * 128 <= (64u << 20)) {  // beyond 64 MB the kernels fall back to arithmetic masks
-            try {
-                build_bf16_mask_table(r, t->mask_ry, t->mask_rx, mask_kind, &mask_tbl);
-            } catch (const std::bad_alloc&) {
-                *why = "out of host memory building the mask table";
-                return CLEAR_ERR_ALLOC;
-            }
-        }
-    }
-    if (dtype == CLEAR_BF16 && mask_kind == CLEAR_MASK_SWIN && r % 8 == 0 && shift % 8 == 0) {
-        // Windows whose edges fall on multiples of 8: a 4 x 8 query patch and a 4 x 8 key block each lie in one
-        // window, so inside the grid a block is either wholly admitted or out of reach.  The table then only
-        // needs its all-ones and all-zeros entries (the entry for offset (0, 0) in front of them is never used).
-        t->mask_ry = t->mask_rx = 0;
-        try {
-            build_bf16_mask_table(r, 0, 0, mask_kind, &mask_tbl);
-        } catch (const std::bad_alloc&) {
-            *why = "out of host memory building the mask table";
-            return CLEAR_ERR_ALLOC;
-        }
-    }
-    std::vector<int> wave_desc;
-    if (!mask_tbl.empty()) {
-        // mask-table entries reach 16-bit indices only up to 65535; beyond that (r in the thousands) the kernels use arithmetic masks
-        const size_t entries = mask_tbl.size() / 16;
-        if (entries <= 0xffff && k_col.size() * (size_t)(kBf16NWY * kBf16NWX) * sizeof(int) <= ((size_t)256 << 20)) {
-            try {
-                build_wave_descriptors(t->sched, k_col, n_plain, t->mask_ry, t->mask_rx, &wave_desc);
-            } catch (const std::bad_alloc&) {
-                *why = "out of host memory building the per-wave tile descriptors";
-                return CLEAR_ERR_ALLOC;
-            }
-        } else {
-            mask_tbl.clear();
-        }
-    }
     // Order of a head's query tiles over its workgroups.  An XCD (32 CUs, one workgroup each, one 4 MB L2) works through
     // a contiguous range of that order, so the tiles in flight on it are 32 consecutive entries.  Row by row on a wide
     // grid they are a 1 x 32 strip of tiles, whose keys - 16 + 2 (r - 1) rows across 512 columns - the next strip
-    // needs again but finds evicted.  Dealt out in blocks of 2 x 16 tiles, strips of 16 tile columns taken top to
-    // bottom, the tiles in flight form a more compact patch: a quarter fewer L2 misses at a 512 x 512 grid (18.9 ->
-    // 14.1 GB per launch of 24 heads), same time.  Grids up to 16 tiles wide keep the plain order (no table).
-    constexpr int kOrderRows = 2, kOrderCols = 16;
-    std::vector<int> qt_order;
+    // needs again but finds evicted.  Dealt out in blocks of 4 x 8 tiles, strips of 8 tile columns taken top to bottom, and with the
+    // key tiles in an order that overlapping windows share (order_forward_tiles), the tiles in flight read 8.0 GB past the L2 at a 512 x
+    // 512 grid and 24 heads (2 x 16 blocks: 11.3; 21 in neither order); the power saved there is worth 1 % of the time on
+    // a part that runs at its power limit.  Grids up to 8 tiles wide keep the plain order (no table).
+    constexpr int kOrderRows = 4, kOrderCols = 8;
+    std::vector<int> order;
     if (dtype == CLEAR_BF16 && !strided && t->sched.n_qtx > kOrderCols) {
         const Schedule& sc = t->sched;
         try {
-            qt_order.reserve((size_t)sc.n_qty * sc.n_qtx);
+            order.reserve((size_t)sc.n_qty * sc.n_qtx);
             for (int bx = 0; bx < sc.n_qtx; bx += kOrderCols)
                 for (int by = 0; by < sc.n_qty; by += kOrderRows)
                     for (int ty = by; ty < std::min(by + kOrderRows, sc.n_qty); ++ty)
-                        for (int tx = bx; tx < std::min(bx + kOrderCols, sc.n_qtx); ++tx) qt_order.push_back(ty * sc.n_qtx + tx);
+                        for (int tx = bx; tx < std::min(bx + kOrderCols, sc.n_qtx); ++tx) order.push_back(ty * sc.n_qtx + tx);
         } catch (const std::bad_alloc&) {
             *why = "out of host memory building the query-tile order";
             return CLEAR_ERR_ALLOC;
         }
     }
     hipError_t e = hipSuccess;
-    if (e == hipSuccess && !qt_order.empty()) {
-        e = hipMalloc((void**)&t->d_qt_order, qt_order.size() * sizeof(int));
-        if (e == hipSuccess) e = hipMemcpy(t->d_qt_order, qt_order.data(), qt_order.size() * sizeof(int), hipMemcpyHostToDevice);
-    }
-    if (e == hipSuccess) e = hipMalloc((void**)&t->d_row_ptr, t->sched.row_ptr.size() * sizeof(int));
-    if (e == hipSuccess) e = hipMalloc((void**)&t->d_col_idx, (k_col.size() + 1) * sizeof(int));
-    if (e == hipSuccess) e = hipMalloc((void**)&t->d_n_plain, (n_plain.size() + 1) * sizeof(int));
-    if (e == hipSuccess) e = hipMemcpy(t->d_row_ptr, t->sched.row_ptr.data(), t->sched.row_ptr.size() * sizeof(int), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !k_col.empty()) e = hipMemcpy(t->d_col_idx, k_col.data(), k_col.size() * sizeof(int), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !n_plain.empty()) e = hipMemcpy(t->d_n_plain, n_plain.data(), n_plain.size() * sizeof(int), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !mask_tbl.empty()) {
-        e = hipMalloc((void**)&t->d_mask_tbl, mask_tbl.size() * sizeof(unsigned long long));
-        if (e == hipSuccess) e = hipMemcpy(t->d_mask_tbl, mask_tbl.data(), mask_tbl.size() * sizeof(unsigned long long), hipMemcpyHostToDevice);
-    }
-    if (e == hipSuccess && !wave_desc.empty()) {
-        e = hipMalloc((void**)&t->d_wave_desc, wave_desc.size() * sizeof(int));
-        if (e == hipSuccess) e = hipMemcpy(t->d_wave_desc, wave_desc.data(), wave_desc.size() * sizeof(int), hipMemcpyHostToDevice);
+    try {
+        e = dtype == CLEAR_BF16 ? build_forward_tables(n_text, head_dim, strided ? r : 1, gridH, gridW, order, t)
+                                : build_lists(gridH, gridW, r, dtype, mask_kind, shift, t);
+    } catch (const std::bad_alloc&) {
+        *why = "out of host memory building the tile lists";
+        return CLEAR_ERR_ALLOC;
     }
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
@@ -488,7 +579,7 @@ int clear_attn_create_masked(clear_attn_ctx** out, int n_text, int gridH, int gr
     ctx->n_text = n_text; ctx->gridH = gridH; ctx->gridW = gridW;
     ctx->head_dim = head_dim; ctx->r = r; ctx->dtype = dtype;
     ctx->mask_kind = mask_kind; ctx->mask_shift = shift;
-    rc = build_tile_tables(gridH, gridW, head_dim, r, dtype, mask_kind, shift, &ctx->t, &why);
+    rc = build_tile_tables(n_text, gridH, gridW, head_dim, r, dtype, mask_kind, shift, &ctx->t, &why);
     if (rc != CLEAR_OK) {
         clear_attn_destroy(ctx);
         return fail(nullptr, rc, why);
@@ -558,7 +649,7 @@ static int band_tile_tables(clear_attn_ctx* ctx, int y_shift, hipStream_t stream
         TileTables* t = new (std::nothrow) TileTables;
         if (!t) return fail(ctx, CLEAR_ERR_ALLOC, "out of host memory");
         std::string why;
-        const int rc = build_tile_tables(ctx->gridH + y_shift, ctx->gridW, ctx->head_dim, ctx->r, ctx->dtype, ctx->mask_kind, ctx->mask_shift, t, &why);
+        const int rc = build_tile_tables(ctx->n_text, ctx->gridH + y_shift, ctx->gridW, ctx->head_dim, ctx->r, ctx->dtype, ctx->mask_kind, ctx->mask_shift, t, &why);
         if (rc != CLEAR_OK) {
             t->release();
             delete t;
@@ -568,6 +659,79 @@ static int band_tile_tables(clear_attn_ctx* ctx, int y_shift, hipStream_t stream
     }
     *out = slot;
     return CLEAR_OK;
+}
+
+// Launch shape of a bf16 forward call: how many waves share 32 image queries (`groups`) and 32 text queries (`tq_groups`), the key
+// ranges of the text queries, and which rows' workgroups go out first.
+//
+// One workgroup fills a CU, so what a call of a few workgroups per CU takes is decided by how evenly they fill the CUs and by the length of
+// the longest.  Waves that share queries halve or quarter a workgroup's walk over its keys and double or quadruple the number
+// of workgroups, at the price of staging every key tile twice or four times; key ranges do the same for the text queries at the price of
+// partial results and a kernel that merges them.  Every combination is priced with the measured cost of a workgroup - a fixed part
+// (dispatch, query rows and first tiles, output), a part per stage (barrier and refill of the pipeline) and a part per 32-key block of
+// the two waves of a SIMD - and the time at which the last CU finishes, longest workgroups first; the cheapest is taken.  (24 heads,
+// 32 x 32 grid, 512 text tokens, r = 8: 40 -> 32 us against one wave per patch throughout; 2 heads: 36 -> 20 us.)  Beyond 16 workgroups
+// per CU the evenness takes care of itself: one wave per patch, and choose_text_splits.
+struct ForwardShape {
+    int groups, tq_groups, n_splits, split_keys;
+    bool text_first;
+};
+static ForwardShape choose_forward_shape(const clear_attn_ctx* ctx, const TileTables& tt, int BH, long long NV, const int (&n_image_tiles)[3], int n_classes)
+{
+    const int n_text = ctx->n_text, num_cus = ctx->num_cus, per_block = bf16_text_queries_per_block();
+    const long long image_wgs = (long long)BH * n_classes * n_image_tiles[0];
+    ForwardShape best = {1, 1, 1, kKeyTileKeys, false};
+    auto text_tiles = [&](int groups) { return (n_text * groups + per_block - 1) / per_block; };
+    if (image_wgs > 16LL * num_cus) {
+        if (n_text > 0) choose_text_splits(NV, BH, text_tiles(1), num_cus, image_wgs <= 64LL * num_cus, &best.n_splits, &best.split_keys);
+        return best;
+    }
+    // cycles; a SIMD's two waves together take `block` per block of either
+    const double fixed = 16e3, stage = ctx->head_dim == 64 ? 1100 : 900, block = ctx->head_dim == 64 ? 400 : 520;
+    const int stage_keys = bf16_tiles_per_stage(ctx->head_dim) * kKeyTileKeys;
+    double best_time = 1e300;
+    for (int gi = 0; gi < 3; ++gi) {
+        const ForwardTables& f = tt.fwd[gi];
+        if (f.qth == 0) continue;  // not built
+        const double n_image = (double)BH * n_classes * n_image_tiles[gi], c_image = fixed + f.stages * stage + 2 * f.steps * block;
+        for (int ti = 0; ti < (n_text > 0 ? 3 : 1); ++ti) {
+            const int tg = 1 << ti;
+            long long last_keys = -1;
+            for (int s = 1; s <= (n_text > 0 ? std::min(max_text_splits(NV), 16) : 1); ++s) {
+                double n_text_wgs = 0, c_text = 0, merge = 0;
+                long long keys = (NV + s - 1) / s;
+                keys = (keys + kKeyTileKeys - 1) / kKeyTileKeys * kKeyTileKeys;
+                const int real = (int)((NV + keys - 1) / keys);
+                if (n_text > 0) {
+                    if (keys == last_keys) continue;
+                    last_keys = keys;
+                    const double bytes = (double)BH * real * n_text * (ctx->head_dim + 2) * sizeof(float);
+                    if (real > 1 && bytes > (double)kScratchBytes) break;  // (clear_attn_forward_noalloc takes the same shape)
+                    const double stages = std::ceil((double)keys / stage_keys);
+                    n_text_wgs = (double)BH * text_tiles(tg) * real;
+                    c_text = fixed + stages * stage + 2 * block * stages * std::max(1.0, (double)stage_keys / 32 / tg) * std::min(1.0, (double)keys / (stages * stage_keys));
+                    if (real > 1) merge = 12e3 + 2 * bytes / 2000;  // a kernel of its own; partial results written and read back
+                }
+                // longest first: c1 n1, then c2 n2
+                const bool text_first = c_text > c_image;
+                const double c1 = text_first ? c_text : c_image, c2 = text_first ? c_image : c_text, n1 = text_first ? n_text_wgs : n_image, n2 = text_first ? n_image : n_text_wgs;
+                const double q = std::floor(n1 / num_cus), r = n1 - q * num_cus;
+                double lo = (q + (r > 0)) * c1, hi = lo + (n2 > 0 ? (std::ceil(n2 / num_cus) + 1) * c2 : 0);
+                auto fits = [&](double t) { return r * std::floor((t - (q + 1) * c1) / c2) + (num_cus - r) * std::floor((t - q * c1) / c2) >= n2; };
+                if (n2 == 0 || fits(lo)) hi = lo;
+                for (int i = 0; i < 24 && hi > lo; ++i) {
+                    const double mid = 0.5 * (lo + hi);
+                    (fits(mid) ? hi : lo) = mid;
+                }
+                const double time = hi + merge;
+                if (time < best_time * 0.98) {  // (in doubt the simpler shape)
+                    best_time = time;
+                    best = {1 << gi, tg, real, (int)keys, text_first};
+                }
+            }
+        }
+    }
+    return best;
 }
 
 // Validates the arguments of a forward call and fills the kernel parameters.
@@ -641,8 +805,28 @@ static int prepare_forward(clear_attn_ctx* ctx, const void* Q, const void* K, co
             if (rc != CLEAR_OK) return rc;
         }
     }
-    const Schedule& s = tt->sched;
-    const long long n_q_tiles = (long long)s.n_qty * s.n_qtx;
+    int n_qty = tt->sched.n_qty, n_qtx = tt->sched.n_qtx, qth = tt->sched.qth;
+    const int own_y0 = band ? band->own_y0 + y_shift : 0, own_y1 = band ? band->own_y1 + y_shift : gridH;  // in tile coordinates
+    const long long NV = band ? (long long)(band->text_keys ? n_text : 0) + (long long)(band->own_y1 - band->own_y0) * gridW : N;
+    const int n_classes = ctx->mask_kind == CLEAR_MASK_STRIDED ? r * r : 1;
+    ForwardShape shape = {1, 1, 1, kKeyTileKeys, false};
+    const ForwardTables* ft = &tt->fwd[0];
+    if (ctx->dtype == CLEAR_BF16) {
+        // (decided once per context, B*H and band)
+        clear_attn_ctx::ShapeOf& of = ctx->shape_of;
+        if (of.BH != BH || of.tables != tt || of.own_y0 != own_y0 || of.own_y1 != own_y1 || of.NV != NV) {
+            int n_image_tiles[3] = {};
+            for (int i = 0; i < 3; ++i)
+                if (tt->fwd[i].qth) n_image_tiles[i] = ((own_y1 + tt->fwd[i].qth - 1) / tt->fwd[i].qth - own_y0 / tt->fwd[i].qth) * tt->fwd[i].n_qtx;
+            if (n_classes > 1) n_image_tiles[0] = n_qty * n_qtx;
+            const ForwardShape sh = choose_forward_shape(ctx, *tt, BH, NV, n_image_tiles, n_classes);
+            of = {BH, own_y0, own_y1, NV, tt, sh.groups, sh.tq_groups, sh.n_splits, sh.split_keys, sh.text_first};
+        }
+        shape = {of.groups, of.tq_groups, of.n_splits, of.split_keys, of.text_first};
+        ft = &tt->fwd[shape.groups == 4 ? 2 : shape.groups - 1];
+        n_qty = ft->n_qty; n_qtx = ft->n_qtx; qth = ft->qth;
+    }
+    const long long n_q_tiles = (long long)n_qty * n_qtx;
     if (n_q_tiles * BH > 0x7fffffffLL) return fail(ctx, CLEAR_ERR_INVALID_ARG, "too many workgroups: B*H*query tiles must fit in 31 bits");
 
     FwdParams p;
@@ -652,16 +836,17 @@ static int prepare_forward(clear_attn_ctx* ctx, const void* Q, const void* K, co
     p.B = B; p.H = H; p.n_text = n_text; p.gridH = gridH; p.gridW = gridW; p.r2 = r * r;
     p.N = N;
     p.n_q_tiles = (int)n_q_tiles;
-    p.n_qtx = s.n_qtx;
-    p.n_ktx = s.n_ktx;
-    p.row_ptr = tt->d_row_ptr;
-    p.col_idx = tt->d_col_idx;
-    p.n_plain = tt->d_n_plain;
-    p.qt_order = band ? nullptr : tt->d_qt_order;  // (a band launches a range of tile rows)
-    p.mask_tbl = tt->d_mask_tbl;
-    p.wave_desc = tt->d_wave_desc;
-    p.mask_ry = tt->mask_ry;
-    p.mask_rx = tt->mask_rx;
+    p.n_qtx = n_qtx;
+    p.row_ptr = ctx->dtype == CLEAR_BF16 ? ft->d_row_ptr : tt->d_row_ptr;
+    p.col_idx = ctx->dtype == CLEAR_BF16 ? ft->d_col_idx : tt->d_col_idx;
+    p.qt_order = band || shape.groups > 1 ? nullptr : tt->d_qt_order;  // (a band launches a range of tile rows)
+    p.program = ft->d_words;
+    p.program_ptr = ft->d_ptr;
+    p.block_masks = tt->d_block_masks;
+    p.groups = shape.groups;
+    p.tq_groups = shape.tq_groups;
+    p.text_words = ft->text_words[p.tq_groups / 2];
+    p.text_first = shape.text_first;
     p.y_shift = y_shift;
     p.mask_kind = ctx->mask_kind; p.mask_r = r; p.mask_shift = ctx->mask_shift;
     p.n_classes = 1; p.stride = 1; p.stride_rx = p.stride_ry = 0;
@@ -673,22 +858,19 @@ static int prepare_forward(clear_attn_ctx* ctx, const void* Q, const void* K, co
         if (n_q_tiles * BH * p.n_classes > 0x7fffffffLL) return fail(ctx, CLEAR_ERR_INVALID_ARG, "too many workgroups: B*H*r*r*query tiles must fit in 31 bits");
     }
     p.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)head_dim));
-    p.own_y0 = 0;
-    p.own_y1 = gridH;
+    p.own_y0 = own_y0;
+    p.own_y1 = own_y1;
     p.qt_begin = 0;
     p.n_q_tiles_launch = (int)n_q_tiles;
-    p.NV = N;
+    p.NV = NV;
     p.vkeys_text = 0x7fffffff;
     p.vshift = 0;
     if (band) {
-        p.own_y0 = band->own_y0 + y_shift;  // in tile coordinates
-        p.own_y1 = band->own_y1 + y_shift;
-        const int ty0 = p.own_y0 / s.qth, ty1 = (p.own_y1 + s.qth - 1) / s.qth;  // tile rows that hold owned rows
-        p.qt_begin = ty0 * s.n_qtx;
-        p.n_q_tiles_launch = (ty1 - ty0) * s.n_qtx;
+        const int ty0 = p.own_y0 / qth, ty1 = (p.own_y1 + qth - 1) / qth;  // tile rows that hold owned rows
+        p.qt_begin = ty0 * n_qtx;
+        p.n_q_tiles_launch = (ty1 - ty0) * n_qtx;
         // keys of the text queries: [the text keys,] then the owned image rows
         p.vkeys_text = band->text_keys ? n_text : 0;
-        p.NV = (long long)p.vkeys_text + (long long)(band->own_y1 - band->own_y0) * gridW;
         p.vshift = (int)((long long)n_text + (long long)band->own_y0 * gridW - p.vkeys_text);
         p.band_o = band->text_o;
         p.band_lse = band->text_lse;
@@ -697,8 +879,9 @@ static int prepare_forward(clear_attn_ctx* ctx, const void* Q, const void* K, co
     if (n_text > 0) {
         if (ctx->dtype == CLEAR_BF16) {
             const int per_block = bf16_text_queries_per_block();
-            p.n_tq_tiles = (n_text + per_block - 1) / per_block;
-            choose_text_splits(p.NV, BH, p.n_tq_tiles, ctx->num_cus, launches_together(ctx, p), &p.n_splits, &p.split_keys);
+            p.n_tq_tiles = (n_text * p.tq_groups + per_block - 1) / per_block;
+            p.n_splits = shape.n_splits;
+            p.split_keys = shape.split_keys;
         }
         if (noalloc) {
             // partial outputs, then (maximum, denominator) pairs, both inside the static scratch array
@@ -956,6 +1139,18 @@ int clear_attn_reserve_backward(clear_attn_ctx* ctx, int BH)
     if (ctx->dtype != CLEAR_BF16) return fail(ctx, CLEAR_ERR_UNSUPPORTED, "the backward pass is built for bf16 only");
 
     if (BH <= ctx->bwd_BH) return CLEAR_OK;
+    if (!ctx->t.lists) {
+        hipError_t e = hipErrorOutOfMemory;
+        try {
+            e = build_lists(ctx->gridH, ctx->gridW, ctx->r, ctx->dtype, ctx->mask_kind, ctx->mask_shift, &ctx->t);
+        } catch (const std::bad_alloc&) {
+            return fail(ctx, CLEAR_ERR_ALLOC, "out of host memory building the backward tile lists");
+        }
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(ctx, e == hipErrorOutOfMemory ? CLEAR_ERR_ALLOC : CLEAR_ERR_HIP, std::string("HIP error building the backward tile lists: ") + hipGetErrorString(e));
+        }
+    }
     if (ctx->d_bwd_delta) (void)hipFree(ctx->d_bwd_delta);
     if (ctx->d_bwd_ws) (void)hipFree(ctx->d_bwd_ws);
     ctx->d_bwd_delta = ctx->d_bwd_ws = nullptr;
@@ -1187,7 +1382,7 @@ int clear_attn_executed_pairs(const clear_attn_ctx* ctx, unsigned long long* pai
     if (ctx->mask_kind == CLEAR_MASK_STRIDED)
         *pairs_per_head = executed_pairs_bf16_strided(ctx->t.sched, ctx->n_text, ctx->gridH, ctx->gridW, ctx->r, ctx->mask_shift);
     else
-        *pairs_per_head = (ctx->dtype == CLEAR_BF16) ? executed_pairs_bf16(ctx->t.sched, ctx->n_text, 0) : executed_pairs_f32(ctx->t.sched, ctx->n_text);
+        *pairs_per_head = (ctx->dtype == CLEAR_BF16) ? executed_pairs_bf16(ctx->t.sched, ctx->n_text, 0, false) : executed_pairs_f32(ctx->t.sched, ctx->n_text);
     return CLEAR_OK;
 }
 

@@ -40,7 +40,8 @@ long long schedule_pair_bound(int gridH, int gridW, int r, int qth, int qtw, int
 constexpr long long kMaxSchedulePairs = 1LL << 28;  // 2.4 GB of host and device tables; create refuses more
 unsigned long long mask_count(int n_text, int gridH, int gridW, int r, int mask_kind = 0, int mask_shift = 0);
 // Pairs fed to the matrix pipeline per (batch, head) by the bf16 kernels (image pass + text-query pass).
-unsigned long long executed_pairs_bf16(const Schedule& s, int n_text, int text_split_keys);
+// whole_tiles: a wave runs both 32-key blocks of a tile it reaches (the backward kernels' masked tiles); otherwise blocks one by one.
+unsigned long long executed_pairs_bf16(const Schedule& s, int n_text, int text_split_keys, bool whole_tiles = true);
 // The same for a strided context (s: the schedule of the class sub-grid; gridH, gridW: the real grid).
 unsigned long long executed_pairs_bf16_strided(const Schedule& s, int n_text, int gridH, int gridW, int stride, int layer);
 // Pairs the fp32 path multiplies: 4 x 4 query patches against the cells of 16 keys they reach.
@@ -52,6 +53,48 @@ struct TensorStrides {
     long long sb, sh, sn;
 };
 
+// Programs of the bf16 forward kernels' computing waves: a word per 32-key block of the wave's key list, in stage order
+// (a stage: 2 tiles at head_dim 128, 4 at 64; the text tiles first, then the listed image tiles).
+constexpr unsigned kProgramPlaceMask = 15;       // where the block lies in its stage buffer, in units of 2 KB
+constexpr int kProgramMaskShift = 4;             // bits 4 .. 29: its lane masks (an id)
+constexpr unsigned kProgramStageEnd = 1u << 31;  // the wave's last word of this stage
+constexpr unsigned kProgramNoBlock = 1u << 30;   // nothing to do in this stage (only where the word before it masks everything out)
+constexpr unsigned kProgramFlags = kProgramStageEnd | kProgramNoBlock | kProgramPlaceMask;
+constexpr unsigned kMaskIdNone = 0;       // every pair of the block is admitted
+constexpr unsigned kMaskIdNothing = 1;    // none is
+constexpr unsigned kMaskIdFirstKeys = 1;  // + k, 1 <= k < 32: the first k keys of the block are
+constexpr unsigned kMaskIdFree = 33;      // masks of image blocks from here on
+constexpr int bf16_tiles_per_stage(int head_dim) { return head_dim == 64 ? 4 : 2; }
+struct BlockPrograms {
+    std::vector<unsigned> words;               // two spare words at the end
+    std::vector<unsigned> ptr;                 // [variants][n_q_tiles][kBf16NWY * kBf16NWX]: where a wave's program starts
+    double mean_stages, mean_steps;            // of a query tile: stages, blocks per wave
+    unsigned text_words[3];                    // for 1, 2, 4 waves per patch of text queries: [wave][keys of the stage][blocks per stage / waves]
+                                               // words of a stage with that many keys (0: a whole stage that is not the last)
+};
+// Query tiles whose lists and programs are the same but for their place: interior ones, mostly.
+struct QueryTilePatterns {
+    std::vector<int> id;     // per query tile: its pattern
+    std::vector<int> first;  // per pattern: the first query tile that has it
+};
+QueryTilePatterns query_tile_patterns(const Schedule& s);
+// Tile lists of the bf16 forward kernels (per query tile, origins row << 16 | col): pairs of a tile and its point mirror through the
+// centre of the query tile (a stage at head_dim 128: what one wave's queries do not reach of it another's do), in the order of
+// their place on the raster modulo 4 x 4 tiles, which is the same for both of a pair, whatever query tile it is seen from:
+// query tiles whose windows overlap then need a key tile at about the same step of their lists.
+void order_forward_tiles(const Schedule& s, const QueryTilePatterns& pat, std::vector<int>* k_col);
+struct ProgramInput {
+    const Schedule* sched;  // query tiles of 16 / groups rows
+    const QueryTilePatterns* pat;
+    const std::vector<int>* k_col;  // its tile lists (order_forward_tiles)
+    int groups;                     // waves a query patch's blocks are dealt to, in turn
+};
+// Programs for one or several numbers of waves per patch; masks, for all of them: [mask id][16 score registers], bit l = lane l keeps the
+// score.  stride > 1 (strided mask): the schedule is that of a residue class on its larger extents, and there are four variants, as the
+// keys' class has gridH / stride or one more rows, gridW / stride or one more columns.
+void build_block_programs(const std::vector<ProgramInput>& in, int n_text, int head_dim, int stride, int gridH, int gridW,
+                          std::vector<BlockPrograms>* out, std::vector<unsigned long long>* masks);
+
 struct FwdParams {
     const void* Q;
     const void* K;
@@ -62,15 +105,15 @@ struct FwdParams {
     long long N;       // tokens per (batch, head)
     int n_q_tiles;     // image query tiles per head
     int n_qtx;         // query tiles per tile row
-    int n_ktx;         // key tiles per tile row
     const int* row_ptr;  // device CSR
-    const int* col_idx;  // per query tile: key tile origins (row << 16 | col), tiles inside the grid first (ascending), then the ones cut by the border
-    const int* n_plain;  // per query tile: how many of its key tiles lie inside the grid
+    const int* col_idx;  // per query tile: key tile origins (row << 16 | col)
     const int* qt_order;  // bf16 image-query kernel, whole-grid launches: the query tile that the i-th workgroup of a head takes (null: i)
-    const unsigned long long* mask_tbl;  // bf16 kernels: lane masks per relative block offset (may be null)
-    int mask_ry, mask_rx;
-    const int* wave_desc;  // bf16 kernels, with mask_tbl: per listed key tile (kernel order) and wave of the workgroup, the mask-table
-                           // entries of the tile's two blocks (low / high 16 bits), or kWaveSkipsTile (see build_wave_descriptors)
+    const unsigned* program;      // bf16 kernels: the wave programs (BlockPrograms on the device)
+    const unsigned* program_ptr;
+    const unsigned long long* block_masks;
+    unsigned text_words;          // where the text-query rows' words lie among the programs, for tq_groups
+    bool text_first;              // bf16, one launch for both: the text-query workgroups go first
+    int groups, tq_groups;  // bf16 kernels: waves that share a patch of 32 queries (1, 2 or 4), image and text-query rows
     float scale_log2e;  // log2(e) / sqrt(head_dim)
     // text-query pass: dense rows split along the keys, partial results merged afterwards
     int n_tq_tiles;   // text query tiles per head
@@ -112,7 +155,7 @@ hipError_t launch_bf16_d128(const FwdParams& p, hipStream_t stream, int phase);
 hipError_t launch_bf16_d64(const FwdParams& p, hipStream_t stream, int phase);
 hipError_t launch_f32_d64(const FwdParams& p, hipStream_t stream, int phase);
 int bf16_text_queries_per_block();
-// What each wave of a bf16 workgroup does with each listed key tile that lies inside the grid (those are masked from the
+// What each wave of a bf16 backward workgroup does with each listed tile that lies inside the grid (those are masked from the
 // table): desc[e * waves + w] for entry e of the kernel-order tile list `k_col` (origins row << 16 | col) and wave w
 // (patch row w / 2, patch column w % 2 of the query tile) = table entry of block 0 | table entry of block 1 << 16,
 // where a block that is wholly admitted takes the all-ones entry and one out of reach the all-zeros entry; or
@@ -141,12 +184,14 @@ struct BwdParams {
     long long N;
     int n_q_tiles, n_qtx;
     const int* row_ptr;
-    const int* col_idx;
-    const int* n_plain;
+    const int* col_idx;  // tiles inside the grid first, then the ones cut by the border
+    const int* n_plain;  // per row tile: how many of its tiles lie inside the grid
     const int* qt_order;  // as in FwdParams
-    const unsigned long long* mask_tbl;
+    const unsigned long long* mask_tbl;  // lane masks per relative block offset (may be null)
     int mask_ry, mask_rx;
-    const int* wave_desc;  // as in FwdParams (rows and columns swap roles for dK and dV; the masks with a table are symmetric)
+    const int* wave_desc;  // with mask_tbl: per listed tile inside the grid (kernel order) and wave of the workgroup, the mask-table
+                           // entries of the tile's two blocks (low / high 16 bits), or kWaveSkipsTile (build_wave_descriptors; rows
+                           // and columns swap roles for dK and dV: the masks with a table are symmetric)
     int mask_kind, mask_r, mask_shift;  // MaskKind, radius / window size, Swin shift
     int n_classes, stride, stride_rx, stride_ry;  // strided mask, as in FwdParams (otherwise 1, 1, 0, 0)
     float scale_log2e;  // log2(e) / sqrt(head_dim)

@@ -11,13 +11,23 @@
 // 8*(reg/4) + 4*(l/32) + reg%4 of every 32 x 32 accumulator tile, so the row maximum and the
 // softmax denominator of Eq. 1 need one exchange with lane l ^ 32 and no LDS round trip.
 //
-// A workgroup of NWY x NWX waves owns a (4*NWY) x (8*NWX) patch of image queries (or 32*NWY*NWX
-// text queries) and walks a list of 64-key tiles: the text keys, then the 8 x 8 image key tiles its
-// schedule row lists (Sec. 3.2: text keys for every query, image keys inside the radius-r disc).
-// K and V tiles are staged in LDS once per workgroup, by four further waves that do nothing else
-// (one per SIMD, one stage ahead of the computing waves, one workgroup barrier per stage); every
-// computing wave classifies each 32-key block against its own 4 x 8 query patch and skips the blocks
-// its disc cannot reach.
+// A workgroup of 8 computing waves owns a 16 x 16 patch of image queries (or 256 text queries), 32 queries per wave, and
+// walks a list of 64-key tiles: the text keys, then the 8 x 8 image key tiles its schedule row lists (Sec. 3.2: text
+// keys for every query, image keys inside the radius-r disc).  K and V tiles are staged in LDS once per workgroup, by
+// four further waves that do nothing else (one per SIMD, one stage ahead of the computing waves, one workgroup
+// barrier per stage).
+//
+// Every computing wave follows a program of its own, made on the host (build_block_programs): one word per 32-key
+// block its queries reach, with the block's place in the stage and its lane masks.  The blocks run as one software
+// pipeline across stages and barriers: the S product of a block is issued together with the exponentials and the P V
+// product of the block before it.
+//
+// What bounds it: for one or two rounds of workgroups, cycles - a workgroup takes about 16 000 and 900 a stage beside the 520 that a SIMD's
+// two blocks take, 384 of them matrix cycles -; for large grids the chip's power budget, so bytes and instructions count there and
+// waiting hardly does (order_forward_tiles: a third less L2 misses took 5 % of the time; 9 % fewer cycles of waiting took none).
+// Against the version that worked by 64-key tiles inside a stage, with index arithmetic and masks per element at the grid's border,
+// and a launch and a merge pass of its own for the text queries (24 heads, head_dim 128, 512 text tokens): 32 x 32 grid, r = 8:
+// 48.6 -> 31.6 us; 64 x 64, r = 16: 132 -> 114 us; 512 x 512, r = 16: 8.00 -> 7.67 ms; 192 x 320, r = 32: 3.66 -> 3.46 ms.
 #include <hip/hip_runtime.h>
 
 #include "bf16_common.h"
@@ -36,36 +46,40 @@
 namespace clear {
 namespace {
 
-// Careful pass, one staged tile: block by block, exact running maximum, O and the denominator rescaled
-// at every block (Eq. 1 as a textbook online softmax).  Slow; only runs when the fast pass gave up.
-template <int CODE>
-__device__ __forceinline__ void careful_stage(WaveState& ws, const bf16x8 (&qf)[KS], const LaneOffsets& lo, unsigned tile_lds,
-                                              int cls0, int cls1, bool linear, const MaskArgs& ma)
+constexpr int NW = kBf16NWY * kBf16NWX;  // computing waves
+constexpr int NLW = 4;                   // loading waves
+constexpr int STAGE_HALF = TPS * TILE_BYTES;  // K (or V) of one stage: 32 KB
+// K is double-buffered.  V is needed one block longer than K, past the barrier that ends its stage, and has three buffers:
+// 160 KB together, all the LDS of a CU.
+constexpr int NKBUF = 2, NVBUF = 3;
+constexpr int FWD_LDS_BYTES = (NKBUF + NVBUF) * STAGE_HALF;
+constexpr int FLAG_BYTES = 64;  // at the end of the LDS, used between passes only
+constexpr int BLOCKS_PER_STAGE = 2 * TPS;
+
+// LDS layout of a staged tile (64 tokens x D channels): planes of 32 channels (64 bytes), each 64 rows x 64 bytes = 4 KB,
+// filled by 1 KB load instructions of 16 rows x 64 bytes (lane i: slot i % 4 of row i / 4; four neighbouring lanes read 64
+// contiguous bytes).  Inside a row of 64 bytes the 16-byte chunk q sits in slot q ^ plane_swz(row).  Both operand reads
+// are then free of bank conflicts, and their addresses are one of two per-lane offsets plus a constant that fits
+// the instruction: no address arithmetic per operand.
+__device__ __forceinline__ int plane_swz(int row) { return (((row >> 2) & 1) << 1) | ((row >> 3) & 1); }
+constexpr int PLANE_BYTES = TILE_KEYS * 64;
+constexpr int NPLANE = D / 32;
+static_assert(NPLANE * PLANE_BYTES == TILE_BYTES, "a tile is NPLANE planes");
+
+// K operand, contraction step ks: chunk 2 ks + hh of key row qi.  `base`: lane offset for even / odd ks + block address.
+__device__ __forceinline__ bf16x8 read_k(const unsigned (&base)[2], int ks)
 {
-    const TileAddr ta = tile_addr(tile_lds, lo);
-#pragma unroll 1
-    for (int kb = 0; kb < 2; ++kb) {
-        const int cls = kb ? cls1 : cls0;
-        if (cls == kBlockSkip) continue;
-        f32x16 s = qk_block(ta, kb, qf);
-        if (cls == kBlockPartial) {
-            if (linear)
-                apply_mask<kMaskLinear, CODE>(s, kb, ma);
-            else
-                apply_mask<kMaskImage, CODE>(s, kb, ma);
-        }
-        const float m_new = fmaxf(ws.m_run, wave_pair_max(max_block(s)));
-        const float alpha = __builtin_amdgcn_exp2f((ws.m_run - m_new) * ws.c);
-        ws.l_run *= alpha;
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) ws.oacc[db][r] *= alpha;
-        ws.m_run = m_new;
-        bf16x8 pf[2];
-        ws.l_run += exp_block(s, ws.c, m_new * ws.c, pf);
-        pv_block(ws.oacc, ta, kb, pf);
-    }
+    return *(lds_bf16x8_ptr)(size_t)(base[ks & 1] + (unsigned)((ks >> 1) * PLANE_BYTES));
+}
+// V^T operand for keys 16 s2 + 4 hh + {0..3} and 16 s2 + 8 + 4 hh + {0..3} of the block, channels 32 db .. 32 db + 31: two 16-bit
+// transpose reads.  Within 16 lanes, lane j addresses row j / 4 and channels 4 (j % 4) .. + 3 of the group's 16-channel slice.
+__device__ __forceinline__ bf16x8 read_v(const unsigned (&base)[2], int s2, int db)
+{
+    const unsigned imm = (unsigned)(db * PLANE_BYTES + s2 * 1024);
+    union { struct { short4v lo, hi; } h; bf16x8 v; } u;
+    u.h.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(size_t)(base[0] + imm));
+    u.h.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(size_t)(base[1] + imm));
+    return u.v;
 }
 
 // Reference maximum of the fast pass: a query adopts the maximum of the first block in which it sees an
@@ -77,167 +91,22 @@ __device__ __forceinline__ void adopt_reference(WaveState& ws, float mx_pair)
     ws.m_run = (ws.m_run == M_INIT) ? fmaxf(mx_pair, M_INIT) : ws.m_run;
 }
 
-// Loading waves: CLEAR_LOADER_WAVES extra waves per workgroup do nothing but issue the staging loads, one stage
-// ahead of the computing waves, which then never stall on the memory pipeline's issue queue.  0 = every
-// wave stages its share of each tile itself, right after the stage barrier.
-#ifndef CLEAR_LOADER_WAVES
-#define CLEAR_LOADER_WAVES 4
-#endif
-constexpr int kLoaderWaves = CLEAR_LOADER_WAVES;
-
-// Fast pass, one staged tile.  The reference maximum of a query never moves once set, so O is only
-// ever touched by the matrix pipeline and there is no data-dependent branch.
-// The tile's two 32-key blocks run as one hand-ordered pipeline of 32 matrix instructions (head_dim 128;
-// 16 at head_dim 64, where every phase below is half as long and carries two score pairs per slot):
-//   slots  0- 7  S of block 0
-//   slots  8-15  S of block 1                      | mask, maximum, reference, P[0..7] of block 0
-//   slots 16-19  P V of block 0, keys of P[0..7]   | P[8..15] of block 0
-//   slots 20-23  P V of block 0, keys of P[8..15]  | mask, maximum, reference, P[0..7] of block 1
-//   slots 24-27  P V of block 1, keys of P[0..7]   | P[8..15] of block 1
-//   slots 28-31  P V of block 1, keys of P[8..15]
-// LDS operands are read two slots ahead of the matrix instruction that consumes them.
-// A wave runs the whole tile or none of it: a block its disc cannot reach is masked out entirely (its
-// scores become -inf, its P zero), which keeps one code shape for every tile of a loop.
-// ADOPT = true while some query of the wave still has no reference maximum (the first tiles): the block
-// maxima are formed and adopted.  ADOPT = false afterwards: no maximum is needed at all.
-template <int MASK, bool ADOPT, int CODE>
-__device__ __forceinline__ void fast_stage(WaveState& ws, const bf16x8 (&qf)[KS], const LaneOffsets& lo,
-                                           unsigned tile_lds, const MaskArgs& ma)
+// Lane masks of a block: 16 words, one per score register, kept in scalar registers from the block's S product to its
+// exponentials.
+struct MaskWords {
+    unsigned long long w[16];
+};
+__device__ __forceinline__ void mask_scores(f32x16& s, const MaskWords& mw)
 {
-    constexpr int kb0 = 0;
-    constexpr bool has1 = true;
-    const TileAddr ta = tile_addr(tile_lds, lo);
-    const float c = ws.c;
-    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    bf16x8 pf0[2], pf1[2];
-    float sum = 0.f;
-
-    // slots: [0, S1) S of block 0, [S1, PV0) S of block 1, [PV0, PV1) P V of block 0, [PV1, NSLOT) P V of block 1
-    constexpr int S1 = KS, PV0 = 2 * KS, PV1 = PV0 + 2 * NDB, NSLOT = PV1 + 2 * NDB;
-    // operand ring: K operands for the S slots, V operands for the P V slots (V slot i: s2 = (i / NDB) % 2, db = i % NDB)
-    auto k_operand = [&](int slot) { return read_k_operand(ta, slot / KS, slot % KS); };
-    auto v_operand = [&](int slot) {
-        const int i = slot - PV0;
-        return read_v_operand(ta, i / (2 * NDB), (i / NDB) & 1, i % NDB);
-    };
-    auto block1_slot = [](int slot) { return (slot >= S1 && slot < PV0) || slot >= PV1; };
-    // operands are read PD slots ahead into a ring of PD + 2 (the extra entry keeps a read from landing on
-    // the registers the previous matrix instruction is still reading)
-    constexpr int PD = CLEAR_OPERAND_PREFETCH, RING = PD + 2;
-    bf16x8 op[RING];
 #pragma unroll
-    for (int i = 0; i < PD; ++i) op[i] = k_operand(i);
-    f32x16 s0 = zero, s1 = zero;
-    float mc = ws.m_run * c, mc1 = mc;
-    // kMaskTable: the 16 lane masks of a block sit in scalar registers.  Block 0's are fetched before the
-    // pipeline starts (their latency overlaps that of the first LDS operands), block 1's as soon as block
-    // 0's have been used, a dozen slots before they are needed.
-    unsigned long long mw[16];
-    if (MASK == kMaskTable) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mw[r] = ma.row[kb0 & 1][r];
-    }
-    auto run_slot = [&](auto slot_tag) __attribute__((always_inline)) {
-        constexpr int slot = decltype(slot_tag)::value;
-        // prefetch the operand of slot + PD
-        if (slot + PD < NSLOT && (!block1_slot(slot + PD) || has1)) {
-            if (slot + PD < PV0)
-                op[(slot + PD) % RING] = k_operand(slot + PD);
-            else
-                op[(slot + PD) % RING] = v_operand(slot + PD);
-        }
-        // matrix instruction of this slot
-        constexpr int pv_i = slot >= PV0 ? slot - PV0 : 0, pv_db = pv_i % NDB, pv_s2 = (pv_i / NDB) & 1;
-        if (slot < S1)
-            s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], qf[slot], s0, 0, 0, 0);
-        else if (slot < PV0) {
-            if (has1) s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], qf[slot - S1], s1, 0, 0, 0);
-        } else if (slot < PV1)
-            ws.oacc[pv_db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], pf0[pv_s2], ws.oacc[pv_db], 0, 0, 0);
-        else if (has1)
-            ws.oacc[pv_db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], pf1[pv_s2], ws.oacc[pv_db], 0, 0, 0);
-        // vector work riding along
-        if (slot == S1) {
-            if (MASK == kMaskTable) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) s0[r] = __builtin_amdgcn_inverse_ballot_w64(mw[r]) ? s0[r] : -INFINITY;
-            } else {
-                apply_mask<MASK, CODE>(s0, kb0, ma);
-            }
-            if (ADOPT) {
-                adopt_reference(ws, wave_pair_max(max_block(s0)));
-                mc = ws.m_run * c;
-            }
-        }
-        if (slot == S1 + 1 && MASK == kMaskTable) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) mw[r] = ma.row[(kb0 + 1) & 1][r];
-        }
-        if (slot == PV0 && has1) {
-            if (MASK == kMaskTable) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) s1[r] = __builtin_amdgcn_inverse_ballot_w64(mw[r]) ? s1[r] : -INFINITY;
-            } else {
-                apply_mask<MASK, CODE>(s1, kb0 + 1, ma);
-            }
-            if (ADOPT) {
-                adopt_reference(ws, wave_pair_max(max_block(s1)));
-                mc1 = ws.m_run * c;
-            }
-        }
-        // Exponentials as a three-deep vector pipeline over pairs of scores, so that the instructions of
-        // one slot do not wait on each other: at head_dim 128 pair g of block 0 is scaled in slot 8 + g,
-        // exponentiated in slot 9 + g, summed and packed in slot 10 + g; block 1 runs the same eight slots
-        // later.  P[0..7] of a block is complete three slots before the matrix instruction that needs it.
-        // (head_dim 64: two pairs per slot from slot 4 on, block 1 four slots later.)
-#pragma unroll
-        for (int g = 0; g < 8; ++g) {
-            constexpr int PPS = 8 / KS;  // score pairs per slot
-            const int b0 = S1 + g / PPS, b1 = PV0 + g / PPS;
-            if (slot == b0) {
-                s0[2 * g] = __builtin_fmaf(s0[2 * g], c, -mc);
-                s0[2 * g + 1] = __builtin_fmaf(s0[2 * g + 1], c, -mc);
-            }
-            if (slot == b0 + 1) {
-                s0[2 * g] = __builtin_amdgcn_exp2f(s0[2 * g]);
-                s0[2 * g + 1] = __builtin_amdgcn_exp2f(s0[2 * g + 1]);
-            }
-            if (slot == b0 + 2) {
-                sum += s0[2 * g] + s0[2 * g + 1];
-                pf0[g >> 2][2 * (g & 3)] = (__bf16)s0[2 * g];
-                pf0[g >> 2][2 * (g & 3) + 1] = (__bf16)s0[2 * g + 1];
-            }
-            if (has1) {
-                if (slot == b1) {
-                    s1[2 * g] = __builtin_fmaf(s1[2 * g], c, -mc1);
-                    s1[2 * g + 1] = __builtin_fmaf(s1[2 * g + 1], c, -mc1);
-                }
-                if (slot == b1 + 1) {
-                    s1[2 * g] = __builtin_amdgcn_exp2f(s1[2 * g]);
-                    s1[2 * g + 1] = __builtin_amdgcn_exp2f(s1[2 * g + 1]);
-                }
-                if (slot == b1 + 2) {
-                    sum += s1[2 * g] + s1[2 * g + 1];
-                    pf1[g >> 2][2 * (g & 3)] = (__bf16)s1[2 * g];
-                    pf1[g >> 2][2 * (g & 3) + 1] = (__bf16)s1[2 * g + 1];
-                }
-            }
-        }
-        SCHED_FENCE();
-    };
-    static_for<NSLOT>(run_slot);  // (not a loop: one that contains inline asm is not unrolled)
-    ws.l_run += sum;
+    for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_inverse_ballot_w64(mw.w[r]) ? s[r] : -INFINITY;
 }
 
 // One workgroup of a forward launch: workgroup `bid` of `nblk` (image-query rows, or with TEXTQ the text-query rows).
-template <int NWY, int NWX, bool TEXTQ, int CODE>
+template <bool TEXTQ>
 __device__ __forceinline__ void clear_fwd_bf16_workgroup(const FwdParams& p, const int bid, const int nblk)
 {
-    constexpr int NW = NWY * NWX;
-    constexpr int NI = TILE_KEYS / ROWS_PER_LOAD / NW;  // 1 KB load instructions per wave per tile, for K and for V each, when every wave loads
-    static_assert(NI * NW * ROWS_PER_LOAD == TILE_KEYS, "the waves' load instructions cover the tile's 64 rows exactly");
-
-    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];  // [NBUF][TPS][K tile | V tile]
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];  // [NKBUF][TPS] K tiles, [NVBUF][TPS] V tiles
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
     const int tid = threadIdx.x;
@@ -245,13 +114,7 @@ __device__ __forceinline__ void clear_fwd_bf16_workgroup(const FwdParams& p, con
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int qi = lane & 31;   // query slot inside the wave's patch
     const int hh = lane >> 5;   // which half of the contraction slice this lane feeds
-    // waves NW .. NW + NLW - 1 only load; with NLW = 0 every wave loads its share (NI row groups per tile)
-    constexpr int NLW = kLoaderWaves;
-    static_assert(NLW > 0 || NBUF == 2, "without loading waves a stage is fetched while the one before it is computed");
-    constexpr int NI_L = NLW > 0 ? TILE_KEYS / ROWS_PER_LOAD / NLW : NI;
-    static_assert(NLW == 0 || NI_L * NLW * ROWS_PER_LOAD == TILE_KEYS, "the loading waves' instructions cover the tile's 64 rows exactly");
-    const bool loader = NLW > 0 && wave >= NW;
-    const int ldw = NLW > 0 ? wave - NW : wave;  // index among the waves that load
+    const bool loader = wave >= NW;
 
     // ---- workgroup -> (batch*head, query tile[, key split]); XCD-aware: workgroups are dealt
     // round-robin to the 8 XCDs, so give each XCD one contiguous range of the logical index.
@@ -261,16 +124,21 @@ __device__ __forceinline__ void clear_fwd_bf16_workgroup(const FwdParams& p, con
         const int q = nblk >> 3, rem = nblk & 7;
         vid = xcd * q + imin(xcd, rem) + idx;
     }
-    int bh, qt, split = 0;
+    int bh, qt, split = 0, variant = 0;
     // Image queries live on a qH x qW grid and their image keys on a kH x kW grid; grid point (y, x) is image
     // token (y * stride + oy, x * stride + ox) of the raster.  Plain masks: both are the raster itself.
     // Strided mask: the workgroup belongs to one residue class of the queries, (q_oy, q_ox) = (y % stride,
-    // x % stride), and reads the keys of the class moved by (stride_ry, stride_rx).
+    // x % stride), and reads the keys of the class moved by (stride_ry, stride_rx); the wave programs come in four
+    // variants, as the key class has the larger or the smaller extent on either axis.
     // Row bands may move the grid down by y_shift rows in these coordinates (so that a query tile starts at the first
     // owned row): grid rows then start at y_shift, and only where a token's address is formed is the shift taken off.
-    int stride = 1, q_oy = 0, q_ox = 0, k_oy = 0, k_ox = 0;
+    const int stride = TEXTQ ? 1 : p.stride;
+    int q_oy = 0, q_ox = 0, k_oy = 0, k_ox = 0;
     const int y_shift = TEXTQ ? 0 : p.y_shift;
-    int qH = p.gridH + y_shift, qW = p.gridW, kH = p.gridH + y_shift, kW = p.gridW;
+    int qH = p.gridH + y_shift, qW = p.gridW, kH = qH, kW = qW;
+    // `groups` waves share a patch of 32 queries and deal its key blocks out among themselves
+    const int groups = TEXTQ ? p.tq_groups : p.groups, patches = NW / groups;
+    const int patch = wave % patches, group = wave / patches;
     if (TEXTQ) {
         split = vid % p.n_splits;
         const int t = vid / p.n_splits;
@@ -280,10 +148,9 @@ __device__ __forceinline__ void clear_fwd_bf16_workgroup(const FwdParams& p, con
         qt = p.qt_begin + vid % p.n_q_tiles_launch;
         if (p.qt_order) qt = ((const_int_ptr)p.qt_order)[qt];  // the order in which a head's query tiles are dealt out
         bh = vid / p.n_q_tiles_launch;
-        if (CODE == kCodeFull) {
+        if (stride > 1) {
             const int cls = bh % p.n_classes;
             bh /= p.n_classes;
-            stride = p.stride;
             q_oy = cls / stride;
             q_ox = cls % stride;
             k_oy = (q_oy + p.stride_ry) % stride;
@@ -292,13 +159,97 @@ __device__ __forceinline__ void clear_fwd_bf16_workgroup(const FwdParams& p, con
             qW = (p.gridW - q_ox + stride - 1) / stride;
             kH = (p.gridH - k_oy + stride - 1) / stride;
             kW = (p.gridW - k_ox + stride - 1) / stride;
+            variant = 2 * (kH > p.gridH / stride) + (kW > p.gridW / stride);
         }
     }
     const int batch = bh / p.H, head = bh % p.H;
     const __bf16* const Qh = (const __bf16*)p.Q + batch * p.qs.sb + head * p.qs.sh;
-    const unsigned char* const Kh = (const unsigned char*)((const __bf16*)p.K + batch * p.ks.sb + head * p.ks.sh);
-    const unsigned char* const Vh = (const unsigned char*)((const __bf16*)p.V + batch * p.vs.sb + head * p.vs.sh);
-    const unsigned k_pitch = (unsigned)p.ks.sn * 2, v_pitch = (unsigned)p.vs.sn * 2;  // bytes from one token row to the next
+
+    // ---- stage list: the linear tiles (tokens [lin_begin, lin_limit), 64 a tile), then the image tiles of the CSR row, TPS to a
+    // stage; linear and image tiles do not share a stage
+    int n_lin_tiles, n_img_tiles = 0, csr_begin = 0;
+    int lin_begin = 0, lin_limit = 0;
+    if (TEXTQ) {
+        lin_begin = split * p.split_keys;
+        lin_limit = (long long)lin_begin + p.split_keys < p.NV ? lin_begin + p.split_keys : (int)p.NV;
+    } else {
+        const const_int_ptr row_ptr = (const_int_ptr)p.row_ptr;
+        lin_limit = p.n_text;
+        csr_begin = row_ptr[qt];
+        n_img_tiles = row_ptr[qt + 1] - csr_begin;
+    }
+    n_lin_tiles = (lin_limit - lin_begin + TILE_KEYS - 1) / TILE_KEYS;
+    const int n_lin_stages = (n_lin_tiles + TPS - 1) / TPS;
+    const int n_stages = n_lin_stages + (n_img_tiles + TPS - 1) / TPS;
+
+    unsigned* const flags = (unsigned*)(smem + FWD_LDS_BYTES - FLAG_BYTES);
+    if (loader) {
+        // A loading wave stays one stage ahead of the computing waves: after the barrier that hands stage s over, everyone has
+        // left K of stage s - 1 and V of stage s - 2, whose buffers take stage s + 1.  It covers 16 rows of every tile.
+        const int ldw = wave - NW;
+        const unsigned char* const Kh = (const unsigned char*)((const __bf16*)p.K + batch * p.ks.sb + head * p.ks.sh);
+        const unsigned char* const Vh = (const unsigned char*)((const __bf16*)p.V + batch * p.vs.sb + head * p.vs.sh);
+        const unsigned k_pitch = (unsigned)p.ks.sn * 2, v_pitch = (unsigned)p.vs.sn * 2;  // bytes from one token row to the next
+        const int row = 16 * ldw + (lane >> 2);
+        const unsigned chunk_off = (unsigned)(((lane & 3) ^ plane_swz(row)) << 4);
+        const const_int_ptr col_idx = (const_int_ptr)p.col_idx;
+        auto issue_tile = [&](int token, unsigned k_tile, unsigned v_tile) __attribute__((always_inline)) {
+            const unsigned ko = (unsigned)token * k_pitch + chunk_off, vo = (unsigned)token * v_pitch + chunk_off;
+            auto load_plane = [&](auto pl_tag) __attribute__((always_inline)) {
+                constexpr int pl = decltype(pl_tag)::value;
+                load_to_lds_16B(Kh, ko + pl * 64, k_tile + pl * PLANE_BYTES + ldw * 1024);
+                load_to_lds_16B(Vh, vo + pl * 64, v_tile + pl * PLANE_BYTES + ldw * 1024);
+            };
+            static_for<NPLANE>(load_plane);  // (not a loop: one that contains inline asm is not unrolled)
+        };
+        auto issue_stage = [&](int s, int kb, int vb) {
+            auto load_tile = [&](auto j_tag) __attribute__((always_inline)) {
+                constexpr int j = decltype(j_tag)::value;
+                const unsigned k_tile = lds_base + (unsigned)(kb * STAGE_HALF + j * TILE_BYTES), v_tile = lds_base + (unsigned)((NKBUF + vb) * STAGE_HALF + j * TILE_BYTES);
+                // addresses are clamped to valid tokens: slots beyond the range or the grid are masked in the compute
+                if (s < n_lin_stages) {
+                    const int i = s * TPS + j;
+                    if (i >= n_lin_tiles) return;
+                    int token = imin(lin_begin + i * TILE_KEYS + row, lin_limit - 1);
+                    if (TEXTQ && token >= p.vkeys_text) token += p.vshift;  // position in the key list -> token
+                    issue_tile(token, k_tile, v_tile);
+                } else {
+                    const int i = (s - n_lin_stages) * TPS + j;
+                    if (i >= n_img_tiles) return;
+                    const int packed = col_idx[csr_begin + i];  // tile origin, row << 16 | col
+                    const int ky = imax(imin((packed >> 16) + (row >> 3), kH - 1) - y_shift, 0);  // (rows above the grid: out of every owned query's reach)
+                    const int kx = imin((packed & 0xffff) + (row & 7), kW - 1);
+                    issue_tile(p.n_text + (ky * stride + k_oy) * p.gridW + kx * stride + k_ox, k_tile, v_tile);
+                }
+            };
+            static_for<TPS>(load_tile);
+        };
+        auto loader_pass = [&]() {
+            int kb = 0, vb = 0;
+            if (n_stages > 0) issue_stage(0, 0, 0);
+            for (int s = 0; s < n_stages; ++s) {
+                wait_vmcnt<0>();
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                kb ^= 1;
+                vb = vb + 1 == NVBUF ? 0 : vb + 1;
+                if (s + 1 < n_stages) issue_stage(s + 1, kb, vb);
+            }
+        };
+        loader_pass();
+        __syncthreads();
+        __syncthreads();
+        unsigned redo = 0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) redo |= flags[i];
+        if (__builtin_amdgcn_readfirstlane(redo) != 0) {
+            __syncthreads();
+            loader_pass();
+            __syncthreads();
+        }
+        if (groups > 1) __syncthreads();
+        return;
+    }
 
     // ---- this lane's query
     int wy0 = 0, wx0 = 0;  // origin of the wave's 4 x 8 query patch (image mode)
@@ -306,14 +257,14 @@ __device__ __forceinline__ void clear_fwd_bf16_workgroup(const FwdParams& p, con
     int q_token;
     bool q_valid, wave_has_queries;
     if (TEXTQ) {
-        const int q0 = qt * (NW * 32) + wave * 32;
+        const int q0 = (qt * patches + patch) * kTextQueriesPerWave;
         q_token = q0 + qi;
         q_valid = q_token < p.n_text;
         wave_has_queries = q0 < p.n_text;
         if (!q_valid) q_token = p.n_text - 1;
     } else {
-        wy0 = (qt / p.n_qtx) * (NWY * kWaveQH) + (wave / NWX) * kWaveQH;
-        wx0 = (qt % p.n_qtx) * (NWX * kWaveQW) + (wave % NWX) * kWaveQW;
+        wy0 = ((qt / p.n_qtx) * (patches / kBf16NWX) + patch / kBf16NWX) * kWaveQH;
+        wx0 = (qt % p.n_qtx) * (kBf16NWX * kWaveQW) + (patch % kBf16NWX) * kWaveQW;
         qy = wy0 + (qi >> 3);
         qx = wx0 + (qi & 7);
         // (row-band mode: only the rows [own_y0, own_y1) carry queries; the halo rows are keys only)
@@ -328,243 +279,55 @@ __device__ __forceinline__ void clear_fwd_bf16_workgroup(const FwdParams& p, con
         const __bf16* qrow = Qh + (long long)q_token * p.qs.sn + 8 * hh;
 #pragma unroll
         for (int s = 0; s < KS; ++s)  // (read once: non-temporal, so that the rows do not push K and V tiles out of the L2)
-            if (!loader) qf[s] = __builtin_nontemporal_load((const bf16x8*)(qrow + 16 * s));
+            qf[s] = __builtin_nontemporal_load((const bf16x8*)(qrow + 16 * s));
     }
-    const const_int_ptr row_ptr = (const_int_ptr)p.row_ptr, col_idx = (const_int_ptr)p.col_idx, n_plain = (const_int_ptr)p.n_plain;
-    const const_u64_ptr mask_tbl = (const_u64_ptr)p.mask_tbl;
 
-    // ---- tile list: tokens [lin_begin, lin_limit) in 64-key tiles, then (image mode) the CSR row.
-    // Tiles fall into four consecutive categories, each with its own code shape:
-    //   [cb0, cb1) whole linear tiles   [cb1, cb2) the ragged linear tile (at most one)
-    //   [cb2, cb3) image tiles inside the grid (masks from the table)   [cb3, cb4) image tiles cut by the border
-    // A stage is up to TPS consecutive tiles of one category.
-    int n_tiles, n_lin_tiles, csr_begin = 0;
-    int lin_begin = 0, lin_limit = 0;
+    // ---- the wave's program.  Image-query rows: its own words.  Text-query rows: every stage but the last takes the same words again.
+    const const_u32_ptr words = (const_u32_ptr)p.program;
+    const const_u64_ptr mask_words = (const_u64_ptr)p.block_masks;
+    constexpr int STAGE_KEYS = TPS * TILE_KEYS;
+    unsigned pc_first, pc, pc_wrap, pc_tail = 0;
+    int whole_left = 0;  // text: stages before the last one
     if (TEXTQ) {
-        lin_begin = split * p.split_keys;
-        lin_limit = (long long)lin_begin + p.split_keys < p.NV ? lin_begin + p.split_keys : (int)p.NV;
-        n_lin_tiles = (lin_limit - lin_begin + TILE_KEYS - 1) / TILE_KEYS;
-        n_tiles = n_lin_tiles;
+        const int per_stage = BLOCKS_PER_STAGE / groups;
+        pc_first = p.text_words + (unsigned)(group * (STAGE_KEYS + 1) * per_stage);
+        pc_tail = pc_first + (unsigned)((lin_limit - lin_begin - (n_stages - 1) * STAGE_KEYS) * per_stage);
     } else {
-        lin_limit = p.n_text;
-        n_lin_tiles = (p.n_text + TILE_KEYS - 1) / TILE_KEYS;
-        csr_begin = row_ptr[qt];
-        n_tiles = n_lin_tiles + (row_ptr[qt + 1] - csr_begin);
+        pc_first = ((const_u32_ptr)p.program_ptr)[((long long)variant * p.n_q_tiles + qt) * NW + wave];
     }
-    const int cb1 = (lin_limit - lin_begin) / TILE_KEYS, cb2 = n_lin_tiles;
-    constexpr bool dense_image = !TEXTQ && CODE == kCodeFull;  // strided: tiles inside the class grid need no mask
-    const int cb3 = TEXTQ ? n_lin_tiles : ((p.mask_tbl || dense_image) ? n_lin_tiles + n_plain[qt] : n_lin_tiles);
-    const int cb4 = n_tiles;
-    auto stage_len = [&](int t) {  // tiles in the stage that starts at tile t
-        const int e = t < cb1 ? cb1 : (t < cb2 ? cb2 : (t < cb3 ? cb3 : cb4));
-        return imin(TPS, e - t);
-    };
-
-    // Tile origin: linear -> (first token, -1); image -> (row, col) of the 8 x 8 tile.
-    auto tile_origin = [&](int i, int& a, int& b) {
-        if (i < n_lin_tiles) {
-            a = lin_begin + i * TILE_KEYS;
-            b = -1;
-        } else {
-            const int packed = col_idx[csr_begin + i - n_lin_tiles];  // tile origin, row << 16 | col
-            a = packed >> 16;
-            b = packed & 0xffff;
+    auto start_program = [&]() {
+        pc = pc_first;
+        pc_wrap = ~0u;
+        if (TEXTQ) {
+            whole_left = n_stages - 1;
+            if (whole_left == 0) pc = pc_tail;
+            else pc_wrap = pc_first + BLOCKS_PER_STAGE / groups;
         }
     };
-
-    // ---- LDS-direct staging.  Load instruction ii of a tile covers ROWS_PER_LOAD rows (4 at head_dim 128); lane i
-    // writes slot i % CHUNKS of row ROWS_PER_LOAD ii + i / CHUNKS and therefore fetches logical chunk (i % CHUNKS) ^ swz(row).
-    // Addresses are clamped to valid tokens; slots beyond the range or the grid are masked in the compute.
-    auto issue_tile = [&](int i, unsigned lds_tile) {
-        int a, b;
-        tile_origin(i, a, b);
-        auto load_row_group = [&](auto n_tag) __attribute__((always_inline)) {
-            const int ii = ldw * NI_L + decltype(n_tag)::value;
-            const int row = ROWS_PER_LOAD * ii + lane / CHUNKS;
-            int token;
-            if (b < 0) {
-                token = imin(a + row, lin_limit - 1);
-                if (TEXTQ && token >= p.vkeys_text) token += p.vshift;  // position in the key list -> token
-            } else {
-                const int ky = imax(imin(a + (row >> 3), kH - 1) - y_shift, 0);  // (rows above the grid: out of every owned query's reach)
-                const int kx = imin(b + (row & 7), kW - 1);
-                token = p.n_text + (ky * stride + k_oy) * p.gridW + kx * stride + k_ox;
-            }
-            const unsigned chunk_off = (unsigned)(((lane % CHUNKS) ^ swz(row)) << 4);
-            load_to_lds_16B(Kh, (unsigned)token * k_pitch + chunk_off, lds_tile + ii * 1024);
-            load_to_lds_16B(Vh, (unsigned)token * v_pitch + chunk_off, lds_tile + TILE_BYTES + ii * 1024);
-        };
-        static_for<NI_L>(load_row_group);  // (not a loop: one that contains inline asm is not unrolled)
-    };
-    auto issue_stage = [&](int t, int buf) {  // the stage that starts at tile t goes to stage buffer buf
-        const int len = stage_len(t);
-        auto load_tile = [&](auto j_tag) __attribute__((always_inline)) {
-            constexpr int j = decltype(j_tag)::value;
-            if (j < len) issue_tile(t + j, lds_base + (unsigned)buf * STAGE_BYTES + (unsigned)j * (2 * TILE_BYTES));
-        };
-        static_for<TPS>(load_tile);
-    };
-
-    __shared__ int s_redo;  // set when the fast pass has to be repeated by the careful one
-    auto stage_sync = [&]() {
-        wait_vmcnt<0>();
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-    };
-    if (NLW > 0 && loader) {
-        // A loading wave walks the stage list like the computing waves, one barrier per stage, and stays one
-        // stage ahead: after the barrier that hands stage s over, everyone has left the other buffer, which it
-        // refills with stage s + 1.  Same barrier count as run_pass below, pass for pass.
-        auto loader_pass = [&]() {
-            constexpr int PFD = NBUF - 1;        // stages in flight ahead of the one being computed
-            constexpr int LPS = TPS * 2 * NI_L;  // this wave's load instructions per full stage
-            static_assert(PFD == 1 || TPS == 1, "counting loads per stage needs stages of one size");
-            static_assert(PFD <= 3 && (PFD - 1) * LPS < 64, "the waits below are written out for up to three stages ahead");
-            int nx = 0, nbuf = 0, n_issued = 0;
-            for (int i = 0; i < PFD && nx < n_tiles; ++i) {
-                issue_stage(nx, nbuf);
-                nx += stage_len(nx);
-                nbuf = next_buf(nbuf);
-                ++n_issued;
-            }
-            int k = 0;
-            for (int t = 0; t < n_tiles; ++k) {
-                // stage k has landed once at most the loads of the stages issued after it are outstanding
-                const int ahead = n_issued - 1 - k;
-                if (PFD > 2 && ahead >= 2)
-                    wait_vmcnt<(PFD > 2 ? 2 * LPS : 0)>();
-                else if (PFD > 1 && ahead == 1)
-                    wait_vmcnt<(PFD > 1 ? LPS : 0)>();
-                else
-                    wait_vmcnt<0>();
-                __builtin_amdgcn_s_barrier();
-                asm volatile("" ::: "memory");
-                t += stage_len(t);
-                if (nx < n_tiles) {
-                    issue_stage(nx, nbuf);
-                    nx += stage_len(nx);
-                    nbuf = next_buf(nbuf);
-                    ++n_issued;
-                }
-            }
-            wait_vmcnt<0>();
-        };
-        loader_pass();
-        __syncthreads();
-        if (s_redo != 0) {
-            __syncthreads();
-            loader_pass();
-            __syncthreads();
+    auto word = [&]() -> unsigned {
+        const unsigned w = words[pc++];
+        if (TEXTQ && pc == pc_wrap) {
+            const bool last = --whole_left == 0;
+            pc = last ? pc_tail : pc_first;
+            pc_wrap = last ? ~0u : pc_wrap;
         }
-        return;
-    }
+        return w;
+    };
 
     // ---- running softmax state: one query per lane (shared with lane ^ 32)
     WaveState ws;
     ws.c = p.scale_log2e;
 
-    // ---- per-lane LDS read offsets inside a staged tile
-    LaneOffsets lo;
-    // K operand: key row qi of the block, logical chunk 2 ks + hh (16 bytes = 8 channels)
-    lo.k0 = (unsigned)(qi * ROW_BYTES + ((hh ^ swz(qi)) << 4));
-    // V operand (transpose read): within each group of 16 lanes, lane j addresses key row j / 4 and channels
-    // 4 (j % 4) .. + 3 of the group's 16-channel slice; it receives channel lane % 16 for 4 rows.  Rows of
-    // the first read: 4 hh + j / 4 (+ 16 s2 + 32 blk), of the second: + 8.
-    {
-        const int j = lane & 15, g2 = (lane >> 4) & 1;
-        const int row = 4 * hh + (j >> 2);
-        const int chunk = 2 * g2 + ((j & 3) >> 1);
-        lo.v0 = (unsigned)(row * ROW_BYTES + ((chunk ^ swz(row)) << 4) + 8 * (j & 1));
-    }
-
-    // Stage hand-over: this wave's loads of the stage about to be computed have landed; after the barrier
-    // so have everyone's, and every wave has left the other buffer, which is refilled with the next stage.
-    int pf_tile = 0;  // first tile of the next stage to load
-    auto begin_stage = [&](int buf) {
-        stage_sync();
-        if (NLW == 0 && pf_tile < n_tiles) {
-            issue_stage(pf_tile, buf ^ 1);
-            pf_tile += stage_len(pf_tile);
-        }
-    };
-    // Classifies the two key blocks of tile t against this wave's query patch and gathers what the
-    // element masks need.
-    struct TileInfo {
-        int cls0, cls1;
-        bool linear;
-        unsigned tile_lds;  // LDS address of the staged tile (K half, then V half)
-        MaskArgs ma;
-    };
-    auto tile_info = [&](int t, int buf, int j) -> TileInfo {
-        TileInfo si;
-        int ta, tb;
-        tile_origin(t, ta, tb);
-        si.linear = tb < 0;
-        if (!wave_has_queries) {
-            si.cls0 = si.cls1 = kBlockSkip;
-        } else if (si.linear) {
-            si.cls0 = classify_linear_block(ta, 32, lin_limit);
-            si.cls1 = classify_linear_block(ta + 32, 32, lin_limit);
-        } else if (TEXTQ) {
-            si.cls0 = si.cls1 = kBlockSkip;
-        } else if (CODE == kCodeFull) {
-            si.cls0 = classify_full_block(wy0, wx0, qH, qW, ta, tb, kKeyBlockH, kKeyBlockW, kH, kW);
-            si.cls1 = classify_full_block(wy0, wx0, qH, qW, ta + kKeyBlockH, tb, kKeyBlockH, kKeyBlockW, kH, kW);
-        } else if (CODE == kCodeDisc) {
-            si.cls0 = classify_image_block(wy0, wx0, kWaveQH, kWaveQW, ta, tb, kKeyBlockH, kKeyBlockW, kH, kW, p.r2);
-            si.cls1 = classify_image_block(wy0, wx0, kWaveQH, kWaveQW, ta + kKeyBlockH, tb, kKeyBlockH, kKeyBlockW, kH, kW, p.r2);
-        } else {
-            const MaskSpec spec = {p.mask_kind, p.mask_r, p.mask_shift};
-            si.cls0 = classify_image_block_spec(spec, wy0, wx0, kWaveQH, kWaveQW, ta, tb, kKeyBlockH, kKeyBlockW, kH, kW);
-            si.cls1 = classify_image_block_spec(spec, wy0, wx0, kWaveQH, kWaveQW, ta + kKeyBlockH, tb, kKeyBlockH, kKeyBlockW, kH, kW);
-        }
-        si.tile_lds = lds_base + (unsigned)buf * STAGE_BYTES + (unsigned)j * (2 * TILE_BYTES);
-        si.ma.hh = hh;
-        si.ma.a = ta;                          // linear: first token of the tile; image: tile origin row
-        si.ma.b = si.linear ? lin_limit : tb;  // linear: token limit;             image: tile origin col
-        si.ma.qy = qy; si.ma.qx = qx; si.ma.gridH = kH; si.ma.gridW = kW; si.ma.r2 = p.r2;
-        si.ma.kind = p.mask_kind; si.ma.r = p.mask_r; si.ma.shift = p.mask_shift;
-        si.ma.row[0] = si.ma.row[1] = mask_tbl;
-        if (!TEXTQ && !si.linear && p.mask_tbl) {
-            // lane masks of the two blocks: whole blocks use the all-ones entry, unreachable blocks the all-zeros
-            // entry at the end of the table
-            const int ncol = 2 * p.mask_rx + 1;
-            const int ones = (2 * p.mask_ry + 1) * ncol, zeros = ones + 1;
-            const int dbx = (tb - wx0) >> 3;
-            const int dby = (ta - wy0) >> 2;
-            const int i0 = (si.cls0 == kBlockPartial) ? (dby + p.mask_ry) * ncol + dbx + p.mask_rx : (si.cls0 == kBlockFull ? ones : zeros);
-            const int i1 = (si.cls1 == kBlockPartial) ? (dby + 1 + p.mask_ry) * ncol + dbx + p.mask_rx : (si.cls1 == kBlockFull ? ones : zeros);
-            si.ma.row[0] = mask_tbl + 16 * i0;
-            si.ma.row[1] = mask_tbl + 16 * i1;
-        }
-        return si;
-    };
-
-    // Image tiles inside the grid, lane masks from the table: what this wave does with each of them was worked out
-    // on the host when the context was made (one word per tile and wave: the table entries of the tile's two
-    // blocks, or kWaveSkipsTile), so the tile loop neither classifies nor computes mask addresses.  The words of
-    // a stage are fetched before its barrier, whose wait hides their latency.
-    const const_int_ptr wave_desc = (const_int_ptr)p.wave_desc;
-    struct TableStage {
-        int d[TPS];
-    };
-    auto table_stage = [&](int t) {
-        TableStage ts;
+    // ---- per-lane LDS read offsets inside a staged block
+    unsigned k_lane[2], v_lane[2];
 #pragma unroll
-        for (int j = 0; j < TPS; ++j) {
-            const int e = imin(t + j, cb3 - 1) - n_lin_tiles;  // (a stage may end early: its last word is read twice)
-            const int d = wave_desc[(long long)(csr_begin + e) * NW + wave];
-            ts.d[j] = (t + j < cb3 && wave_has_queries) ? d : kWaveSkipsTile;
-        }
-        return ts;
-    };
-    auto stage_tile_lds = [&](int buf, int j) { return lds_base + (unsigned)buf * STAGE_BYTES + (unsigned)j * (2 * TILE_BYTES); };
-    auto table_mask_args = [&](int d) {
-        MaskArgs ma;
-        ma.row[0] = mask_tbl + 16 * (d & 0xffff);
-        ma.row[1] = mask_tbl + 16 * ((unsigned)d >> 16);
-        return ma;
-    };
+    for (int e = 0; e < 2; ++e) {
+        k_lane[e] = lds_base + (unsigned)((qi >> 4) * 1024 + (qi & 15) * 64 + (((2 * e + hh) ^ plane_swz(qi & 15)) << 4));
+        const int j = lane & 15, row = 4 * hh + (j >> 2) + 8 * e;
+        v_lane[e] = lds_base + (unsigned)(NKBUF * STAGE_HALF + row * 64 + (((2 * ((lane >> 4) & 1) + ((j & 3) >> 1)) ^ plane_swz(row)) << 4) + 8 * (j & 1));
+    }
+    auto block_offset = [](unsigned w) { return (w & kProgramPlaceMask) << 11; };
+    auto mask_id = [](unsigned w) { return (w & ~kProgramFlags) >> kProgramMaskShift; };
 
     // Prologue of the block on the query row (RMS norm over the head's channels - this lane holds half of them,
     // lane ^ 32 the others -, rotary embedding for image queries, back to bf16).  Runs once, after the first
@@ -615,8 +378,8 @@ __device__ __forceinline__ void clear_fwd_bf16_workgroup(const FwdParams& p, con
 
     };
 
-    // One pass over the stage list.  CAREFUL = false: fast pass (fixed reference maximum); returns the
-    // lanes that ran out of headroom.  CAREFUL = true: exact online softmax, slow.
+    // One pass over the program.  CAREFUL = false: fast pass (fixed reference maximum); returns the
+    // lanes that ran out of headroom.  CAREFUL = true: exact online softmax, block by block, slow.
     auto run_pass = [&](auto careful_tag) -> unsigned long long {
         constexpr bool CAREFUL = decltype(careful_tag)::value;
 #pragma unroll
@@ -625,147 +388,263 @@ __device__ __forceinline__ void clear_fwd_bf16_workgroup(const FwdParams& p, con
             for (int r = 0; r < 16; ++r) ws.oacc[db][r] = 0.f;
         ws.m_run = M_INIT;
         ws.l_run = 0.f;
-        unsigned long long bad = 0;
-        // prologue: the first stage is in flight
-        pf_tile = 0;
-        if (NLW == 0 && n_tiles > 0) {
-            issue_stage(0, 0);
-            pf_tile = stage_len(0);
-        }
-        // The Q fragments are waited for here, once, with the first tiles already on their way: otherwise the
-        // wait lands inside the key loop, where it would also drain the tile prefetches.
+        // The Q fragments are waited for here, once, with the first tiles already on their way.
 #pragma unroll
         for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(qf[s]));
         if (!CAREFUL) query_prologue();  // the fast pass always comes first
-        int buf = 0;
-        if (CAREFUL) {
-            for (int t = 0; t < n_tiles;) {
-                begin_stage(buf);
-                const int len = stage_len(t);
-                for (int j = 0; j < len; ++j) {
-                    const TileInfo si = tile_info(t + j, buf, j);
-                    careful_stage<CODE>(ws, qf, lo, si.tile_lds, si.cls0, si.cls1, si.linear, si.ma);
-                }
-                t += len;
-                buf = next_buf(buf);
-            }
-        } else {
-            // One loop per tile category (and per mode), so that every loop body has a single shape.  Each
-            // category starts in "adopt" mode and switches to the leaner loop once every query of the wave
-            // has its reference maximum.
-            bool adopting = true;
-            auto still_adopting = [&]() { return __builtin_amdgcn_ballot_w64(ws.m_run == M_INIT) != 0; };
-            int t = 0;
+        auto barrier = [&]() {
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        };
+        if (!wave_has_queries) {
+            for (int s = 0; s < n_stages; ++s) barrier();
+            return 0;
+        }
+        if (n_stages == 0) return 0;
+        int stage = 0;
+        unsigned k_at = 0, v_at = 0;  // stage buffers in use, bytes
+        auto next_stage = [&]() {
+            ++stage;
+            k_at ^= STAGE_HALF;
+            v_at = v_at + STAGE_HALF == NVBUF * STAGE_HALF ? 0 : v_at + STAGE_HALF;
+            barrier();
+        };
+        start_program();
 
-            // whole linear tiles
-            for (; t < cb1 && adopting; t += TPS, buf = next_buf(buf)) {
-                begin_stage(buf);
-#pragma unroll 1
-                for (int j = 0; j < imin(TPS, cb1 - t); ++j) {
-                    const TileInfo si = tile_info(t + j, buf, j);
-                    if (wave_has_queries) fast_stage<kMaskNone, true, CODE>(ws, qf, lo, si.tile_lds, si.ma);
-                }
-                adopting = wave_has_queries && still_adopting();
-            }
-            for (; t < cb1; t += TPS, buf = next_buf(buf)) {
-                begin_stage(buf);
-#pragma unroll 1
-                for (int j = 0; j < imin(TPS, cb1 - t); ++j) {
-                    const TileInfo si = tile_info(t + j, buf, j);
-                    if (wave_has_queries) fast_stage<kMaskNone, false, CODE>(ws, qf, lo, si.tile_lds, si.ma);
-                }
-            }
-            t = cb1;
-            // the ragged linear tile: at most one, keep it simple
-            for (; t < cb2; t += TPS, buf = next_buf(buf)) {
-                begin_stage(buf);
-                const TileInfo si = tile_info(t, buf, 0);
-                if (si.cls0 != kBlockSkip) {
-                    fast_stage<kMaskLinear, true, CODE>(ws, qf, lo, si.tile_lds, si.ma);
-                    adopting = still_adopting();
-                }
-            }
-            t = cb2;
-            if constexpr (dense_image) {
-                // strided mask, tiles inside the class grid: every key of the tile is admitted for every query
-                for (; t < cb3 && adopting; t += TPS, buf = next_buf(buf)) {
-                    begin_stage(buf);
-#pragma unroll 1
-                    for (int j = 0; j < imin(TPS, cb3 - t); ++j) {
-                        const TileInfo si = tile_info(t + j, buf, j);
-                        if (wave_has_queries) fast_stage<kMaskNone, true, CODE>(ws, qf, lo, si.tile_lds, si.ma);
-                    }
-                    adopting = wave_has_queries && still_adopting();
-                }
-                for (; t < cb3; t += TPS, buf = next_buf(buf)) {
-                    begin_stage(buf);
-#pragma unroll 1
-                    for (int j = 0; j < imin(TPS, cb3 - t); ++j) {
-                        const TileInfo si = tile_info(t + j, buf, j);
-                        if (wave_has_queries) fast_stage<kMaskNone, false, CODE>(ws, qf, lo, si.tile_lds, si.ma);
-                    }
-                }
-            }
-            if (!TEXTQ) {
-                // image tiles inside the grid (lane masks from the table); the strided variant has run them above
-                if constexpr (CODE != kCodeFull) {
-                for (; t < cb3 && adopting; t += TPS, buf = next_buf(buf)) {
-                    const TableStage ts = table_stage(t);
-                    begin_stage(buf);
+        if constexpr (CAREFUL) {
+            barrier();
+            for (;;) {
+                const unsigned w = word();
+                const unsigned off = block_offset(w), id = mask_id(w);
+                if (id != kMaskIdNothing && !(w & kProgramNoBlock)) {
+                    const unsigned kb[2] = {k_lane[0] + k_at + off, k_lane[1] + k_at + off}, vb[2] = {v_lane[0] + v_at + off, v_lane[1] + v_at + off};
+                    f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int j = 0; j < TPS; ++j)
-                        if (ts.d[j] != kWaveSkipsTile) fast_stage<kMaskTable, true, CODE>(ws, qf, lo, stage_tile_lds(buf, j), table_mask_args(ts.d[j]));
-                    adopting = wave_has_queries && still_adopting();
-                }
-                for (; t < cb3; t += TPS, buf = next_buf(buf)) {
-                    const TableStage ts = table_stage(t);
-                    begin_stage(buf);
+                    for (int ks = 0; ks < KS; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k(kb, ks), qf[ks], s, 0, 0, 0);
+                    if (id != kMaskIdNone) {
+                        MaskWords mw;
 #pragma unroll
-                    for (int j = 0; j < TPS; ++j)
-                        if (ts.d[j] != kWaveSkipsTile) fast_stage<kMaskTable, false, CODE>(ws, qf, lo, stage_tile_lds(buf, j), table_mask_args(ts.d[j]));
-                }
-                }
-                t = cb3;
-                // image tiles cut by the border: few, keep them simple
-                for (; t < cb4; t += TPS, buf = next_buf(buf)) {
-                    begin_stage(buf);
-#pragma unroll 1
-                    for (int j = 0; j < imin(TPS, cb4 - t); ++j) {
-                        const TileInfo si = tile_info(t + j, buf, j);
-                        if (si.cls0 != kBlockSkip || si.cls1 != kBlockSkip) fast_stage<kMaskImage, true, CODE>(ws, qf, lo, si.tile_lds, si.ma);
+                        for (int r = 0; r < 16; ++r) mw.w[r] = mask_words[16 * (size_t)id + r];
+                        mask_scores(s, mw);
                     }
+                    const float m_new = fmaxf(ws.m_run, wave_pair_max(max_block(s)));
+                    const float alpha = __builtin_amdgcn_exp2f((ws.m_run - m_new) * ws.c);
+                    ws.l_run *= alpha;
+#pragma unroll
+                    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) ws.oacc[db][r] *= alpha;
+                    ws.m_run = m_new;
+                    bf16x8 pf[2];
+                    ws.l_run += exp_block(s, ws.c, m_new * ws.c, pf);
+#pragma unroll
+                    for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+                        for (int db = 0; db < NDB; ++db) ws.oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_v(vb, s2, db), pf[s2], ws.oacc[db], 0, 0, 0);
+                }
+                if (w & kProgramStageEnd) {
+                    if (stage + 1 == n_stages) break;
+                    next_stage();
                 }
             }
+            return 0;
+        } else {
+            // Fast pass: a software pipeline over blocks.  One step issues KS matrix instructions of S = K Q^T for block n and
+            // 2 NDB of O += V P for the block before it, in program order, each LDS operand read PD instructions ahead; the
+            // vector work rides along:
+            //   slots [0, KS)          S of block n        | exponentials, sum, P of block n - 1 (from `t`)
+            //   slots [KS, NSLOT)      P V of block n - 1  | the last of them; then scale and mask the scores of block n into `t`
+            // The reference maximum of a query never moves once set, so O is only ever touched by the matrix pipeline.
+            constexpr int PD = CLEAR_OPERAND_PREFETCH, RING = PD == 1 ? 2 : 4, NSLOT = KS + 2 * NDB;
+            static_assert(NSLOT % RING == 0 && PD <= KS && PD < RING, "the operand ring carries over from step to step");
+            bf16x8 op[RING];
+            float t[16];  // (s - m) c of the block whose exponentials are due
+#pragma unroll
+            for (int r = 0; r < 16; ++r) t[r] = -INFINITY;  // (nothing before the first block: P = 0)
+            const float c = ws.c;
+            unsigned w = word(), w_next = word();  // (a program is followed by two more readable words)
+            barrier();
+            unsigned kb[2], vb[2], v_old = v_at + block_offset(w);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) kb[e] = k_lane[e] + k_at + block_offset(w);
+#pragma unroll
+            for (int i = 0; i < PD; ++i) op[i] = read_k(kb, i);
+            const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+
+            // returns whether this was the last block
+            auto step = [&](auto adopt_tag) __attribute__((always_inline)) -> bool {
+                constexpr bool ADOPT = decltype(adopt_tag)::value;
+                const unsigned id = mask_id(w);
+                const unsigned v_new = v_at + block_offset(w);
+#pragma unroll
+                for (int e = 0; e < 2; ++e) vb[e] = v_lane[e] + v_old;
+                unsigned kn[2];  // block n + 1, if it is in the same stage (otherwise what is read there is read again after the barrier)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) kn[e] = k_lane[e] + k_at + block_offset(w_next);
+                const unsigned w_after = word();
+                float mc = ws.m_run * c, sum = 0.f;
+                bf16x8 pf[2];
+                f32x16 s;
+                MaskWords mw;
+                auto operand = [&](int slot) { return slot < KS ? read_k(kb, slot) : slot < NSLOT ? read_v(vb, (slot - KS) / NDB, (slot - KS) % NDB) : read_k(kn, slot - NSLOT); };
+                auto run_slot = [&](auto slot_tag) __attribute__((always_inline)) {
+                    constexpr int slot = decltype(slot_tag)::value;
+                    op[(slot + PD) % RING] = operand(slot + PD);
+                    SCHED_FENCE();  // (the read stays in front of the matrix instruction, which then waits for older reads only)
+                    constexpr int i = slot >= KS ? slot - KS : 0;
+                    if (slot == 0 && id != kMaskIdNone) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) mw.w[r] = mask_words[16 * (size_t)id + r];
+                    }
+                    if (slot < KS)
+                        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], qf[slot < KS ? slot : 0], slot == 0 ? zero : s, 0, 0, 0);
+                    else
+                        ws.oacc[i % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], pf[i / NDB], ws.oacc[i % NDB], 0, 0, 0);
+                    // exponentials as a vector pipeline over pairs of scores: exponentiated in slot a, summed and packed in slot a + 1
+#pragma unroll
+                    for (int g = 0; g < 8; ++g) {
+                        const int a = KS == 8 ? (g < 4 ? g + g / 2 : g + 2) : (g < 4 ? g / 2 : g / 2 + 1);
+                        if (slot == a) {
+                            t[2 * g] = __builtin_amdgcn_exp2f(t[2 * g]);
+                            t[2 * g + 1] = __builtin_amdgcn_exp2f(t[2 * g + 1]);
+                        }
+                        if (slot == a + 1) {
+                            sum += t[2 * g] + t[2 * g + 1];
+                            pf[g >> 2][2 * (g & 3)] = (__bf16)t[2 * g];
+                            pf[g >> 2][2 * (g & 3) + 1] = (__bf16)t[2 * g + 1];
+                            asm volatile("" : "+v"(sum));  // (the sum is formed here, not where it is used)
+                        }
+                    }
+                    constexpr int FIRST = KS == 8 ? KS + 3 : KS + 2;  // the scores of block n are complete; four of them per slot, or eight
+                    constexpr int PER = KS == 8 ? 4 : 8;
+                    if (!ADOPT && slot >= FIRST && (slot - FIRST) * PER < 16) {
+#pragma unroll
+                        for (int u = 0; u < PER; ++u) {
+                            const int r = slot >= FIRST ? (slot - FIRST) * PER + u : 0;
+                            t[r & 15] = __builtin_fmaf(s[r & 15], c, -mc);
+                        }
+                    }
+                    SCHED_FENCE();
+                };
+                static_for<NSLOT>(run_slot);  // (not a loop: one that contains inline asm is not unrolled)
+                if (ADOPT) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) t[r] = s[r];
+                }
+                if (id != kMaskIdNone) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) t[r] = __builtin_amdgcn_inverse_ballot_w64(mw.w[r]) ? t[r] : -INFINITY;
+                }
+                if (ADOPT) {
+                    float mx = t[0];
+#pragma unroll
+                    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, t[r]);
+                    adopt_reference(ws, wave_pair_max(mx));
+                    mc = ws.m_run * c;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) t[r] = __builtin_fmaf(t[r], c, -mc);
+                }
+                ws.l_run += sum;
+                v_old = v_new;
+                unsigned ended = w;
+                w = w_next;
+                w_next = w_after;
+#pragma unroll
+                for (int e = 0; e < 2; ++e) kb[e] = kn[e];
+                if (ended & kProgramStageEnd) {
+                    for (;;) {
+                        if (stage + 1 == n_stages) return true;
+                        next_stage();
+                        if (!(w & kProgramNoBlock)) break;  // a stage without a block of this wave, and nothing left over from before
+                        w = w_next;
+                        w_next = word();
+                    }
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) kb[e] = k_lane[e] + k_at + block_offset(w);
+#pragma unroll
+                    for (int i = 0; i < PD; ++i) op[i] = read_k(kb, i);
+                }
+                return false;
+            };
+            // While some query of the wave has no reference maximum yet (the first blocks), the block maxima are formed and
+            // adopted; after that no maximum is needed at all.
+            bool done = false, adopting = true;
+            while (!done && adopting) {
+                done = step(std::true_type{});
+                adopting = __builtin_amdgcn_ballot_w64(ws.m_run == M_INIT) != 0;
+            }
+            while (!done) done = step(std::false_type{});
+            // the last block's P V
+#pragma unroll
+            for (int e = 0; e < 2; ++e) vb[e] = v_lane[e] + v_old;
+            bf16x8 pf[2];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float pv = __builtin_amdgcn_exp2f(t[r]);
+                ws.l_run += pv;
+                pf[r >> 3][r & 7] = (__bf16)pv;
+            }
+#pragma unroll
+            for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+                for (int db = 0; db < NDB; ++db) ws.oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_v(vb, s2, db), pf[s2], ws.oacc[db], 0, 0, 0);
             // the fast pass stands only if every sum stayed finite and moderate
             float chk = ws.l_run;
 #pragma unroll
             for (int db = 0; db < NDB; ++db)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) chk += __builtin_fabsf(ws.oacc[db][r]);
-            bad = __builtin_amdgcn_ballot_w64(!(chk < FAST_SUM_LIMIT));
+            return __builtin_amdgcn_ballot_w64(!(chk < FAST_SUM_LIMIT));
         }
-        wait_vmcnt<0>();  // loads into slots that nothing reads must not outlive the pass (or the workgroup's LDS)
-        return bad;
     };
 
-    // Fast pass first.  If any query of the workgroup met a score more than 2^FAST_HEADROOM_LOG2 above
-    // its reference (in the exponent), the whole workgroup repeats the tile walk with the careful pass.
-    if (tid == 0) s_redo = 0;  // ordered before any write below by the barriers of the stage loop
+    // Fast pass first.  If a query of the workgroup ran out of the range of fp32 on its fixed reference, the whole workgroup repeats
+    // the walk with the careful pass.
     const unsigned long long bad = run_pass(std::false_type{});
-    if (bad != 0 && lane == 0) s_redo = 1;
+    __syncthreads();  // every wave has left the stage buffers
+    if (lane == 0) flags[wave] = bad != 0;
     __syncthreads();
-    if (s_redo != 0) {
-        __syncthreads();  // every wave has read the flag and left the ring buffers
+    unsigned redo = 0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) redo |= flags[i];
+    if (__builtin_amdgcn_readfirstlane(redo) != 0) {
+        __syncthreads();  // every wave has read the flags
         run_pass(std::true_type{});
         __syncthreads();  // the epilogue reuses the stage buffers
     }
 
-    const float m_run = ws.m_run;
-    const float l_run = ws.l_run;
+    float m_run = ws.m_run;
     f32x16(&oacc)[NDB] = ws.oacc;
     // ---- epilogue
-    const float l_tot = wave_pair_sum(l_run);
-    if (TEXTQ) {
+    float l_tot = wave_pair_sum(ws.l_run);
+    if (groups > 1) {
+        // Join the waves of a patch: the others leave maximum, sum and O in LDS, lane by lane, the first adds them up.
+        constexpr int FLOATS = NDB * 16 + 2;
+        float* const area = (float*)smem + ((group - 1) * patches + patch) * (FLOATS * 64) + lane;
+        if (group > 0) {
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) area[(16 * db + r) * 64] = oacc[db][r];
+            area[NDB * 16 * 64] = m_run;
+            area[(NDB * 16 + 1) * 64] = l_tot;
+        }
+        __syncthreads();
+        if (group > 0) return;
+#pragma unroll 1
+        for (int g = 1; g < groups; ++g) {
+            const float* const other = (const float*)smem + ((g - 1) * patches + patch) * (FLOATS * 64) + lane;
+            const float mo = other[NDB * 16 * 64], m_new = fmaxf(m_run, mo);
+            const float wa = __builtin_amdgcn_exp2f((m_run - m_new) * ws.c), wb = __builtin_amdgcn_exp2f((mo - m_new) * ws.c);
+            m_run = m_new;
+            l_tot = l_tot * wa + other[(NDB * 16 + 1) * 64] * wb;
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) oacc[db][r] = oacc[db][r] * wa + other[(16 * db + r) * 64] * wb;
+        }
+    }
+    if (TEXTQ && p.n_splits > 1) {
         if (q_valid) {
             const long long row = ((long long)bh * p.n_splits + split) * p.n_text + q_token;
             float* wo = p.ws_o + row * D;
@@ -781,54 +660,78 @@ __device__ __forceinline__ void clear_fwd_bf16_workgroup(const FwdParams& p, con
                 p.ws_ml[row * 2 + 1] = l_tot;
             }
         }
-    } else {
-        // The wave's 32 x D output tile is turned round in LDS (the stage buffers are idle by now: every wave
-        // has passed the barrier above) so that it leaves as whole rows: a lane owns a query, and
-        // storing from that layout would scatter 8-byte pieces over 32 rows per instruction.
-        if (p.lse && q_valid && hh == 0) p.lse[(long long)bh * p.N + q_token] = __logf(l_tot) + m_run * p.scale_log2e * 0.6931471805599453f;
-        constexpr int OROW = ROW_BYTES + 16;  // padded row pitch in LDS
-        unsigned char* const wbase = smem + wave * (32 * OROW);
-        const float inv = 1.0f / l_tot;
+        return;
+    }
+    const float inv = 1.0f / l_tot;
+    const float lse = __logf(l_tot) + m_run * p.scale_log2e * 0.6931471805599453f;
+    if (TEXTQ && p.band_o) {
+        if (!q_valid) return;
+        const long long row = (long long)bh * p.n_text + q_token;
+        if (hh == 0) p.band_lse[row] = lse;
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                bf16x4 v;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) v[t] = (__bf16)(oacc[db][4 * g + t] * inv);
-                *(bf16x4*)(wbase + qi * OROW + (32 * db + 8 * g + 4 * hh) * 2) = v;
+                f32x4 v = {oacc[db][4 * g] * inv, oacc[db][4 * g + 1] * inv, oacc[db][4 * g + 2] * inv, oacc[db][4 * g + 3] * inv};
+                *(f32x4*)(p.band_o + row * D + 32 * db + 8 * g + 4 * hh) = v;
             }
-        // CHUNKS lanes per row, ROWS_PER_LOAD rows per store instruction
+        return;
+    }
+    // The wave's 32 x D output tile is turned round in LDS (the stage buffers are idle by now: every wave
+    // has passed the barrier above) so that it leaves as whole rows: a lane owns a query, and
+    // storing from that layout would scatter 8-byte pieces over 32 rows per instruction.
+    if (p.lse && q_valid && hh == 0) p.lse[(long long)bh * p.N + q_token] = lse;
+    constexpr int OROW = ROW_BYTES + 16;  // padded row pitch in LDS
+    static_assert(NW * 32 * OROW <= FWD_LDS_BYTES - FLAG_BYTES, "the output tiles leave the flags alone");
+    unsigned char* const wbase = smem + (groups > 1 ? (NW * (NDB * 16 + 2) * 64 * 4 * 3) / 4 : 0) + patch * (32 * OROW);
 #pragma unroll
-        for (int i = 0; i < 32 / ROWS_PER_LOAD; ++i) {
-            const int row = ROWS_PER_LOAD * i + lane / CHUNKS;  // query slot of the patch
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            bf16x4 v;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[t] = (__bf16)(oacc[db][4 * g + t] * inv);
+            *(bf16x4*)(wbase + qi * OROW + (32 * db + 8 * g + 4 * hh) * 2) = v;
+        }
+    // CHUNKS lanes per row, ROWS_PER_LOAD rows per store instruction
+#pragma unroll
+    for (int i = 0; i < 32 / ROWS_PER_LOAD; ++i) {
+        const int row = ROWS_PER_LOAD * i + lane / CHUNKS;  // query slot of the patch
+        const f32x4 chunk = *(const f32x4*)(wbase + row * OROW + (lane % CHUNKS) * 16);
+        long long token;
+        bool store;
+        if (TEXTQ) {
+            token = (qt * patches + patch) * kTextQueriesPerWave + row;
+            store = token < p.n_text;
+        } else {
             const int oy = wy0 + (row >> 3), ox = wx0 + (row & 7);
-            const f32x4 chunk = *(const f32x4*)(wbase + row * OROW + (lane % CHUNKS) * 16);
-            if (oy < qH && ox < qW && oy >= p.own_y0 && oy < p.own_y1) {
-                __bf16* orow = (__bf16*)p.O + batch * p.os.sb + head * p.os.sh + ((long long)p.n_text + (long long)((oy - y_shift) * stride + q_oy) * p.gridW + ox * stride + q_ox) * p.os.sn;
-                __builtin_nontemporal_store(chunk, (f32x4*)(orow + (lane % CHUNKS) * 8));  // whole rows, never read again here
-            }
+            token = (long long)p.n_text + (long long)((oy - y_shift) * stride + q_oy) * p.gridW + ox * stride + q_ox;
+            store = oy < qH && ox < qW && oy >= p.own_y0 && oy < p.own_y1;
+        }
+        if (store) {
+            __bf16* orow = (__bf16*)p.O + batch * p.os.sb + head * p.os.sh + token * p.os.sn;
+            __builtin_nontemporal_store(chunk, (f32x4*)(orow + (lane % CHUNKS) * 8));  // whole rows, never read again here
         }
     }
 }
 
-template <int NWY, int NWX, bool TEXTQ, int CODE>
-__global__ void __launch_bounds__((NWY * NWX + kLoaderWaves) * 64, (NWY * NWX <= 4 && kLoaderWaves == 0) ? 2 : 1) clear_fwd_bf16_kernel(const FwdParams p)
+template <bool TEXTQ>
+__global__ void __launch_bounds__((NW + NLW) * 64, 1) clear_fwd_bf16_kernel(const FwdParams p)
 {
-    clear_fwd_bf16_workgroup<NWY, NWX, TEXTQ, CODE>(p, (int)blockIdx.x, (int)gridDim.x);
+    clear_fwd_bf16_workgroup<TEXTQ>(p, (int)blockIdx.x, (int)gridDim.x);
 }
 
-// Image-query and text-query rows in one launch: workgroups [0, n_image) are the image-query ones, the rest the
-// text-query ones.  For problems of a few rounds of workgroups, where the image-query launch alone leaves CUs idle
+// Image-query and text-query rows in one launch: workgroups [0, n_first) are the ones of one kind (p.text_first), the rest those of
+// the other.  For problems of a few rounds of workgroups, where a launch of image-query rows alone leaves CUs idle
 // at its end and a launch of its own for the text-query rows costs more than it computes.
-template <int NWY, int NWX, int CODE>
-__global__ void __launch_bounds__((NWY * NWX + kLoaderWaves) * 64, 1) clear_fwd_bf16_both_kernel(const FwdParams p, const int n_image)
+__global__ void __launch_bounds__((NW + NLW) * 64, 1) clear_fwd_bf16_both_kernel(const FwdParams p, const int n_first)
 {
-    const int bid = (int)blockIdx.x;
-    if (bid < n_image)
-        clear_fwd_bf16_workgroup<NWY, NWX, false, CODE>(p, bid, n_image);
+    const int bid = (int)blockIdx.x, rest = (int)gridDim.x - n_first;
+    const bool first = bid < n_first;
+    if (first != p.text_first)
+        clear_fwd_bf16_workgroup<false>(p, first ? bid : bid - n_first, first ? n_first : rest);
     else
-        clear_fwd_bf16_workgroup<NWY, NWX, true, kCodeDisc>(p, bid - n_image, (int)gridDim.x - n_image);
+        clear_fwd_bf16_workgroup<true>(p, first ? bid : bid - n_first, first ? n_first : rest);
 }
 
 // Combines the key-split partial results of the text-query rows: with m the largest running
@@ -863,27 +766,24 @@ __global__ void __launch_bounds__(256) clear_text_merge_kernel(const FwdParams p
     }
 }
 
-template <int NWY, int NWX, bool TEXTQ, int CODE>
+template <bool TEXTQ>
 hipError_t launch_fwd(const FwdParams& p, int nblk, hipStream_t stream)
 {
-    const size_t smem = (size_t)NBUF * STAGE_BYTES;
-    auto kern = clear_fwd_bf16_kernel<NWY, NWX, TEXTQ, CODE>;
+    auto kern = clear_fwd_bf16_kernel<TEXTQ>;
     static LdsLimitOnce lds_limit;  // one per kernel instantiation
-    hipError_t e = lds_limit.ensure((const void*)kern, (int)smem);
+    hipError_t e = lds_limit.ensure((const void*)kern, FWD_LDS_BYTES);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(nblk), dim3((NWY * NWX + kLoaderWaves) * 64), smem, stream, p);
+    hipLaunchKernelGGL(kern, dim3(nblk), dim3((NW + NLW) * 64), FWD_LDS_BYTES, stream, p);
     return hipGetLastError();
 }
 
-template <int NWY, int NWX, int CODE>
 hipError_t launch_fwd_both(const FwdParams& p, int n_image, int n_text_wgs, hipStream_t stream)
 {
-    const size_t smem = (size_t)NBUF * STAGE_BYTES;
-    auto kern = clear_fwd_bf16_both_kernel<NWY, NWX, CODE>;
-    static LdsLimitOnce lds_limit;  // one per kernel instantiation
-    hipError_t e = lds_limit.ensure((const void*)kern, (int)smem);
+    static LdsLimitOnce lds_limit;
+    hipError_t e = lds_limit.ensure((const void*)clear_fwd_bf16_both_kernel, FWD_LDS_BYTES);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(n_image + n_text_wgs), dim3((NWY * NWX + kLoaderWaves) * 64), smem, stream, p, n_image);
+    hipLaunchKernelGGL(clear_fwd_bf16_both_kernel, dim3(n_image + n_text_wgs), dim3((NW + NLW) * 64), FWD_LDS_BYTES, stream, p,
+                       p.text_first ? n_text_wgs : n_image);
     return hipGetLastError();
 }
 
@@ -898,26 +798,17 @@ hipError_t launch_bf16(const FwdParams& p, hipStream_t stream, int phase)
 {
     const int BH = p.B * p.H;
     hipError_t e = hipSuccess;
-    if (phase == kPhaseImageAndTextQuery) {
-        const int n_image = BH * p.n_classes * p.n_q_tiles_launch, n_text_wgs = p.n_text > 0 ? BH * p.n_tq_tiles * p.n_splits : 0;
-        const int code = mask_code_of(p.mask_kind);
-        return code == kCodeDisc   ? launch_fwd_both<kBf16NWY, kBf16NWX, kCodeDisc>(p, n_image, n_text_wgs, stream)
-               : code == kCodeFull ? launch_fwd_both<kBf16NWY, kBf16NWX, kCodeFull>(p, n_image, n_text_wgs, stream)
-                                   : launch_fwd_both<kBf16NWY, kBf16NWX, kCodeGeneric>(p, n_image, n_text_wgs, stream);
-    }
+    const int n_image = BH * p.n_classes * p.n_q_tiles_launch, n_text_wgs = p.n_text > 0 ? BH * p.n_tq_tiles * p.n_splits : 0;
+    if (phase == kPhaseImageAndTextQuery) return launch_fwd_both(p, n_image, n_text_wgs, stream);
     if (phase == kPhaseAll || phase == kPhaseImage) {
-        const int nblk = BH * p.n_classes * p.n_q_tiles_launch;
-        const int code = mask_code_of(p.mask_kind);  // one kernel per family of image masks
-        e = code == kCodeDisc   ? launch_fwd<kBf16NWY, kBf16NWX, false, kCodeDisc>(p, nblk, stream)
-            : code == kCodeFull ? launch_fwd<kBf16NWY, kBf16NWX, false, kCodeFull>(p, nblk, stream)
-                                : launch_fwd<kBf16NWY, kBf16NWX, false, kCodeGeneric>(p, nblk, stream);
+        e = launch_fwd<false>(p, n_image, stream);
         if (e != hipSuccess) return e;
     }
-    if (p.n_text > 0 && (phase == kPhaseAll || phase == kPhaseTextQuery)) {
-        e = launch_fwd<kBf16NWY, kBf16NWX, true, kCodeDisc>(p, BH * p.n_tq_tiles * p.n_splits, stream);
+    if (n_text_wgs > 0 && (phase == kPhaseAll || phase == kPhaseTextQuery)) {
+        e = launch_fwd<true>(p, n_text_wgs, stream);
         if (e != hipSuccess) return e;
     }
-    if (p.n_text > 0 && (phase == kPhaseAll || phase == kPhaseTextMerge)) {
+    if (n_text_wgs > 0 && p.n_splits > 1 && (phase == kPhaseAll || phase == kPhaseTextMerge)) {
         constexpr int rows_per_block = 256 / D;
         hipLaunchKernelGGL(clear_text_merge_kernel<__bf16>, dim3((BH * p.n_text + rows_per_block - 1) / rows_per_block), dim3(256), 0, stream, p, D);
         e = hipGetLastError();

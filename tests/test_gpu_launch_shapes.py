@@ -51,3 +51,40 @@ def test_f32_launch_shapes(B, H, n_text, gh, gw, r, kind, shift):
             ref = orc.attention_rows(*(t[b, h].double().numpy() for t in (Q, K, V)), rows, n_text, gh, gw, r)
         mx, rms = error_metrics(O[b, h].numpy()[rows], ref)
         assert mx <= TOL["f32"][0] and rms <= TOL["f32"][1], (mx, rms)
+
+
+# bf16: few workgroups (several waves per query patch, joined in LDS; text rows in one key range and written directly), about one per
+# CU, and several (one wave per patch, text rows in key ranges and merged), text tiles of every filling, tiles cut by both
+# borders, masks that depend on more than the offset
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("B,H,n_text,gh,gw,r,kind,shift", [
+    (1, 1, 31, 20, 20, 6, ca.CLEAR_MASK_DISC, 0),
+    (1, 2, 512, 33, 31, 16, ca.CLEAR_MASK_DISC, 0),
+    (2, 6, 65, 37, 45, 9, ca.CLEAR_MASK_DISC, 0),
+    (1, 14, 97, 61, 50, 16, ca.CLEAR_MASK_DISC, 0),
+    (1, 24, 200, 76, 68, 13, ca.CLEAR_MASK_DISC, 0),
+    (1, 3, 0, 130, 120, 32, ca.CLEAR_MASK_DISC, 0),
+    (1, 5, 40, 50, 66, 12, ca.CLEAR_MASK_SWIN, 5),
+    (1, 9, 12, 43, 39, 7, ca.CLEAR_MASK_SQUARE, 0),
+    (1, 2, 50, 38, 45, 5, ca.CLEAR_MASK_STRIDED, 17),
+])
+def test_bf16_launch_shapes(d, B, H, n_text, gh, gw, r, kind, shift):
+    print(f"[case] bf16 d={d} B={B} H={H} n_text={n_text} grid={gh}x{gw} r={r} kind={kind}", flush=True)
+    Q, K, V = make_qkv_shape(B, H, n_text, gh, gw, d, "bf16", seed=5000 + gh, device="cpu")
+    ctx = ca.ClearAttn(n_text, gh, gw, d, r, ca.CLEAR_BF16, kind, shift)
+    try:
+        Qd, Kd, Vd = Q.to(DEV), K.to(DEV), V.to(DEV)
+        O = torch.full(Q.shape, float("nan"), dtype=Q.dtype, device=DEV)
+        ctx.forward(Qd, Kd, Vd, O)
+        again = ctx.forward(Qd, Kd, Vd)
+        torch.cuda.synchronize()
+    finally:
+        ctx.destroy()
+    assert torch.isfinite(O.float()).all() and torch.equal(O, again)
+    O = O.float().cpu()
+    rows = _rows(n_text, gh, gw, seed=gh)
+    for b, h in ((0, 0), (B - 1, H - 1)):
+        with orc.mask_kind(kind, shift):
+            ref = orc.attention_rows(*(t[b, h].double().numpy() for t in (Q, K, V)), rows, n_text, gh, gw, r)
+        mx, rms = error_metrics(O[b, h].numpy()[rows], ref)
+        assert mx <= TOL["bf16"][0] and rms <= TOL["bf16"][1], (mx, rms)
