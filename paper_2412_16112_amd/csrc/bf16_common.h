@@ -137,24 +137,6 @@ __device__ __forceinline__ void prologue_chunk_values(float (&x)[8], float inv_r
         }
     }
 }
-// The same, fetching the chunk's table entries: gain8 / ry8 / rx8 point at its 8 floats of the gain vector and
-// of the token's two table rows (null: that step is skipped).
-__device__ __forceinline__ void prologue_chunk(float (&x)[8], float inv_rms, const float* gain8, const float* ry8, const float* rx8)
-{
-    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    f32x4 g0 = zero, g1 = zero, a0 = zero, a1 = zero, b0 = zero, b1 = zero;
-    if (gain8) {
-        g0 = *(const f32x4*)gain8;
-        g1 = *(const f32x4*)(gain8 + 4);
-    }
-    if (ry8) {
-        a0 = *(const f32x4*)ry8;
-        a1 = *(const f32x4*)(ry8 + 4);
-        b0 = *(const f32x4*)rx8;
-        b1 = *(const f32x4*)(rx8 + 4);
-    }
-    prologue_chunk_values(x, inv_rms, gain8 != nullptr, g0, g1, ry8 != nullptr, a0, a1, b0, b1);
-}
 
 struct WaveState {
     f32x16 oacc[NDB];  // O^T tiles: channel 32*db + 8*(reg/4) + 4*hh + reg%4 of this lane's query

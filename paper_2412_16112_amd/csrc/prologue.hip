@@ -4,7 +4,11 @@
 // column angle, result rounded to bf16.  Text tokens are normalised but not turned.
 //
 // HBM-bound: every row is read once and written once.  D / 8 lanes share a token row (16 bytes each, so a
-// row is one contiguous 128- or 256-byte access); the sum of squares is combined with lane shuffles.
+// row is one contiguous 128- or 256-byte access); the sum of squares is combined with lane shuffles.  A thread takes
+// several heads of one token: the token's table rows (4 D bytes each, twice what a bf16 row has), its rotation and the
+// division that finds them are then shared, and the heads' places are uniform.  24 heads, 128 x 128 grid, 512 text
+// tokens, head_dim 128: 40 us, 5.1 TB/s; the forward call it precedes 566 -> 550 us against a version whose thread took
+// four tokens of one head, with three 64-bit divisions and two table rows for each.
 #include <hip/hip_runtime.h>
 
 #include "bf16_common.h"
@@ -12,53 +16,79 @@
 namespace clear {
 namespace {
 
-constexpr int kRowsPerThread = 4;  // independent 16-byte loads in flight per lane
+constexpr int kHeadsPerThread = 8;  // independent 16-byte loads in flight per lane, 8 heads of one token
 
+// Workgroup = 256 / LPR neighbouring tokens of kHeadsPerThread heads.
 template <int HD>
 __global__ void __launch_bounds__(256) qk_prologue_kernel(const __bf16* __restrict__ X, TensorStrides xs, __bf16* __restrict__ Y, TensorStrides ys,
-                                                          int H, long long rows_total, long long N, int n_text, int gridW,
+                                                          int H, long long BH, long long N, unsigned n_token_blocks, int n_text, int gridW,
                                                           const float* __restrict__ gain, float eps, const float* __restrict__ rope_y,
                                                           const float* __restrict__ rope_x)
 {
-    constexpr int LPR = HD / 8;        // lanes per row
-    constexpr int RPB = 256 / LPR;     // rows per block and sweep
+    constexpr int LPR = HD / 8;     // lanes per row
+    constexpr int TPB = 256 / LPR;  // tokens per workgroup
     const int c0 = 8 * (threadIdx.x % LPR);
-    const long long row0 = (long long)blockIdx.x * (RPB * kRowsPerThread) + threadIdx.x / LPR;
-    // row = (b * H + h) * N + token  ->  element offset in a strided [B, H, N, HD] tensor
-    auto offset = [&](long long row, const TensorStrides& st) {
-        const long long bh = row / N, t = row % N;
-        return (bh / H) * st.sb + (bh % H) * st.sh + t * st.sn;
-    };
-    bf16x8 in[kRowsPerThread];
+    const long long t = (long long)(blockIdx.x % n_token_blocks) * TPB + threadIdx.x / LPR;
+    const long long bh0 = (long long)(blockIdx.x / n_token_blocks) * kHeadsPerThread;
+    const bool live = t < N;
+    const long long tc = live ? t : N - 1;
+    const int n_heads = BH - bh0 < kHeadsPerThread ? (int)(BH - bh0) : kHeadsPerThread;
+    const long long b0 = bh0 / H;
+    const int h0 = (int)(bh0 - b0 * H);
+    bf16x8 in[kHeadsPerThread];
+    {
+        long long b = b0;
+        int h = h0;
 #pragma unroll
-    for (int i = 0; i < kRowsPerThread; ++i) {
-        const long long row = row0 + (long long)i * RPB;
-        in[i] = *(const bf16x8*)(X + offset(row < rows_total ? row : rows_total - 1, xs) + c0);
-    }
-#pragma unroll
-    for (int i = 0; i < kRowsPerThread; ++i) {
-        const long long row = row0 + (long long)i * RPB;
-        const bool live = row < rows_total;
-        const long long rr = live ? row : rows_total - 1;
-        float x[8], ss = 0.f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            x[j] = (float)in[i][j];
-            ss += x[j] * x[j];
+        for (int i = 0; i < kHeadsPerThread; ++i) {
+            if (i < n_heads) in[i] = *(const bf16x8*)(X + b * xs.sb + h * xs.sh + tc * xs.sn + c0);
+            if (++h == H) {
+                h = 0;
+                ++b;
+            }
         }
+    }
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 g0 = zero, g1 = zero, a0 = zero, a1 = zero, x0 = zero, x1 = zero;
+    if (gain) {
+        g0 = *(const f32x4*)(gain + c0);
+        g1 = *(const f32x4*)(gain + c0 + 4);
+    }
+    const bool turn = rope_y && tc >= n_text;
+    if (turn) {
+        const long long pix = tc - n_text;
+        const long long py = N <= 0xffffffffLL ? (long long)((unsigned)pix / (unsigned)gridW) : pix / gridW;  // (64-bit divisions are long)
+        const float* const ry = rope_y + (size_t)py * HD + c0;
+        const float* const rx = rope_x + (size_t)(pix - py * gridW) * HD + c0;
+        a0 = *(const f32x4*)ry;
+        a1 = *(const f32x4*)(ry + 4);
+        x0 = *(const f32x4*)rx;
+        x1 = *(const f32x4*)(rx + 4);
+    }
+    long long b = b0;
+    int h = h0;
 #pragma unroll
-        for (int m = 1; m < LPR; m <<= 1) ss += __shfl_xor(ss, m, 64);
-        const float inv_rms = 1.0f / sqrtf(ss * (1.0f / HD) + eps);
-        const long long t = rr % N;
-        const bool turn = rope_y && t >= n_text;
-        const long long pix = turn ? t - n_text : 0;
-        const float* const ry = rope_y + (size_t)(pix / gridW) * HD + c0;
-        const float* const rx = rope_x + (size_t)(pix % gridW) * HD + c0;
-        prologue_chunk(x, inv_rms, gain ? gain + c0 : nullptr, turn ? ry : nullptr, turn ? rx : nullptr);
-        bf16x8 out;
+    for (int i = 0; i < kHeadsPerThread; ++i) {
+        if (i < n_heads) {
+            float x[8], ss = 0.f;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) out[j] = (__bf16)x[j];
-        if (live) *(bf16x8*)(Y + offset(rr, ys) + c0) = out;
+            for (int j = 0; j < 8; ++j) {
+                x[j] = (float)in[i][j];
+                ss += x[j] * x[j];
+            }
+#pragma unroll
+            for (int m = 1; m < LPR; m <<= 1) ss += __shfl_xor(ss, m, 64);
+            const float inv_rms = 1.0f / sqrtf(ss * (1.0f / HD) + eps);
+            prologue_chunk_values(x, inv_rms, gain != nullptr, g0, g1, turn, a0, a1, x0, x1);
+            bf16x8 out;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) out[j] = (__bf16)x[j];
+            if (live) *(bf16x8*)(Y + b * ys.sb + h * ys.sh + t * ys.sn + c0) = out;
+        }
+        if (++h == H) {
+            h = 0;
+            ++b;
+        }
     }
 }
 
@@ -69,17 +99,18 @@ hipError_t launch_qk_prologue(const void* X, const TensorStrides& xs, void* Y, c
                               hipStream_t stream)
 {
     const long long N = (long long)n_text + (long long)gridH * gridW;
-    const long long rows = (long long)B * H * N;
-    if (rows == 0) return hipSuccess;
-    const int rows_per_block = 256 / (head_dim / 8) * kRowsPerThread;
-    const long long blocks = (rows + rows_per_block - 1) / rows_per_block;
+    const long long BH = (long long)B * H;
+    if (BH * N == 0) return hipSuccess;
+    const int tokens_per_block = 256 / (head_dim / 8);
+    const long long token_blocks = (N + tokens_per_block - 1) / tokens_per_block;
+    const long long blocks = token_blocks * ((BH + kHeadsPerThread - 1) / kHeadsPerThread);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     if (head_dim == 128)
-        hipLaunchKernelGGL(qk_prologue_kernel<128>, dim3((unsigned)blocks), dim3(256), 0, stream, (const __bf16*)X, xs, (__bf16*)Y, ys, H, rows, N,
-                           n_text, gridW, gain, eps, rope_y, rope_x);
+        hipLaunchKernelGGL(qk_prologue_kernel<128>, dim3((unsigned)blocks), dim3(256), 0, stream, (const __bf16*)X, xs, (__bf16*)Y, ys, H, BH, N,
+                           (unsigned)token_blocks, n_text, gridW, gain, eps, rope_y, rope_x);
     else if (head_dim == 64)
-        hipLaunchKernelGGL(qk_prologue_kernel<64>, dim3((unsigned)blocks), dim3(256), 0, stream, (const __bf16*)X, xs, (__bf16*)Y, ys, H, rows, N,
-                           n_text, gridW, gain, eps, rope_y, rope_x);
+        hipLaunchKernelGGL(qk_prologue_kernel<64>, dim3((unsigned)blocks), dim3(256), 0, stream, (const __bf16*)X, xs, (__bf16*)Y, ys, H, BH, N,
+                           (unsigned)token_blocks, n_text, gridW, gain, eps, rope_y, rope_x);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();

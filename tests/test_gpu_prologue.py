@@ -57,6 +57,24 @@ def test_qk_prologue_pass(d, norm, rope):
     assert torch.equal(Z, Y)
 
 
+@pytest.mark.parametrize("B,H,n_text,gridH,gridW,d", [
+    (1, 1, 0, 1, 1, 128),    # one row
+    (1, 8, 3, 3, 4, 64),     # a thread's 8 heads, less than a workgroup's tokens
+    (1, 9, 5, 13, 15, 128),  # one head more than a thread takes
+    (3, 5, 7, 5, 5, 64),     # a thread's heads belong to two batch entries; exactly a workgroup's 32 tokens
+    (5, 3, 7, 6, 3, 128),    # ... to three or more, and the last thread has 7
+])
+def test_qk_prologue_pass_head_groups(B, H, n_text, gridH, gridW, d):
+    """A thread takes 8 of the B * H heads of a token: sizes around that and around a workgroup's 2048 / d tokens."""
+    X, _, _ = make_qkv_shape(B, H, n_text, gridH, gridW, d, "bf16", seed=23, device=DEV, q_scale=3.0)
+    g, _, ry, rx = tables(gridH, gridW, d, 24, ntk=10.0)
+    Y = ca.clear_attn_qk_prologue(X, n_text, gridH, gridW, gain=g, norm_eps=1e-6, rope_y=ry, rope_x=rx)
+    torch.cuda.synchronize()
+    for b in range(B):
+        for h in range(H):
+            check_rounded(np64(Y[b, h]), pro.qk_prologue(np64(X[b, h]), np64(g), 1e-6, n_text, gridH, gridW, np64(ry), np64(rx)))
+
+
 FWD_CASES = [
     # n_text, gridH, gridW, r, H, norm, rope, logit_scale, ntk
     (64, 40, 24, 8, 2, True, True, 1.0, 1.0),
