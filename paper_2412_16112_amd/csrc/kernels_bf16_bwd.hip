@@ -769,43 +769,80 @@ __global__ void __launch_bounds__(512, 1) clear_bwd_bf16_all_kernel(const BwdPar
     clear_bwd_bf16_workgroup<kBwdQ, true, kCodeDisc>(p, bid - n_text_wgs, n_text_wgs);
 }
 
-// delta_i = dO_i . O_i for every row: D / 8 lanes per row (8 channels = 16 bytes each).
-__global__ void __launch_bounds__(256) clear_bwd_delta_kernel(const __bf16* O, TensorStrides os, const __bf16* dO, TensorStrides dos, int H,
-                                                              long long N, float* delta, long long rows)
+// delta_i = dO_i . O_i for every row: D / 8 lanes per row (8 channels = 16 bytes each).  A workgroup takes 256 / CHUNKS
+// neighbouring tokens of kDeltaHeads heads, so that a lane has 2 kDeltaHeads loads in flight and the head's place is
+// uniform: with one row a lane, 64-bit divisions that found its place stood in front of its only two loads.  24 heads,
+// 4 608 tokens, head_dim 128: 11.8 us, 4.8 TB/s.  With the reduction below, a training step's call 576 -> 564 us.
+constexpr int kDeltaHeads = 4, kDeltaTokens = 256 / CHUNKS;
+__global__ void __launch_bounds__(256) clear_bwd_delta_kernel(const __bf16* O, TensorStrides os, const __bf16* dO, TensorStrides dos, int H, int BH,
+                                                              long long N, unsigned n_token_blocks, float* delta)
 {
-    auto offset = [&](long long row, const TensorStrides& st) {  // row = (b * H + h) * N + token
-        const long long bh = row / N, t = row % N;
-        return (bh / H) * st.sb + (bh % H) * st.sh + t * st.sn;
-    };
-    const long long row = (long long)blockIdx.x * (256 / CHUNKS) + threadIdx.x / CHUNKS;
+    const long long t = (long long)(blockIdx.x % n_token_blocks) * kDeltaTokens + threadIdx.x / CHUNKS;
+    const int bh0 = (int)(blockIdx.x / n_token_blocks) * kDeltaHeads;
     const int part = threadIdx.x % CHUNKS;
-    float s = 0.f;
-    if (row < rows) {
-        const bf16x8 o = *(const bf16x8*)(O + offset(row, os) + 8 * part);
-        const bf16x8 g = *(const bf16x8*)(dO + offset(row, dos) + 8 * part);
+    const long long tc = t < N ? t : N - 1;
+    const int n_heads = imin(kDeltaHeads, BH - bh0);
+    bf16x8 o[kDeltaHeads], g[kDeltaHeads];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) s += (float)o[j] * (float)g[j];
+    for (int i = 0; i < kDeltaHeads; ++i) {
+        if (i < n_heads) {
+            const int b = (bh0 + i) / H, h = (bh0 + i) % H;
+            o[i] = *(const bf16x8*)(O + b * os.sb + h * os.sh + tc * os.sn + 8 * part);
+            g[i] = *(const bf16x8*)(dO + b * dos.sb + h * dos.sh + tc * dos.sn + 8 * part);
+        }
     }
 #pragma unroll
-    for (int off = CHUNKS / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (row < rows && part == 0) delta[row] = s;
+    for (int i = 0; i < kDeltaHeads; ++i) {
+        if (i < n_heads) {
+            float s = 0.f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s += (float)o[i][j] * (float)g[i][j];
+#pragma unroll
+            for (int off = CHUNKS / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+            if (t < N && part == 0) delta[(long long)(bh0 + i) * N + t] = s;
+        }
+    }
 }
 
-// Adds up the column-split partial sums of the text rows and stores them as bf16: one workgroup per
-// (mode, batch*head, text row), one thread per channel.
-__global__ void __launch_bounds__(D) clear_bwd_reduce_kernel(const BwdParams p)
+// Adds up the column-split partial sums of the text rows and stores them as bf16: 4 channels a thread, 1024 / D rows
+// (mode, batch*head, text row) a workgroup.  Four partial sums are read at a time; they are added in the order of the splits.
+// (One channel a thread and one row a workgroup before: 36 864 workgroups of 128 threads at 24 heads and 512 text tokens.)
+constexpr int kReduceRows = 1024 / D;
+__global__ void __launch_bounds__(256) clear_bwd_reduce_kernel(const BwdParams p)
 {
-    const int ch = threadIdx.x;
+    typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+    const unsigned ch = 4 * (threadIdx.x % (D / 4));
     const long long BHn = (long long)p.B * p.H * p.n_text;
-    const int mode = (int)(blockIdx.x / BHn);
-    const long long row = blockIdx.x % BHn;
-    const int bh = (int)(row / p.n_text), q = (int)(row % p.n_text);
-    float s = 0.f;
-    for (int k = 0; k < p.n_splits; ++k)
-        s += p.ws[((((long long)mode * p.B * p.H + bh) * p.n_splits + k) * p.n_text + q) * D + ch];
-    __bf16* out = (__bf16*)(mode == kBwdQ ? p.dQ : (mode == kBwdK ? p.dK : p.dV));
+    const long long gr = (long long)blockIdx.x * kReduceRows + threadIdx.x / (D / 4);
+    if (gr >= 3 * BHn) return;
+    const int mode = gr >= 2 * BHn ? 2 : (gr >= BHn ? 1 : 0);
+    const long long row = gr - mode * BHn;
+    int bh, q;
+    if (BHn <= 0x7fffffffLL) {  // (64-bit divisions are long)
+        bh = (int)((unsigned)row / (unsigned)p.n_text);
+        q = (int)((unsigned)row % (unsigned)p.n_text);
+    } else {
+        bh = (int)(row / p.n_text);
+        q = (int)(row % p.n_text);
+    }
+    const float* part = p.ws + ((((long long)mode * p.B * p.H + bh) * p.n_splits) * p.n_text + q) * D + ch;
+    const long long pitch = (long long)p.n_text * D;  // from one split to the next
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    int k = 0;
+    for (; k + 4 <= p.n_splits; k += 4, part += 4 * pitch) {
+        const f32x4 v0 = *(const f32x4*)part, v1 = *(const f32x4*)(part + pitch), v2 = *(const f32x4*)(part + 2 * pitch), v3 = *(const f32x4*)(part + 3 * pitch);
+        s += v0;
+        s += v1;
+        s += v2;
+        s += v3;
+    }
+    for (; k < p.n_splits; ++k, part += pitch) s += *(const f32x4*)part;
+    __bf16* const out = (__bf16*)(mode == kBwdQ ? p.dQ : (mode == kBwdK ? p.dK : p.dV));
     const TensorStrides& st = mode == kBwdQ ? p.dqs : (mode == kBwdK ? p.dks : p.dvs);
-    out[(bh / p.H) * st.sb + (bh % p.H) * st.sh + q * st.sn + ch] = (__bf16)s;
+    bf16x4 r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r[j] = (__bf16)s[j];
+    *(bf16x4*)(out + (bh / p.H) * st.sb + (bh % p.H) * st.sh + q * st.sn + ch) = r;
 }
 
 template <int MODE, bool LINROWS, int CODE>
@@ -853,9 +890,8 @@ hipError_t launch_bf16_backward(const BwdParams& p, const void* O, float* delta,
     hipError_t e = hipSuccess;
     // (kBwdPhaseAll: no delta kernel; the dQ kernels form delta and run before the dK / dV kernels, which read it)
     if (phase == kBwdPhaseDelta) {
-        const long long rows = (long long)BH * p.N;
-        constexpr int rows_per_block = 256 / CHUNKS;
-        hipLaunchKernelGGL(clear_bwd_delta_kernel, dim3((unsigned)((rows + rows_per_block - 1) / rows_per_block)), dim3(256), 0, stream, (const __bf16*)O, p.os, (const __bf16*)p.dO, p.dos, p.H, p.N, delta, rows);
+        const unsigned token_blocks = (unsigned)((p.N + kDeltaTokens - 1) / kDeltaTokens), head_blocks = (unsigned)((BH + kDeltaHeads - 1) / kDeltaHeads);
+        hipLaunchKernelGGL(clear_bwd_delta_kernel, dim3(token_blocks * head_blocks), dim3(256), 0, stream, (const __bf16*)O, p.os, (const __bf16*)p.dO, p.dos, p.H, BH, p.N, token_blocks, delta);
         e = hipGetLastError();
     }
     const int nimg = BH * p.n_classes * p.n_q_tiles;
@@ -894,7 +930,7 @@ hipError_t launch_bf16_backward(const BwdParams& p, const void* O, float* delta,
 #endif
     }
     if (e == hipSuccess && (all || phase == kBwdPhaseReduce)) {
-        hipLaunchKernelGGL(clear_bwd_reduce_kernel, dim3((unsigned)(3LL * BH * p.n_text)), dim3(D), 0, stream, p);
+        hipLaunchKernelGGL(clear_bwd_reduce_kernel, dim3((unsigned)((3LL * BH * p.n_text + kReduceRows - 1) / kReduceRows)), dim3(256), 0, stream, p);
         e = hipGetLastError();
     }
     return e;

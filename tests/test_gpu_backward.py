@@ -68,6 +68,28 @@ def test_backward_batch_of_two():
         check_grad("dV", dV[b, h].float().cpu().numpy(), rV)
 
 
+@pytest.mark.parametrize("B,H,n_text,gridH,gridW", [
+    (1, 1, 1, 64, 33),     # one text row, one range of columns
+    (1, 5, 33, 80, 131),   # five ranges (four at a time and one more), rows no multiple of a workgroup's
+    (2, 3, 19, 100, 83),   # four ranges; a thread's four heads belong to two batch entries
+])
+def test_backward_small_passes(B, H, n_text, gridH, gridW):
+    """The passes beside the matrix kernels, at sizes around their groups: delta (4 heads of 16 tokens a workgroup) and
+    the sums of the text rows' partial results (8 rows a workgroup, 4 partial results at a time)."""
+    r = 4
+    Q, K, V, dO, O, lse, dQ, dK, dV = run_case(n_text, gridH, gridW, r, H, seed=83, B=B)
+    N = n_text + gridH * gridW
+    text = np.arange(n_text)
+    rows = np.unique(np.concatenate([text, [N - 17, N - 16, N - 2, N - 1]]))
+    for b, h in {(0, 0), (B - 1, H - 1), (B - 1, 0)}:
+        q, k, v, g = (t[b, h].float().cpu().numpy() for t in (Q, K, V, dO))
+        check_grad("dQ", dQ[b, h].float().cpu().numpy()[rows], orc.backward_dq_rows(q, k, v, g, rows, n_text, gridH, gridW, r))
+        cols = np.unique([0, n_text - 1, N - 1])
+        rK, rV = orc.backward_dkv_cols(q, k, v, g, cols, n_text, gridH, gridW, r)
+        check_grad("dK", dK[b, h].float().cpu().numpy()[cols], rK)
+        check_grad("dV", dV[b, h].float().cpu().numpy()[cols], rV)
+
+
 def test_forward_lse_is_the_log_of_the_softmax_denominator():
     n_text, gridH, gridW, r = 37, 20, 24, 5
     Q, K, V, dO, O, lse, *_ = run_case(n_text, gridH, gridW, r, 1, seed=77, q_scale=2.0)
