@@ -22,6 +22,7 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(4))) short short4v;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_any;  // in callers' fp32 tensors, which need only be 4-byte aligned
 
 #ifndef CLEAR_HEAD_DIM
 #define CLEAR_HEAD_DIM 128

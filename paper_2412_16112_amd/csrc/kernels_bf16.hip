@@ -673,7 +673,7 @@ __device__ __forceinline__ void clear_fwd_bf16_workgroup(const FwdParams& p, con
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 f32x4 v = {oacc[db][4 * g] * inv, oacc[db][4 * g + 1] * inv, oacc[db][4 * g + 2] * inv, oacc[db][4 * g + 3] * inv};
-                *(f32x4*)(p.band_o + row * D + 32 * db + 8 * g + 4 * hh) = v;
+                *(f32x4_any*)(p.band_o + row * D + 32 * db + 8 * g + 4 * hh) = v;
             }
         return;
     }

@@ -309,7 +309,7 @@ __global__ void __launch_bounds__(kWaves * 64, CELLS == 2 ? 5 : 2) clear_fwd_f32
     }
     if (lse_out && g == 0) *lse_out = lse;
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb) *(f32x4*)(orow + 16 * cb + 4 * g) = o[cb] * inv;
+    for (int cb = 0; cb < 4; ++cb) *(f32x4_any*)(orow + 16 * cb + 4 * g) = o[cb] * inv;
 }
 
 // Log-sum-exp combination of the key-split partial results of the text-query rows: 16 lanes per row, 4 channels each.
@@ -331,7 +331,7 @@ __global__ void __launch_bounds__(256) clear_text_merge_f32_kernel(const FwdPara
     }
     const float lse = logf(den) + m * p.scale_log2e * 0.6931471805599453f;
     float* out = p.band_o ? p.band_o + row * HD : (float*)p.O + ((long long)bh * p.N + q) * HD;
-    *(f32x4*)(out + ch) = num / den;
+    *(f32x4_any*)(out + ch) = num / den;
     if (ch == 0) {
         if (p.band_o)
             p.band_lse[row] = lse;

@@ -161,3 +161,23 @@ def test_merge_exact_against_numpy_merge():
     ref = pp.merge_exact(o.reshape(n_parts, -1, d), lse.reshape(n_parts, -1)).reshape(B, H, n_text, d)
     np.testing.assert_allclose(O[:, :, :n_text].cpu().numpy(), ref, rtol=2e-5, atol=2e-6)
     assert (O[:, :, n_text:] == 0).all()
+
+
+@pytest.mark.parametrize("dtype,H,n_text,gridH,gridW,d", [("bf16", 2, 37, 24, 24, 128), ("bf16", 24, 70, 112, 96, 64), ("bf16", 24, 70, 112, 96, 128),
+                                                          ("f32", 1, 9, 24, 24, 64), ("f32", 12, 70, 64, 64, 64)])
+def test_band_text_results_need_element_alignment_only(dtype, H, n_text, gridH, gridW, d):
+    """text_o and text_lse aligned to 4 bytes: the same bits as aligned to 16, with one key range and with several."""
+    Q, K, V = make_qkv_shape(1, H, n_text, gridH, gridW, d, dtype, seed=55, device="cuda:0")
+    ctx = ca.ClearAttn(n_text, gridH, gridW, d, 8, ca._dtype_code(Q))
+    got = []
+    try:
+        for skip in (0, 1):
+            to = torch.full((H * n_text * d + skip,), float("nan"), device="cuda:0")[skip:].view(1, H, n_text, d)
+            tl = torch.full((H * n_text + skip,), float("nan"), device="cuda:0")[skip:].view(1, H, n_text)
+            ctx.forward_band(Q, K, V, torch.zeros_like(Q), 8, gridH, True, to, tl)
+            torch.cuda.synchronize()
+            got.append((to, tl))
+    finally:
+        ctx.destroy()
+    assert torch.isfinite(got[0][0]).all() and torch.isfinite(got[0][1]).all()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
