@@ -163,6 +163,34 @@ def test_merge_exact_against_numpy_merge():
     assert (O[:, :, n_text:] == 0).all()
 
 
+# head_dim a multiple of four and not, parts in whole groups of four and a remainder, more rows than a workgroup takes,
+# tensors aligned to their elements only
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("mode", [ca.CLEAR_MERGE_EXACT, ca.CLEAR_MERGE_AVERAGE])
+@pytest.mark.parametrize("n_parts,d,n_text,skip", [(1, 1, 3, 0), (3, 6, 5, 1), (4, 64, 21, 0), (9, 128, 9, 1), (6, 132, 4, 3), (64, 1023, 2, 1)])
+def test_merge_text_shapes(dtype, mode, n_parts, d, n_text, skip):
+    B, H, N = 2, 3, n_text + 11
+    gen = torch.Generator(device="cuda:0").manual_seed(n_parts * 1000 + d)
+
+    def at_offset(shape, dtype, scale):
+        n = int(np.prod(shape))
+        return (scale * torch.randn(n + skip, generator=gen, device="cuda:0")).to(dtype)[skip:].view(shape)
+
+    to = [at_offset((B, H, n_text, d), torch.float32, 1.0) for _ in range(n_parts)]
+    tl = [at_offset((B, H, n_text), torch.float32, 4.0) for _ in range(n_parts)]
+    O = at_offset((B, H, N, d), dtype, 1.0)
+    rest = O[:, :, n_text:].clone()
+    ca.clear_attn_merge_text(to, tl, O, n_text, mode)
+    torch.cuda.synchronize()
+    o, lse = torch.stack(to).double(), torch.stack(tl).double()
+    w = torch.softmax(lse, 0) if mode == ca.CLEAR_MERGE_EXACT else torch.full_like(lse, 1.0 / n_parts)
+    ref, size = (w[..., None] * o).sum(0), (w[..., None] * o.abs()).sum(0)
+    # n_parts products and sums in fp32, exponentials of |x| < 64 to a relative 64 x 2^-23; bf16: half an ulp of the result
+    bound = size * (n_parts + 64) * 2.0 ** -22 + (ref.abs() * 2.0 ** -8 if dtype == torch.bfloat16 else 0.0) + 1e-30
+    assert ((O[:, :, :n_text].double() - ref).abs() <= bound).all()
+    assert torch.equal(O[:, :, n_text:], rest)
+
+
 @pytest.mark.parametrize("dtype,H,n_text,gridH,gridW,d", [("bf16", 2, 37, 24, 24, 128), ("bf16", 24, 70, 112, 96, 64), ("bf16", 24, 70, 112, 96, 128),
                                                           ("f32", 1, 9, 24, 24, 64), ("f32", 12, 70, 64, 64, 64)])
 def test_band_text_results_need_element_alignment_only(dtype, H, n_text, gridH, gridW, d):
