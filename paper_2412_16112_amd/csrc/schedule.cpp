@@ -516,8 +516,10 @@ static void build_block_programs_for(const Schedule& s, const QueryTilePatterns&
                 for (int k = 0; k < per; ++k) {
                     const int b = k * waves_per_patch + g, left = keys == 0 ? 32 : keys - 32 * b;
                     if (left <= 0 && k > 0) break;
+                    // (a wave without a key left names the stage's first block: its own lies in a tile that is not staged)
                     const unsigned id = left >= 32 ? kMaskIdNone : left > 0 ? kMaskIdFirstKeys + (unsigned)left : kMaskIdNothing;
-                    out->words.push_back((unsigned)((b >> 1) * tile_units + (b & 1)) | id << kProgramMaskShift);
+                    const unsigned place = left > 0 ? (unsigned)((b >> 1) * tile_units + (b & 1)) : 0;
+                    out->words.push_back(place | id << kProgramMaskShift);
                     ++used;
                 }
                 out->words.back() |= kProgramStageEnd;

@@ -12,6 +12,8 @@
 #include "../../paper_2412_16112_amd/csrc/block_class.h"
 #include "../../paper_2412_16112_amd/csrc/clear_internal.h"
 
+int check_block_programs();  // block_programs.cpp
+
 static int failures = 0;
 #define EXPECT(cond)                                                       \
     do {                                                                   \
@@ -214,6 +216,7 @@ int main()
     counts();
     mask_tables();
     wave_descriptors();
+    failures += check_block_programs();
     bands_and_argument_checks();
     if (failures) {
         std::printf("%d check(s) failed\n", failures);

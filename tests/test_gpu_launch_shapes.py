@@ -58,6 +58,7 @@ def test_f32_launch_shapes(B, H, n_text, gh, gw, r, kind, shift):
 # borders, masks that depend on more than the offset
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("B,H,n_text,gh,gw,r,kind,shift", [
+    (1, 1, 8, 16, 16, 4, ca.CLEAR_MASK_DISC, 0),  # four waves per patch of text queries, two of them without a key in the last stage
     (1, 1, 31, 20, 20, 6, ca.CLEAR_MASK_DISC, 0),
     (1, 2, 512, 33, 31, 16, ca.CLEAR_MASK_DISC, 0),
     (2, 6, 65, 37, 45, 9, ca.CLEAR_MASK_DISC, 0),
@@ -88,3 +89,28 @@ def test_bf16_launch_shapes(d, B, H, n_text, gh, gw, r, kind, shift):
             ref = orc.attention_rows(*(t[b, h].double().numpy() for t in (Q, K, V)), rows, n_text, gh, gw, r)
         mx, rms = error_metrics(O[b, h].numpy()[rows], ref)
         assert mx <= TOL["bf16"][0] and rms <= TOL["bf16"][1], (mx, rms)
+
+
+# one key range of text queries whose last stage holds one key tile of two (or of four at 64 channels)
+@pytest.mark.parametrize("B,H,n_text,gh,gw,r,d", [(1, 1, 8, 16, 16, 4, 128), (1, 1, 8, 16, 16, 4, 64), (1, 1, 31, 16, 16, 8, 128),
+                                                   (1, 1, 128, 12, 12, 5, 128), (1, 1, 9, 20, 20, 6, 64), (2, 2, 100, 14, 14, 6, 128)])
+def test_bf16_small_call_does_not_depend_on_what_ran_before(B, H, n_text, gh, gw, r, d):
+    """Kernels leave their data in the LDS.  An fp32 call on every CU, with finite values of which every other 16 bits read
+    as a bf16 NaN or infinity, in front of a small bf16 call: the same bits as without."""
+    print(f"[case] B={B} H={H} n_text={n_text} grid={gh}x{gw} d={d}", flush=True)
+    Q, K, V = make_qkv_shape(B, H, n_text, gh, gw, d, "bf16", seed=61, device=DEV)
+    q32, k32, v32 = make_qkv_shape(1, 16, 64, 64, 64, 64, "f32", seed=62, device=DEV)
+    ctx, ctx32 = ca.ClearAttn(n_text, gh, gw, d, r, ca.CLEAR_BF16), ca.ClearAttn(64, 64, 64, 64, 8, ca.CLEAR_F32)
+    got = []
+    try:
+        for low in (0x0000, 0x7FC0, 0x7F80, 0x3F80):
+            dirty = [((t.view(torch.int32) & -65536) | low).view(torch.float32) for t in (q32, k32, v32)]
+            ctx32.forward(*dirty)
+            got.append(ctx.forward(Q, K, V))
+            torch.cuda.synchronize()
+    finally:
+        ctx.destroy()
+        ctx32.destroy()
+    assert torch.isfinite(got[0].float()).all()
+    for O in got[1:]:
+        assert torch.equal(O, got[0])
