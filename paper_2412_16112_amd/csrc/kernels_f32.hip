@@ -193,13 +193,14 @@ __global__ void __launch_bounds__(kWaves * 64, CELLS == 2 ? 5 : 2) clear_fwd_f32
         for (int cb = 0; cb < 4; ++cb)
             v_addr[t][cb] = lds_base + (unsigned)(HALF_BYTES + (4 * g + t) * 256 + (((4 * cb + (qi >> 2)) ^ f32_swz(4 * g + t)) << 4) + (qi & 3) * 4);
 
-    auto run_stage = [&](auto buf_tag) __attribute__((always_inline)) {
+    auto run_stage = [&](auto buf_tag, auto text_tag) __attribute__((always_inline)) {
         constexpr int buf = decltype(buf_tag)::value;
+        constexpr bool TEXT = decltype(text_tag)::value;
         wait_vmcnt<0>();
         __syncthreads();  // the stage has landed, and everyone has left the other buffer
         const Stage nxt = next_stage(cur.i + 1);
         if (nxt.i < n_stages) issue_stage(nxt, buf ^ 1);
-        const bool linear = cur.i < n_lin;
+        const bool linear = TEXT || cur.i < n_lin;
         const long long lin_left = lin_limit - lin_begin - (long long)cur.i * STAGE_KEYS;  // keys of the range from this stage on
         const int left = lin_left < STAGE_KEYS ? (int)lin_left : STAGE_KEYS;
         const bool cut = cur.a + PART_H > p.gridH || cur.b + kKeyTileW > p.gridW;
@@ -249,20 +250,40 @@ __global__ void __launch_bounds__(kWaves * 64, CELLS == 2 ? 5 : 2) clear_fwd_f32
 #pragma unroll
             for (int t = 0; t < 4; ++t) pr[t] = __builtin_amdgcn_exp2f((s[t] - m) * sc);
             l += (pr[0] + pr[1]) + (pr[2] + pr[3]);
+            if constexpr (TEXT) {
+                // Over all the keys of a range a sum that takes a rounding per key loses more than the shorter walks of the image rows:
+                // the cell's products are summed on their own and added in one step.  (38 heads, 64 x 64 grid, 333 text tokens, relative
+                // error of the text rows against 64 bits: 8.6e-7 -> 6.5e-7; for image rows too it would be 7.6e-7 -> 5.5e-7 at 3 % of the time.)
+                f32x4 oc[4] = {zero, zero, zero, zero};
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
+                for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int cb = 0; cb < 4; ++cb)
-                    o[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(*(lds_f32_ptr)(size_t)(v_addr[t][cb] + at), pr[t], o[cb], 0, 0, 0);
+                    for (int cb = 0; cb < 4; ++cb)
+                        oc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(*(lds_f32_ptr)(size_t)(v_addr[t][cb] + at), pr[t], oc[cb], 0, 0, 0);
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) o[cb] += oc[cb];
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int cb = 0; cb < 4; ++cb)
+                        o[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(*(lds_f32_ptr)(size_t)(v_addr[t][cb] + at), pr[t], o[cb], 0, 0, 0);
+            }
         };
         static_for<CELLS>(run_cell);
         cur = nxt;
     };
-    while (cur.i < n_stages) {
-        run_stage(std::integral_constant<int, 0>{});
-        if (cur.i >= n_stages) break;
-        run_stage(std::integral_constant<int, 1>{});
-    }
+    auto walk = [&](auto text_tag) __attribute__((always_inline)) {
+        while (cur.i < n_stages) {
+            run_stage(std::integral_constant<int, 0>{}, text_tag);
+            if (cur.i >= n_stages) break;
+            run_stage(std::integral_constant<int, 1>{}, text_tag);
+        }
+    };
+    if (textq)
+        walk(std::true_type{});
+    else
+        walk(std::false_type{});
 
     l = quad_sum(l);
     if (groups > 1) {

@@ -114,3 +114,26 @@ def test_bf16_small_call_does_not_depend_on_what_ran_before(B, H, n_text, gh, gw
     assert torch.isfinite(got[0].float()).all()
     for O in got[1:]:
         assert torch.equal(O, got[0])
+
+
+@pytest.mark.parametrize("H,n_text,gh,gw,range_keys", [(12, 77, 64, 44, 2893), (4, 64, 320, 320, 1664)])
+def test_f32_text_rows_round_once_per_cell_of_keys(H, n_text, gh, gw, range_keys):
+    """Relative error of the text rows, dense sums over key ranges of at most `range_keys`, against 64 bits.  A range is
+    added up in steps of 16 keys: each step rounds the running sum by half an ulp of 2^-24 (root mean square below 2^-25), and as a sum of
+    random terms grows like a root, k steps leave 2^-25 sqrt(k / 2) of the result.  12 such halves cover the rest (logits of 64
+    products, exponentials, normalisation).  A rounding per key would leave 4 times the first part."""
+    print(f"[case] f32 text rows H={H} n_text={n_text} grid={gh}x{gw}", flush=True)
+    Q, K, V = make_qkv_shape(1, H, n_text, gh, gw, 64, "f32", seed=71, device=DEV)
+    ctx = ca.ClearAttn(n_text, gh, gw, 64, 4, ca.CLEAR_F32)
+    try:
+        O = ctx.forward(Q, K, V)
+        torch.cuda.synchronize()
+    finally:
+        ctx.destroy()
+    num = den = 0.0
+    for h in range(H):
+        ref = torch.softmax(Q[0, h, :n_text].double() @ K[0, h].double().T / 8, 1) @ V[0, h].double()
+        num += ((O[0, h, :n_text].double() - ref) ** 2).sum().item()
+        den += (ref ** 2).sum().item()
+    rel = (num / den) ** 0.5
+    assert rel <= 2.0 ** -25 * ((range_keys / 16 / 2) ** 0.5 + 12), rel
