@@ -15,6 +15,7 @@
 
 #include "block_class.h"
 #include "clear_internal.h"
+#include "launch_shape.h"
 
 using namespace clear;
 
@@ -111,7 +112,6 @@ static thread_local std::string g_create_error;
 // the text-query rows.  One copy per GPU, held from the first use of the library on that GPU until the process
 // ends.  On the host `scratch` only names the symbol: its address on the current device comes from
 // hipGetSymbolAddress (scratch_address below), and that pointer is what kernels and copies are given.
-constexpr size_t kScratchBytes = (size_t)112 << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mutex;
@@ -171,79 +171,7 @@ static int check_kernel(int head_dim, int dtype, std::string* why)
     return CLEAR_ERR_UNSUPPORTED;
 }
 
-// The maximum number of key splits of the text-query pass; the workspace is sized for it.
-static int max_text_splits(long long N)
-{
-    // at least 512 keys per split, at most 64 splits
-    long long s = (N + 511) / 512;
-    if (s < 1) s = 1;
-    if (s > 64) s = 64;
-    return (int)s;
-}
-
-// Splits for a given batch*heads: at least two workgroups per CU when the keys allow it, and a workgroup
-// count that fills whole rounds of the CUs (a partial last round idles most of the chip).
-// `together`: the text-query workgroups go out in one launch with the image-query ones (launch_all) and fill the CUs
-// that those leave idle, so whole rounds do not matter; what then costs is the number of splits (partial results
-// written, read back and merged) and the length of a text-query workgroup when it is the last to finish: one round
-// of workgroups at most, of at least 2 048 keys each.  (Measured over 1 - 32 splits, 24 heads: 2 splits at a 64 x 64
-// grid and 5 at 128 x 128 and 256 x 256 beat the whole-rounds choice of 5, 16 and 16 by 6 %, 8 % and 2 %.)
-static void choose_text_splits(long long N, int BH, int n_tq_tiles, int num_cus, bool together, int* n_splits, int* split_keys)
-{
-    const int max_s = max_text_splits(N);
-    const long long units = (long long)BH * n_tq_tiles;
-    int best = 1;
-    double best_score = -1.0;
-    if (together && units < num_cus) {
-        best = (int)std::min<long long>(max_s, num_cus / units);
-        while (best > 1 && N / best < 2048) --best;
-    } else {
-        for (int s = 1; s <= max_s; ++s) {
-            long long keys = (N + s - 1) / s;
-            keys = ((keys + kKeyTileKeys - 1) / kKeyTileKeys) * kKeyTileKeys;
-            const long long real = (N + keys - 1) / keys;  // splits that actually hold keys
-            const long long wgs = units * real;
-            const long long rounds = (wgs + num_cus - 1) / num_cus;
-            double score = (double)wgs / (double)(rounds * num_cus);  // fraction of the rounds that is busy
-            if (wgs < 2LL * num_cus) score *= 0.5;                    // too few workgroups to hide a workgroup's start-up
-            if (score > best_score + 1e-9) {
-                best_score = score;
-                best = s;
-            }
-        }
-    }
-    long long keys = (N + best - 1) / best;
-    keys = ((keys + kKeyTileKeys - 1) / kKeyTileKeys) * kKeyTileKeys;  // whole 64-key stages
-    *split_keys = (int)keys;
-    *n_splits = (int)((N + keys - 1) / keys);
-}
-
 constexpr size_t kGroupsMaxTiles = 64;
-
-// Launch shape of the fp32 kernel.  A workgroup is four waves of 16 queries, all on one 8 x 8 patch of queries (64 text
-// queries); with `groups` = 2 or 4 waves on every 16 queries a patch of 4 x 8 or 4 x 4 (32 or 16 text queries) walks its
-// keys in a half or a quarter of the steps, at two or four times the staging traffic per pair.  So: as many waves per
-// patch as it takes to have two workgroups for every CU.  Text-query
-// rows: key ranges of 1 024 and more, about the length of an image query's walk, so that no text workgroup is the
-// last one running by far; shorter ones, down to 256, where that leaves CUs without work.
-static void choose_f32_shape(long long NV, int BH, int num_cus, FwdParams* p)
-{
-    const long long image = (long long)BH * p->n_q_tiles_launch * 4;
-    auto text_units = [&](int groups) { return (long long)BH * ((p->n_text * groups + 63) / 64); };
-    p->f32_groups = 1;
-    while (p->f32_groups < 4 && image * p->f32_groups + text_units(p->f32_groups) < 2LL * num_cus) p->f32_groups *= 2;
-    const int groups = p->f32_groups;
-    p->n_tq_tiles = (p->n_text * groups + 63) / 64;
-    if (p->n_text == 0) return;
-    long long splits = NV / 1024;
-    const long long idle = 2LL * num_cus - image * groups;
-    if (idle > 0) splits = std::max(splits, std::min(NV / (256 * groups), idle / text_units(groups)));
-    splits = std::max(1LL, std::min<long long>(splits, max_text_splits(NV)));
-    long long keys = (NV + splits - 1) / splits;
-    keys = ((keys + kKeyTileKeys - 1) / kKeyTileKeys) * kKeyTileKeys;
-    p->split_keys = (int)keys;
-    p->n_splits = (int)((NV + keys - 1) / keys);
-}
 
 // Kernel-side tile lists of a schedule: per query tile, the origins (row << 16 | col) of its key tiles, those inside the
 // grid (the first cutH rows, cutW columns) first, border tiles last; n_plain: how many lie inside.
@@ -661,79 +589,6 @@ static int band_tile_tables(clear_attn_ctx* ctx, int y_shift, hipStream_t stream
     return CLEAR_OK;
 }
 
-// Launch shape of a bf16 forward call: how many waves share 32 image queries (`groups`) and 32 text queries (`tq_groups`), the key
-// ranges of the text queries, and which rows' workgroups go out first.
-//
-// One workgroup fills a CU, so what a call of a few workgroups per CU takes is decided by how evenly they fill the CUs and by the length of
-// the longest.  Waves that share queries halve or quarter a workgroup's walk over its keys and double or quadruple the number
-// of workgroups, at the price of staging every key tile twice or four times; key ranges do the same for the text queries at the price of
-// partial results and a kernel that merges them.  Every combination is priced with the measured cost of a workgroup - a fixed part
-// (dispatch, query rows and first tiles, output), a part per stage (barrier and refill of the pipeline) and a part per 32-key block of
-// the two waves of a SIMD - and the time at which the last CU finishes, longest workgroups first; the cheapest is taken.  (24 heads,
-// 32 x 32 grid, 512 text tokens, r = 8: 40 -> 32 us against one wave per patch throughout; 2 heads: 36 -> 20 us.)  Beyond 16 workgroups
-// per CU the evenness takes care of itself: one wave per patch, and choose_text_splits.
-struct ForwardShape {
-    int groups, tq_groups, n_splits, split_keys;
-    bool text_first;
-};
-static ForwardShape choose_forward_shape(const clear_attn_ctx* ctx, const TileTables& tt, int BH, long long NV, const int (&n_image_tiles)[3], int n_classes)
-{
-    const int n_text = ctx->n_text, num_cus = ctx->num_cus, per_block = bf16_text_queries_per_block();
-    const long long image_wgs = (long long)BH * n_classes * n_image_tiles[0];
-    ForwardShape best = {1, 1, 1, kKeyTileKeys, false};
-    auto text_tiles = [&](int groups) { return (n_text * groups + per_block - 1) / per_block; };
-    if (image_wgs > 16LL * num_cus) {
-        if (n_text > 0) choose_text_splits(NV, BH, text_tiles(1), num_cus, image_wgs <= 64LL * num_cus, &best.n_splits, &best.split_keys);
-        return best;
-    }
-    // cycles; a SIMD's two waves together take `block` per block of either
-    const double fixed = 16e3, stage = ctx->head_dim == 64 ? 1100 : 900, block = ctx->head_dim == 64 ? 400 : 520;
-    const int stage_keys = bf16_tiles_per_stage(ctx->head_dim) * kKeyTileKeys;
-    double best_time = 1e300;
-    for (int gi = 0; gi < 3; ++gi) {
-        const ForwardTables& f = tt.fwd[gi];
-        if (f.qth == 0) continue;  // not built
-        const double n_image = (double)BH * n_classes * n_image_tiles[gi], c_image = fixed + f.stages * stage + 2 * f.steps * block;
-        for (int ti = 0; ti < (n_text > 0 ? 3 : 1); ++ti) {
-            const int tg = 1 << ti;
-            long long last_keys = -1;
-            for (int s = 1; s <= (n_text > 0 ? std::min(max_text_splits(NV), 16) : 1); ++s) {
-                double n_text_wgs = 0, c_text = 0, merge = 0;
-                long long keys = (NV + s - 1) / s;
-                keys = (keys + kKeyTileKeys - 1) / kKeyTileKeys * kKeyTileKeys;
-                const int real = (int)((NV + keys - 1) / keys);
-                if (n_text > 0) {
-                    if (keys == last_keys) continue;
-                    last_keys = keys;
-                    const double bytes = (double)BH * real * n_text * (ctx->head_dim + 2) * sizeof(float);
-                    if (real > 1 && bytes > (double)kScratchBytes) break;  // (clear_attn_forward_noalloc takes the same shape)
-                    const double stages = std::ceil((double)keys / stage_keys);
-                    n_text_wgs = (double)BH * text_tiles(tg) * real;
-                    c_text = fixed + stages * stage + 2 * block * stages * std::max(1.0, (double)stage_keys / 32 / tg) * std::min(1.0, (double)keys / (stages * stage_keys));
-                    if (real > 1) merge = 12e3 + 2 * bytes / 2000;  // a kernel of its own; partial results written and read back
-                }
-                // longest first: c1 n1, then c2 n2
-                const bool text_first = c_text > c_image;
-                const double c1 = text_first ? c_text : c_image, c2 = text_first ? c_image : c_text, n1 = text_first ? n_text_wgs : n_image, n2 = text_first ? n_image : n_text_wgs;
-                const double q = std::floor(n1 / num_cus), r = n1 - q * num_cus;
-                double lo = (q + (r > 0)) * c1, hi = lo + (n2 > 0 ? (std::ceil(n2 / num_cus) + 1) * c2 : 0);
-                auto fits = [&](double t) { return r * std::floor((t - (q + 1) * c1) / c2) + (num_cus - r) * std::floor((t - q * c1) / c2) >= n2; };
-                if (n2 == 0 || fits(lo)) hi = lo;
-                for (int i = 0; i < 24 && hi > lo; ++i) {
-                    const double mid = 0.5 * (lo + hi);
-                    (fits(mid) ? hi : lo) = mid;
-                }
-                const double time = hi + merge;
-                if (time < best_time * 0.98) {  // (in doubt the simpler shape)
-                    best_time = time;
-                    best = {1 << gi, tg, real, (int)keys, text_first};
-                }
-            }
-        }
-    }
-    return best;
-}
-
 // Validates the arguments of a forward call and fills the kernel parameters.
 // band == nullptr: the whole grid.
 struct BandArgs {
@@ -819,7 +674,9 @@ static int prepare_forward(clear_attn_ctx* ctx, const void* Q, const void* K, co
             for (int i = 0; i < 3; ++i)
                 if (tt->fwd[i].qth) n_image_tiles[i] = ((own_y1 + tt->fwd[i].qth - 1) / tt->fwd[i].qth - own_y0 / tt->fwd[i].qth) * tt->fwd[i].n_qtx;
             if (n_classes > 1) n_image_tiles[0] = n_qty * n_qtx;
-            const ForwardShape sh = choose_forward_shape(ctx, *tt, BH, NV, n_image_tiles, n_classes);
+            ForwardProblem fp = {n_text, head_dim, BH, NV, n_classes, ctx->num_cus, {}};
+            for (int i = 0; i < 3; ++i) fp.sets[i] = {n_image_tiles[i], tt->fwd[i].stages, tt->fwd[i].steps};
+            const ForwardShape sh = choose_forward_shape(fp);
             of = {BH, own_y0, own_y1, NV, tt, sh.groups, sh.tq_groups, sh.n_splits, sh.split_keys, sh.text_first};
         }
         shape = {of.groups, of.tq_groups, of.n_splits, of.split_keys, of.text_first};
@@ -875,7 +732,13 @@ static int prepare_forward(clear_attn_ctx* ctx, const void* Q, const void* K, co
         p.band_o = band->text_o;
         p.band_lse = band->text_lse;
     }
-    if (ctx->dtype == CLEAR_F32) choose_f32_shape(p.NV, BH, ctx->num_cus, &p);
+    if (ctx->dtype == CLEAR_F32) {
+        const F32Shape sh = choose_f32_shape(p.NV, BH, n_text, head_dim, p.n_q_tiles_launch, ctx->num_cus);
+        p.f32_groups = sh.groups;
+        p.n_tq_tiles = sh.n_tq_tiles;
+        p.n_splits = sh.n_splits;
+        p.split_keys = sh.split_keys;
+    }
     if (n_text > 0) {
         if (ctx->dtype == CLEAR_BF16) {
             const int per_block = bf16_text_queries_per_block();
@@ -885,11 +748,10 @@ static int prepare_forward(clear_attn_ctx* ctx, const void* Q, const void* K, co
         }
         if (noalloc) {
             // partial outputs, then (maximum, denominator) pairs, both inside the static scratch array
-            const size_t rows = (size_t)BH * p.n_splits * n_text;
-            const size_t o_bytes = (rows * head_dim * sizeof(float) + 255) & ~(size_t)255, ml_bytes = rows * 2 * sizeof(float);
-            if (o_bytes + ml_bytes > kScratchBytes)
+            const size_t o_bytes = text_partial_o_bytes(BH, p.n_splits, n_text, head_dim), bytes = text_partial_bytes(BH, p.n_splits, n_text, head_dim);
+            if (bytes > kScratchBytes)
                 return fail(ctx, CLEAR_ERR_UNSUPPORTED,
-                            "clear_attn_forward_noalloc: the text-query partial results need " + std::to_string(o_bytes + ml_bytes) +
+                            "clear_attn_forward_noalloc: the text-query partial results need " + std::to_string(bytes) +
                                 " bytes, the static scratch array holds " + std::to_string(kScratchBytes) +
                                 " (B*H * key splits * n_text * (head_dim + 2) floats); use clear_attn_forward");
             p.ws_o = (float*)ctx->scratch;

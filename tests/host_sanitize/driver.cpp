@@ -11,6 +11,7 @@
 #include "../../include/clear_attn.h"
 #include "../../paper_2412_16112_amd/csrc/block_class.h"
 #include "../../paper_2412_16112_amd/csrc/clear_internal.h"
+#include "../../paper_2412_16112_amd/csrc/launch_shape.h"
 
 int check_block_programs();  // block_programs.cpp
 
@@ -175,6 +176,47 @@ static void wave_descriptors()
         }
 }
 
+// The launch shapes: key ranges of the text-query rows cover the keys, fit the workspace, and fit the static scratch array wherever
+// the plain rule (whole rounds of workgroups of 256 text queries) would, so that clear_attn_forward_noalloc serves those calls.
+static void launch_shapes()
+{
+    using namespace clear;
+    const int cus = 256, per_block = bf16_text_queries_per_block();
+    auto check_ranges = [&](long long NV, int n_splits, int split_keys) {
+        EXPECT(n_splits >= 1 && n_splits <= max_text_splits(NV) && split_keys % kKeyTileKeys == 0);
+        EXPECT((long long)(n_splits - 1) * split_keys < NV && NV <= (long long)n_splits * split_keys);
+    };
+    for (int BH : {1, 2, 3, 7, 24, 38, 76, 152, 1000})
+        for (int n_text : {1, 8, 77, 333, 512, 2048})
+            for (int side : {1, 7, 16, 20, 33, 64, 80, 128, 144, 256, 512, 1024}) {
+                const long long NV = n_text + (long long)side * side;
+                const int n_q_tiles = ((side + 15) / 16) * ((side + 15) / 16), n_tq = (n_text + per_block - 1) / per_block;
+                for (int f32 = 0; f32 < 2; ++f32)
+                    for (int head_dim : {64, 128}) {
+                        if (f32 && head_dim != 64) continue;
+                        int plain = 0, plain_keys = 0, n_splits, split_keys;
+                        choose_text_splits(NV, BH, n_tq, cus, !f32 && (long long)BH * n_q_tiles <= 64LL * cus, &plain, &plain_keys);
+                        if (f32) {
+                            const F32Shape sh = choose_f32_shape(NV, BH, n_text, head_dim, n_q_tiles, cus);
+                            EXPECT(sh.groups == 1 || sh.groups == 2 || sh.groups == 4);
+                            EXPECT(sh.n_tq_tiles == (n_text * sh.groups + 63) / 64);
+                            n_splits = sh.n_splits;
+                            split_keys = sh.split_keys;
+                        } else {
+                            ForwardProblem fp = {n_text, head_dim, BH, NV, 1, cus, {}};
+                            for (int i = 0; i < (n_q_tiles <= 64 ? 3 : 1); ++i) fp.sets[i] = {n_q_tiles << i, 20.0, 25.0 / (1 << i)};
+                            const ForwardShape sh = choose_forward_shape(fp);
+                            EXPECT((sh.groups == 1 || sh.groups == 2 || sh.groups == 4) && (sh.tq_groups == 1 || sh.tq_groups == 2 || sh.tq_groups == 4));
+                            EXPECT(fp.sets[sh.groups / 2].n_image_tiles > 0);
+                            n_splits = sh.n_splits;
+                            split_keys = sh.split_keys;
+                        }
+                        check_ranges(NV, n_splits, split_keys);
+                        if (text_partial_bytes(BH, plain, n_text, head_dim) <= kScratchBytes) EXPECT(text_partial_bytes(BH, n_splits, n_text, head_dim) <= kScratchBytes);
+                    }
+            }
+}
+
 static void bands_and_argument_checks()
 {
     int y0, y1, ht, hb;
@@ -217,6 +259,7 @@ int main()
     mask_tables();
     wave_descriptors();
     failures += check_block_programs();
+    launch_shapes();
     bands_and_argument_checks();
     if (failures) {
         std::printf("%d check(s) failed\n", failures);

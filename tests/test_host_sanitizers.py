@@ -20,7 +20,7 @@ def test_host_entry_points_clean_under_asan_and_ubsan(tmp_path):
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
            "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
            "-Xarch_host", "-fno-sanitize-recover=undefined", "-x", "hip",
-           os.path.join(CSRC, "clear_attn_api.cpp"), os.path.join(CSRC, "schedule.cpp"),
+           os.path.join(CSRC, "clear_attn_api.cpp"), os.path.join(CSRC, "schedule.cpp"), os.path.join(CSRC, "launch_shape.cpp"),
            os.path.join(HERE, "launch_stubs.cpp"), os.path.join(HERE, "driver.cpp"), os.path.join(HERE, "block_programs.cpp"), "-o", exe]
     build = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert build.returncode == 0, build.stdout[-4000:]

@@ -62,6 +62,22 @@ def test_noalloc_without_text_tokens_needs_no_scratch():
     assert max_abs <= TOL["bf16"][0] and rel_rms <= TOL["bf16"][1]
 
 
+@pytest.mark.parametrize("H,n_text,gh,gw", [(24, 512, 256, 256), (152, 512, 80, 80)])
+def test_noalloc_f32_key_ranges_fit_the_scratch_array(H, n_text, gh, gw):
+    """Shapes at which a key range per 1 024 keys would need more than the 112 MiB array."""
+    _announce(f"noalloc fp32 H={H} n_text={n_text} grid={gh}x{gw}")
+    Q, K, V = make_qkv_shape(1, H, n_text, gh, gw, 64, "f32", seed=35, device=DEV)
+    ctx = ca.ClearAttn(n_text, gh, gw, 64, 8, ca.CLEAR_F32)
+    try:
+        O_na, O_fw = torch.full_like(Q, float("nan")), torch.empty_like(Q)
+        ctx.forward_noalloc(Q, K, V, O_na)
+        ctx.forward(Q, K, V, O_fw)
+        torch.cuda.synchronize()
+    finally:
+        ctx.destroy()
+    assert torch.isfinite(O_na).all() and torch.equal(O_na, O_fw)
+
+
 def test_noalloc_rejects_what_does_not_fit_and_launches_nothing():
     """B*H * splits * n_text * (d + 2) floats beyond the 112 MiB array: CLEAR_ERR_UNSUPPORTED with the sizes, O untouched."""
     _announce("noalloc, too large for the scratch array")
