@@ -171,6 +171,9 @@ static int check_kernel(int head_dim, int dtype, std::string* why)
     return CLEAR_ERR_UNSUPPORTED;
 }
 
+// Grids of up to this many query tiles get the tables for two and four waves per patch too.  They are made with the context, as a call may
+// neither allocate nor wait (stream capture, clear_attn_forward_noalloc), and a context does not know its B*H yet; they double its
+// host time (64 x 64: 148 us with them).  Larger grids fill the 256 CUs with four heads or more; one or two heads there leave CUs idle.
 constexpr size_t kGroupsMaxTiles = 64;
 
 // Kernel-side tile lists of a schedule: per query tile, the origins (row << 16 | col) of its key tiles, those inside the

@@ -63,6 +63,7 @@ constexpr unsigned kProgramFlags = kProgramStageEnd | kProgramNoBlock | kProgram
 constexpr unsigned kMaskIdNone = 0;       // every pair of the block is admitted
 constexpr unsigned kMaskIdNothing = 1;    // none is
 constexpr unsigned kMaskIdFirstKeys = 1;  // + k, 1 <= k < 32: the first k keys of the block are
+constexpr size_t kMaxProgramWords = 0xfffffff0u;
 constexpr unsigned kMaskIdFree = 33;      // masks of image blocks from here on
 constexpr int bf16_tiles_per_stage(int head_dim) { return head_dim == 64 ? 4 : 2; }
 struct BlockPrograms {

@@ -6,6 +6,8 @@
 #include <algorithm>
 #include <array>
 #include <map>
+#include <new>
+#include <cstddef>
 #include <unordered_map>
 #include <utility>
 
@@ -234,86 +236,68 @@ class BlockMasks {
     {
         words_->assign((size_t)kMaskIdFree * 16, 0ull);
         for (int reg = 0; reg < 16; ++reg) (*words_)[(size_t)kMaskIdNone * 16 + reg] = ~0ull;
-        // block offsets that a patch and a block of a listed tile can have
-        reach_y_ = (spec.r + kWaveQH + kKeyTileKeys / kKeyBlockW) / kKeyBlockH + 1;
-        reach_x_ = (spec.r + kWaveQW + kKeyBlockW) / kKeyBlockW;
-        const size_t offsets = (size_t)(2 * reach_y_ + 1) * (2 * reach_x_ + 1);
-        if (spec.kind == kMaskDisc && offsets <= (1u << 16)) whole_.assign(offsets, 0);
         for (int k = 1; k < 32; ++k)
             for (int reg = 0; reg < 16; ++reg) {
                 const int key = 8 * (reg >> 2) + (reg & 3);  // of the lower lanes; the upper lanes hold the key 4 further on
                 (*words_)[(size_t)(kMaskIdFirstKeys + k) * 16 + reg] = (key < k ? 0xffffffffull : 0) | (key + 4 < k ? 0xffffffffull << 32 : 0);
             }
     }
-    // The disc's mask id for a patch and a block that lie inside the grid, by the offset between them (both are aligned to blocks), or
-    // kOutOfReach; has_table(): whether that offset, and the one of the block below it, have a place in the table.
-    static constexpr unsigned kOutOfReach = ~0u;
-    bool has_table(int dy, int dx) const
+    const MaskSpec& spec() const { return spec_; }
+    // The disc: a patch at (wy0, wx0) against a block at (ky0, kx0) of which the first `rows` rows and `cols` columns are keys.
+    unsigned of_disc(int wy0, int wx0, int ky0, int kx0, int rows, int cols)
     {
-        return !whole_.empty() && abs(dy) < (reach_y_ - 1) * kKeyBlockH && abs(dx) < reach_x_ * kKeyBlockW;
-    }
-    unsigned of_whole(int dy, int dx)
-    {
-        unsigned& slot = whole_[(size_t)(dy / kKeyBlockH + reach_y_) * (2 * reach_x_ + 1) + dx / kKeyBlockW + reach_x_];
-        if (slot == 0) {
-            constexpr int far = 1 << 20;  // a grid without borders
-            const int cls = classify_image_block(far / 2, far / 2, kWaveQH, kWaveQW, far / 2 + dy, far / 2 + dx, kKeyBlockH, kKeyBlockW, far, far, spec_.r * spec_.r);
-            slot = cls == kBlockSkip ? kOutOfReach : 1 + (cls == kBlockFull ? kMaskIdNone : id(far / 2, far / 2, far / 2 + dy, far / 2 + dx, kKeyBlockH, kKeyBlockW));
-        }
-        return slot == kOutOfReach ? kOutOfReach : slot - 1;
-    }
-    // The mask of a patch at (wy0, wx0) against a block at (ky0, kx0) of which the first `rows` rows and `cols` columns are keys.
-    unsigned id(int wy0, int wx0, int ky0, int kx0, int rows, int cols)
-    {
-        if (spec_.kind == kMaskDisc) {
-            // depends on the offset alone
-            const unsigned long long key = ((unsigned long long)(unsigned)(ky0 - wy0) << 32) ^ ((unsigned long long)(unsigned)(kx0 - wx0) << 8) ^ (unsigned)(rows << 4 | cols);
-            auto it = by_offset_.find(key);
-            if (it != by_offset_.end()) return it->second;
-            // one byte (8 query columns) per row offset and key column
-            unsigned char byte[kWaveQH + kKeyBlockH - 1][kKeyBlockW];
-            for (int d = 0; d < kWaveQH + kKeyBlockH - 1; ++d) {
-                const long long dy = (long long)ky0 - wy0 + d - (kWaveQH - 1), lim = (long long)spec_.r * spec_.r - dy * dy;
-                unsigned near = 0;  // bit t: dx = kx0 - wx0 + t - 7 is close enough
-                for (int t = 0; t < kWaveQW + kKeyBlockW - 1; ++t) {
-                    const long long dx = (long long)kx0 - wx0 + t - (kWaveQW - 1);
-                    near |= (unsigned)(dx * dx < lim) << t;
-                }
-                for (int kx = 0; kx < kKeyBlockW; ++kx) {
-                    unsigned v = 0;
-                    for (int qx = 0; qx < kWaveQW; ++qx) v |= (near >> (kx - qx + kWaveQW - 1) & 1) << qx;
-                    byte[d][kx] = (unsigned char)v;
-                }
+        // depends on the offset alone
+        const unsigned long long key = ((unsigned long long)(unsigned)(ky0 - wy0) << 32) ^ ((unsigned long long)(unsigned)(kx0 - wx0) << 8) ^ (unsigned)(rows << 4 | cols);
+        auto it = by_offset_.find(key);
+        if (it != by_offset_.end()) return it->second;
+        // one byte (8 query columns) per row offset and key column
+        unsigned char byte[kWaveQH + kKeyBlockH - 1][kKeyBlockW];
+        for (int d = 0; d < kWaveQH + kKeyBlockH - 1; ++d) {
+            const long long dy = (long long)ky0 - wy0 + d - (kWaveQH - 1), lim = (long long)spec_.r * spec_.r - dy * dy;
+            unsigned near = 0;  // bit t: dx = kx0 - wx0 + t - 7 is close enough
+            for (int t = 0; t < kWaveQW + kKeyBlockW - 1; ++t) {
+                const long long dx = (long long)kx0 - wx0 + t - (kWaveQW - 1);
+                near |= (unsigned)(dx * dx < lim) << t;
             }
-            const unsigned id = add();
-            for (int reg = 0; reg < 16; ++reg) {
-                unsigned long long w = 0;
-                const int ky = reg >> 2;
-                for (int hh = 0; hh < 2; ++hh) {
-                    const int kx = 4 * hh + (reg & 3);
-                    if (ky < rows && kx < cols)
-                        for (int qy = 0; qy < kWaveQH; ++qy) w |= (unsigned long long)byte[ky - qy + kWaveQH - 1][kx] << (32 * hh + 8 * qy);
-                }
-                (*words_)[(size_t)id * 16 + reg] = w;
+            for (int kx = 0; kx < kKeyBlockW; ++kx) {
+                unsigned v = 0;
+                for (int qx = 0; qx < kWaveQW; ++qx) v |= (near >> (kx - qx + kWaveQW - 1) & 1) << qx;
+                byte[d][kx] = (unsigned char)v;
             }
-            by_offset_.emplace(key, id);
-            return id;
         }
-        // the other masks are a condition per axis
-        unsigned row_ok = 0;
-        unsigned long long col_ok = 0;
-        const bool all = spec_.kind == kMaskFull;
-        for (int q = 0; q < kWaveQH; ++q)
-            for (int k = 0; k < rows; ++k)
-                if (all || axis_admits(spec_.kind, spec_.r, spec_.shift, wy0 + q, ky0 + k)) row_ok |= 1u << (4 * q + k);
-        for (int q = 0; q < kWaveQW; ++q)
-            for (int k = 0; k < cols; ++k)
-                if (all || axis_admits(spec_.kind, spec_.r, spec_.shift, wx0 + q, kx0 + k)) col_ok |= 1ull << (8 * q + k);
+        const unsigned id = add();
+        for (int reg = 0; reg < 16; ++reg) {
+            unsigned long long w = 0;
+            const int ky = reg >> 2;
+            for (int hh = 0; hh < 2; ++hh) {
+                const int kx = 4 * hh + (reg & 3);
+                if (ky < rows && kx < cols)
+                    for (int qy = 0; qy < kWaveQH; ++qy) w |= (unsigned long long)byte[ky - qy + kWaveQH - 1][kx] << (32 * hh + 8 * qy);
+            }
+            (*words_)[(size_t)id * 16 + reg] = w;
+        }
+        by_offset_.emplace(key, id);
+        return id;
+    }
+    // The other masks, a condition per axis: bit 4 qy + ky of row_ok, bit 8 qx + kx of col_ok.
+    unsigned of_axes(unsigned row_ok, unsigned long long col_ok)
+    {
         const auto key = std::make_pair(col_ok, row_ok);
         auto it = by_axis_.find(key);
         if (it != by_axis_.end()) return it->second;
+        // score register `reg` of lane l is query l % 32 of the patch against key 8 (reg / 4) + 4 (l / 32) + reg % 4 of the block
+        unsigned queries[kKeyBlockW] = {};  // per key column: the query columns that have it
+        for (int kx = 0; kx < kKeyBlockW; ++kx)
+            for (int qx = 0; qx < kWaveQW; ++qx) queries[kx] |= (unsigned)(col_ok >> (8 * qx + kx) & 1) << qx;
         const unsigned id = add();
-        fill(id, [&](int qy, int qx, int ky, int kx) { return (row_ok >> (4 * qy + ky) & 1) && (col_ok >> (8 * qx + kx) & 1); });
+        for (int reg = 0; reg < 16; ++reg) {
+            unsigned long long w = 0;
+            const int ky = reg >> 2;
+            for (int hh = 0; hh < 2; ++hh)
+                for (int qy = 0; qy < kWaveQH; ++qy)
+                    if (row_ok >> (4 * qy + ky) & 1) w |= (unsigned long long)queries[4 * hh + (reg & 3)] << (32 * hh + 8 * qy);
+            (*words_)[(size_t)id * 16 + reg] = w;
+        }
         by_axis_.emplace(key, id);
         return id;
     }
@@ -324,23 +308,195 @@ class BlockMasks {
         words_->resize(words_->size() + 16);
         return (unsigned)(words_->size() / 16 - 1);
     }
-    // Score register `reg` of lane l is query l % 32 of the patch against key 8 (reg / 4) + 4 (l / 32) + reg % 4 of the block.
-    template <typename F>
-    void fill(size_t id, F admits)
-    {
-        for (int reg = 0; reg < 16; ++reg) {
-            unsigned long long w = 0;
-            for (int l = 0; l < 64; ++l)
-                if (admits((l & 31) >> 3, l & 7, reg >> 2, 4 * (l >> 5) + (reg & 3))) w |= 1ull << l;
-            (*words_)[id * 16 + reg] = w;
-        }
-    }
     MaskSpec spec_;
     std::vector<unsigned long long>* words_;
-    int reach_y_, reach_x_;
-    std::vector<unsigned> whole_;
     std::unordered_map<unsigned long long, unsigned> by_offset_;
     std::map<std::pair<unsigned long long, unsigned>, unsigned> by_axis_;
+};
+
+// What a patch has to do with the blocks of its query tile's list: per block kOutOfReach, or 1 + the id of its lane masks.  That is
+// asked for every patch and listed block (100 x 117 tokens, r = 31: 240 000 times), so a tile's own part of an answer is worked out once
+// for all patches (Tile), and answers() is a loop of table reads without branches.
+constexpr unsigned kOutOfReach = 0, kUnknown = ~0u;
+
+// The disc.  An answer depends on the offset between patch and block and on how much of either the grid's border cuts off, of which
+// there is one amount per axis: a table by offset for each combination of the two cuts, filled as they are met.
+class DiscBlocks {
+  public:
+    struct Tile {
+        int at[2];   // of the tile's two blocks: place in a patch's tables for a patch at the origin
+        int y0, x0;
+    };
+    // `questions`: how many there will be
+    DiscBlocks(BlockMasks* masks, int gridH, int gridW, long long questions) : masks_(masks), gridH_(gridH), gridW_(gridW)
+    {
+        const int r = masks->spec().r;
+        reach_y_ = imin((r + kWaveQH + kKeyTileH) / kKeyBlockH, ceil_div(gridH, kKeyBlockH)) + 2;
+        reach_x_ = imin((r + kWaveQW + kKeyBlockW) / kKeyBlockW, ceil_div(gridW, kKeyBlockW)) + 2;
+        pitch_ = 2 * reach_x_ + 1;
+        size_ = (2LL * reach_y_ + 1) * pitch_;
+        tabled_ = size_ * kTables <= std::max(1LL << 16, questions) && size_ * kTables < (1LL << 30);  // (filling more costs more than it saves)
+    }
+    Tile tile(int ky0, int kx0) const
+    {
+        Tile t = {{0, 0}, ky0, kx0};
+        for (int kb = 0; kb < 2 && tabled_; ++kb) {
+            const int by = ky0 + kKeyBlockH * kb;
+            const int table = by >= gridH_ || kx0 >= gridW_ ? kOutside : (by + kKeyBlockH > gridH_ ? 1 : 0) | (kx0 + kKeyBlockW > gridW_ ? 2 : 0);
+            t.at[kb] = (int)(table * size_) + by / kKeyBlockH * pitch_ + kx0 / kKeyBlockW;
+        }
+        return t;
+    }
+    // for a patch with queries
+    void answers(int wy0, int wx0, const std::vector<Tile>& tiles, unsigned* out)
+    {
+        const MaskSpec& spec = masks_->spec();
+        auto ask = [&](const Tile& t, int kb) {
+            const int by = t.y0 + kKeyBlockH * kb;
+            const int cls = classify_image_block_spec(spec, wy0, wx0, kWaveQH, kWaveQW, by, t.x0, kKeyBlockH, kKeyBlockW, gridH_, gridW_);
+            if (cls == kBlockSkip) return kOutOfReach;
+            if (cls == kBlockFull) return 1 + kMaskIdNone;
+            return 1 + masks_->of_disc(wy0, wx0, by, t.x0, imin(gridH_ - by, kKeyBlockH), imin(gridW_ - t.x0, kKeyBlockW));
+        };
+        const size_t n = tiles.size();
+        if (!tabled_) {
+            for (size_t i = 0; i < n; ++i)
+                for (int kb = 0; kb < 2; ++kb) out[2 * i + kb] = ask(tiles[i], kb);
+            return;
+        }
+        std::vector<unsigned>& mine = tables_[(wy0 + kWaveQH > gridH_ ? 1 : 0) | (wx0 + kWaveQW > gridW_ ? 2 : 0)];
+        if (mine.empty()) {
+            mine.assign((size_t)(kTables * size_), kUnknown);
+            std::fill(mine.begin() + (std::ptrdiff_t)(kOutside * size_), mine.end(), kOutOfReach);
+        }
+        unsigned* const table = mine.data() + (reach_y_ - wy0 / kWaveQH) * pitch_ + reach_x_ - wx0 / kWaveQW;
+        const Tile* const tile = tiles.data();
+        bool unknown = false;
+        for (size_t i = 0; i < n; ++i)
+            for (int kb = 0; kb < 2; ++kb) {
+                const unsigned answer = table[tile[i].at[kb]];
+                out[2 * i + kb] = answer;
+                unknown |= answer == kUnknown;
+            }
+        if (!unknown) return;
+        for (size_t i = 0; i < n; ++i)
+            for (int kb = 0; kb < 2; ++kb)
+                if (out[2 * i + kb] == kUnknown) out[2 * i + kb] = table[tile[i].at[kb]] = ask(tile[i], kb);
+    }
+
+  private:
+    static_assert(kWaveQH == kKeyBlockH && kWaveQW == kKeyBlockW, "patches and blocks lie on one lattice");
+    static constexpr int kOutside = 4, kTables = 5;  // a block's cut: bit 0 rows, bit 1 columns; or wholly outside
+    BlockMasks* masks_;
+    int gridH_, gridW_, reach_y_, reach_x_, pitch_;
+    long long size_;
+    bool tabled_;
+    std::vector<unsigned> tables_[4];  // by the patch's cut
+};
+
+// Masks that are a condition per axis: square, Swin, and the residue classes of the strided mask, in which every pair is admitted (there the
+// query grid, qH x qW, and the key grid, kH x kW, may differ by a row or a column).
+class AxisBlocks {
+  public:
+    struct Tile {
+        int y, x;  // the tile's first block row, its block column
+    };
+    AxisBlocks(BlockMasks* masks, int qH, int qW, int kH, int kW) : masks_(masks)
+    {
+        rows_.build(masks->spec(), qH, kH, kWaveQH, kKeyBlockH);
+        cols_.build(masks->spec(), qW, kW, kWaveQW, kKeyBlockW);
+        ids_.assign(rows_.bits.size() * cols_.bits.size(), kUnknown);
+        for (size_t i = 0; i < rows_.bits.size(); ++i) ids_[i * cols_.bits.size()] = kOutOfReach;
+        for (size_t j = 0; j < cols_.bits.size(); ++j) ids_[j] = kOutOfReach;
+    }
+    Tile tile(int ky0, int kx0) const { return {ky0 / kKeyBlockH, kx0 / kKeyBlockW}; }
+    void answers(int wy0, int wx0, const std::vector<Tile>& tiles, unsigned* out)
+    {
+        const unsigned *const row = rows_.of(wy0 / kWaveQH), *const col = cols_.of(wx0 / kWaveQW);
+        const size_t n = tiles.size(), pitch = cols_.bits.size();
+        const Tile* const tile = tiles.data();
+        unsigned* const ids = ids_.data();
+        bool unknown = false;
+        for (size_t i = 0; i < n; ++i)
+            for (int kb = 0; kb < 2; ++kb) {
+                const unsigned answer = ids[row[tile[i].y + kb] * pitch + col[tile[i].x]];
+                out[2 * i + kb] = answer;
+                unknown |= answer == kUnknown;
+            }
+        if (!unknown) return;
+        for (size_t i = 0; i < n; ++i)
+            for (int kb = 0; kb < 2; ++kb) {
+                if (out[2 * i + kb] != kUnknown) continue;
+                const unsigned ry = row[tile[i].y + kb], rx = col[tile[i].x];
+                unsigned& answer = ids[ry * pitch + rx];
+                if (answer == kUnknown) {
+                    const unsigned long long row_ok = rows_.bits[ry], col_ok = cols_.bits[rx];
+                    answer = 1 + (row_ok == 0xffff && col_ok == ~0ull ? kMaskIdNone : masks_->of_axes((unsigned)row_ok, col_ok));
+                }
+                out[2 * i + kb] = answer;
+            }
+    }
+
+  private:
+    // One axis: per patch and block which condition holds between them, as its place in `bits` (0: no pair is admitted).
+    class Axis {
+      public:
+        std::vector<unsigned long long> bits;  // the distinct conditions: bit (block size) q + k
+        void build(const MaskSpec& m, int q_end, int k_end, int q_size, int k_size)
+        {
+            all_ = m.kind == kMaskFull;  // (the same for every patch)
+            const int n_a = all_ ? 1 : ceil_div(q_end, q_size), n_b = ceil_div(k_end, k_size);
+            std::vector<int> window;  // Swin
+            if (m.kind == kMaskSwin)
+                for (int y = 0; y < imax(q_end, k_end) + q_size; ++y) window.push_back((y + m.shift) / m.r);
+            auto admits = [&](int q, int k) { return all_ || (m.kind == kMaskSwin ? window[q] == window[k] : axis_admits(m.kind, m.r, m.shift, q, k)); };
+            span_ = all_ ? n_b : imin(n_b, (2 * (imin(m.r, q_end + k_end) - 1) + q_size - 1) / k_size + 2);
+            first_.assign(n_a, 0);
+            code_.assign((size_t)n_a * span_, 0);
+            dense_.assign((size_t)n_b + 2, 0);  // (a listed tile may lie in the one row or column that only the larger classes have)
+            bits.assign(1, 0);
+            std::map<unsigned long long, unsigned> seen;
+            for (int a = 0; a < n_a; ++a) {
+                const int q0 = a * q_size;
+                first_[a] = all_ ? 0 : imin(imax(0, q0 - m.r + 1) / k_size, n_b - span_);
+                for (int i = 0; i < span_; ++i) {
+                    const int k0 = (first_[a] + i) * k_size;
+                    unsigned long long ok = 0;
+                    bool any = false;  // a query of the grid has a key
+                    for (int q = 0; q < q_size; ++q)
+                        for (int k = 0; k < k_size && k0 + k < k_end; ++k)
+                            if (admits(q0 + q, k0 + k)) {
+                                ok |= 1ull << (k_size * q + k);
+                                any |= q0 + q < q_end;
+                            }
+                    if (!any) continue;
+                    const auto known = seen.emplace(ok, (unsigned)bits.size());
+                    if (known.second) bits.push_back(ok);
+                    code_[(size_t)a * span_ + i] = known.first->second;
+                }
+            }
+        }
+        // the conditions of patch a, by block
+        const unsigned* of(int a)
+        {
+            if (all_) a = 0;
+            if (a != shown_) {
+                if (shown_ >= 0) std::fill_n(dense_.begin() + first_[shown_], span_, 0);
+                std::copy_n(code_.begin() + (std::ptrdiff_t)a * span_, span_, dense_.begin() + first_[a]);
+                shown_ = a;
+            }
+            return dense_.data();
+        }
+
+      private:
+        bool all_ = false;
+        int span_ = 0, shown_ = -1;   // blocks kept per patch
+        std::vector<int> first_;      // the first of them
+        std::vector<unsigned> code_, dense_;
+    };
+    BlockMasks* masks_;
+    Axis rows_, cols_;
+    std::vector<unsigned> ids_;  // by the two conditions
 };
 
 }  // namespace
@@ -378,6 +534,7 @@ void order_forward_tiles(const Schedule& s, const QueryTilePatterns& pat, std::v
     struct Pair {
         int key, a, b;  // b: -1 without a partner
     };
+    constexpr int kKeys = 16;  // places modulo 4 x 4; tiles without a partner follow, by the same key
     std::vector<Pair> pairs;
     std::vector<unsigned char> listed((size_t)s.n_kty * s.n_ktx, 0);
     k_col->assign(s.col_idx.size(), 0);
@@ -389,10 +546,11 @@ void order_forward_tiles(const Schedule& s, const QueryTilePatterns& pat, std::v
         const int cy2 = 2 * (qt / s.n_qtx) * s.qth + s.qth - s.kth, cx2 = 2 * (qt % s.n_qtx) * s.qtw + s.qtw - s.ktw;
         const bool on_tiles = cy2 % s.kth == 0 && cx2 % s.ktw == 0;
         pairs.clear();
+        int place[2 * kKeys + 1] = {};  // where the tiles of a key go
         for (int e = begin; e < end; ++e) {
             const int id = s.col_idx[e];
             if (listed[id] != 1) continue;
-            const int y = id / s.n_ktx, x = id % s.n_ktx, my = cy2 / s.kth - y, mx = cx2 / s.ktw - x;
+            const int y = id / s.n_ktx, x = id - y * s.n_ktx, my = cy2 / s.kth - y, mx = cx2 / s.ktw - x;
             const int mirror = on_tiles && my >= 0 && mx >= 0 && my < s.n_kty && mx < s.n_ktx ? my * s.n_ktx + mx : -1;
             Pair p = {0, id, -1};
             listed[id] = 2;
@@ -400,15 +558,17 @@ void order_forward_tiles(const Schedule& s, const QueryTilePatterns& pat, std::v
                 listed[mirror] = 2;
                 p.b = mirror;
             }
-            p.key = imin(mod4(y) * 4 + mod4(x), mod4(1 - y) * 4 + mod4(1 - x));
+            p.key = imin(mod4(y) * 4 + mod4(x), mod4(1 - y) * 4 + mod4(1 - x)) + (p.b < 0 ? kKeys : 0);
+            place[p.key + 1] += p.b >= 0 ? 2 : 1;
             pairs.push_back(p);
         }
-        std::stable_sort(pairs.begin(), pairs.end(), [](const Pair& p, const Pair& q) { return (p.b < 0) != (q.b < 0) ? q.b < 0 : p.key < q.key; });
-        int w = begin;
-        auto put = [&](int id) { (*k_col)[w++] = (id / s.n_ktx) * s.kth << 16 | (id % s.n_ktx) * s.ktw; };
+        for (int k = 0; k < 2 * kKeys; ++k) place[k + 1] += place[k];
+        auto origin = [&](int id) { return (id / s.n_ktx) * s.kth << 16 | (id % s.n_ktx) * s.ktw; };
         for (const Pair& p : pairs) {
-            put(p.a);
-            if (p.b >= 0) put(p.b);
+            int* const to = k_col->data() + begin + place[p.key];
+            to[0] = origin(p.a);
+            if (p.b >= 0) to[1] = origin(p.b);
+            place[p.key] += p.b >= 0 ? 2 : 1;
         }
         for (int e = begin; e < end; ++e) listed[s.col_idx[e]] = 0;
     }
@@ -421,90 +581,117 @@ void order_forward_tiles(const Schedule& s, const QueryTilePatterns& pat, std::v
     }
 }
 
-static void build_block_programs_for(const Schedule& s, const QueryTilePatterns& pat, const std::vector<int>& k_col, int n_text, int head_dim, int groups,
-                                     int stride, int gridH, int gridW, BlockMasks& masks, BlockPrograms* out)
+namespace {
+
+// The image-query programs of one table set and variant (of the key grid's extents), appended to out->words; out->ptr of the variant, and the
+// words of a pattern's waves.
+template <int GROUPS, class Blocks>
+void build_image_programs(const ProgramInput& in, int n_text, int head_dim, Blocks& blocks, unsigned* ptr, std::vector<unsigned>* words, std::vector<double>* steps_of)
 {
-    const bool strided = stride > 1;
-    const int waves = kBf16NWY * kBf16NWX, patches = waves / groups, tps = bf16_tiles_per_stage(head_dim);
+    const Schedule& s = *in.sched;
+    const int waves = kBf16NWY * kBf16NWX, patches = waves / GROUPS, tps = bf16_tiles_per_stage(head_dim);
     const int tile_units = kKeyTileKeys * head_dim * 2 / 2048;  // a staged K (or V) tile in the units of kProgramPlaceMask
-    const size_t n_q_tiles = s.row_ptr.size() - 1;
-    const MaskSpec spec = {strided ? (int)kMaskFull : s.mask_kind, s.r, s.mask_shift};
-    const int n_variants = strided ? 4 : 1;
-    out->ptr.resize((size_t)n_variants * n_q_tiles * waves);
-    out->words.clear();
-    std::vector<unsigned> scratch;
-    const int n_lin_tiles = ceil_div(n_text, kKeyTileKeys), n_lin_stages = ceil_div(n_lin_tiles, tps);
-    double all_stages = 0, all_steps = 0;
-    for (int v = 0; v < n_variants; ++v) {
-        const int kH = strided ? gridH / stride + (v >> 1) : s.gridH, kW = strided ? gridW / stride + (v & 1) : s.gridW;
-        std::vector<double> steps_of(pat.first.size(), 0);
-        for (size_t k = 0; k < pat.first.size(); ++k) {
-            const size_t qt = pat.first[k];
-            const int n_img = s.row_ptr[qt + 1] - s.row_ptr[qt], n_stages = n_lin_stages + ceil_div(n_img, tps);
-            const size_t room = (size_t)n_stages * 2 * tps;
-            scratch.resize(room * groups);
-            for (int patch = 0; patch < patches; ++patch) {
-                const int wy0 = (int)(qt / s.n_qtx) * s.qth + (patch / kBf16NWX) * kWaveQH, wx0 = (int)(qt % s.n_qtx) * s.qtw + (patch % kBf16NWX) * kWaveQW;
-                const bool inside_patch = wy0 + kWaveQH <= s.gridH && wx0 + kWaveQW <= s.gridW;
-                unsigned* end[4];
-                for (int g = 0; g < groups; ++g) end[g] = scratch.data() + (size_t)g * room;
-                unsigned turn = 0;
-                auto put = [&](unsigned place, unsigned id) { *end[turn++ & (unsigned)(groups - 1)]++ = place | id << kProgramMaskShift; };
-                for (int st = 0; st < n_stages; ++st) {
-                    unsigned* const had[4] = {end[0], end[1], end[2], end[3]};
-                    const int first = st < n_lin_stages ? st * tps : (st - n_lin_stages) * tps, last = imin(first + tps, st < n_lin_stages ? n_lin_tiles : n_img);
-                    for (int i = first; i < last; ++i) {
-                        const unsigned place = (unsigned)((i - first) * tile_units);
-                        if (st < n_lin_stages) {
-                            for (int kb = 0; kb < 2; ++kb) {
-                                const int left = n_text - (i * 2 + kb) * 32;
-                                if (left > 0) put(place + kb, left >= 32 ? kMaskIdNone : kMaskIdFirstKeys + (unsigned)left);
-                            }
-                            continue;
-                        }
-                        const int packed = k_col[s.row_ptr[qt] + i], ky0 = packed >> 16, kx0 = packed & 0xffff;
-                        if (inside_patch && ky0 + s.kth <= kH && kx0 + s.ktw <= kW && masks.has_table(ky0 - wy0, kx0 - wx0)) {
-                            for (int kb = 0; kb < 2; ++kb) {
-                                const unsigned id = masks.of_whole(ky0 - wy0 + kKeyBlockH * kb, kx0 - wx0);
-                                if (id != BlockMasks::kOutOfReach) put(place + kb, id);
-                            }
-                            continue;
-                        }
-                        for (int kb = 0; kb < 2; ++kb) {
-                            const int by = ky0 + kKeyBlockH * kb;
-                            const int cls = strided ? classify_full_block(wy0, wx0, s.gridH, s.gridW, by, kx0, kKeyBlockH, kKeyBlockW, kH, kW)
-                                                    : classify_image_block_spec(spec, wy0, wx0, kWaveQH, kWaveQW, by, kx0, kKeyBlockH, kKeyBlockW, kH, kW);
-                            if (cls == kBlockSkip) continue;
-                            put(place + kb, cls == kBlockFull ? kMaskIdNone : masks.id(wy0, wx0, by, kx0, imin(kH - by, kKeyBlockH), imin(kW - kx0, kKeyBlockW)));
-                        }
-                    }
-                    for (int g = 0; g < groups; ++g) {
-                        if (end[g] == had[g]) {
-                            // no block here: one that masks everything finishes what the wave has pending, after that nothing is left to do
-                            const bool idle = had[g] > scratch.data() + (size_t)g * room && ((had[g][-1] & ~kProgramFlags) >> kProgramMaskShift) == kMaskIdNothing;
-                            *end[g]++ = kMaskIdNothing << kProgramMaskShift | (idle ? kProgramNoBlock : 0);
-                        }
-                        end[g][-1] |= kProgramStageEnd;
-                    }
+    const int n_lin_stages = ceil_div(ceil_div(n_text, kKeyTileKeys), tps);
+    int most = 0;  // the longest list
+    size_t at_most = 0;  // words
+    for (int qt : in.pat->first) {
+        const int n_img = s.row_ptr[qt + 1] - s.row_ptr[qt];
+        most = imax(most, n_img);
+        at_most += (size_t)(n_lin_stages + ceil_div(n_img, tps)) * 2 * tps * waves;
+    }
+    words->reserve(words->size() + std::min<size_t>(at_most, 1u << 22));
+    std::vector<typename Blocks::Tile> tiles;
+    std::vector<unsigned> answers((size_t)most * 2);
+    const size_t room = (size_t)(n_lin_stages + ceil_div(most, tps)) * 2 * tps + 1;  // (a word may be written past the last and not kept)
+    std::vector<unsigned> scratch(room * GROUPS);                                    // the programs of the waves that share a patch
+    unsigned *end[GROUPS], *had[GROUPS];
+    for (int g = 0; g < GROUPS; ++g) end[g] = scratch.data() + (size_t)g * room;
+    unsigned turn = 0;  // the waves of a patch take its blocks in turn
+    auto put = [&](unsigned word, bool reached) __attribute__((always_inline)) {
+        *end[turn] = word;  // (without a branch: the edge of a disc cannot be foreseen)
+        end[turn] += reached;
+        turn = (turn + reached) % GROUPS;
+    };
+    auto begin_stage = [&]() __attribute__((always_inline)) {
+        for (int g = 0; g < GROUPS; ++g) had[g] = end[g];
+    };
+    auto end_stage = [&]() __attribute__((always_inline)) {
+        for (int g = 0; g < GROUPS; ++g) {
+            if (end[g] == had[g]) {
+                // no block here: one that masks everything finishes what the wave has pending, after that nothing is left to do
+                const bool idle = had[g] > scratch.data() + (size_t)g * room && ((had[g][-1] & ~kProgramFlags) >> kProgramMaskShift) == kMaskIdNothing;
+                *end[g]++ = kMaskIdNothing << kProgramMaskShift | (idle ? kProgramNoBlock : 0);
+            }
+            end[g][-1] |= kProgramStageEnd;
+        }
+    };
+    // the text keys' stages, the same for every patch
+    for (int st = 0; st < n_lin_stages; ++st) {
+        begin_stage();
+        for (int j = 0; j < tps; ++j)
+            for (int kb = 0; kb < 2; ++kb) {
+                const int left = n_text - ((st * tps + j) * 2 + kb) * 32;
+                if (left > 0) put((unsigned)(j * tile_units + kb) | (left >= 32 ? kMaskIdNone : kMaskIdFirstKeys + (unsigned)left) << kProgramMaskShift, true);
+            }
+        end_stage();
+    }
+    unsigned* text_end[GROUPS];
+    for (int g = 0; g < GROUPS; ++g) text_end[g] = end[g];
+    const unsigned text_turn = turn;
+    struct Piece {
+        size_t at, size;
+    };
+    std::vector<Piece> last((size_t)waves, Piece{0, 0});  // the waves' programs before this one
+    for (size_t k = 0; k < in.pat->first.size(); ++k) {
+        const size_t qt = in.pat->first[k];
+        const int begin = s.row_ptr[qt], n_img = s.row_ptr[qt + 1] - begin;
+        tiles.clear();
+        for (int e = begin; e < begin + n_img; ++e) tiles.push_back(blocks.tile((*in.k_col)[e] >> 16, (*in.k_col)[e] & 0xffff));
+        for (int patch = 0; patch < patches; ++patch) {
+            const int wy0 = (int)(qt / s.n_qtx) * s.qth + (patch / kBf16NWX) * kWaveQH, wx0 = (int)(qt % s.n_qtx) * s.qtw + (patch % kBf16NWX) * kWaveQW;
+            const bool queries = wy0 < s.gridH && wx0 < s.gridW;  // (a wave without any follows no program; the mean counts it as out of reach of every block)
+            if (queries)
+                blocks.answers(wy0, wx0, tiles, answers.data());
+            else
+                std::fill(answers.begin(), answers.end(), kOutOfReach);
+            for (int g = 0; g < GROUPS; ++g) end[g] = text_end[g];
+            turn = text_turn;
+            const unsigned* answer = answers.data();
+            for (int first = 0; first < n_img; first += tps) {
+                begin_stage();
+                const int n = imin(tps, n_img - first);
+                for (int j = 0; j < n; ++j)
+                    for (int kb = 0; kb < 2; ++kb, ++answer) put((unsigned)(j * tile_units + kb) | (*answer - 1) << kProgramMaskShift, *answer != kOutOfReach);
+                end_stage();
+            }
+            for (int g = 0; g < GROUPS; ++g) {
+                const unsigned *const from = scratch.data() + (size_t)g * room, *const to = end[g];
+                const int wave = g * patches + patch;
+                const size_t size = (size_t)(to - from);
+                (*steps_of)[k] += (double)size;
+                if (!queries) continue;
+                // Waves whose programs are the same share one: those of a class of the strided mask, or of a window that holds the whole grid.
+                const Piece candidates[2] = {last[wave], last[wave > 0 ? wave - 1 : 0]};
+                const Piece* same = nullptr;
+                for (const Piece& c : candidates)
+                    if (!same && c.size == size && std::equal(from, to, words->begin() + (std::ptrdiff_t)c.at)) same = &c;
+                if (same) {
+                    last[wave] = *same;
+                } else {
+                    last[wave] = {words->size(), size};
+                    words->insert(words->end(), from, to);
+                    if (words->size() > kMaxProgramWords) throw std::bad_alloc();  // (places in it are 32-bit numbers)
                 }
-                for (int g = 0; g < groups; ++g) {
-                    const unsigned* const begin = scratch.data() + (size_t)g * room;
-                    steps_of[k] += (double)(end[g] - begin);
-                    out->ptr[((size_t)v * n_q_tiles + qt) * waves + g * patches + patch] = (unsigned)out->words.size();
-                    out->words.insert(out->words.end(), begin, (const unsigned*)end[g]);
-                }
+                ptr[qt * waves + wave] = (unsigned)last[wave].at;
             }
         }
-        for (size_t qt = 0; qt < n_q_tiles; ++qt) {
-            const int k = pat.id[qt];
-            unsigned* const of_variant = out->ptr.data() + (size_t)v * n_q_tiles * waves;
-            if (pat.first[k] != (int)qt) std::copy(of_variant + (size_t)pat.first[k] * waves, of_variant + (size_t)(pat.first[k] + 1) * waves, of_variant + qt * waves);
-            all_stages += n_lin_stages + ceil_div(s.row_ptr[qt + 1] - s.row_ptr[qt], tps);
-            all_steps += steps_of[k];
-        }
     }
-    out->mean_stages = all_stages / (double)(n_variants * n_q_tiles);
-    out->mean_steps = all_steps / (double)(n_variants * n_q_tiles * waves);
+}
+
+// The words of a text-query stage, for every number of keys left and wave of a patch.
+void build_text_words(int head_dim, BlockPrograms* out)
+{
+    const int tps = bf16_tiles_per_stage(head_dim), tile_units = kKeyTileKeys * head_dim * 2 / 2048;
     // text-query rows: every stage holds the same blocks, the last one as many as there are keys left
     const int stage_blocks = 2 * tps;
     for (int i = 0; i < 3; ++i) {
@@ -530,14 +717,61 @@ static void build_block_programs_for(const Schedule& s, const QueryTilePatterns&
     out->words.push_back(0);
 }
 
+}  // namespace
+
 void build_block_programs(const std::vector<ProgramInput>& in, int n_text, int head_dim, int stride, int gridH, int gridW,
                           std::vector<BlockPrograms>* out, std::vector<unsigned long long>* masks)
 {
-    const Schedule& s = *in[0].sched;
-    BlockMasks set({stride > 1 ? (int)kMaskFull : s.mask_kind, s.r, s.mask_shift}, masks);
+    const Schedule& s = *in[0].sched;  // (the sets differ in the height of their query tiles only)
+    const bool strided = stride > 1;
+    const int waves = kBf16NWY * kBf16NWX, tps = bf16_tiles_per_stage(head_dim), n_variants = strided ? 4 : 1;
+    BlockMasks set({strided ? (int)kMaskFull : s.mask_kind, s.r, s.mask_shift}, masks);
     out->resize(in.size());
-    for (size_t i = 0; i < in.size(); ++i)
-        build_block_programs_for(*in[i].sched, *in[i].pat, *in[i].k_col, n_text, head_dim, in[i].groups, stride, gridH, gridW, set, &(*out)[i]);
+    std::vector<double> steps(in.size(), 0.0);
+    for (size_t i = 0; i < in.size(); ++i) {
+        (*out)[i].words.clear();
+        (*out)[i].ptr.assign((size_t)n_variants * (in[i].sched->row_ptr.size() - 1) * waves, 0);
+    }
+    int n_built = 0;
+    for (int v = 0; v < n_variants; ++v) {
+        // (the larger class of an axis exists where the stride does not divide it)
+        if (strided && (((v >> 1) && gridH % stride == 0) || ((v & 1) && gridW % stride == 0))) continue;
+        ++n_built;
+        auto run = [&](auto&& blocks) {
+            for (size_t i = 0; i < in.size(); ++i) {
+                BlockPrograms& o = (*out)[i];
+                const QueryTilePatterns& pat = *in[i].pat;
+                const size_t n_q_tiles = in[i].sched->row_ptr.size() - 1;
+                unsigned* const ptr = o.ptr.data() + (size_t)v * n_q_tiles * waves;
+                std::vector<double> steps_of(pat.first.size(), 0);
+                if (in[i].groups == 1) build_image_programs<1>(in[i], n_text, head_dim, blocks, ptr, &o.words, &steps_of);
+                if (in[i].groups == 2) build_image_programs<2>(in[i], n_text, head_dim, blocks, ptr, &o.words, &steps_of);
+                if (in[i].groups == 4) build_image_programs<4>(in[i], n_text, head_dim, blocks, ptr, &o.words, &steps_of);
+                for (size_t qt = 0; qt < n_q_tiles; ++qt) {
+                    const size_t first = pat.first[pat.id[qt]];
+                    if (first != qt) std::copy(ptr + first * waves, ptr + (first + 1) * waves, ptr + qt * waves);
+                    steps[i] += steps_of[pat.id[qt]];
+                }
+            }
+        };
+        if (set.spec().kind == kMaskDisc) {
+            long long questions = 0;
+            for (const ProgramInput& p : in)
+                for (int qt : p.pat->first) questions += (p.sched->row_ptr[qt + 1] - p.sched->row_ptr[qt]) * 2LL * (waves / p.groups);
+            run(DiscBlocks(&set, s.gridH, s.gridW, questions));
+        } else {
+            run(AxisBlocks(&set, s.gridH, s.gridW, strided ? gridH / stride + (v >> 1) : s.gridH, strided ? gridW / stride + (v & 1) : s.gridW));
+        }
+    }
+    for (size_t i = 0; i < in.size(); ++i) {
+        const std::vector<int>& row_ptr = in[i].sched->row_ptr;
+        const size_t n_q_tiles = row_ptr.size() - 1;
+        double stages = 0;
+        for (size_t qt = 0; qt < n_q_tiles; ++qt) stages += ceil_div(ceil_div(n_text, kKeyTileKeys), tps) + ceil_div(row_ptr[qt + 1] - row_ptr[qt], tps);
+        (*out)[i].mean_stages = stages / (double)n_q_tiles;
+        (*out)[i].mean_steps = steps[i] / ((double)n_built * n_q_tiles * waves);
+        build_text_words(head_dim, &(*out)[i]);
+    }
 }
 
 unsigned long long executed_pairs_bf16_strided(const Schedule& s, int n_text, int gridH, int gridW, int stride, int layer)
