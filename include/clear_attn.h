@@ -19,7 +19,8 @@
  * -even to bf16 on output) and dtype CLEAR_F32 with head_dim 64 (plain fp32 accuracy path).
  * n_text >= 0, gridH, gridW >= 1 (at most 32767 each), r >= 1.  bf16 contexts need N < 2^24 (the kernels address
  * one head with 32-bit byte offsets) and clear_attn_create refuses more with CLEAR_ERR_UNSUPPORTED, as it refuses
- * a tile schedule of more than 2^31 - 1 (query tile, key tile) pairs (r close to the grid size on a large grid);
+ * a tile schedule of more than 2^28 (query tile, key tile) pairs (r close to the grid size on a large grid; the tables of
+ * a bf16 context take up to 73 bytes a pair there, host memory in passing and device memory as long as it lives);
  * fp32 contexts need N < 2^31.  Offsets across heads and batch items are 64-bit.
  *
  * Errors: every function returns a clear_status; nothing throws or aborts; invalid arguments are

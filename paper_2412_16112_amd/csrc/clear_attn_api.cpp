@@ -19,25 +19,39 @@
 
 using namespace clear;
 
-// Tables that go to the device together, in one allocation and one copy.
+// Tables that go to the device together, in one allocation and, where they are small, one copy.  The vectors have to live until upload().
 class TablePack {
   public:
     template <typename T>
     size_t add(const std::vector<T>& v)
     {
-        const size_t at = (bytes_.size() + 255) & ~(size_t)255;
-        bytes_.resize(at + std::max<size_t>(v.size(), 1) * sizeof(T));
-        if (!v.empty()) memcpy(bytes_.data() + at, v.data(), v.size() * sizeof(T));
+        const size_t at = (size_ + 255) & ~(size_t)255;
+        pieces_.push_back({v.data(), v.size() * sizeof(T), at});
+        size_ = at + std::max<size_t>(v.size(), 1) * sizeof(T);
         return at;
     }
     hipError_t upload(unsigned char** device) const
     {
-        hipError_t e = hipMalloc((void**)device, bytes_.size());
-        return e == hipSuccess ? hipMemcpy(*device, bytes_.data(), bytes_.size(), hipMemcpyHostToDevice) : e;
+        hipError_t e = hipMalloc((void**)device, size_);
+        if (e != hipSuccess) return e;
+        if (size_ <= ((size_t)4 << 20)) {
+            std::vector<unsigned char> bytes(size_);
+            for (const Piece& p : pieces_)
+                if (p.size) memcpy(bytes.data() + p.at, p.data, p.size);
+            return hipMemcpy(*device, bytes.data(), size_, hipMemcpyHostToDevice);
+        }
+        for (const Piece& p : pieces_)  // (no second copy of large tables on the host)
+            if (e == hipSuccess && p.size) e = hipMemcpy(*device + p.at, p.data, p.size, hipMemcpyHostToDevice);
+        return e;
     }
 
   private:
-    std::vector<unsigned char> bytes_;
+    struct Piece {
+        const void* data;
+        size_t size, at;
+    };
+    std::vector<Piece> pieces_;
+    size_t size_ = 0;
 };
 
 // What the bf16 forward kernels follow, for one number of waves per query patch (1, 2, 4: query tiles of 16, 8, 4 rows).

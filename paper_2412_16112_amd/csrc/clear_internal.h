@@ -37,7 +37,10 @@ struct Schedule {
 void build_schedule(int gridH, int gridW, int r, int qth, int qtw, int kth, int ktw, Schedule* s, int mask_kind = 0, int mask_shift = 0);
 // Upper bound, in 64 bits, on the (query tile, key tile) pairs build_schedule would list (it stores them with int indices).
 long long schedule_pair_bound(int gridH, int gridW, int r, int qth, int qtw, int kth, int ktw);
-constexpr long long kMaxSchedulePairs = 1LL << 28;  // 2.4 GB of host and device tables; create refuses more
+// (query tile, key tile) pairs a context may have; create refuses more.  A pair takes 9 bytes of tile lists and, in a bf16 context, up to 16
+// words of wave programs (typically 14: 0.7 GB at 768 x 768, r = 400, 13 million pairs) where neither query tiles nor waves
+// share any, as with r about half of a large grid.  Windows that hold the whole grid share nearly all of them.
+constexpr long long kMaxSchedulePairs = 1LL << 28;
 unsigned long long mask_count(int n_text, int gridH, int gridW, int r, int mask_kind = 0, int mask_shift = 0);
 // Pairs fed to the matrix pipeline per (batch, head) by the bf16 kernels (image pass + text-query pass).
 // whole_tiles: a wave runs both 32-key blocks of a tile it reaches (the backward kernels' masked tiles); otherwise blocks one by one.
@@ -63,7 +66,7 @@ constexpr unsigned kProgramFlags = kProgramStageEnd | kProgramNoBlock | kProgram
 constexpr unsigned kMaskIdNone = 0;       // every pair of the block is admitted
 constexpr unsigned kMaskIdNothing = 1;    // none is
 constexpr unsigned kMaskIdFirstKeys = 1;  // + k, 1 <= k < 32: the first k keys of the block are
-constexpr size_t kMaxProgramWords = 0xfffffff0u;
+constexpr size_t kMaxProgramWords = 0xffff0000u;  // places among them are 32-bit numbers; more are refused as out of memory
 constexpr unsigned kMaskIdFree = 33;      // masks of image blocks from here on
 constexpr int bf16_tiles_per_stage(int head_dim) { return head_dim == 64 ? 4 : 2; }
 struct BlockPrograms {

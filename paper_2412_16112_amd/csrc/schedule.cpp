@@ -265,6 +265,11 @@ class BlockMasks {
                 byte[d][kx] = (unsigned char)v;
             }
         }
+        // far inside a large disc the offset does not matter: then one mask per cut
+        bool all = true;
+        for (const auto& row : byte)
+            for (unsigned char v : row) all &= v == 0xff;
+        if (all) return by_offset_.emplace(key, of_axes(0x1111u * ((1u << rows) - 1), 0x0101010101010101ull * ((1u << cols) - 1))).first->second;
         const unsigned id = add();
         for (int reg = 0; reg < 16; ++reg) {
             unsigned long long w = 0;

@@ -187,8 +187,31 @@ void check_shape(const Shape& sh, int head_dim)
 
 }  // namespace
 
+// Waves and query tiles whose programs are the same share one: without that a window that holds the whole grid took 16 words a
+// (query tile, key tile) pair.
+static void check_sharing()
+{
+    const Shape shapes[] = {{64, 256, 256, 400, CLEAR_MASK_DISC, 0}, {0, 253, 251, 400, CLEAR_MASK_DISC, 0}, {10, 200, 203, 300, CLEAR_MASK_SQUARE, 0},
+                            {10, 200, 203, 512, CLEAR_MASK_SWIN, 0}, {10, 256, 254, 2, CLEAR_MASK_STRIDED, 1}};
+    for (const Shape& sh : shapes) {
+        const int stride = sh.kind == CLEAR_MASK_STRIDED ? sh.r : 1;
+        Schedule s;
+        build_schedule((sh.gridH + stride - 1) / stride, (sh.gridW + stride - 1) / stride, stride > 1 ? sh.gridH + sh.gridW : sh.r, kBf16QTileH, kBf16QTileW,
+                       kKeyTileH, kKeyTileW, &s, stride > 1 ? (int)kMaskDisc : sh.kind, 0);
+        const QueryTilePatterns pat = query_tile_patterns(s);
+        std::vector<int> k_col;
+        order_forward_tiles(s, pat, &k_col);
+        std::vector<BlockPrograms> prog;
+        std::vector<unsigned long long> masks;
+        build_block_programs({{&s, &pat, &k_col, 1}}, sh.n_text, 128, stride, sh.gridH, sh.gridW, &prog, &masks);
+        const size_t text_words = 257 + 2 * 129 * 2 + 4 * 129 + 2048;
+        EXPECT(prog[0].words.size() <= 2 * s.col_idx.size() * (stride > 1 ? 2 : 1) + s.row_ptr.size() * 8 + text_words);
+    }
+}
+
 int check_block_programs()
 {
+    check_sharing();
     const Shape shapes[] = {{8, 16, 16, 4, CLEAR_MASK_DISC, 0},     {0, 1, 1, 1, CLEAR_MASK_DISC, 0},       {77, 48, 85, 16, CLEAR_MASK_DISC, 0},
                             {130, 37, 29, 9, CLEAR_MASK_DISC, 0},   {5, 7, 70, 32, CLEAR_MASK_DISC, 0},     {31, 80, 3, 11, CLEAR_MASK_DISC, 0},
                             {40, 33, 45, 100, CLEAR_MASK_DISC, 0},  {64, 72, 104, 5, CLEAR_MASK_DISC, 0},   {1, 50, 66, 12, CLEAR_MASK_SWIN, 5},

@@ -137,3 +137,21 @@ def test_f32_text_rows_round_once_per_cell_of_keys(H, n_text, gh, gw, range_keys
         den += (ref ** 2).sum().item()
     rel = (num / den) ** 0.5
     assert rel <= 2.0 ** -25 * ((range_keys / 16 / 2) ** 0.5 + 12), rel
+
+
+@pytest.mark.parametrize("n_text,gh,gw,r", [(40, 253, 251, 400), (7, 320, 320, 300)])
+def test_bf16_window_of_the_size_of_the_grid(n_text, gh, gw, r):
+    """Windows that hold the whole grid (the waves share one program, border masks do not depend on the offset), or about all of it
+    (every query tile has programs of its own, tables of several MB copied piece by piece)."""
+    print(f"[case] n_text={n_text} grid={gh}x{gw} r={r}", flush=True)
+    Q, K, V = make_qkv_shape(1, 1, n_text, gh, gw, 128, "bf16", seed=81, device=DEV)
+    ctx = ca.ClearAttn(n_text, gh, gw, 128, r, ca.CLEAR_BF16)
+    try:
+        O = ctx.forward(Q, K, V)
+        torch.cuda.synchronize()
+    finally:
+        ctx.destroy()
+    rows = _rows(n_text, gh, gw, seed=r, n=64)
+    ref = orc.attention_rows(*(t[0, 0].double().cpu().numpy() for t in (Q, K, V)), rows, n_text, gh, gw, r)
+    mx, rms = error_metrics(O[0, 0].float().cpu().numpy()[rows], ref)
+    assert mx <= TOL["bf16"][0] and rms <= TOL["bf16"][1], (mx, rms)
