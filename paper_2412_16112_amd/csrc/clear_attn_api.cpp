@@ -30,18 +30,26 @@ class TablePack {
         size_ = at + std::max<size_t>(v.size(), 1) * sizeof(T);
         return at;
     }
-    hipError_t upload(unsigned char** device) const
+    hipError_t upload(unsigned char** device) const  // *device is null afterwards unless everything is there
     {
+        std::vector<unsigned char> bytes(size_ <= ((size_t)4 << 20) ? size_ : 0);
         hipError_t e = hipMalloc((void**)device, size_);
-        if (e != hipSuccess) return e;
-        if (size_ <= ((size_t)4 << 20)) {
-            std::vector<unsigned char> bytes(size_);
+        if (e != hipSuccess) {
+            *device = nullptr;
+            return e;
+        }
+        if (!bytes.empty()) {
             for (const Piece& p : pieces_)
                 if (p.size) memcpy(bytes.data() + p.at, p.data, p.size);
-            return hipMemcpy(*device, bytes.data(), size_, hipMemcpyHostToDevice);
+            e = hipMemcpy(*device, bytes.data(), size_, hipMemcpyHostToDevice);
+        } else {
+            for (const Piece& p : pieces_)  // (no second copy of large tables on the host)
+                if (e == hipSuccess && p.size) e = hipMemcpy(*device + p.at, p.data, p.size, hipMemcpyHostToDevice);
         }
-        for (const Piece& p : pieces_)  // (no second copy of large tables on the host)
-            if (e == hipSuccess && p.size) e = hipMemcpy(*device + p.at, p.data, p.size, hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            (void)hipFree(*device);
+            *device = nullptr;
+        }
         return e;
     }
 

@@ -1,9 +1,11 @@
 // Host-side entry points of the library run under the host sanitizers (AddressSanitizer + UndefinedBehaviorSanitizer),
 // on a machine without a GPU: the schedule builder on ragged, thin, tiny and large shapes and every mask kind, the
 // lattice counts, the lane-mask tables, the per-wave tile descriptors, the band layout, and the argument checks of the calls that need a device
-// (each must return an error code before any launch).  Results are cross-checked where a second way to get them
+// (each must return an error code before any launch), the wave
+// programs (block_programs.cpp), the launch shapes, and contexts over a stand-in for the HIP runtime that can be made to fail (fake_hip.cpp).  Results are cross-checked where a second way to get them
 // exists; the point of the run is that no sanitizer report appears.  Exit code 0 = clean.
 #include <algorithm>
+#include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -12,6 +14,7 @@
 #include "../../paper_2412_16112_amd/csrc/block_class.h"
 #include "../../paper_2412_16112_amd/csrc/clear_internal.h"
 #include "../../paper_2412_16112_amd/csrc/launch_shape.h"
+#include "fake_hip.h"
 
 int check_block_programs();  // block_programs.cpp
 
@@ -252,6 +255,47 @@ static void bands_and_argument_checks()
     clear_attn_destroy(nullptr);
 }
 
+// Contexts over the stand-in runtime (fake_hip.cpp): what a call does when the runtime fails in the middle of it.
+static void contexts()
+{
+    const int n_text = 40, gh = 33, gw = 45, d = 128, r = 8;
+    const size_t N = n_text + (size_t)gh * gw;
+    std::vector<float> buffers[9];
+    void* t[9];  // Q, K, V, O, dO, dQ, dK, dV, lse
+    for (int i = 0; i < 9; ++i) {
+        buffers[i].assign(N * d + 16, 0.f);
+        t[i] = (void*)(((uintptr_t)buffers[i].data() + 15) & ~(uintptr_t)15);
+    }
+    const long long before = fake::live;
+    clear_attn_ctx* ctx = nullptr;
+    EXPECT(clear_attn_create(&ctx, n_text, gh, gw, d, r, CLEAR_BF16) == CLEAR_OK);
+    auto backward = [&]() {
+        return clear_attn_backward(ctx, t[0], t[1], t[2], t[3], t[4], (const float*)t[8], t[5], t[6], t[7], 1, 1, n_text, gh, gw, d, r, nullptr);
+    };
+    // the backward tile lists are made with the first backward call: one that fails halfway leaves nothing behind
+    for (int good = 0; good < 2; ++good) {
+        const long long live = fake::live;
+        fake::backward_launches = 0;
+        fake::copies_until_error = good ? -1 : 0;
+        EXPECT(backward() == (good ? CLEAR_OK : CLEAR_ERR_HIP));
+        fake::copies_until_error = -1;
+        if (!good) EXPECT(fake::live == live && fake::backward_launches == 0);
+    }
+    EXPECT(fake::backward_launches > 0 && fake::backward.row_ptr && fake::backward.col_idx && fake::backward.n_plain);
+    EXPECT(clear_attn_forward(ctx, t[0], t[1], t[2], t[3], 1, 1, n_text, gh, gw, d, r, nullptr) == CLEAR_OK);
+    EXPECT(fake::forward.program && fake::forward.program_ptr && fake::forward.block_masks && fake::forward.row_ptr);
+    clear_attn_destroy(ctx);
+    EXPECT(fake::live == before);
+    // a context whose upload fails leaves nothing behind either
+    fake::copies_until_error = 0;
+    EXPECT(clear_attn_create(&ctx, n_text, gh, gw, d, r, CLEAR_BF16) == CLEAR_ERR_HIP);
+    fake::copies_until_error = -1;
+    fake::no_memory = true;
+    EXPECT(clear_attn_create(&ctx, n_text, gh, gw, d, r, CLEAR_BF16) == CLEAR_ERR_ALLOC);
+    fake::no_memory = false;
+    EXPECT(fake::live == before);
+}
+
 int main()
 {
     schedules();
@@ -261,6 +305,7 @@ int main()
     failures += check_block_programs();
     launch_shapes();
     bands_and_argument_checks();
+    contexts();
     if (failures) {
         std::printf("%d check(s) failed\n", failures);
         return 1;

@@ -21,7 +21,8 @@ def test_host_entry_points_clean_under_asan_and_ubsan(tmp_path):
            "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
            "-Xarch_host", "-fno-sanitize-recover=undefined", "-x", "hip",
            os.path.join(CSRC, "clear_attn_api.cpp"), os.path.join(CSRC, "schedule.cpp"), os.path.join(CSRC, "launch_shape.cpp"),
-           os.path.join(HERE, "launch_stubs.cpp"), os.path.join(HERE, "driver.cpp"), os.path.join(HERE, "block_programs.cpp"), "-o", exe]
+           os.path.join(HERE, "launch_stubs.cpp"), os.path.join(HERE, "driver.cpp"), os.path.join(HERE, "block_programs.cpp"),
+           os.path.join(HERE, "fake_hip.cpp"), "-o", exe]
     build = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert build.returncode == 0, build.stdout[-4000:]
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0", UBSAN_OPTIONS="print_stacktrace=1")
