@@ -168,7 +168,6 @@ constexpr int kWaveSkipsTile = -1;
 void build_wave_descriptors(const Schedule& s, const std::vector<int>& k_col, const std::vector<int>& n_plain, int mask_ry, int mask_rx,
                             std::vector<int>* desc);
 void build_bf16_mask_table(int r, int ry, int rx, int mask_kind, std::vector<unsigned long long>* tbl);
-int f32_text_queries_per_block();
 // Backward pass (kernels_bf16_bwd.hip).
 struct BwdParams {
     const void* Q;

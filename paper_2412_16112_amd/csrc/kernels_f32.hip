@@ -60,7 +60,7 @@ typedef __attribute__((address_space(3))) const float* lds_f32_ptr;
 // DISC: the mask of Eq. 3 (its element test is a few instructions); otherwise whichever mask p.mask_kind names.
 // CELLS: key cells per stage; half a tile (2, 32 KB of LDS for two stages: five workgroups per CU) unless four waves share a patch.
 template <bool DISC, int CELLS>
-__global__ void __launch_bounds__(kWaves * 64, CELLS == 2 ? 5 : 2) clear_fwd_f32_kernel(const FwdParams p, const int n_image)
+__global__ void __launch_bounds__(kWaves * 64, CELLS == 2 ? 5 : 2) clear_fwd_f32_kernel(const FwdParams p, const int image_first, const int n_image)
 {
     constexpr int STAGE_KEYS = CELLS * kCell, HALF_BYTES = STAGE_KEYS * HD * 4;
     constexpr int PARTS = TILE_KEYS / STAGE_KEYS, PART_H = kKeyTileH / PARTS;  // stages per key tile; rows of an image tile in one
@@ -77,7 +77,7 @@ __global__ void __launch_bounds__(kWaves * 64, CELLS == 2 ? 5 : 2) clear_fwd_f32
     {
         const int bid = textq ? (int)blockIdx.x - n_image : (int)blockIdx.x, nblk = textq ? (int)gridDim.x - n_image : n_image;
         const int xcd = bid & 7, idx = bid >> 3, q = nblk >> 3, rem = nblk & 7;
-        vid = xcd * q + imin(xcd, rem) + idx;
+        vid = (textq ? 0 : image_first) + xcd * q + imin(xcd, rem) + idx;
     }
     int bh, qt = 0, split = 0;
     int ty0 = 0, tx0 = 0, th = 0, tw = 0;  // image: the rectangle of queries of this workgroup
@@ -363,24 +363,29 @@ __global__ void __launch_bounds__(256) clear_text_merge_f32_kernel(const FwdPara
 
 }  // namespace
 
-int f32_text_queries_per_block() { return kWaves * kCell; }
-
 hipError_t launch_f32_d64(const FwdParams& p, hipStream_t stream, int phase)
 {
     const int BH = p.B * p.H;
     hipError_t e = hipSuccess;
     const bool all = phase == kPhaseAll || phase == kPhaseImageAndTextQuery;
     const int subs = 4 * p.f32_groups;  // workgroups per 16 x 16 query tile
-    const int n_image = all || phase == kPhaseImage ? BH * p.n_q_tiles_launch * subs : 0;
-    const int n_text = p.n_text > 0 && (all || phase == kPhaseTextQuery) ? BH * p.n_tq_tiles * p.n_splits : 0;
-    if (n_image + n_text > 0) {
-        const bool disc = p.mask_kind == kMaskDisc, wide = p.f32_groups == 4;
-        auto kern = disc ? (wide ? clear_fwd_f32_kernel<true, 4> : clear_fwd_f32_kernel<true, 2>)
-                         : (wide ? clear_fwd_f32_kernel<false, 4> : clear_fwd_f32_kernel<false, 2>);
-        hipLaunchKernelGGL(kern, dim3(n_image + n_text), dim3(kWaves * 64), 0, stream, p, n_image);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
+    const long long n_image = all || phase == kPhaseImage ? (long long)BH * p.n_q_tiles_launch * subs : 0;
+    const long long n_text = p.n_text > 0 && (all || phase == kPhaseTextQuery) ? (long long)BH * p.n_tq_tiles * p.n_splits : 0;
+    constexpr long long kMost = 0xffffffffLL / (kWaves * 64);  // workgroups a launch can have
+    if (n_image > 0x7fffffffLL || n_text > kMost) return hipErrorInvalidConfiguration;
+    const bool disc = p.mask_kind == kMaskDisc, wide = p.f32_groups == 4;
+    auto kern = disc ? (wide ? clear_fwd_f32_kernel<true, 4> : clear_fwd_f32_kernel<true, 2>)
+                     : (wide ? clear_fwd_f32_kernel<false, 4> : clear_fwd_f32_kernel<false, 2>);
+    auto run = [&](long long first, long long n_img, long long n_txt) {
+        if (n_img + n_txt == 0) return hipSuccess;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(n_img + n_txt)), dim3(kWaves * 64), 0, stream, p, (int)first, (int)n_img);
+        return hipGetLastError();
+    };
+    long long first = 0;
+    for (; e == hipSuccess && n_image - first + n_text > kMost; first += kMost < n_image - first ? kMost : n_image - first)  // (thin grids of many heads)
+        e = run(first, kMost < n_image - first ? kMost : n_image - first, 0);
+    if (e == hipSuccess) e = run(first, n_image - first, n_text);
+    if (e != hipSuccess) return e;
     if (p.n_text > 0 && p.n_splits > 1 && (phase == kPhaseAll || phase == kPhaseTextMerge)) {
         hipLaunchKernelGGL(clear_text_merge_f32_kernel, dim3((unsigned)(((long long)BH * p.n_text + 15) / 16)), dim3(256), 0, stream, p);
         e = hipGetLastError();

@@ -21,14 +21,14 @@ constexpr int kHeadsPerThread = 8;  // independent 16-byte loads in flight per l
 // Workgroup = 256 / LPR neighbouring tokens of kHeadsPerThread heads.
 template <int HD>
 __global__ void __launch_bounds__(256) qk_prologue_kernel(const __bf16* __restrict__ X, TensorStrides xs, __bf16* __restrict__ Y, TensorStrides ys,
-                                                          int H, long long BH, long long N, unsigned n_token_blocks, int n_text, int gridW,
+                                                          int H, long long BH, long long t_first, long long N, unsigned n_token_blocks, int n_text, int gridW,
                                                           const float* __restrict__ gain, float eps, const float* __restrict__ rope_y,
                                                           const float* __restrict__ rope_x)
 {
     constexpr int LPR = HD / 8;     // lanes per row
     constexpr int TPB = 256 / LPR;  // tokens per workgroup
     const int c0 = 8 * (threadIdx.x % LPR);
-    const long long t = (long long)(blockIdx.x % n_token_blocks) * TPB + threadIdx.x / LPR;
+    const long long t = t_first + (long long)(blockIdx.x % n_token_blocks) * TPB + threadIdx.x / LPR;
     const long long bh0 = (long long)(blockIdx.x / n_token_blocks) * kHeadsPerThread;
     const bool live = t < N;
     const long long tc = live ? t : N - 1;
@@ -102,18 +102,19 @@ hipError_t launch_qk_prologue(const void* X, const TensorStrides& xs, void* Y, c
     const long long BH = (long long)B * H;
     if (BH * N == 0) return hipSuccess;
     const int tokens_per_block = 256 / (head_dim / 8);
-    const long long token_blocks = (N + tokens_per_block - 1) / tokens_per_block;
-    const long long blocks = token_blocks * ((BH + kHeadsPerThread - 1) / kHeadsPerThread);
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (head_dim == 128)
-        hipLaunchKernelGGL(qk_prologue_kernel<128>, dim3((unsigned)blocks), dim3(256), 0, stream, (const __bf16*)X, xs, (__bf16*)Y, ys, H, BH, N,
+    const long long head_blocks = (BH + kHeadsPerThread - 1) / kHeadsPerThread;
+    const long long most = 0xffffffffLL / 256 / head_blocks;  // token blocks a launch can have
+    if (most < 1) return hipErrorInvalidValue;
+    if (head_dim != 128 && head_dim != 64) return hipErrorInvalidValue;
+    auto kern = head_dim == 128 ? qk_prologue_kernel<128> : qk_prologue_kernel<64>;
+    for (long long first = 0; first < N; first += most * tokens_per_block) {  // (one launch but for tensors of tens of GB)
+        const long long left = (N - first + tokens_per_block - 1) / tokens_per_block, token_blocks = left < most ? left : most;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(token_blocks * head_blocks)), dim3(256), 0, stream, (const __bf16*)X, xs, (__bf16*)Y, ys, H, BH, first, N,
                            (unsigned)token_blocks, n_text, gridW, gain, eps, rope_y, rope_x);
-    else if (head_dim == 64)
-        hipLaunchKernelGGL(qk_prologue_kernel<64>, dim3((unsigned)blocks), dim3(256), 0, stream, (const __bf16*)X, xs, (__bf16*)Y, ys, H, BH, N,
-                           (unsigned)token_blocks, n_text, gridW, gain, eps, rope_y, rope_x);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace clear

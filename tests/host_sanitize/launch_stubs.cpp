@@ -38,5 +38,4 @@ hipError_t launch_qk_prologue(const void*, const TensorStrides&, void*, const Te
     return hipErrorNotSupported;
 }
 int bf16_text_queries_per_block() { return kBf16NWY * kBf16NWX * kTextQueriesPerWave; }
-int f32_text_queries_per_block() { return kF32QTileH * kF32QTileW; }
 }  // namespace clear

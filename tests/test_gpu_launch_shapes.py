@@ -155,3 +155,20 @@ def test_bf16_window_of_the_size_of_the_grid(n_text, gh, gw, r):
     ref = orc.attention_rows(*(t[0, 0].double().cpu().numpy() for t in (Q, K, V)), rows, n_text, gh, gw, r)
     mx, rms = error_metrics(O[0, 0].float().cpu().numpy()[rows], ref)
     assert mx <= TOL["bf16"][0] and rms <= TOL["bf16"][1], (mx, rms)
+
+
+def test_f32_more_workgroups_than_a_launch_can_have():
+    """2 050 heads of a 1 x 32 767 grid are 2^24 workgroups of 256 threads and more, which no single launch can have.  r = 1 without text: a
+    token sees itself alone, so O = V."""
+    H, gw = 2050, 32767
+    print(f"[case] f32 H={H} grid=1x{gw}", flush=True)
+    V = torch.empty((1, H, gw, 64), device=DEV)
+    V.normal_(generator=torch.Generator(device=DEV).manual_seed(91))
+    O = torch.empty_like(V)
+    ctx = ca.ClearAttn(0, 1, gw, 64, 1, ca.CLEAR_F32)
+    try:
+        ctx.forward(V, V, V, O)
+        torch.cuda.synchronize()
+    finally:
+        ctx.destroy()
+    assert all(torch.equal(O[0, h:h + 82], V[0, h:h + 82]) for h in range(0, H, 82))

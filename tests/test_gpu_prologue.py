@@ -75,6 +75,18 @@ def test_qk_prologue_pass_head_groups(B, H, n_text, gridH, gridW, d):
             check_rounded(np64(Y[b, h]), pro.qk_prologue(np64(X[b, h]), np64(g), 1e-6, n_text, gridH, gridW, np64(ry), np64(rx)))
 
 
+def test_qk_prologue_pass_of_more_tokens_than_a_launch_covers():
+    """One head of 2^28 tokens and more, in place: 2^24 workgroups of 16 tokens are more than a launch can have.  Every token is
+    a row of ones, so that after the norm (mean square 1, eps 0) every row is the gain."""
+    gridH, gridW, d = 16385, 16384, 128
+    X = torch.ones((1, 1, gridH * gridW, d), dtype=torch.bfloat16, device=DEV)
+    gain = torch.linspace(0.5, 2.0, d, device=DEV).contiguous()
+    assert ca.clear_attn_qk_prologue(X, 0, gridH, gridW, gain=gain, norm_eps=0.0, out=X) is X
+    torch.cuda.synchronize()
+    want = gain.to(torch.bfloat16)
+    assert all(bool((X[0, 0, at:at + (1 << 24)] == want).all()) for at in range(0, gridH * gridW, 1 << 24))
+
+
 FWD_CASES = [
     # n_text, gridH, gridW, r, H, norm, rope, logit_scale, ntk
     (64, 40, 24, 8, 2, True, True, 1.0, 1.0),
