@@ -151,6 +151,28 @@ struct FwdParams {
     int f32_groups;  // fp32 kernel: waves per 16-query patch (1, 2 or 4 of a workgroup's 4)
 };
 
+// Launches `per_head` workgroups for every (batch, head) of p, in one launch or, where they are more than the `most` that one can have (2^32
+// threads: beyond that the runtime drops the excess without an error), in one for several batch items or heads at a time: shift(&q, b, h) moves
+// the pointers of q to batch item b, head h; launch(q, n) launches n workgroups.
+template <class Params, class Shift, class Launch>
+hipError_t launch_by_heads(const Params& p, long long per_head, long long most, Shift shift, Launch launch)
+{
+    if (per_head * p.B * p.H <= most) return launch(p, (int)(per_head * p.B * p.H));
+    if (per_head > most) return hipErrorInvalidConfiguration;
+    const bool whole = per_head * p.H <= most;  // a launch takes all heads of several batch items, or several heads of one
+    const int nb = whole ? (int)(most / (per_head * p.H)) : 1, nh = whole ? p.H : (int)(most / per_head);
+    hipError_t e = hipSuccess;
+    for (int b = 0; b < p.B && e == hipSuccess; b += nb)
+        for (int h = 0; h < p.H && e == hipSuccess; h += nh) {
+            Params q = p;
+            q.B = p.B - b < nb ? p.B - b : nb;
+            q.H = p.H - h < nh ? p.H - h : nh;
+            shift(&q, b, h);
+            e = launch(q, (int)(per_head * q.B * q.H));
+        }
+    return e;
+}
+
 // Launchers (kernels_bf16.hip, kernels_f32.hip).  Each returns the first HIP error met.
 // phase: kPhaseAll, or one of the three kernels of a forward pass (used to time them one by one).
 // kPhaseImageAndTextQuery (bf16 only): the first two in one launch.

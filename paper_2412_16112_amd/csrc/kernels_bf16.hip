@@ -821,10 +821,18 @@ hipError_t launch_bf16(const FwdParams& p, hipStream_t stream, int phase)
 {
     const int BH = p.B * p.H;
     hipError_t e = hipSuccess;
-    const int n_image = BH * p.n_classes * p.n_q_tiles_launch, n_text_wgs = p.n_text > 0 ? BH * p.n_tq_tiles * p.n_splits : 0;
-    if (phase == kPhaseImageAndTextQuery) return launch_fwd_both(p, n_image, n_text_wgs, stream);
+    const int n_text_wgs = p.n_text > 0 ? BH * p.n_tq_tiles * p.n_splits : 0;
+    const long long per_head = (long long)p.n_classes * p.n_q_tiles_launch;
+    if (phase == kPhaseImageAndTextQuery) return launch_fwd_both(p, (int)(BH * per_head), n_text_wgs, stream);  // (64 image workgroups per CU at most)
     if (phase == kPhaseAll || phase == kPhaseImage) {
-        e = launch_fwd<false>(p, n_image, stream);
+        auto shift = [&](FwdParams* q, int b, int h) {
+            q->Q = (const __bf16*)p.Q + b * p.qs.sb + h * p.qs.sh;
+            q->K = (const __bf16*)p.K + b * p.ks.sb + h * p.ks.sh;
+            q->V = (const __bf16*)p.V + b * p.vs.sb + h * p.vs.sh;
+            q->O = (__bf16*)p.O + b * p.os.sb + h * p.os.sh;
+            if (p.lse) q->lse = p.lse + ((long long)b * p.H + h) * p.N;
+        };
+        e = launch_by_heads(p, per_head, 0xffffffffLL / ((NW + NLW) * 64), shift, [&](const FwdParams& q, int n) { return launch_fwd<false>(q, n, stream); });
         if (e != hipSuccess) return e;
     }
     if (n_text_wgs > 0 && (phase == kPhaseAll || phase == kPhaseTextQuery)) {

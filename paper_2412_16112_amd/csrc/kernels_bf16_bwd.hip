@@ -894,10 +894,10 @@ hipError_t launch_bf16_backward(const BwdParams& p, const void* O, float* delta,
         hipLaunchKernelGGL(clear_bwd_delta_kernel, dim3(token_blocks * head_blocks), dim3(256), 0, stream, (const __bf16*)O, p.os, (const __bf16*)p.dO, p.dos, p.H, BH, p.N, token_blocks, delta);
         e = hipGetLastError();
     }
-    const int nimg = BH * p.n_classes * p.n_q_tiles;
+    const long long per_head = (long long)p.n_classes * p.n_q_tiles;
 #if CLEAR_BWD_FUSED_KV
     if (phase == kBwdPhaseFour) {
-        const int nlin4 = p.n_text > 0 ? BH * p.n_tq_tiles * p.n_splits : 0;
+        const int nlin4 = p.n_text > 0 ? BH * p.n_tq_tiles * p.n_splits : 0, nimg = (int)(BH * per_head);  // (64 image workgroups per CU at most)
         const int code = mask_code_of(p.mask_kind);
         return code == kCodeDisc   ? launch_bwd_all<kCodeDisc>(p, nimg, nlin4, stream)
                : code == kCodeFull ? launch_bwd_all<kCodeFull>(p, nimg, nlin4, stream)
@@ -910,14 +910,32 @@ hipError_t launch_bf16_backward(const BwdParams& p, const void* O, float* delta,
         pq.O = O;
         pq.delta_out = delta;
     }
-    if (e == hipSuccess && (all || phase == kBwdPhaseImageQ)) e = launch_bwd<kBwdQ, false>(pq, nimg, stream);
+    auto shift = [&](BwdParams* q, int b, int h) {
+        auto at = [&](const void* t, const TensorStrides& st) { return (const __bf16*)t + b * st.sb + h * st.sh; };
+        const long long row = ((long long)b * p.H + h) * p.N;
+        q->Q = at(p.Q, p.qs);
+        q->K = at(p.K, p.ks);
+        q->V = at(p.V, p.vs);
+        q->dO = at(p.dO, p.dos);
+        q->dQ = (void*)at(p.dQ, p.dqs);
+        q->dK = (void*)at(p.dK, p.dks);
+        q->dV = (void*)at(p.dV, p.dvs);
+        if (q->O) q->O = at(q->O, p.os);
+        q->lse = p.lse + row;
+        q->delta = p.delta + row;
+        if (q->delta_out) q->delta_out += row;
+    };
+    auto launch_image = [&](const BwdParams& params, auto mode_tag) {
+        return launch_by_heads(params, per_head, 0xffffffffLL / 512, shift, [&](const BwdParams& q, int n) { return launch_bwd<decltype(mode_tag)::value, false>(q, n, stream); });
+    };
+    if (e == hipSuccess && (all || phase == kBwdPhaseImageQ)) e = launch_image(pq, std::integral_constant<int, kBwdQ>{});
     if (e == hipSuccess && nlin > 0 && (all || phase == kBwdPhaseTextQ)) e = launch_bwd<kBwdQ, true>(pq, nlin, stream);
     if (e == hipSuccess && (all || phase == kBwdPhaseImageKV)) {
 #if CLEAR_BWD_FUSED_KV
-        e = launch_bwd<kBwdKV, false>(p, nimg, stream);
+        e = launch_image(p, std::integral_constant<int, kBwdKV>{});
 #else
-        e = launch_bwd<kBwdK, false>(p, nimg, stream);
-        if (e == hipSuccess) e = launch_bwd<kBwdV, false>(p, nimg, stream);
+        e = launch_image(p, std::integral_constant<int, kBwdK>{});
+        if (e == hipSuccess) e = launch_image(p, std::integral_constant<int, kBwdV>{});
 #endif
     }
     if (e != hipSuccess || p.n_text == 0) return e;

@@ -172,3 +172,29 @@ def test_f32_more_workgroups_than_a_launch_can_have():
     finally:
         ctx.destroy()
     assert all(torch.equal(O[0, h:h + 82], V[0, h:h + 82]) for h in range(0, H, 82))
+
+
+def test_bf16_more_workgroups_than_a_launch_can_have():
+    """Thin grids of many heads: 2 731 heads of 1 x 32 767 are more than 2^32 threads for the forward kernel (768 a workgroup, 2 048
+    workgroups a head), 4 097 for the backward kernels (512 a workgroup).  r = 1 without text: a token sees itself alone, so O = V, dV = dO and
+    dQ = dK = 0 but for what two fp32 sums of the same 64 products differ by, dP and delta: 2 x 64 x 2^-24 of the products' sizes, which add up to
+    less than 100, times a key below 6 and the scale 1/8: 6e-4."""
+    H, gw = 4097, 32767
+    print(f"[case] bf16 H={H} grid=1x{gw}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(92)
+    V, dO = (torch.empty((1, H, gw, 64), dtype=torch.bfloat16, device=DEV).normal_(generator=gen) for _ in range(2))
+    ctx = ca.ClearAttn(0, 1, gw, 64, 1, ca.CLEAR_BF16)
+    heads = [(h, min(h + 100, H)) for h in range(0, H, 100)]
+    try:
+        O, lse = ctx.forward_lse(V, V, V)
+        torch.cuda.synchronize()
+        assert all(torch.equal(O[0, a:b], V[0, a:b]) for a, b in heads)
+        for a, b in heads:
+            s = (V[0, a:b].float() ** 2).sum(-1) / 8
+            assert ((lse[0, a:b] - s).abs() <= 1e-5 * (1 + s)).all()
+        dQ, dK, dV = ctx.backward(V, V, V, O, dO, lse)
+        torch.cuda.synchronize()
+    finally:
+        ctx.destroy()
+    assert all(torch.equal(dV[0, a:b], dO[0, a:b]) for a, b in heads)
+    assert all(float(t[0, a:b].abs().max()) <= 6e-4 for t in (dQ, dK) for a, b in heads)
