@@ -148,8 +148,10 @@ int clear_attn_schedule_size(const clear_attn_ctx* ctx, int* q_tile_h, int* q_ti
 int clear_attn_schedule_copy(const clear_attn_ctx* ctx, int* row_ptr, int* col_idx,
                              unsigned char* flags);
 
-/* Number of (query slot, key slot) pairs per (batch, head) that the kernels actually push through
- * the matrix pipeline, masked and padding slots included ("executed" work; useful work is sumM). */
+/* Number of (query slot, key slot) pairs per (batch, head) that the forward kernels actually push through
+ * the matrix pipeline, masked and padding slots included ("executed" work; useful work is sumM): 32 x 32 blocks in bf16, 16 x 16 in
+ * fp32, those included that mask everything and only flush the pipeline.  (bf16 calls of a few workgroups per CU, in which several waves
+ * share a patch of queries, run a few more of these.) */
 int clear_attn_executed_pairs(const clear_attn_ctx* ctx, unsigned long long* pairs_per_head);
 
 /* ---- Other local masks through the same scheduler (the sparse-attention variants the paper compares CLEAR

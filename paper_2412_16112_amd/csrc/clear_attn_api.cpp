@@ -79,6 +79,7 @@ struct TileTables {
     ForwardTables fwd[3];        // bf16: 1, 2, 4 waves per patch (the latter two only for small grids)
     unsigned char* forward = nullptr;  // all of their tables, and
     unsigned long long* d_block_masks = nullptr;
+    unsigned long long executed_pairs = 0;  // bf16: per head, see executed_pairs_bf16
     int* d_qt_order = nullptr;         // the order in which a head's query tiles are dealt to the workgroups (may be null)
     // fp32 kernel, and the bf16 backward kernels (built with the backward workspace)
     unsigned char* lists = nullptr;  // all of the below
@@ -250,7 +251,7 @@ static void order_key_tiles(const Schedule& sc, int cutH, int cutW, std::vector<
 
 // Tables of the bf16 forward kernels on the current device: one wave per query patch and, where the query tiles of one head do not fill the chip
 // by themselves, several (see choose_forward_shape); order: may be empty.
-static hipError_t build_forward_tables(int n_text, int head_dim, int stride, int gridH, int gridW, const std::vector<int>& order, TileTables* t)
+static hipError_t build_forward_tables(int n_text, int head_dim, int stride, int layer, int gridH, int gridW, const std::vector<int>& order, TileTables* t)
 {
     const Schedule& sched = t->sched;
     const int n = stride == 1 && sched.row_ptr.size() - 1 <= kGroupsMaxTiles ? 3 : 1;
@@ -268,6 +269,7 @@ static hipError_t build_forward_tables(int n_text, int head_dim, int stride, int
     std::vector<BlockPrograms> prog;
     std::vector<unsigned long long> masks;
     build_block_programs(in, n_text, head_dim, stride, gridH, gridW, &prog, &masks);
+    t->executed_pairs = executed_pairs_bf16(prog[0], n_text, gridH, gridW, stride, layer);
     TablePack pack;
     size_t at[3][4] = {};
     for (int i = 0; i < n; ++i) {
@@ -397,7 +399,7 @@ static int build_tile_tables(int n_text, int gridH, int gridW, int head_dim, int
     }
     hipError_t e = hipSuccess;
     try {
-        e = dtype == CLEAR_BF16 ? build_forward_tables(n_text, head_dim, strided ? r : 1, gridH, gridW, order, t)
+        e = dtype == CLEAR_BF16 ? build_forward_tables(n_text, head_dim, strided ? r : 1, strided ? shift : 0, gridH, gridW, order, t)
                                 : build_lists(gridH, gridW, r, dtype, mask_kind, shift, t);
     } catch (const std::bad_alloc&) {
         *why = "out of host memory building the tile lists";
@@ -1266,10 +1268,7 @@ int clear_attn_schedule_copy(const clear_attn_ctx* ctx, int* row_ptr, int* col_i
 int clear_attn_executed_pairs(const clear_attn_ctx* ctx, unsigned long long* pairs_per_head)
 {
     if (!ctx || !pairs_per_head) return fail(nullptr, CLEAR_ERR_INVALID_ARG, "NULL argument");
-    if (ctx->mask_kind == CLEAR_MASK_STRIDED)
-        *pairs_per_head = executed_pairs_bf16_strided(ctx->t.sched, ctx->n_text, ctx->gridH, ctx->gridW, ctx->r, ctx->mask_shift);
-    else
-        *pairs_per_head = (ctx->dtype == CLEAR_BF16) ? executed_pairs_bf16(ctx->t.sched, ctx->n_text, 0, false) : executed_pairs_f32(ctx->t.sched, ctx->n_text);
+    *pairs_per_head = ctx->dtype == CLEAR_BF16 ? ctx->t.executed_pairs : executed_pairs_f32(ctx->t.sched, ctx->n_text);
     return CLEAR_OK;
 }
 

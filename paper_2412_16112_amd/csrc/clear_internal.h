@@ -42,11 +42,6 @@ long long schedule_pair_bound(int gridH, int gridW, int r, int qth, int qtw, int
 // share any, as with r about half of a large grid.  Windows that hold the whole grid share nearly all of them.
 constexpr long long kMaxSchedulePairs = 1LL << 28;
 unsigned long long mask_count(int n_text, int gridH, int gridW, int r, int mask_kind = 0, int mask_shift = 0);
-// Pairs fed to the matrix pipeline per (batch, head) by the bf16 kernels (image pass + text-query pass).
-// whole_tiles: a wave runs both 32-key blocks of a tile it reaches (the backward kernels' masked tiles); otherwise blocks one by one.
-unsigned long long executed_pairs_bf16(const Schedule& s, int n_text, int text_split_keys, bool whole_tiles = true);
-// The same for a strided context (s: the schedule of the class sub-grid; gridH, gridW: the real grid).
-unsigned long long executed_pairs_bf16_strided(const Schedule& s, int n_text, int gridH, int gridW, int stride, int layer);
 // Pairs the fp32 path multiplies: 4 x 4 query patches against the cells of 16 keys they reach.
 unsigned long long executed_pairs_f32(const Schedule& s, int n_text);
 
@@ -75,6 +70,8 @@ struct BlockPrograms {
     double mean_stages, mean_steps;            // of a query tile: stages, blocks per wave
     unsigned text_words[3];                    // for 1, 2, 4 waves per patch of text queries: [wave][keys of the stage][blocks per stage / waves]
                                                // words of a stage with that many keys (0: a whole stage that is not the last)
+    unsigned long long blocks[4][4] = {};      // [variant of the key class][of the query class]: blocks that the waves of a head (of a class of it) run
+                                               // (one wave per patch only)
 };
 // Query tiles whose lists and programs are the same but for their place: interior ones, mostly.
 struct QueryTilePatterns {
@@ -98,6 +95,10 @@ struct ProgramInput {
 // keys' class has gridH / stride or one more rows, gridW / stride or one more columns.
 void build_block_programs(const std::vector<ProgramInput>& in, int n_text, int head_dim, int stride, int gridH, int gridW,
                           std::vector<BlockPrograms>* out, std::vector<unsigned long long>* masks);
+
+// Pairs fed to the matrix pipeline per (batch, head) by the bf16 forward kernels with one wave per patch: every block that a wave runs, those
+// included that mask everything and only finish what is pending.
+unsigned long long executed_pairs_bf16(const BlockPrograms& prog, int n_text, int gridH, int gridW, int stride, int layer);
 
 struct FwdParams {
     const void* Q;

@@ -192,41 +192,6 @@ void build_wave_descriptors(const Schedule& s, const std::vector<int>& k_col, co
     }
 }
 
-unsigned long long executed_pairs_bf16(const Schedule& s, int n_text, int text_split_keys, bool whole_tiles)
-{
-    (void)text_split_keys;  // splits are multiples of the 64-key stage: the block count does not depend on them
-    const long long N = (long long)n_text + (long long)s.gridH * s.gridW;
-    unsigned long long blocks = 0;  // executed (32 query x 32 key) blocks
-    const int n_text_tiles = ceil_div(n_text, kKeyTileKeys);
-    const int nwy = s.qth / kWaveQH, nwx = s.qtw / kWaveQW;
-    const MaskSpec spec = {s.mask_kind, s.r, s.mask_shift};
-    for (int ty = 0; ty < s.n_qty; ++ty)
-        for (int tx = 0; tx < s.n_qtx; ++tx) {
-            const int qt = ty * s.n_qtx + tx;
-            for (int wy = 0; wy < nwy; ++wy)
-                for (int wx = 0; wx < nwx; ++wx) {
-                    const int y0 = ty * s.qth + wy * kWaveQH, x0 = tx * s.qtw + wx * kWaveQW;
-                    if (y0 >= s.gridH || x0 >= s.gridW) continue;  // wave has no query: it computes nothing
-                    if (whole_tiles)
-                        blocks += 2ull * n_text_tiles;
-                    else
-                        blocks += ceil_div(n_text, 32);
-                    for (int e = s.row_ptr[qt]; e < s.row_ptr[qt + 1]; ++e) {
-                        const int ky0 = (s.col_idx[e] / s.n_ktx) * s.kth, kx0 = (s.col_idx[e] % s.n_ktx) * s.ktw;
-                        int reached = 0;
-                        for (int kb = 0; kb < 2; ++kb)
-                            reached += classify_image_block_spec(spec, y0, x0, kWaveQH, kWaveQW, ky0 + kKeyBlockH * kb, kx0, kKeyBlockH,
-                                                                 kKeyBlockW, s.gridH, s.gridW) != kBlockSkip;
-                        blocks += whole_tiles ? 2 * (reached > 0) : reached;
-                    }
-                }
-        }
-    // text-query pass: every wave that holds at least one text query visits every 32-key block of [0, N)
-    const unsigned long long text_waves = (unsigned long long)ceil_div(n_text, kTextQueriesPerWave);
-    blocks += whole_tiles ? text_waves * 2ull * (unsigned long long)((N + kKeyTileKeys - 1) / kKeyTileKeys) : text_waves * (unsigned long long)((N + 31) / 32);
-    return blocks * 1024ull;
-}
-
 namespace {
 
 // Lane masks of (4 x 8 query patch, 4 x 8 key block) pairs, each distinct one kept once.
@@ -591,7 +556,8 @@ namespace {
 // The image-query programs of one table set and variant (of the key grid's extents), appended to out->words; out->ptr of the variant, and the
 // words of a pattern's waves.
 template <int GROUPS, class Blocks>
-void build_image_programs(const ProgramInput& in, int n_text, int head_dim, Blocks& blocks, unsigned* ptr, std::vector<unsigned>* words, std::vector<double>* steps_of)
+void build_image_programs(const ProgramInput& in, int n_text, int head_dim, Blocks& blocks, unsigned* ptr, std::vector<unsigned>* words, std::vector<double>* steps_of,
+                          std::vector<unsigned>* blocks_of)
 {
     const Schedule& s = *in.sched;
     const int waves = kBf16NWY * kBf16NWX, patches = waves / GROUPS, tps = bf16_tiles_per_stage(head_dim);
@@ -612,6 +578,7 @@ void build_image_programs(const ProgramInput& in, int n_text, int head_dim, Bloc
     unsigned *end[GROUPS], *had[GROUPS];
     for (int g = 0; g < GROUPS; ++g) end[g] = scratch.data() + (size_t)g * room;
     unsigned turn = 0;  // the waves of a patch take its blocks in turn
+    int idle_words[GROUPS] = {};
     auto put = [&](unsigned word, bool reached) __attribute__((always_inline)) {
         *end[turn] = word;  // (without a branch: the edge of a disc cannot be foreseen)
         end[turn] += reached;
@@ -626,6 +593,7 @@ void build_image_programs(const ProgramInput& in, int n_text, int head_dim, Bloc
                 // no block here: one that masks everything finishes what the wave has pending, after that nothing is left to do
                 const bool idle = had[g] > scratch.data() + (size_t)g * room && ((had[g][-1] & ~kProgramFlags) >> kProgramMaskShift) == kMaskIdNothing;
                 *end[g]++ = kMaskIdNothing << kProgramMaskShift | (idle ? kProgramNoBlock : 0);
+                idle_words[g] += idle;
             }
             end[g][-1] |= kProgramStageEnd;
         }
@@ -641,7 +609,11 @@ void build_image_programs(const ProgramInput& in, int n_text, int head_dim, Bloc
         end_stage();
     }
     unsigned* text_end[GROUPS];
-    for (int g = 0; g < GROUPS; ++g) text_end[g] = end[g];
+    int text_idle[GROUPS];
+    for (int g = 0; g < GROUPS; ++g) {
+        text_end[g] = end[g];
+        text_idle[g] = idle_words[g];
+    }
     const unsigned text_turn = turn;
     struct Piece {
         size_t at, size;
@@ -654,12 +626,15 @@ void build_image_programs(const ProgramInput& in, int n_text, int head_dim, Bloc
         for (int e = begin; e < begin + n_img; ++e) tiles.push_back(blocks.tile((*in.k_col)[e] >> 16, (*in.k_col)[e] & 0xffff));
         for (int patch = 0; patch < patches; ++patch) {
             const int wy0 = (int)(qt / s.n_qtx) * s.qth + (patch / kBf16NWX) * kWaveQH, wx0 = (int)(qt % s.n_qtx) * s.qtw + (patch % kBf16NWX) * kWaveQW;
-            const bool queries = wy0 < s.gridH && wx0 < s.gridW;  // (a wave without any follows no program; the mean counts it as out of reach of every block)
+            const bool queries = wy0 < s.gridH && wx0 < s.gridW;  // (a wave without any follows no program; the mean of the steps counts it as out of reach of every block)
             if (queries)
                 blocks.answers(wy0, wx0, tiles, answers.data());
             else
                 std::fill(answers.begin(), answers.end(), kOutOfReach);
-            for (int g = 0; g < GROUPS; ++g) end[g] = text_end[g];
+            for (int g = 0; g < GROUPS; ++g) {
+                end[g] = text_end[g];
+                idle_words[g] = text_idle[g];
+            }
             turn = text_turn;
             const unsigned* answer = answers.data();
             for (int first = 0; first < n_img; first += tps) {
@@ -675,6 +650,7 @@ void build_image_programs(const ProgramInput& in, int n_text, int head_dim, Bloc
                 const size_t size = (size_t)(to - from);
                 (*steps_of)[k] += (double)size;
                 if (!queries) continue;
+                (*blocks_of)[k * waves + wave] = (unsigned)size - (unsigned)idle_words[g];
                 // Waves whose programs are the same share one: those of a class of the strided mask, or of a window that holds the whole grid.
                 const Piece candidates[2] = {last[wave], last[wave > 0 ? wave - 1 : 0]};
                 const Piece* same = nullptr;
@@ -749,14 +725,31 @@ void build_block_programs(const std::vector<ProgramInput>& in, int n_text, int h
                 const size_t n_q_tiles = in[i].sched->row_ptr.size() - 1;
                 unsigned* const ptr = o.ptr.data() + (size_t)v * n_q_tiles * waves;
                 std::vector<double> steps_of(pat.first.size(), 0);
-                if (in[i].groups == 1) build_image_programs<1>(in[i], n_text, head_dim, blocks, ptr, &o.words, &steps_of);
-                if (in[i].groups == 2) build_image_programs<2>(in[i], n_text, head_dim, blocks, ptr, &o.words, &steps_of);
-                if (in[i].groups == 4) build_image_programs<4>(in[i], n_text, head_dim, blocks, ptr, &o.words, &steps_of);
+                std::vector<unsigned> blocks_of(pat.first.size() * waves, 0);
+                if (in[i].groups == 1) build_image_programs<1>(in[i], n_text, head_dim, blocks, ptr, &o.words, &steps_of, &blocks_of);
+                if (in[i].groups == 2) build_image_programs<2>(in[i], n_text, head_dim, blocks, ptr, &o.words, &steps_of, &blocks_of);
+                if (in[i].groups == 4) build_image_programs<4>(in[i], n_text, head_dim, blocks, ptr, &o.words, &steps_of, &blocks_of);
                 for (size_t qt = 0; qt < n_q_tiles; ++qt) {
                     const size_t first = pat.first[pat.id[qt]];
                     if (first != qt) std::copy(ptr + first * waves, ptr + (first + 1) * waves, ptr + qt * waves);
                     steps[i] += steps_of[pat.id[qt]];
                 }
+                // executed blocks, of the waves that have queries (of a class of either extent)
+                if (in[i].groups > 1) continue;
+                std::vector<unsigned long long> blocks_in(pat.first.size(), 0);
+                for (size_t j = 0; j < blocks_of.size(); ++j) blocks_in[j / waves] += blocks_of[j];
+                for (int u = 0; u < n_variants; ++u)
+                    for (size_t qt = 0; qt < n_q_tiles; ++qt) {
+                        if (!strided) {
+                            o.blocks[v][u] += blocks_in[pat.id[qt]];
+                            continue;
+                        }
+                        const Schedule& sc = *in[i].sched;
+                        for (int w = 0; w < waves; ++w) {
+                            const int wy0 = (int)(qt / sc.n_qtx) * sc.qth + (w / kBf16NWX) * kWaveQH, wx0 = (int)(qt % sc.n_qtx) * sc.qtw + (w % kBf16NWX) * kWaveQW;
+                            if (wy0 < gridH / stride + (u >> 1) && wx0 < gridW / stride + (u & 1)) o.blocks[v][u] += blocks_of[(size_t)pat.id[qt] * waves + w];
+                        }
+                    }
             }
         };
         if (set.spec().kind == kMaskDisc) {
@@ -779,39 +772,21 @@ void build_block_programs(const std::vector<ProgramInput>& in, int n_text, int h
     }
 }
 
-unsigned long long executed_pairs_bf16_strided(const Schedule& s, int n_text, int gridH, int gridW, int stride, int layer)
+unsigned long long executed_pairs_bf16(const BlockPrograms& prog, int n_text, int gridH, int gridW, int stride, int layer)
 {
     const long long N = (long long)n_text + (long long)gridH * gridW;
-    const int rx = layer % stride, ry = (layer / stride) % stride;
-    const int n_text_tiles = ceil_div(n_text, kKeyTileKeys);
-    const int nwy = s.qth / kWaveQH, nwx = s.qtw / kWaveQW;
-    auto extent = [&](int n, int a) { return a < n ? (n - a + stride - 1) / stride : 0; };
-    unsigned long long blocks = 0;
-    for (int b = 0; b < stride; ++b)
-        for (int a = 0; a < stride; ++a) {
-            const int qH = extent(gridH, b), qW = extent(gridW, a);
-            const int kH = extent(gridH, (b + ry) % stride), kW = extent(gridW, (a + rx) % stride);
-            for (int ty = 0; ty < s.n_qty; ++ty)
-                for (int tx = 0; tx < s.n_qtx; ++tx) {
-                    const int qt = ty * s.n_qtx + tx;
-                    for (int wy = 0; wy < nwy; ++wy)
-                        for (int wx = 0; wx < nwx; ++wx) {
-                            const int y0 = ty * s.qth + wy * kWaveQH, x0 = tx * s.qtw + wx * kWaveQW;
-                            if (y0 >= qH || x0 >= qW) continue;
-                            for (int t = 0; t < n_text_tiles; ++t)
-                                blocks += 2 * (classify_linear_block((long long)t * kKeyTileKeys, 32, n_text) != kBlockSkip);
-                            for (int e = s.row_ptr[qt]; e < s.row_ptr[qt + 1]; ++e) {
-                                const int ky0 = (s.col_idx[e] / s.n_ktx) * s.kth, kx0 = (s.col_idx[e] % s.n_ktx) * s.ktw;
-                                bool any = false;
-                                for (int kb = 0; kb < 2; ++kb)
-                                    any |= classify_full_block(y0, x0, qH, qW, ky0 + kKeyBlockH * kb, kx0, kKeyBlockH, kKeyBlockW, kH, kW) != kBlockSkip;
-                                blocks += 2 * any;
-                            }
-                        }
-                }
-        }
-    const unsigned long long text_waves = (unsigned long long)ceil_div(n_text, kTextQueriesPerWave);
-    blocks += text_waves * 2ull * (unsigned long long)((N + kKeyTileKeys - 1) / kKeyTileKeys);
+    unsigned long long blocks = 0;  // (32 query x 32 key) blocks
+    if (stride == 1) {
+        blocks = prog.blocks[0][0];
+    } else {
+        const int rx = layer % stride, ry = (layer / stride) % stride;
+        auto larger = [&](int n, int a) { return a < n % stride; };  // whether class a of an axis has the larger extent
+        for (int b = 0; b < stride; ++b)
+            for (int a = 0; a < stride; ++a)
+                blocks += prog.blocks[2 * larger(gridH, (b + ry) % stride) + larger(gridW, (a + rx) % stride)][2 * larger(gridH, b) + larger(gridW, a)];
+    }
+    // text-query rows: every wave that holds at least one text query visits every 32-key block of [0, N)
+    blocks += (unsigned long long)ceil_div(n_text, kTextQueriesPerWave) * (unsigned long long)((N + 31) / 32);
     return blocks * 1024ull;
 }
 

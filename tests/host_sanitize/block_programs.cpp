@@ -77,6 +77,7 @@ struct Shape {
 void check_image_programs(const Shape& sh, const Schedule& s, const std::vector<int>& k_col, const BlockPrograms& prog,
                           const std::vector<unsigned long long>& masks, int head_dim, int groups)
 {
+    unsigned long long ran[4][4] = {};  // blocks run: by key class and query class
     const bool strided = sh.kind == CLEAR_MASK_STRIDED && sh.r > 1;  // (r = 1 admits every pair: one class)
     const MaskSpec spec = {sh.kind, sh.r, sh.shift};
     const int tps = bf16_tiles_per_stage(head_dim), tile_units = kKeyTileKeys * head_dim * 2 / 2048;
@@ -112,6 +113,8 @@ void check_image_programs(const Shape& sh, const Schedule& s, const std::vector<
                             EXPECT((size_t)w.id * 16 + 16 <= masks.size());
                         }
                         flushed = w.no_block || w.id == kMaskIdNothing;
+                        for (int u = 0; u < (strided ? 4 : 1) && !w.no_block; ++u)
+                            if (!strided || (wy0 < sh.gridH / sh.r + (u >> 1) && wx0 < sh.gridW / sh.r + (u & 1))) ++ran[v][u];
                         if (!w.no_block && i < (linear ? n_lin_tiles : n_img) && (size_t)w.id * 16 + 16 <= masks.size())
                             for (int q = 0; q < 32; ++q) {
                                 const int qy = wy0 + (q >> 3), qx = wx0 + (q & 7);
@@ -144,6 +147,18 @@ void check_image_programs(const Shape& sh, const Schedule& s, const std::vector<
             }
         }
     }
+    if (groups > 1) return;
+    // the count the library reports: what the classes' waves run, and every 32-key block for every 32 text queries
+    unsigned long long want = 0;
+    const int stride = strided ? sh.r : 1;
+    for (int b = 0; b < stride; ++b)
+        for (int a = 0; a < stride; ++a) {
+            auto extra = [&](int n, int c) { return (n - c + stride - 1) / stride - n / stride; };  // rows (columns) of class c beyond n / stride
+            const int ky = (b + sh.shift / stride) % stride, kx = (a + sh.shift) % stride;
+            want += strided ? ran[2 * extra(sh.gridH, ky) + extra(sh.gridW, kx)][2 * extra(sh.gridH, b) + extra(sh.gridW, a)] : ran[0][0];
+        }
+    want += (unsigned long long)((sh.n_text + 31) / 32) * ((sh.n_text + (unsigned long long)sh.gridH * sh.gridW + 31) / 32);
+    EXPECT(executed_pairs_bf16(prog, sh.n_text, sh.gridH, sh.gridW, stride, strided ? sh.shift : 0) == want * 1024);
 }
 
 void check_shape(const Shape& sh, int head_dim)
