@@ -86,6 +86,7 @@ struct TileTables {
     int* d_row_ptr = nullptr;
     int* d_col_idx = nullptr;   // kernel order: tiles inside the grid first, border tiles last
     int* d_n_plain = nullptr;
+    int* d_row_order = nullptr;  // the order in which the backward kernels deal out a head's row tiles (may be null)
     unsigned long long* d_mask_tbl = nullptr;
     int* d_wave_desc = nullptr;  // per listed key tile and wave: mask-table entries of its blocks (bf16, with d_mask_tbl)
     int mask_ry = 0, mask_rx = 0;
@@ -249,11 +250,32 @@ static void order_key_tiles(const Schedule& sc, int cutH, int cutW, std::vector<
     }
 }
 
+// Order of a head's query tiles over its workgroups.  An XCD (32 CUs, one workgroup each, one 4 MB L2) works through
+// a contiguous range of that order, so the tiles in flight on it are 32 consecutive entries.  Row by row on a wide
+// grid they are a 1 x 32 strip of tiles, whose keys - 16 + 2 (r - 1) rows across 512 columns - the next strip
+// needs again but finds evicted.  So they are dealt out in blocks of rows x cols tiles, strips of cols tile columns taken top to bottom; grids up to
+// cols tiles wide keep the plain order (empty).
+static std::vector<int> tile_order(const Schedule& s, int rows, int cols)
+{
+    std::vector<int> order;
+    if (s.n_qtx <= cols) return order;
+    order.reserve((size_t)s.n_qty * s.n_qtx);
+    for (int bx = 0; bx < s.n_qtx; bx += cols)
+        for (int by = 0; by < s.n_qty; by += rows)
+            for (int ty = by; ty < std::min(by + rows, s.n_qty); ++ty)
+                for (int tx = bx; tx < std::min(bx + cols, s.n_qtx); ++tx) order.push_back(ty * s.n_qtx + tx);
+    return order;
+}
+
 // Tables of the bf16 forward kernels on the current device: one wave per query patch and, where the query tiles of one head do not fill the chip
-// by themselves, several (see choose_forward_shape); order: may be empty.
-static hipError_t build_forward_tables(int n_text, int head_dim, int stride, int layer, int gridH, int gridW, const std::vector<int>& order, TileTables* t)
+// by themselves, several (see choose_forward_shape).
+static hipError_t build_forward_tables(int n_text, int head_dim, int stride, int layer, int gridH, int gridW, TileTables* t)
 {
     const Schedule& sched = t->sched;
+    // With the key tiles in an order that overlapping windows share (order_forward_tiles), the tiles in flight read 8.0 GB past the L2 at a 512 x
+    // 512 grid and 24 heads (2 x 16 blocks: 11.3; 21 in neither order); the power saved there is worth 1 % of the time on
+    // a part that runs at its power limit.
+    const std::vector<int> order = stride == 1 ? tile_order(sched, 4, 8) : std::vector<int>();
     const int n = stride == 1 && sched.row_ptr.size() - 1 <= kGroupsMaxTiles ? 3 : 1;
     Schedule sub[3];
     QueryTilePatterns pat[3];
@@ -338,7 +360,11 @@ static hipError_t build_lists(int gridH, int gridW, int r, int dtype, int mask_k
             mask_tbl.clear();
         }
     }
+    // The backward kernels keep blocks of 2 x 16: their key tiles are in another order than the forward kernels'.  (24 heads, 144 x 160 grid, which is too
+    // narrow for them: 2.416 ms in 4 x 8 blocks, 2.400 row by row; 256 x 256, 192 x 320 and 512 x 512 within 0.2 % of each other in either.)
+    const std::vector<int> order = dtype == CLEAR_BF16 && !strided ? tile_order(t->sched, 2, 16) : std::vector<int>();
     TablePack pack;
+    const size_t order_at = order.empty() ? 0 : pack.add(order);
     const size_t row_ptr = pack.add(t->sched.row_ptr), col_idx = pack.add(k_col), plain = pack.add(n_plain);
     const size_t masks = mask_tbl.empty() ? 0 : pack.add(mask_tbl), desc = wave_desc.empty() ? 0 : pack.add(wave_desc);
     hipError_t e = pack.upload(&t->lists);
@@ -346,6 +372,7 @@ static hipError_t build_lists(int gridH, int gridW, int r, int dtype, int mask_k
     t->d_row_ptr = (int*)(t->lists + row_ptr);
     t->d_col_idx = (int*)(t->lists + col_idx);
     t->d_n_plain = (int*)(t->lists + plain);
+    t->d_row_order = order.empty() ? nullptr : (int*)(t->lists + order_at);
     t->d_mask_tbl = mask_tbl.empty() ? nullptr : (unsigned long long*)(t->lists + masks);
     t->d_wave_desc = wave_desc.empty() ? nullptr : (int*)(t->lists + desc);
     return hipSuccess;
@@ -375,31 +402,9 @@ static int build_tile_tables(int n_text, int gridH, int gridW, int head_dim, int
         *why = "out of host memory building the schedule";
         return CLEAR_ERR_ALLOC;
     }
-    // Order of a head's query tiles over its workgroups.  An XCD (32 CUs, one workgroup each, one 4 MB L2) works through
-    // a contiguous range of that order, so the tiles in flight on it are 32 consecutive entries.  Row by row on a wide
-    // grid they are a 1 x 32 strip of tiles, whose keys - 16 + 2 (r - 1) rows across 512 columns - the next strip
-    // needs again but finds evicted.  Dealt out in blocks of 4 x 8 tiles, strips of 8 tile columns taken top to bottom, and with the
-    // key tiles in an order that overlapping windows share (order_forward_tiles), the tiles in flight read 8.0 GB past the L2 at a 512 x
-    // 512 grid and 24 heads (2 x 16 blocks: 11.3; 21 in neither order); the power saved there is worth 1 % of the time on
-    // a part that runs at its power limit.  Grids up to 8 tiles wide keep the plain order (no table).
-    constexpr int kOrderRows = 4, kOrderCols = 8;
-    std::vector<int> order;
-    if (dtype == CLEAR_BF16 && !strided && t->sched.n_qtx > kOrderCols) {
-        const Schedule& sc = t->sched;
-        try {
-            order.reserve((size_t)sc.n_qty * sc.n_qtx);
-            for (int bx = 0; bx < sc.n_qtx; bx += kOrderCols)
-                for (int by = 0; by < sc.n_qty; by += kOrderRows)
-                    for (int ty = by; ty < std::min(by + kOrderRows, sc.n_qty); ++ty)
-                        for (int tx = bx; tx < std::min(bx + kOrderCols, sc.n_qtx); ++tx) order.push_back(ty * sc.n_qtx + tx);
-        } catch (const std::bad_alloc&) {
-            *why = "out of host memory building the query-tile order";
-            return CLEAR_ERR_ALLOC;
-        }
-    }
     hipError_t e = hipSuccess;
     try {
-        e = dtype == CLEAR_BF16 ? build_forward_tables(n_text, head_dim, strided ? r : 1, strided ? shift : 0, gridH, gridW, order, t)
+        e = dtype == CLEAR_BF16 ? build_forward_tables(n_text, head_dim, strided ? r : 1, strided ? shift : 0, gridH, gridW, t)
                                 : build_lists(gridH, gridW, r, dtype, mask_kind, shift, t);
     } catch (const std::bad_alloc&) {
         *why = "out of host memory building the tile lists";
@@ -1117,7 +1122,7 @@ static int backward_impl(clear_attn_ctx* ctx, const void* Q, const void* K, cons
     p.N = N;
     p.n_q_tiles = s.n_qty * s.n_qtx;
     p.n_qtx = s.n_qtx;
-    p.row_ptr = ctx->t.d_row_ptr; p.col_idx = ctx->t.d_col_idx; p.n_plain = ctx->t.d_n_plain; p.qt_order = ctx->t.d_qt_order; p.mask_tbl = ctx->t.d_mask_tbl;
+    p.row_ptr = ctx->t.d_row_ptr; p.col_idx = ctx->t.d_col_idx; p.n_plain = ctx->t.d_n_plain; p.qt_order = ctx->t.d_row_order; p.mask_tbl = ctx->t.d_mask_tbl;
     p.wave_desc = ctx->t.d_wave_desc;
     p.mask_ry = ctx->t.mask_ry; p.mask_rx = ctx->t.mask_rx;
     p.mask_kind = ctx->mask_kind; p.mask_r = r; p.mask_shift = ctx->mask_shift;

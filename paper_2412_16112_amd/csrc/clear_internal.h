@@ -212,7 +212,7 @@ struct BwdParams {
     const int* row_ptr;
     const int* col_idx;  // tiles inside the grid first, then the ones cut by the border
     const int* n_plain;  // per row tile: how many of its tiles lie inside the grid
-    const int* qt_order;  // as in FwdParams
+    const int* qt_order;  // the row tile that the i-th workgroup of a head takes (null: i)
     const unsigned long long* mask_tbl;  // lane masks per relative block offset (may be null)
     int mask_ry, mask_rx;
     const int* wave_desc;  // with mask_tbl: per listed tile inside the grid (kernel order) and wave of the workgroup, the mask-table

@@ -282,6 +282,36 @@ static void contexts()
     EXPECT(fake::live == before);
 }
 
+// The orders in which a head's tiles are dealt to the workgroups: permutations in blocks of 4 x 8 tiles (forward) and 2 x 16 (backward), of which
+// grids no wider than a block need none.
+static void tile_orders()
+{
+    const int grids[][2] = {{64, 64}, {144, 160}, {100, 272}, {70, 300}};
+    for (const auto& g : grids) {
+        const int n_qty = (g[0] + 15) / 16, n_qtx = (g[1] + 15) / 16;
+        std::vector<float> buffer(16);
+        clear_attn_ctx* ctx = nullptr;
+        EXPECT(clear_attn_create(&ctx, 0, g[0], g[1], 64, 4, CLEAR_BF16) == CLEAR_OK);
+        const size_t bytes = (size_t)g[0] * g[1] * 64 * 2 * 24;
+        auto at = [&](int i) { return (void*)(uintptr_t)((i + 1) * ((bytes + 4095) & ~(size_t)4095)); };  // (never read: the launchers are stand-ins)
+        EXPECT(clear_attn_forward(ctx, at(0), at(1), at(2), at(3), 1, 24, 0, g[0], g[1], 64, 4, nullptr) == CLEAR_OK);
+        EXPECT(clear_attn_backward(ctx, at(0), at(1), at(2), at(3), at(4), (const float*)at(8), at(5), at(6), at(7), 1, 24, 0, g[0], g[1], 64, 4, nullptr) == CLEAR_OK);
+        const int* const orders[2] = {fake::forward.groups == 1 ? fake::forward.qt_order : nullptr, fake::backward.qt_order};
+        const int rows[2] = {4, 2}, cols[2] = {8, 16};
+        for (int k = 0; k < 2; ++k) {
+            if (k == 1 || fake::forward.groups == 1) EXPECT((orders[k] != nullptr) == (n_qtx > cols[k]));
+            if (!orders[k]) continue;
+            std::vector<char> seen((size_t)n_qty * n_qtx, 0);
+            for (int i = 0; i < n_qty * n_qtx; ++i) {
+                EXPECT(orders[k][i] >= 0 && orders[k][i] < n_qty * n_qtx && !seen[(size_t)orders[k][i]]);
+                seen[(size_t)orders[k][i]] = 1;
+            }
+            for (int i = 0; i < std::min(rows[k], n_qty) * cols[k]; ++i) EXPECT(orders[k][i] == i / cols[k] * n_qtx + i % cols[k]);
+        }
+        clear_attn_destroy(ctx);
+    }
+}
+
 int main()
 {
     schedules();
@@ -292,6 +322,7 @@ int main()
     launch_shapes();
     bands_and_argument_checks();
     contexts();
+    tile_orders();
     if (failures) {
         std::printf("%d check(s) failed\n", failures);
         return 1;
