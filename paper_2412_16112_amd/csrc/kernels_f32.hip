@@ -81,18 +81,14 @@ __global__ void __launch_bounds__(kWaves * 64, CELLS == 2 ? 5 : 2) clear_fwd_f32
     }
     int bh, qt = 0, split = 0;
     int ty0 = 0, tx0 = 0, th = 0, tw = 0;  // image: the rectangle of queries of this workgroup
-    int qy = 0, qx = 0, wy0 = 0, wx0 = 0;
-    long long q_token;
-    bool q_valid, wave_has_queries;
+    int wy0 = 0, wx0 = 0, q0 = 0;  // first query of this wave
+    bool wave_has_queries;
     if (textq) {
         split = vid % p.n_splits;
         const int t = vid / p.n_splits;
         bh = t / p.n_tq_tiles;
-        const int q0 = (t % p.n_tq_tiles) * (patches * kCell) + patch * kCell;
-        q_token = q0 + qi;
-        q_valid = q_token < p.n_text;
+        q0 = (t % p.n_tq_tiles) * (patches * kCell) + patch * kCell;
         wave_has_queries = q0 < p.n_text;
-        if (!q_valid) q_token = p.n_text - 1;
     } else {
         // 16 x 16 query tiles of the schedule, cut into 8 x 8, 4 x 8 or 4 x 4 ones
         th = groups == 1 ? 8 : 4;
@@ -106,12 +102,13 @@ __global__ void __launch_bounds__(kWaves * 64, CELLS == 2 ? 5 : 2) clear_fwd_f32
         if (ty0 >= p.gridH || tx0 >= p.gridW || ty0 >= p.own_y1 || ty0 + th <= p.own_y0) return;  // no query here
         wy0 = ty0 + 4 * (patch >> 1);
         wx0 = tx0 + 4 * (patch & 1);
-        qy = wy0 + (qi >> 2);
-        qx = wx0 + (qi & 3);
-        q_valid = qy < p.gridH && qx < p.gridW && qy >= p.own_y0 && qy < p.own_y1;  // (row-band mode: owned rows only)
         wave_has_queries = wy0 < p.gridH && wx0 < p.gridW;
-        q_token = (long long)p.n_text + (long long)imin(qy, p.gridH - 1) * p.gridW + imin(qx, p.gridW - 1);
     }
+    auto query_token = [&](int i) -> long long {  // query i of this wave (a valid token also where there is none)
+        if (textq) return imin(q0 + i, p.n_text - 1);
+        return (long long)p.n_text + (long long)imin(wy0 + (i >> 2), p.gridH - 1) * p.gridW + imin(wx0 + (i & 3), p.gridW - 1);
+    };
+    const int qy = wy0 + (qi >> 2), qx = wx0 + (qi & 3);
     const long long head_off = (long long)bh * p.N * HD;
     const float* const Kh = (const float*)p.K + head_off;
     const float* const Vh = (const float*)p.V + head_off;
@@ -176,7 +173,7 @@ __global__ void __launch_bounds__(kWaves * 64, CELLS == 2 ? 5 : 2) clear_fwd_f32
     // Q as B operand: contraction step 4 j + t takes channel 4 (4 j + g) + t from lane group g
     f32x4 qf[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) qf[j] = *(const f32x4*)((const float*)p.Q + head_off + q_token * HD + 4 * (4 * j + g));
+    for (int j = 0; j < 4; ++j) qf[j] = *(const f32x4*)((const float*)p.Q + head_off + query_token(qi) * HD + 4 * (4 * j + g));
 
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     f32x4 o[4] = {zero, zero, zero, zero};  // channel 16 cb + 4 g + reg of this lane's query
@@ -285,11 +282,16 @@ __global__ void __launch_bounds__(kWaves * 64, CELLS == 2 ? 5 : 2) clear_fwd_f32
     else
         walk(std::false_type{});
 
+    // (formed again rather than held through the walk)
+    const int end_lane = fresh_lane_id(), end_qi = end_lane & 15, end_g = end_lane >> 4, end_qy = wy0 + (end_qi >> 2), end_qx = wx0 + (end_qi & 3);
+    const long long q_token = query_token(end_qi);
+    const bool q_valid = textq ? q0 + end_qi < p.n_text
+                               : end_qy < p.gridH && end_qx < p.gridW && end_qy >= p.own_y0 && end_qy < p.own_y1;  // (row-band mode: owned rows only)
     l = quad_sum(l);
     if (groups > 1) {
         // join the partial sums of the waves that share a patch: wave by wave in LDS, 18 floats per lane
         __syncthreads();
-        float* const mine = (float*)smem + wave * (18 * 64) + lane;
+        float* const mine = (float*)smem + wave * (18 * 64) + end_lane;
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
@@ -310,12 +312,52 @@ __global__ void __launch_bounds__(kWaves * 64, CELLS == 2 ? 5 : 2) clear_fwd_f32
                 for (int t = 0; t < 4; ++t) o[cb][t] = o[cb][t] * wa + other[(4 * cb + t) * 64] * wb;
         }
     }
+    // A masked pair is multiplied like the others, by a weight of zero: an infinity or NaN in V then reaches queries that do not see it.  Where a sum is
+    // not finite, the wave goes through its keys once more, one by one, and leaves the masked ones out (maximum and sum of the weights stand).
+    float finite = 0.f;
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) finite += 0.f * o[cb][t];
+    if (__builtin_amdgcn_ballot_w64(!(finite == 0.f)) != 0) {
+        const float* const Qr = (const float*)p.Q + head_off + q_token * HD + 4 * end_g;  // this lane's channels, of Q, K and V: 16 cb + 4 g + reg
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) o[cb] = zero;
+        auto visit = [&](long long token, bool admitted) {
+            float s = 0.f;
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) {
+                const f32x4 a = *(const f32x4*)(Qr + 16 * cb), b = *(const f32x4*)(Kh + token * HD + 16 * cb + 4 * end_g);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) s = __builtin_fmaf(a[t], b[t], s);
+            }
+            const float w = __builtin_amdgcn_exp2f((quad_sum(s) - m) * sc);
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) {
+                const f32x4 v = *(const f32x4*)(Vh + token * HD + 16 * cb + 4 * end_g);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) o[cb][t] = admitted ? __builtin_fmaf(w, v[t], o[cb][t]) : o[cb][t];
+            }
+        };
+#pragma unroll 1
+        for (long long i = lin_begin; i < lin_limit; ++i) visit(textq && i >= p.vkeys_text ? i + p.vshift : i, true);
+        if (!textq) {
+            const int n_img = (n_stages - n_lin) / PARTS;
+#pragma unroll 1
+            for (int e = 0; e < n_img * TILE_KEYS; ++e) {
+                const int packed = col_idx[csr_begin + e / TILE_KEYS], ky = (packed >> 16) + e % TILE_KEYS / kKeyTileW, kx = (packed & 0xffff) + e % kKeyTileW;
+                if (ky >= p.gridH || kx >= p.gridW) continue;
+                const bool admitted = mask_admits(spec, end_qy, end_qx, ky, kx);
+                if (__builtin_amdgcn_ballot_w64(admitted) != 0) visit((long long)p.n_text + (long long)ky * p.gridW + kx, admitted);
+            }
+        }
+    }
     if (!q_valid) return;
     if (textq && p.n_splits > 1) {
         const long long row = ((long long)bh * p.n_splits + split) * p.n_text + q_token;
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) *(f32x4*)(p.ws_o + row * HD + 16 * cb + 4 * g) = o[cb];
-        if (g == 0) {
+        for (int cb = 0; cb < 4; ++cb) *(f32x4*)(p.ws_o + row * HD + 16 * cb + 4 * end_g) = o[cb];
+        if (end_g == 0) {
             p.ws_ml[row * 2] = m;
             p.ws_ml[row * 2 + 1] = l;
         }
@@ -328,9 +370,9 @@ __global__ void __launch_bounds__(kWaves * 64, CELLS == 2 ? 5 : 2) clear_fwd_f32
         orow = p.band_o + ((long long)bh * p.n_text + q_token) * HD;
         lse_out = p.band_lse + (long long)bh * p.n_text + q_token;
     }
-    if (lse_out && g == 0) *lse_out = lse;
+    if (lse_out && end_g == 0) *lse_out = lse;
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb) *(f32x4_any*)(orow + 16 * cb + 4 * g) = o[cb] * inv;
+    for (int cb = 0; cb < 4; ++cb) *(f32x4_any*)(orow + 16 * cb + 4 * end_g) = o[cb] * inv;
 }
 
 // Log-sum-exp combination of the key-split partial results of the text-query rows: 16 lanes per row, 4 channels each.

@@ -198,3 +198,45 @@ def test_bf16_more_workgroups_than_a_launch_can_have():
         ctx.destroy()
     assert all(torch.equal(dV[0, a:b], dO[0, a:b]) for a, b in heads)
     assert all(float(t[0, a:b].abs().max()) <= 6e-4 for t in (dQ, dK) for a, b in heads)
+
+
+@pytest.mark.parametrize("B,H,n_text,gh,gw,r,kind,shift", [
+    (1, 1, 8, 16, 16, 4, ca.CLEAR_MASK_DISC, 0),      # four waves per patch
+    (1, 6, 70, 44, 41, 8, ca.CLEAR_MASK_DISC, 0),     # two, cut tiles
+    (1, 10, 33, 64, 61, 16, ca.CLEAR_MASK_DISC, 0),   # one, several key ranges of the text rows
+    (1, 2, 0, 37, 29, 5, ca.CLEAR_MASK_SQUARE, 0),
+    (1, 3, 20, 50, 66, 12, ca.CLEAR_MASK_SWIN, 5),
+])
+def test_f32_non_finite_values_reach_only_the_queries_that_see_them(B, H, n_text, gh, gw, r, kind, shift):
+    """An infinity and a NaN in V, at tokens inside the grid and in its last corner: queries whose window holds neither come out as
+    if they were not there, the others as the plain sum has them."""
+    print(f"[case] f32 non-finite V H={H} n_text={n_text} grid={gh}x{gw} r={r} kind={kind}", flush=True)
+    Q, K, V = make_qkv_shape(B, H, n_text, gh, gw, 64, "f32", seed=95, device=DEV)
+    spots = [(n_text + (gh // 2) * gw + gw // 3, 5, float("inf")), (n_text + gh * gw - 1, 40, float("nan"))]
+    clean = V.clone()
+    for token, ch, value in spots:
+        V[:, :, token, ch] = value
+    ctx = ca.ClearAttn(n_text, gh, gw, 64, r, ca.CLEAR_F32, kind, shift)
+    try:
+        O, ref = ctx.forward(Q, K, V), ctx.forward(Q, K, clean)
+        torch.cuda.synchronize()
+    finally:
+        ctx.destroy()
+    pos = torch.arange(gh * gw, device=DEV)
+    y, x = pos // gw, pos % gw
+    for token, ch, value in spots:
+        ky, kx = (token - n_text) // gw, (token - n_text) % gw
+        if kind == ca.CLEAR_MASK_DISC:
+            sees = (y - ky) ** 2 + (x - kx) ** 2 < r * r
+        elif kind == ca.CLEAR_MASK_SQUARE:
+            sees = ((y - ky).abs() < r) & ((x - kx).abs() < r)
+        else:
+            sees = ((y + shift) // r == (ky + shift) // r) & ((x + shift) // r == (kx + shift) // r)
+        sees = torch.cat([torch.ones(n_text, dtype=torch.bool, device=DEV), sees])
+        got = O[..., ch]
+        assert (torch.isnan(got) if value != value else torch.isinf(got))[..., sees].all()
+        assert torch.isfinite(got[..., ~sees]).all()
+    finite = torch.isfinite(O)
+    assert int((~finite).sum()) < O.numel() // 20
+    # the keys one by one in place of cells: two fp32 sums of at most some thousand terms, relative to values of order one
+    assert (O - ref).abs()[finite].max() <= 2e-5
