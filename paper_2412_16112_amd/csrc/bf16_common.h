@@ -36,11 +36,10 @@ constexpr int ROW_BYTES = D * 2;     // one token row of K or V
 constexpr int ROWS_PER_LOAD = 1024 / ROW_BYTES;  // token rows one LDS-direct wave load covers
 constexpr int TILE_KEYS = kKeyTileKeys;
 constexpr int TILE_BYTES = TILE_KEYS * ROW_BYTES;  // 16 KB for K, same for V
-// How many matrix instructions ahead the forward tile pipeline reads its LDS operands.  At 128 channels the image-query
-// kernel sits at its 168-register limit (three waves per SIMD with the loading waves): with two slots ahead, and the
-// fourth operand buffer that needs, the compiler keeps a query fragment in scratch memory and reloads it inside every
-// tile (a 16-byte scratch load and a full wait in front of a matrix instruction; 4 % of the kernel's time), with one
-// slot ahead nothing in the tile loops is spilled.  64 channels have the registers for two.
+// How many matrix instructions ahead the forward block pipeline reads its LDS operands.  At 128 channels the image-query
+// kernel sits at its 168-register limit (three waves per SIMD with the loading waves) and spills a few registers outside the loop of
+// steps; a second slot ahead needs the fourth operand buffer.  (On the pipeline by 64-key tiles before this one two slots cost 4 % of the
+// kernel's time in reloads of a query fragment.)  64 channels have the registers for two.
 #ifndef CLEAR_OPERAND_PREFETCH
 #if CLEAR_HEAD_DIM == 128
 #define CLEAR_OPERAND_PREFETCH 1
@@ -56,12 +55,11 @@ constexpr int TPS = CLEAR_TILES_PER_STAGE;           // key tiles (K + V = 32 KB
 #define CLEAR_NBUF 2
 #endif
 constexpr int NBUF = CLEAR_NBUF;                     // stage buffers: one being computed on, the others being filled
-__host__ __device__ constexpr int next_buf(int buf) { return buf + 1 == NBUF ? 0 : buf + 1; }
 constexpr int STAGE_BYTES = TPS * 2 * TILE_BYTES;
 constexpr float FAST_SUM_LIMIT = 1.0e30f;  // the fast pass is discarded when a query's sums leave [0, 1e30)
 constexpr float M_INIT = -1.0e30f;         // finite "no key seen yet" (keeps exp2 arguments free of inf - inf)
 
-// LDS layout of a staged tile: 64 rows of ROW_BYTES, unpadded (the LDS-direct load writes 1 KB per wave
+// LDS layout of a tile as the backward kernels stage it: 64 rows of ROW_BYTES, unpadded (the LDS-direct load writes 1 KB per wave
 // instruction), with the 16-byte chunks of each row permuted: logical chunk c of row k sits in slot
 // c ^ swz(k).
 // 256-byte rows (a row = one sweep over the banks): swz is a bijection on 16 consecutive rows (the 32 key
@@ -146,10 +144,10 @@ struct WaveState {
     float c;         // log2(e) / sqrt(head_dim)
 };
 
-// Per-lane LDS read offsets inside a staged tile.  All operand addresses of a tile derive from two
+// Per-lane LDS read offsets inside a tile as the backward kernels stage it (the forward kernels have a layout of their own).  All operand addresses of a tile derive from two
 // offsets by XOR with small constants and by adding multiples of 4 KB (ds_read immediates):
 //   K operand, block blk, contraction step ks:  ((tile + k0) ^ (ks << 5)) + blk * 32 rows
-//   V operand, block blk, step s2, slice db:    ((tile + TILE_BYTES + v0 [^ V_HI]) ^ (db << 6)) + blk * 32 rows + s2 * 16 rows
+//   V operand, block blk, step s2, slice db:    ((tile + v0 [^ V_HI]) ^ (db << 6)) + blk * 32 rows + s2 * 16 rows
 // (tile addresses are multiples of 1 KB, so the XORs stay inside the offsets' own bits).
 struct LaneOffsets {
     unsigned k0;  // row qi, logical chunk hh:  qi * ROW_BYTES + ((hh ^ swz(qi)) << 4)
@@ -162,14 +160,12 @@ constexpr unsigned V_HI = (1u << 5) | (unsigned)(8 * ROW_BYTES);
 struct TileAddr {
     unsigned kb, vb0, vb1;
 };
-// (v_half: where in the staged tile the half that is read transposed starts; the forward kernels read K row-wise
-// from the first half and V transposed from the second)
-__device__ __forceinline__ TileAddr tile_addr(unsigned tile_lds, const LaneOffsets& lo, unsigned v_half = TILE_BYTES)
+__device__ __forceinline__ TileAddr tile_addr(unsigned tile_lds, const LaneOffsets& lo)
 {
     TileAddr ta;
     ta.kb = tile_lds + lo.k0;
-    ta.vb0 = tile_lds + v_half + lo.v0;
-    ta.vb1 = tile_lds + v_half + (lo.v0 ^ V_HI);
+    ta.vb0 = tile_lds + lo.v0;
+    ta.vb1 = tile_lds + (lo.v0 ^ V_HI);
     return ta;
 }
 
@@ -268,10 +264,6 @@ __device__ __forceinline__ float max_block(const f32x16& s)
     for (int r = 2; r < 16; ++r) mx = fmaxf(mx, s[r]);
     return mx;
 }
-
-// Scheduling hints: ask the backend to emit, in this order, `n` instructions of the given class.
-// Classes (LLVM AMDGPU sched_group_barrier masks): 0x2 VALU, 0x8 MFMA, 0x100 LDS read.
-#define SCHED_GROUP(mask, n) __builtin_amdgcn_sched_group_barrier((mask), (n), 0)
 
 typedef const __attribute__((address_space(3))) bf16x8* lds_bf16x8_ptr;
 typedef __attribute__((address_space(3))) short4v* lds_short4_ptr;

@@ -22,9 +22,10 @@
 // pipeline across stages and barriers: the S product of a block is issued together with the exponentials and the P V
 // product of the block before it.
 //
-// What bounds it: for one or two rounds of workgroups, cycles - a workgroup takes about 16 000 and 900 a stage beside the 520 that a SIMD's
-// two blocks take, 384 of them matrix cycles -; for large grids the chip's power budget, so bytes and instructions count there and
-// waiting hardly does (order_forward_tiles: a third less L2 misses took 5 % of the time; 9 % fewer cycles of waiting took none).
+// What bounds it: for one or two rounds of workgroups, cycles - by the cost model of the launch shapes a workgroup takes about 16 000 and 900 a
+// stage beside 520 for every block of a SIMD's two waves, 512 of them matrix cycles (16 instructions of 32) -; for large grids the chip's power
+// budget, so bytes and instructions count there and waiting hardly does (order_forward_tiles: a third less L2 misses took 5 % of the
+// time; 9 % fewer cycles of waiting took none).
 // Against the version that worked by 64-key tiles inside a stage, with index arithmetic and masks per element at the grid's border,
 // and a launch and a merge pass of its own for the text queries (24 heads, head_dim 128, 512 text tokens): 32 x 32 grid, r = 8:
 // 48.6 -> 31.6 us; 64 x 64, r = 16: 132 -> 114 us; 512 x 512, r = 16: 8.00 -> 7.67 ms; 192 x 320, r = 32: 3.66 -> 3.46 ms.

@@ -340,7 +340,7 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
         constexpr int MASK = decltype(mask_tag)::value;
         // C1 is read row-wise for the scores and (dQ, dK) transposed for the accumulation; C2, TILE_BYTES further on
         // in the staged tile, through the same lane addresses and an immediate offset
-        const TileAddr ta = tile_addr(tile_lds, lo, 0);
+        const TileAddr ta = tile_addr(tile_lds, lo);
         constexpr unsigned kTransposedHalf = MODE == kBwdV ? TILE_BYTES : 0;  // the tile read transposed for the accumulation
         f32x16 s = qk_block(ta, blk, r1f);
         apply_mask<MASK, CODE>(s, blk, ma);
@@ -396,7 +396,7 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
     //   slots [2 KS, end)    dQ^T += K^T dS^T       | dS = P (dP - delta) first, in slot 2 KS
     auto do_block_q = [&](auto mask_tag, unsigned tile_lds, int blk, const MaskArgs& ma) __attribute__((always_inline)) {
         constexpr int MASK = decltype(mask_tag)::value;
-        const TileAddr ta = tile_addr(tile_lds, lo, 0);
+        const TileAddr ta = tile_addr(tile_lds, lo);
         constexpr int S_END = KS, DP_END = 2 * KS, NSLOT = 2 * KS + 2 * NDB;
         auto operand = [&](int slot) {
             if (slot < S_END) return read_k_operand(ta, blk, slot);
@@ -449,7 +449,7 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
     //   last 2 NDB slots         dK^T += Q^T dS^T
     auto do_block_kv = [&](auto mask_tag, unsigned tile_lds, int blk, const MaskArgs& ma, const float* tile_stats) __attribute__((always_inline)) {
         constexpr int MASK = decltype(mask_tag)::value;
-        const TileAddr ta = tile_addr(tile_lds, lo, 0);
+        const TileAddr ta = tile_addr(tile_lds, lo);
         constexpr int S_END = KS, DP_END = 2 * KS, DV_END = DP_END + 2 * NDB, NSLOT = DV_END + 2 * NDB;
         auto operand = [&](int slot) {
             if (slot < S_END) return read_k_operand(ta, blk, slot);
@@ -514,7 +514,7 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
     //   last 2 NDB slots         dK^T += Q^T dS^T     | dS = P (dP - delta) likewise, over P
     auto do_block_kv_early = [&](auto mask_tag, unsigned tile_lds, int blk, const MaskArgs& ma, const float* tile_stats) __attribute__((always_inline)) {
         constexpr int MASK = decltype(mask_tag)::value;
-        TileAddr ta = tile_addr(tile_lds, lo, 0);
+        TileAddr ta = tile_addr(tile_lds, lo);
         constexpr int S_END = KS, DV_END = S_END + 2 * NDB, DP_END = DV_END + KS, NSLOT = DP_END + 2 * NDB;
         auto operand = [&](int slot) {
             // the lane addresses of the 8 + 8 operand positions are formed again at every read (one XOR each) instead

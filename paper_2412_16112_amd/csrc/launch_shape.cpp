@@ -85,9 +85,11 @@ F32Shape choose_f32_shape(long long NV, int BH, int n_text, int head_dim, int n_
 // One workgroup fills a CU, so what a call of a few workgroups per CU takes is decided by how evenly they fill the CUs and by the length of
 // the longest.  Waves that share queries halve or quarter a workgroup's walk over its keys and double or quadruple the number
 // of workgroups, at the price of staging every key tile twice or four times; key ranges do the same for the text queries at the price of
-// partial results and a kernel that merges them.  Every combination is priced with the measured cost of a workgroup - a fixed part
-// (dispatch, query rows and first tiles, output), a part per stage (barrier and refill of the pipeline) and a part per 32-key block of
-// the two waves of a SIMD - and the time at which the last CU finishes, longest workgroups first; the cheapest is taken.  (24 heads,
+// partial results and a kernel that merges them.  Every combination is priced with the cost of a workgroup - a fixed part
+// (dispatch, query rows and first tiles, output), a part per stage (barrier and refill of the pipeline) and a part per 32-key block of either of
+// the two waves of a SIMD, fitted to measured calls - and the time at which the last CU finishes, longest workgroups first; the cheapest is
+// taken.  (Over 14 shapes from 1 head of 64 x 64 to 24 of 128 x 128 the predicted cycles are 1.40 to 2.04 times the measured
+// nanoseconds, 1.58 to 1.81 for ten of them; few workgroups at the upper end, where the clock is high, cut tiles at the lower.)  (24 heads,
 // 32 x 32 grid, 512 text tokens, r = 8: 40 -> 32 us against one wave per patch throughout; 2 heads: 36 -> 20 us.)  Beyond 16 workgroups
 // per CU the evenness takes care of itself: one wave per patch, and choose_text_splits.
 ForwardShape choose_forward_shape(const ForwardProblem& fp)
@@ -100,7 +102,7 @@ ForwardShape choose_forward_shape(const ForwardProblem& fp)
         if (n_text > 0) choose_text_splits(NV, BH, text_tiles(1), num_cus, image_wgs <= 64LL * num_cus, &best.n_splits, &best.split_keys);
         return best;
     }
-    // cycles; a SIMD's two waves together take `block` per block of either
+    // cycles; a SIMD takes `block` for every block of its two waves (at 128 channels 512 of them are matrix cycles)
     const double fixed = 16e3, stage = fp.head_dim == 64 ? 1100 : 900, block = fp.head_dim == 64 ? 400 : 520;
     const int stage_keys = bf16_tiles_per_stage(fp.head_dim) * kKeyTileKeys;
     double best_time = 1e300;
