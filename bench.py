@@ -27,7 +27,7 @@ def forward_kernel_sources_digest():
     shows in the bench line instead of going stale silently."""
     import hashlib
     h = hashlib.sha256()
-    for name in ("kernels_bf16.hip", "kernels_bf16_d64.hip", "bf16_common.h", "block_class.h", "clear_internal.h", "schedule.cpp", "clear_attn_api.cpp"):
+    for name in ("kernels_bf16.hip", "kernels_bf16_d64.hip", "bf16_common.h", "block_class.h", "clear_internal.h", "schedule.cpp", "launch_shape.h", "launch_shape.cpp", "clear_attn_api.cpp"):
         with open(os.path.join(ROOT, "paper_2412_16112_amd", "csrc", name), "rb") as f:
             h.update(name.encode() + b"\0" + f.read() + b"\0")
     return h.hexdigest()

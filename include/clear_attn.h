@@ -16,7 +16,7 @@
  * scaling applied is 1/sqrt(head_dim).  Values must be finite.
  *
  * Supported: dtype CLEAR_BF16 with head_dim 128 or 64 (MFMA path; fp32 accumulation, one round-to-nearest
- * -even to bf16 on output) and dtype CLEAR_F32 with head_dim 64 (plain fp32 accuracy path).
+ * -even to bf16 on output) and dtype CLEAR_F32 with head_dim 64 (fp32 matrix instructions: products and sums in fp32).
  * n_text >= 0, gridH, gridW >= 1 (at most 32767 each), r >= 1.  bf16 contexts need N < 2^24 (the kernels address
  * one head with 32-bit byte offsets) and clear_attn_create refuses more with CLEAR_ERR_UNSUPPORTED, as it refuses
  * a tile schedule of more than 2^28 (query tile, key tile) pairs (r close to the grid size on a large grid; the tables of
@@ -94,7 +94,8 @@ int clear_attn_forward(clear_attn_ctx* ctx, const void* Q, const void* K, const 
  * text-query rows go to a static device array of the library (112 MiB per GPU, held until the process ends)
  * instead of the context's workspace.
  * A call whose partial results (B*H * key splits * n_text * (head_dim + 2) floats) do not fit the array returns
- * CLEAR_ERR_UNSUPPORTED with the sizes in clear_attn_last_error, and launches nothing; the FLUX-8K shape (B*H = 24,
+ * CLEAR_ERR_UNSUPPORTED with the sizes in clear_attn_last_error, and launches nothing; the key
+ * splits are chosen to fit where they can (one split is the least).  The FLUX-8K shape (B*H = 24,
  * 16 splits, 512 text tokens, head_dim 128: 102 MB) fits.  The context's device must be the current one.
  * Every call on a GPU, from any context, shares that GPU's array: calls that overlap in time on one GPU race;
  * order them on one stream or with events.  Nothing in the array has to be cleared between calls.
@@ -169,8 +170,9 @@ int clear_attn_executed_pairs(const clear_attn_ctx* ctx, unsigned long long* pai
  *                      _copy) is that of one class, a ceil(gridH / r) x ceil(gridW / r) grid; clear_attn_schedule_
  *                      host_masked returns CLEAR_ERR_UNSUPPORTED for it.
  * Every other entry point takes a square or Swin context unchanged (forward, forward_band, backward, ...); the
- * executed work differs: the square window has precomputed lane masks like the disc; Swin windows run whole or
- * skipped blocks when r and shift are multiples of 8 and the arithmetic element mask otherwise. */
+ * executed work differs.  The forward pass has precomputed lane masks for every kind; Swin windows whose r and shift are multiples of 8
+ * run whole blocks only.  The backward pass has lane masks for the disc, the square window and such Swin windows, and takes the
+ * arithmetic element mask otherwise. */
 typedef enum { CLEAR_MASK_DISC = 0, CLEAR_MASK_SQUARE = 1, CLEAR_MASK_SWIN = 2, CLEAR_MASK_STRIDED = 3 } clear_mask_kind;
 int clear_attn_create_masked(clear_attn_ctx** out, int n_text, int gridH, int gridW, int head_dim, int r,
                              int dtype, int mask_kind, int shift);

@@ -12,7 +12,7 @@
 // queries reach, staged in LDS half a tile at a time and double-buffered.  The waves hold 4, 2 or 1 patches (`groups` = 1,
 // 2, 4 waves per patch): with several waves per patch each takes a share of every tile's cells and the partial softmax sums are joined
 // in LDS at the end, which gives small problems as many workgroups as the chip has CUs and shorter key walks.
-// A 38-head 64 x 64 grid with 333 text tokens, r = 16: 2.98 -> 0.71 ms
+// A 38-head 64 x 64 grid with 333 text tokens, r = 16: 2.98 -> 0.72 ms
 // (74 TFLOP/s of admitted pairs, 110 where nothing is masked; a large fp32 matrix product reaches 154); one head of 16 x 16
 // tokens with 8 text tokens 0.43 ms -> 12 us.  (Before: vector arithmetic, a thread per query, the whole list of every
 // 16 x 16 tile.  A single 32 KB stage per workgroup: 0.73 ms; two whole-tile stages, two workgroups per CU: 1.17 ms.)

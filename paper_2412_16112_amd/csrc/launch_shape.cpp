@@ -132,6 +132,8 @@ ForwardShape choose_forward_shape(const ForwardProblem& fp)
                 // longest first: c1 n1, then c2 n2
                 const bool text_first = c_text > c_image;
                 const double c1 = text_first ? c_text : c_image, c2 = text_first ? c_image : c_text, n1 = text_first ? n_text_wgs : n_image, n2 = text_first ? n_image : n_text_wgs;
+                // (no shape takes less than its longest workgroup, or than its work spread evenly)
+                if ((std::max(c1, (n1 * c1 + n2 * c2) / num_cus) + merge) * (1 - 1e-9) >= best_time * 0.98) continue;
                 const double q = std::floor(n1 / num_cus), r = n1 - q * num_cus;
                 double lo = (q + (r > 0)) * c1, hi = lo + (n2 > 0 ? (std::ceil(n2 / num_cus) + 1) * c2 : 0);
                 auto fits = [&](double t) { return r * std::floor((t - (q + 1) * c1) / c2) + (num_cus - r) * std::floor((t - q * c1) / c2) >= n2; };
