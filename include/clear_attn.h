@@ -94,8 +94,8 @@ int clear_attn_forward(clear_attn_ctx* ctx, const void* Q, const void* K, const 
  * text-query rows go to a static device array of the library (112 MiB per GPU, held until the process ends)
  * instead of the context's workspace.
  * A call whose partial results (B*H * key splits * n_text * (head_dim + 2) floats) do not fit the array returns
- * CLEAR_ERR_UNSUPPORTED with the sizes in clear_attn_last_error, and launches nothing; the key
- * splits are chosen to fit where they can (one split is the least).  The FLUX-8K shape (B*H = 24,
+ * CLEAR_ERR_UNSUPPORTED with the sizes in clear_attn_last_error, and launches nothing (fp32 calls, and bf16
+ * calls of up to 16 image workgroups per CU, take as few splits as it needs to fit); the FLUX-8K shape (B*H = 24,
  * 16 splits, 512 text tokens, head_dim 128: 102 MB) fits.  The context's device must be the current one.
  * Every call on a GPU, from any context, shares that GPU's array: calls that overlap in time on one GPU race;
  * order them on one stream or with events.  Nothing in the array has to be cleared between calls.

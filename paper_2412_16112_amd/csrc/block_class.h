@@ -1,6 +1,5 @@
-// Wave-level classification of a (32-query patch, 32-key block) pair.  Used by the bf16 kernels
-// (device) and by the host-side count of executed pairs, so that the reported "executed" work is
-// exactly what the kernels feed to the matrix pipeline.
+// Classification of a (query patch, key block) pair.  Used by the fp32 and backward kernels (device), by the host code that writes the
+// wave programs of the bf16 forward kernels, and by the count of the pairs that the fp32 kernel executes.
 #pragma once
 #include <hip/hip_runtime.h>
 
