@@ -61,11 +61,12 @@ constexpr unsigned kProgramFlags = kProgramStageEnd | kProgramNoBlock | kProgram
 constexpr unsigned kMaskIdNone = 0;       // every pair of the block is admitted
 constexpr unsigned kMaskIdNothing = 1;    // none is
 constexpr unsigned kMaskIdFirstKeys = 1;  // + k, 1 <= k < 32: the first k keys of the block are
+constexpr int kProgramSpareWords = 128;   // readable words behind the last program: the kernels fetch 64 at a time and read two ahead
 constexpr size_t kMaxProgramWords = 0xffff0000u;  // places among them are 32-bit numbers; more are refused as out of memory
 constexpr unsigned kMaskIdFree = 33;      // masks of image blocks from here on
 constexpr int bf16_tiles_per_stage(int head_dim) { return head_dim == 64 ? 4 : 2; }
 struct BlockPrograms {
-    std::vector<unsigned> words;               // two spare words at the end
+    std::vector<unsigned> words;               // kProgramSpareWords at the end
     std::vector<unsigned> ptr;                 // [variants][n_q_tiles][kBf16NWY * kBf16NWX]: where a wave's program starts
     double mean_stages, mean_steps;            // of a query tile: stages, blocks per wave
     unsigned text_words[3];                    // for 1, 2, 4 waves per patch of text queries: [wave][keys of the stage][blocks per stage / waves]

@@ -285,33 +285,52 @@ __device__ __forceinline__ void clear_fwd_bf16_workgroup(const FwdParams& p, con
     }
 
     // ---- the wave's program.  Image-query rows: its own words.  Text-query rows: every stage but the last takes the same words again.
-    const const_u32_ptr words = (const_u32_ptr)p.program;
+    // Scalar loads return out of order with LDS reads, so that a wait for an operand with one of them in flight waits for it too.  At 64 channels,
+    // where a step is half as long, the words come in with a vector load, one to a lane, 64 at a time, and a step reads its own with
+    // v_readlane (38 heads, 128 x 128: 461 -> 454 us); at 128 the second round trip at the start costs small calls more (32 x 32: 31.8 -> 32.6 us).
+    constexpr bool LANE_WORDS = D == 64;
+    constexpr int STAGE_KEYS = TPS * TILE_KEYS, TAIL = 32;  // (text: lanes from TAIL on hold the last stage's words)
     const const_u64_ptr mask_words = (const_u64_ptr)p.block_masks;
-    constexpr int STAGE_KEYS = TPS * TILE_KEYS;
-    unsigned pc_first, pc, pc_wrap, pc_tail = 0;
-    int whole_left = 0;  // text: stages before the last one
+    const const_u32_ptr words = (const_u32_ptr)p.program;
+    const unsigned per_stage = (unsigned)(BLOCKS_PER_STAGE / groups);
+    unsigned pc_first, pc_tail = 0;            // where the program starts (text: and the words of the last stage)
+    unsigned pc = 0, pc_wrap = ~0u, prog = 0;  // next word; where the text words start again; LANE_WORDS: lane i has word i of this 64
+    const unsigned* next_words = nullptr;      // image, LANE_WORDS: the 64 words after those
+    int whole_left = 0;                        // text: stages before the last one
     if (TEXTQ) {
-        const int per_stage = BLOCKS_PER_STAGE / groups;
-        pc_first = p.text_words + (unsigned)(group * (STAGE_KEYS + 1) * per_stage);
-        pc_tail = pc_first + (unsigned)((lin_limit - lin_begin - (n_stages - 1) * STAGE_KEYS) * per_stage);
+        pc_first = p.text_words + (unsigned)(group * (STAGE_KEYS + 1)) * per_stage;
+        pc_tail = pc_first + (unsigned)(lin_limit - lin_begin - (n_stages - 1) * STAGE_KEYS) * per_stage;
+        if (LANE_WORDS) {
+            prog = p.program[(lane < TAIL ? pc_first : pc_tail) + (lane & (BLOCKS_PER_STAGE - 1))];
+            pc_first = 0;
+            pc_tail = TAIL;
+        }
     } else {
         pc_first = ((const_u32_ptr)p.program_ptr)[((long long)variant * p.n_q_tiles + qt) * NW + wave];
     }
     auto start_program = [&]() {
         pc = pc_first;
-        pc_wrap = ~0u;
         if (TEXTQ) {
             whole_left = n_stages - 1;
             if (whole_left == 0) pc = pc_tail;
-            else pc_wrap = pc_first + BLOCKS_PER_STAGE / groups;
+            pc_wrap = whole_left == 0 ? ~0u : pc_first + per_stage;
+        } else if (LANE_WORDS) {
+            prog = p.program[pc_first + lane];
+            next_words = p.program + pc_first + 64;
+            pc = 0;
         }
     };
     auto word = [&]() -> unsigned {
-        const unsigned w = words[pc++];
+        const unsigned w = LANE_WORDS ? (unsigned)__builtin_amdgcn_readlane((int)prog, (int)(pc & 63)) : words[pc];
+        ++pc;
         if (TEXTQ && pc == pc_wrap) {
             const bool last = --whole_left == 0;
             pc = last ? pc_tail : pc_first;
             pc_wrap = last ? ~0u : pc_wrap;
+        }
+        if (LANE_WORDS && !TEXTQ && (pc & 63) == 0) {
+            prog = next_words[lane];
+            next_words += 64;
         }
         return w;
     };
@@ -492,7 +511,9 @@ __device__ __forceinline__ void clear_fwd_bf16_workgroup(const FwdParams& p, con
                 auto run_slot = [&](auto slot_tag) __attribute__((always_inline)) {
                     constexpr int slot = decltype(slot_tag)::value;
                     op[(slot + PD) % RING] = operand(slot + PD);
-                    SCHED_FENCE();  // (the read stays in front of the matrix instruction, which then waits for older reads only)
+                    // The read stays in front of the matrix instruction, which then waits for older reads only.  (At 64 channels, with twice the vector
+                    // work to a matrix instruction, the order inside a slot is better left to the compiler: 256 heads, 64 x 64, 473 -> 459 us.)
+                    if (D != 64) SCHED_FENCE();
                     constexpr int i = slot >= KS ? slot - KS : 0;
                     if (slot == 0 && id != kMaskIdNone) {
 #pragma unroll

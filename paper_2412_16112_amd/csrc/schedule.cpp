@@ -694,8 +694,7 @@ void build_text_words(int head_dim, BlockPrograms* out)
                 for (; used < per; ++used) out->words.push_back(0);
             }
     }
-    out->words.push_back(0);
-    out->words.push_back(0);
+    out->words.insert(out->words.end(), kProgramSpareWords, 0u);
 }
 
 }  // namespace

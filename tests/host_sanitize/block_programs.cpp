@@ -99,8 +99,8 @@ void check_image_programs(const Shape& sh, const Schedule& s, const std::vector<
                     size_t pc = prog.ptr[((size_t)v * n_q_tiles + qt) * kWaves + g * patches + patch];
                     bool flushed = false;  // the word before masks everything out
                     for (int st = 0; st < n_stages;) {
-                        if (pc + 2 >= prog.words.size()) {  // (two words are read ahead)
-                            EXPECT(pc + 2 < prog.words.size());
+                        if (pc + kProgramSpareWords >= prog.words.size()) {  // (the kernels read ahead)
+                            EXPECT(pc + kProgramSpareWords < prog.words.size());
                             return;
                         }
                         const Word w = decode(prog.words[pc++], tile_units);

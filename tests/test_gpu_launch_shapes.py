@@ -157,6 +157,26 @@ def test_bf16_window_of_the_size_of_the_grid(n_text, gh, gw, r):
     assert mx <= TOL["bf16"][0] and rms <= TOL["bf16"][1], (mx, rms)
 
 
+@pytest.mark.parametrize("n_text", [0, 928, 960, 991, 1024, 1056, 1100, 2975, 3040])
+def test_bf16_64_channel_programs_around_64_words(n_text):
+    """At 64 channels a wave fetches its program 64 words at a time.  A window that holds a 32 x 32 grid is 32 blocks to every wave, each 32 text keys
+    are one more: programs of 63 to 67 and of 125 to 129 words, and of a few."""
+    H, gh, gw, r = 64, 32, 32, 64
+    print(f"[case] H={H} n_text={n_text} grid={gh}x{gw} r={r}", flush=True)
+    Q, K, V = make_qkv_shape(1, H, n_text, gh, gw, 64, "bf16", seed=83, device=DEV)
+    ctx = ca.ClearAttn(n_text, gh, gw, 64, r, ca.CLEAR_BF16)
+    try:
+        O = ctx.forward(Q, K, V)
+        torch.cuda.synchronize()
+    finally:
+        ctx.destroy()
+    rows = _rows(n_text, gh, gw, seed=n_text, n=64)
+    for h in (0, H - 1):
+        ref = orc.attention_rows(*(t[0, h].double().cpu().numpy() for t in (Q, K, V)), rows, n_text, gh, gw, r)
+        mx, rms = error_metrics(O[0, h].float().cpu().numpy()[rows], ref)
+        assert mx <= TOL["bf16"][0] and rms <= TOL["bf16"][1], (h, mx, rms)
+
+
 def test_f32_more_workgroups_than_a_launch_can_have():
     """2 050 heads of a 1 x 32 767 grid are 2^24 workgroups of 256 threads and more, which no single launch can have.  r = 1 without text: a
     token sees itself alone, so O = V."""
