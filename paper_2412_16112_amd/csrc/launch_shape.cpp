@@ -88,8 +88,10 @@ F32Shape choose_f32_shape(long long NV, int BH, int n_text, int head_dim, int n_
 // partial results and a kernel that merges them.  Every combination is priced with the cost of a workgroup - a fixed part
 // (dispatch, query rows and first tiles, output), a part per stage (barrier and refill of the pipeline) and a part per 32-key block of either of
 // the two waves of a SIMD, fitted to measured calls - and the time at which the last CU finishes, longest workgroups first; the cheapest is
-// taken.  (Over 14 shapes from 1 head of 64 x 64 to 24 of 128 x 128 the predicted cycles are 1.40 to 2.04 times the measured
-// nanoseconds, 1.58 to 1.81 for ten of them; few workgroups at the upper end, where the clock is high, cut tiles at the lower.)  (24 heads,
+// taken.  (128 channels, 10 shapes from 1 head of 64 x 64 to 24 of 128 x 128: the predicted cycles are 1.44 to 1.96 times the measured
+// nanoseconds; few workgroups at the upper end, where the clock is high, cut tiles at the lower.  64 channels, fitted to 24 calls in each of their
+// shapes: the picks take 1.4 % more than the fastest on average, with the numbers of 128 channels about 4; 38 heads, 64 x 64, 333 text tokens
+// 127 -> 112 us, 96 x 96 240 -> 235, 24 heads, 128 x 128 271 -> 260.)  (24 heads,
 // 32 x 32 grid, 512 text tokens, r = 8: 40 -> 32 us against one wave per patch throughout; 2 heads: 36 -> 20 us.)  Beyond 16 workgroups
 // per CU the evenness takes care of itself: one wave per patch, and choose_text_splits.
 ForwardShape choose_forward_shape(const ForwardProblem& fp)
@@ -103,7 +105,8 @@ ForwardShape choose_forward_shape(const ForwardProblem& fp)
         return best;
     }
     // cycles; a SIMD takes `block` for every block of its two waves (at 128 channels 512 of them are matrix cycles)
-    const double fixed = 16e3, stage = fp.head_dim == 64 ? 1100 : 900, block = fp.head_dim == 64 ? 400 : 520;
+    const bool d64 = fp.head_dim == 64;
+    const double fixed = d64 ? 12e3 : 16e3, stage = d64 ? 700 : 900, block = d64 ? 480 : 520, in_doubt = d64 ? 0.99 : 0.98;
     const int stage_keys = bf16_tiles_per_stage(fp.head_dim) * kKeyTileKeys;
     double best_time = 1e300;
     for (int gi = 0; gi < 3; ++gi) {
@@ -133,7 +136,7 @@ ForwardShape choose_forward_shape(const ForwardProblem& fp)
                 const bool text_first = c_text > c_image;
                 const double c1 = text_first ? c_text : c_image, c2 = text_first ? c_image : c_text, n1 = text_first ? n_text_wgs : n_image, n2 = text_first ? n_image : n_text_wgs;
                 // (no shape takes less than its longest workgroup, or than its work spread evenly)
-                if ((std::max(c1, (n1 * c1 + n2 * c2) / num_cus) + merge) * (1 - 1e-9) >= best_time * 0.98) continue;
+                if ((std::max(c1, (n1 * c1 + n2 * c2) / num_cus) + merge) * (1 - 1e-9) >= best_time * in_doubt) continue;
                 const double q = std::floor(n1 / num_cus), r = n1 - q * num_cus;
                 double lo = (q + (r > 0)) * c1, hi = lo + (n2 > 0 ? (std::ceil(n2 / num_cus) + 1) * c2 : 0);
                 auto fits = [&](double t) { return r * std::floor((t - (q + 1) * c1) / c2) + (num_cus - r) * std::floor((t - q * c1) / c2) >= n2; };
@@ -143,7 +146,7 @@ ForwardShape choose_forward_shape(const ForwardProblem& fp)
                     (fits(mid) ? hi : lo) = mid;
                 }
                 const double time = hi + merge;
-                if (time < best_time * 0.98) {  // (in doubt the simpler shape)
+                if (time < best_time * in_doubt) {  // (in doubt the simpler shape)
                     best_time = time;
                     best = {1 << gi, tg, real, (int)keys, text_first};
                 }
