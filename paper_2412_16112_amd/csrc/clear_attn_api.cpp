@@ -274,8 +274,10 @@ static hipError_t build_forward_tables(int n_text, int head_dim, int stride, int
     const Schedule& sched = t->sched;
     // With the key tiles in an order that overlapping windows share (order_forward_tiles), the tiles in flight read 8.0 GB past the L2 at a 512 x
     // 512 grid and 24 heads (2 x 16 blocks: 11.3; 21 in neither order); the power saved there is worth 1 % of the time on
-    // a part that runs at its power limit.
-    const std::vector<int> order = stride == 1 ? tile_order(sched, 4, 8) : std::vector<int>();
+    // a part that runs at its power limit.  Up to 10 tile columns 32 consecutive tiles span three rows and more as they are, and the last strip of
+    // an order by blocks would be a narrow one: plain (24 heads, 96 x 160: r = 24, 64 channels 370 us plain, 392 by blocks; r = 16, 128
+    // channels 414 and 427; 144 x 160 632 and 637; from 12 columns on blocks win: 128 x 192, r = 32 1 229 and 1 221, 256 x 256 1 863 and 1 812).
+    const std::vector<int> order = stride == 1 && sched.n_qtx > 10 ? tile_order(sched, 4, 8) : std::vector<int>();
     const int n = stride == 1 && sched.row_ptr.size() - 1 <= kGroupsMaxTiles ? 3 : 1;
     Schedule sub[3];
     QueryTilePatterns pat[3];

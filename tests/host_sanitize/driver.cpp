@@ -286,7 +286,7 @@ static void contexts()
 // grids no wider than a block need none.
 static void tile_orders()
 {
-    const int grids[][2] = {{64, 64}, {144, 160}, {100, 272}, {70, 300}};
+    const int grids[][2] = {{64, 64}, {96, 160}, {144, 176}, {100, 272}, {70, 300}};
     for (const auto& g : grids) {
         const int n_qty = (g[0] + 15) / 16, n_qtx = (g[1] + 15) / 16;
         std::vector<float> buffer(16);
@@ -297,9 +297,9 @@ static void tile_orders()
         EXPECT(clear_attn_forward(ctx, at(0), at(1), at(2), at(3), 1, 24, 0, g[0], g[1], 64, 4, nullptr) == CLEAR_OK);
         EXPECT(clear_attn_backward(ctx, at(0), at(1), at(2), at(3), at(4), (const float*)at(8), at(5), at(6), at(7), 1, 24, 0, g[0], g[1], 64, 4, nullptr) == CLEAR_OK);
         const int* const orders[2] = {fake::forward.groups == 1 ? fake::forward.qt_order : nullptr, fake::backward.qt_order};
-        const int rows[2] = {4, 2}, cols[2] = {8, 16};
+        const int rows[2] = {4, 2}, cols[2] = {8, 16}, widest_plain[2] = {10, 16};
         for (int k = 0; k < 2; ++k) {
-            if (k == 1 || fake::forward.groups == 1) EXPECT((orders[k] != nullptr) == (n_qtx > cols[k]));
+            if (k == 1 || fake::forward.groups == 1) EXPECT((orders[k] != nullptr) == (n_qtx > widest_plain[k]));
             if (!orders[k]) continue;
             std::vector<char> seen((size_t)n_qty * n_qtx, 0);
             for (int i = 0; i < n_qty * n_qtx; ++i) {
