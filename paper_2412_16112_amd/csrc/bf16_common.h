@@ -59,20 +59,6 @@ constexpr int STAGE_BYTES = TPS * 2 * TILE_BYTES;
 constexpr float FAST_SUM_LIMIT = 1.0e30f;  // the fast pass is discarded when a query's sums leave [0, 1e30)
 constexpr float M_INIT = -1.0e30f;         // finite "no key seen yet" (keeps exp2 arguments free of inf - inf)
 
-// LDS layout of a tile as the backward kernels stage it: 64 rows of ROW_BYTES, unpadded (the LDS-direct load writes 1 KB per wave
-// instruction), with the 16-byte chunks of each row permuted: logical chunk c of row k sits in slot
-// c ^ swz(k).
-// 256-byte rows (a row = one sweep over the banks): swz is a bijection on 16 consecutive rows (the 32 key
-// rows of a K read spread over all banks) and sends 4 consecutive rows to 4 different 64-byte quads (so does
-// the transposed V read).
-// 128-byte rows (two rows per sweep): on the even rows of 16 consecutive rows swz is a bijection onto the 8
-// chunks (K read), and rows k and k + 2, which share a half sweep, land in different 64-byte quads (V read).
-// Both have period 16 in the row.
-__host__ __device__ constexpr int swz(int row)
-{
-    return D == 128 ? (((row & 3) << 2) | ((row >> 2) & 3)) : ((((row >> 1) & 1) << 2) | (((row >> 3) & 1) << 1) | ((row >> 2) & 1));
-}
-
 __device__ __forceinline__ float wave_pair_max(float x)
 {
     // lanes l and l ^ 32 hold the two halves of one query's scores
@@ -144,31 +130,6 @@ struct WaveState {
     float c;         // log2(e) / sqrt(head_dim)
 };
 
-// Per-lane LDS read offsets inside a tile as the backward kernels stage it (the forward kernels have a layout of their own).  All operand addresses of a tile derive from two
-// offsets by XOR with small constants and by adding multiples of 4 KB (ds_read immediates):
-//   K operand, block blk, contraction step ks:  ((tile + k0) ^ (ks << 5)) + blk * 32 rows
-//   V operand, block blk, step s2, slice db:    ((tile + v0 [^ V_HI]) ^ (db << 6)) + blk * 32 rows + s2 * 16 rows
-// (tile addresses are multiples of 1 KB, so the XORs stay inside the offsets' own bits).
-struct LaneOffsets {
-    unsigned k0;  // row qi, logical chunk hh:  qi * ROW_BYTES + ((hh ^ swz(qi)) << 4)
-    unsigned v0;  // transpose read, slice 0, first half of the 16-key step
-};
-// second half of the step: key rows + 8 (8 * ROW_BYTES) and what that does to their swizzle (chunk bit 1 either way)
-constexpr unsigned V_HI = (1u << 5) | (unsigned)(8 * ROW_BYTES);
-
-// Lane addresses of one staged tile (LDS byte addresses).
-struct TileAddr {
-    unsigned kb, vb0, vb1;
-};
-__device__ __forceinline__ TileAddr tile_addr(unsigned tile_lds, const LaneOffsets& lo)
-{
-    TileAddr ta;
-    ta.kb = tile_lds + lo.k0;
-    ta.vb0 = tile_lds + lo.v0;
-    ta.vb1 = tile_lds + (lo.v0 ^ V_HI);
-    return ta;
-}
-
 enum MaskMode : int { kMaskNone = 0, kMaskLinear = 1, kMaskImage = 2, kMaskTable = 3 };
 
 // Which family of image masks a kernel instance is compiled for.  The disc of Eq. 3 is the product path and
@@ -194,17 +155,23 @@ struct MaskArgs {
     const_u64_ptr row[2];  // kMaskTable: 16 lane masks per key block (one per score register)
 };
 
+// Lane masks of a block: 16 words, one per score register, kept in scalar registers from the block's S product to its
+// exponentials.
+struct MaskWords {
+    unsigned long long w[16];
+};
+__device__ __forceinline__ void mask_scores(f32x16& s, const MaskWords& mw)
+{
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_inverse_ballot_w64(mw.w[r]) ? s[r] : -INFINITY;
+}
+
 // Sets the scores of inadmissible (query, key) pairs of key block kb to -inf.  Register r of this lane
 // is key slot 8*(r/4) + 4*hh + r%4 of the block (Eq. 3 for image keys; the token limit for linear tiles).
 template <int MASK, int CODE>
 __device__ __forceinline__ void apply_mask(f32x16& s, int kb, const MaskArgs& ma)
 {
-    if (MASK == kMaskTable) {
-        // precomputed per relative block offset: bit l of row[r] says whether lane l keeps score register r
-        const_u64_ptr row = ma.row[kb & 1];  // wave-uniform address: the words are read into scalar registers
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_inverse_ballot_w64(row[r]) ? s[r] : -INFINITY;
-    } else if (MASK == kMaskLinear) {
+    if (MASK == kMaskLinear) {
         const int base = ma.a + 32 * kb + 4 * ma.hh;
 #pragma unroll
         for (int r = 0; r < 16; ++r)
@@ -268,43 +235,45 @@ __device__ __forceinline__ float max_block(const f32x16& s)
 typedef const __attribute__((address_space(3))) bf16x8* lds_bf16x8_ptr;
 typedef __attribute__((address_space(3))) short4v* lds_short4_ptr;
 
-// (extra: a constant byte offset on top, e.g. TILE_BYTES for the second half of a staged tile, so that both halves
-// share the lane's swizzled addresses and differ in the instruction's immediate offset only)
-__device__ __forceinline__ bf16x8 read_k_operand(const TileAddr& ta, int blk, int ks, unsigned extra = 0)
-{
-    return *(lds_bf16x8_ptr)(size_t)((ta.kb ^ (unsigned)(ks << 5)) + (unsigned)(blk * 32 * ROW_BYTES) + extra);
-}
+// LDS layout of a staged tile (64 tokens x D channels): planes of 32 channels (64 bytes), each 64 rows x 64 bytes = 4 KB,
+// filled by 1 KB load instructions of 16 rows x 64 bytes (lane i: slot i % 4 of row i / 4; four neighbouring lanes read 64
+// contiguous bytes).  Inside a row of 64 bytes the 16-byte chunk q sits in slot q ^ plane_swz(row).  Both operand reads
+// are then free of bank conflicts, and their addresses are one of two per-lane offsets plus a constant that fits
+// the instruction: no address arithmetic per operand.
+__device__ __forceinline__ int plane_swz(int row) { return (((row >> 2) & 1) << 1) | ((row >> 3) & 1); }
+constexpr int PLANE_BYTES = TILE_KEYS * 64;
+constexpr int NPLANE = D / 32;
+constexpr int BLOCK_BYTES = 32 * 64;  // from the first 32-token block of a tile to the second, inside every plane
+static_assert(NPLANE * PLANE_BYTES == TILE_BYTES, "a tile is NPLANE planes");
 
-// V^T fragment for the contraction over key slots 16 s2 + 4 hh + {0..3} and 16 s2 + 8 + 4 hh + {0..3} of
-// block blk, channels 32 db .. 32 db + 31: two 16-bit transpose reads.
-__device__ __forceinline__ bf16x8 read_v_operand(const TileAddr& ta, int blk, int s2, int db, unsigned extra = 0)
+// Lane offsets of the two operand reads inside a block: [0] for even contraction steps / the first half of a step's keys, [1] for odd / the second.
+__device__ __forceinline__ unsigned k_lane_offset(int lane, int e)
 {
-    const unsigned imm = (unsigned)(blk * 32 * ROW_BYTES + s2 * 16 * ROW_BYTES) + extra;
-    const short4v lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(size_t)((ta.vb0 ^ (unsigned)(db << 6)) + imm));
-    const short4v hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(size_t)((ta.vb1 ^ (unsigned)(db << 6)) + imm));
+    const int qi = lane & 31, hh = lane >> 5;
+    return (unsigned)((qi >> 4) * 1024 + (qi & 15) * 64 + (((2 * e + hh) ^ plane_swz(qi & 15)) << 4));
+}
+__device__ __forceinline__ unsigned v_lane_offset(int lane, int e)
+{
+    const int j = lane & 15, row = 4 * (lane >> 5) + (j >> 2) + 8 * e;
+    return (unsigned)(row * 64 + (((2 * ((lane >> 4) & 1) + ((j & 3) >> 1)) ^ plane_swz(row)) << 4) + 8 * (j & 1));
+}
+constexpr unsigned K_LANE_ODD = 32, V_LANE_ODD = 512 | 16;  // [1] is [0] with these bits turned over (block addresses are multiples of 1 KB)
+
+// K operand, contraction step ks: chunk 2 ks + hh of key row qi.  `base`: lane offset for even / odd ks + block address.
+// (extra: a constant byte offset on top, e.g. TILE_BYTES for the second tile of a staged pair)
+__device__ __forceinline__ bf16x8 read_k(const unsigned (&base)[2], int ks, unsigned extra = 0)
+{
+    return *(lds_bf16x8_ptr)(size_t)(base[ks & 1] + (unsigned)((ks >> 1) * PLANE_BYTES) + extra);
+}
+// V^T operand for keys 16 s2 + 4 hh + {0..3} and 16 s2 + 8 + 4 hh + {0..3} of the block, channels 32 db .. 32 db + 31: two 16-bit
+// transpose reads.  Within 16 lanes, lane j addresses row j / 4 and channels 4 (j % 4) .. + 3 of the group's 16-channel slice.
+__device__ __forceinline__ bf16x8 read_v(const unsigned (&base)[2], int s2, int db, unsigned extra = 0)
+{
+    const unsigned imm = (unsigned)(db * PLANE_BYTES + s2 * 1024) + extra;
     union { struct { short4v lo, hi; } h; bf16x8 v; } u;
-    u.h.lo = lo4;
-    u.h.hi = hi4;
+    u.h.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(size_t)(base[0] + imm));
+    u.h.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(size_t)(base[1] + imm));
     return u.v;
-}
-
-__device__ __forceinline__ f32x16 qk_block(const TileAddr& ta, int blk, const bf16x8 (&qf)[KS], unsigned extra = 0)
-{
-    f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k_operand(ta, blk, ks, extra), qf[ks], s, 0, 0, 0);
-    return s;
-}
-
-// O^T += V_blk^T P^T for one 32-key block.  The contraction step s2 pairs P registers 8*s2 .. 8*s2+7
-// with key slots 16*s2 + 4*hh + {0..3} and 16*s2 + 8 + 4*hh + {0..3}.
-__device__ __forceinline__ void pv_block(f32x16 (&oacc)[NDB], const TileAddr& ta, int blk, const bf16x8 (&pf)[2], unsigned extra = 0)
-{
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2)
-            oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_v_operand(ta, blk, s2, db, extra), pf[s2], oacc[db], 0, 0, 0);
 }
 
 // Raises a kernel's dynamic-LDS limit once per device (function attributes belong to the device's copy of the

@@ -58,32 +58,6 @@ constexpr int FWD_LDS_BYTES = (NKBUF + NVBUF) * STAGE_HALF;
 constexpr int FLAG_BYTES = 64;  // at the end of the LDS, used between passes only
 constexpr int BLOCKS_PER_STAGE = 2 * TPS;
 
-// LDS layout of a staged tile (64 tokens x D channels): planes of 32 channels (64 bytes), each 64 rows x 64 bytes = 4 KB,
-// filled by 1 KB load instructions of 16 rows x 64 bytes (lane i: slot i % 4 of row i / 4; four neighbouring lanes read 64
-// contiguous bytes).  Inside a row of 64 bytes the 16-byte chunk q sits in slot q ^ plane_swz(row).  Both operand reads
-// are then free of bank conflicts, and their addresses are one of two per-lane offsets plus a constant that fits
-// the instruction: no address arithmetic per operand.
-__device__ __forceinline__ int plane_swz(int row) { return (((row >> 2) & 1) << 1) | ((row >> 3) & 1); }
-constexpr int PLANE_BYTES = TILE_KEYS * 64;
-constexpr int NPLANE = D / 32;
-static_assert(NPLANE * PLANE_BYTES == TILE_BYTES, "a tile is NPLANE planes");
-
-// K operand, contraction step ks: chunk 2 ks + hh of key row qi.  `base`: lane offset for even / odd ks + block address.
-__device__ __forceinline__ bf16x8 read_k(const unsigned (&base)[2], int ks)
-{
-    return *(lds_bf16x8_ptr)(size_t)(base[ks & 1] + (unsigned)((ks >> 1) * PLANE_BYTES));
-}
-// V^T operand for keys 16 s2 + 4 hh + {0..3} and 16 s2 + 8 + 4 hh + {0..3} of the block, channels 32 db .. 32 db + 31: two 16-bit
-// transpose reads.  Within 16 lanes, lane j addresses row j / 4 and channels 4 (j % 4) .. + 3 of the group's 16-channel slice.
-__device__ __forceinline__ bf16x8 read_v(const unsigned (&base)[2], int s2, int db)
-{
-    const unsigned imm = (unsigned)(db * PLANE_BYTES + s2 * 1024);
-    union { struct { short4v lo, hi; } h; bf16x8 v; } u;
-    u.h.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(size_t)(base[0] + imm));
-    u.h.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(size_t)(base[1] + imm));
-    return u.v;
-}
-
 // Reference maximum of the fast pass: a query adopts the maximum of the first block in which it sees an
 // admissible key (nothing has been accumulated for it before, so nothing needs rescaling) and keeps it:
 // all later exponentials are taken relative to it, 2^{(s - m_ref) c}, whatever their size.  Whether that
@@ -91,17 +65,6 @@ __device__ __forceinline__ bf16x8 read_v(const unsigned (&base)[2], int s2, int 
 __device__ __forceinline__ void adopt_reference(WaveState& ws, float mx_pair)
 {
     ws.m_run = (ws.m_run == M_INIT) ? fmaxf(mx_pair, M_INIT) : ws.m_run;
-}
-
-// Lane masks of a block: 16 words, one per score register, kept in scalar registers from the block's S product to its
-// exponentials.
-struct MaskWords {
-    unsigned long long w[16];
-};
-__device__ __forceinline__ void mask_scores(f32x16& s, const MaskWords& mw)
-{
-#pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_inverse_ballot_w64(mw.w[r]) ? s[r] : -INFINITY;
 }
 
 // One workgroup of a forward launch: workgroup `bid` of `nblk` (image-query rows, or with TEXTQ the text-query rows).
@@ -343,9 +306,8 @@ __device__ __forceinline__ void clear_fwd_bf16_workgroup(const FwdParams& p, con
     unsigned k_lane[2], v_lane[2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-        k_lane[e] = lds_base + (unsigned)((qi >> 4) * 1024 + (qi & 15) * 64 + (((2 * e + hh) ^ plane_swz(qi & 15)) << 4));
-        const int j = lane & 15, row = 4 * hh + (j >> 2) + 8 * e;
-        v_lane[e] = lds_base + (unsigned)(NKBUF * STAGE_HALF + row * 64 + (((2 * ((lane >> 4) & 1) + ((j & 3) >> 1)) ^ plane_swz(row)) << 4) + 8 * (j & 1));
+        k_lane[e] = lds_base + k_lane_offset(lane, e);
+        v_lane[e] = lds_base + (unsigned)(NKBUF * STAGE_HALF) + v_lane_offset(lane, e);
     }
     auto block_offset = [](unsigned w) { return (w & kProgramPlaceMask) << 11; };
     auto mask_id = [](unsigned w) { return (w & ~kProgramFlags) >> kProgramMaskShift; };

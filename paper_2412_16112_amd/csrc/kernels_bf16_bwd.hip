@@ -5,59 +5,36 @@
 //   dp_ij = dO_i . v_j,        ds_ij = p_ij (dp_ij - delta_i):
 //   dQ_i = sum_j ds_ij k_j / sqrt(d),   dK_j = sum_i ds_ij q_i / sqrt(d),   dV_j = sum_i p_ij dO_i.
 //
-// One kernel template computes any of the three.  Its "rows" are the tokens whose gradient a workgroup
+// One kernel template computes either half.  Its "rows" are the tokens whose gradient a workgroup
 // produces (queries for dQ, keys for dK and dV), held one per lane as MFMA B operands like Q in the forward
 // kernel; its "columns" are the tokens summed over, staged in LDS tiles exactly like K and V in the forward
-// kernel, taken from the same tile schedule (the mask is symmetric, so the key tiles a query tile reaches
+// kernel, in tiles of 64 (the mask is symmetric, so the key tiles a query tile reaches
 // are also the query tiles that reach a key tile at its place):
-//   mode  rows      column tiles (C1 | C2)   S = C1 r1^T   dP = C2 r2^T   X    accumulator += T^T X
-//   dQ    queries   K | V                    K q^T         V dO^T         dS   K^T dS
-//   dK    keys      Q | dO                   Q k^T         dO v^T         dS   Q^T dS
-//   dV    keys      Q | dO                   Q k^T         -              P    dO^T P
-//   dK+dV keys      Q | dO                   Q k^T         dO v^T         both of the above from one S (image rows)
+//   mode   rows      column tiles (C1 | C2)   S = C1 r1^T   dP = C2 r2^T   accumulators
+//   dQ     queries   K | V                    K q^T         V dO^T         dQ += K^T dS
+//   dK+dV  keys      Q | dO                   Q k^T         dO v^T         dK += Q^T dS, dV += dO^T P, from one S and one dP
 // lse and delta belong to the query: a per-lane scalar for dQ, a per-column vector (staged next to the tile)
 // for dK and dV.  Text rows sum over every token: they are split along the columns into partial sums that a
-// small kernel adds up, like the text-query rows of the forward pass.  dK and dV of a key tile are produced
-// by one pass from one S and one dP (the separate modes remain for reference).  The blocks are hand-ordered
-// pipelines like the forward kernel's tiles: do_block_q for dQ, do_block_kv for dK + dV at head_dim 64 and
-// do_block_kv_early at head_dim 128 (do_block, the compiler's order, serves the separate dK and dV modes).
+// small kernel adds up, like the text-query rows of the forward pass.
 // delta is formed by the dQ kernels on their way when they run before the dK / dV kernels (BwdParams::delta_out),
 // otherwise by clear_bwd_delta_kernel.
+//
+// What bounds it: a 32 x 32 block is 24 (dQ) or 32 (dK + dV) matrix instructions of 32 cycles, each of which holds the SIMD's vector issue
+// port for about 20 of them, and the vector work of the block fits into the rest only if it is spread evenly and is little:
+// an operand's address is one of two lane offsets plus an immediate (planes, as in the forward kernel; rows of
+// 256 bytes took an XOR per operand), lse and delta go in as the initial accumulators of S and dP instead of 32 subtractions, blocks that are
+// admitted whole take no mask, and P and dS are formed under the matrix instructions of the products between.
+// 24 heads of 128 channels, 512 text tokens, 64 x 64 grid, r = 16, forward and backward: 544 -> 508 us; 128 x 128, 333 text tokens: 1 934 -> 1 809 us;
+// 38 heads of 64 channels, 64 x 64: 476 -> 443 us.
 #include <hip/hip_runtime.h>
 
 #include "bf16_common.h"
 #include "block_class.h"
 #include "clear_internal.h"
 
-#ifndef CLEAR_BWD_FUSED_KV
-#define CLEAR_BWD_FUSED_KV 1
-#endif
-#ifndef CLEAR_BWD_PIPELINED_KV
-#define CLEAR_BWD_PIPELINED_KV (CLEAR_HEAD_DIM == 64 ? 1 : 2)  // dK + dV blocks: 1 = do_block_kv, 2 = do_block_kv_early, 0 = do_block (the compiler's order)
-#endif
 #ifndef CLEAR_BWD_ISSUE_SHARE
 #define CLEAR_BWD_ISSUE_SHARE 2  // 2: the waves stage whole stages in turns, half of them each time; 1: every wave its share of every stage
 #endif
-#ifndef CLEAR_BWD_KV_FRESH_ADDR
-#define CLEAR_BWD_KV_FRESH_ADDR 1  // do_block_kv_early: operand addresses formed at every read (0: sixteen registers hold them; spills)
-#endif
-#ifndef CLEAR_BWD_KV_RING_SLACK
-#define CLEAR_BWD_KV_RING_SLACK 1  // do_block_kv_early: entries of the operand ring beyond the prefetch distance
-#endif
-#ifndef CLEAR_BWD_KV_OPERAND_PREFETCH
-#define CLEAR_BWD_KV_OPERAND_PREFETCH 2  // slots between an LDS operand read and the matrix instruction that takes it (3, 4: spills, slower)
-#endif
-// do_block at 128 channels (only reached with CLEAR_BWD_PIPELINED_KV = 0): form the probabilities and round them to
-// bf16 before the dP products, and take dS from those rounded values, which then carries the rounding of P that dV's
-// operand has anyway.  do_block_kv_early does the same: with the fp32 scores dead that early the block fits the 256
-// registers of two waves per SIMD.
-#ifndef CLEAR_BWD_KV_EARLY_P
-#define CLEAR_BWD_KV_EARLY_P (CLEAR_HEAD_DIM == 128)
-#endif
-#ifndef CLEAR_BWD_PIPELINED_Q
-#define CLEAR_BWD_PIPELINED_Q 1  // dQ blocks as a hand-ordered pipeline (0: the compiler's order, as for dK and dV)
-#endif
-
 #if CLEAR_HEAD_DIM == 64
 // second compilation of this file: its own kernel and launcher names
 #define clear_bwd_bf16_kernel clear_bwd_bf16_d64_kernel
@@ -74,7 +51,8 @@ namespace {
 
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 
-enum BwdMode : int { kBwdQ = 0, kBwdK = 1, kBwdV = 2, kBwdKV = 3 };
+enum BwdMode : int { kBwdQ = 0, kBwdKV = 1 };
+enum BwdPart : int { kPartQ = 0, kPartK = 1, kPartV = 2 };  // partial sums of the text rows, in this order in the workspace
 
 constexpr int STATS_BYTES = TILE_KEYS * 2 * 4;                           // per staged tile: lse2 and delta of its 64 columns
 constexpr int BWD_LDS_BYTES = NBUF * STAGE_BYTES + NBUF * TPS * STATS_BYTES;
@@ -84,7 +62,6 @@ template <int MODE, bool LINROWS, int CODE>
 __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, const int bid, const int nblk)
 {
     constexpr int NWY = kBf16NWY, NWX = kBf16NWX, NW = NWY * NWX;
-    constexpr int NI = TILE_KEYS / ROWS_PER_LOAD / NW;  // 1 KB load instructions per wave per tile, for each of the two tiles
     constexpr int ISSUE_SHARE = CLEAR_BWD_ISSUE_SHARE;  // 2: the waves take turns, half of them staging a whole stage
     constexpr bool COLSTAT = MODE != kBwdQ;  // lse / delta indexed by column
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];  // [NBUF][TPS][C1 tile | C2 tile], then the column statistics
@@ -191,13 +168,13 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
         r1f[s] = *(const bf16x8*)(R1 + (long long)r_token * r1s.sn + 8 * hh + 16 * s);
-        if (MODE != kBwdV) r2f[s] = *(const bf16x8*)(R2 + (long long)r_token * r2s.sn + 8 * hh + 16 * s);
+        r2f[s] = *(const bf16x8*)(R2 + (long long)r_token * r2s.sn + 8 * hh + 16 * s);
     }
-    // lse in units of log2 (the exponentials are 2^x); dQ: this lane's query
-    constexpr float LOG2E = 1.4426950408889634f;
-    float lse2_row = 0.f, delta_row = 0.f;
+    // dQ: lse and delta of this lane's query
+    const float neg_inv_scale = -1.0f / p.scale;
+    float lse_row = 0.f, delta_row = 0.f;
     if (!COLSTAT) {
-        lse2_row = lse[r_token] * LOG2E;
+        lse_row = lse[r_token];
         if (p.delta_out) {
             // delta of this lane's row from the dO fragments it holds and the matching pieces of its O row; the other half
             // of the row's channels sits 32 lanes away
@@ -219,9 +196,9 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
         asm volatile("" : "+v"(r1f[s]));
-        if (MODE != kBwdV) asm volatile("" : "+v"(r2f[s]));
+        asm volatile("" : "+v"(r2f[s]));
     }
-    asm volatile("" : "+v"(lse2_row), "+v"(delta_row));
+    asm volatile("" : "+v"(lse_row), "+v"(delta_row));
 
     const const_int_ptr row_ptr = (const_int_ptr)p.row_ptr, col_idx = (const_int_ptr)p.col_idx, n_plain = (const_int_ptr)p.n_plain;
     const const_u64_ptr mask_tbl = (const_u64_ptr)p.mask_tbl;
@@ -270,6 +247,8 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
     // ---- staging: LDS-direct loads of the two column tiles (same layout and swizzle as K and V in the
     // forward kernel), and for dK / dV the statistics of the tile's 64 queries (wave j of the first TPS waves
     // fetches them for tile j of the stage and writes them to LDS before the next barrier)
+    // A staging wave takes 16 rows of both tiles, all their planes: one token address per tile (half of the rows in turn if the waves do not share).
+    static_assert(NW / ISSUE_SHARE == TILE_KEYS / 16, "the waves that stage a tile cover its rows");
     auto issue_tile = [&](int i, unsigned lds_tile) {
         int a, b;
         tile_origin(i, a, b);
@@ -277,15 +256,16 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
         // since the kernel's start get spilled in the fused dK / dV kernel, and their reload from scratch memory would
         // wait for every load issued before it, the staged tile in front included.
         const int ln = fresh_lane_id();
-#pragma unroll
-        for (int n = 0; n < NI * ISSUE_SHARE; ++n) {
-            const int ii = (wave % (NW / ISSUE_SHARE)) * (NI * ISSUE_SHARE) + n;
-            const int row = ROWS_PER_LOAD * ii + ln / CHUNKS;
-            const int token = slot_token(a, b, row);
-            const unsigned chunk_off = (unsigned)(((ln % CHUNKS) ^ swz(row)) << 4);
-            load_to_lds_16B(C1, (unsigned)token * c1_pitch + chunk_off, lds_tile + ii * 1024);
-            load_to_lds_16B(C2, (unsigned)token * c2_pitch + chunk_off, lds_tile + TILE_BYTES + ii * 1024);
-        }
+        const int part = wave % (NW / ISSUE_SHARE), row = 16 * part + (ln >> 2);
+        const unsigned token = (unsigned)slot_token(a, b, row);
+        const unsigned chunk_off = (unsigned)(((ln & 3) ^ plane_swz(row)) << 4);
+        const unsigned o1 = token * c1_pitch + chunk_off, o2 = token * c2_pitch + chunk_off;
+        auto load_plane = [&](auto pl_tag) __attribute__((always_inline)) {
+            constexpr int pl = decltype(pl_tag)::value;
+            load_to_lds_16B(C1, o1 + pl * 64, lds_tile + pl * PLANE_BYTES + part * 1024);
+            load_to_lds_16B(C2, o2 + pl * 64, lds_tile + TILE_BYTES + pl * PLANE_BYTES + part * 1024);
+        };
+        static_for<NPLANE>(load_plane);
     };
     float st_lse = 0.f, st_delta = 0.f;  // in flight: statistics of slot `lane` of tile `wave` of the next stage
     // Half of the waves stage a whole stage, the other half the next one (each SIMD holds one wave of either half): while
@@ -310,22 +290,15 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
         if (COLSTAT && wave < len) {
             float* dst = stats + ((buf * TPS + wave) * 2) * TILE_KEYS;
             const int ln = fresh_lane_id();
-            dst[ln] = st_lse * LOG2E;
-            dst[TILE_KEYS + ln] = st_delta;
+            dst[ln] = st_lse * neg_inv_scale;
+            dst[TILE_KEYS + ln] = -st_delta;
         }
     };
 
-    LaneOffsets lo;
-    lo.k0 = (unsigned)(qi * ROW_BYTES + ((hh ^ swz(qi)) << 4));
-    {
-        const int j = lane & 15, g2 = (lane >> 4) & 1;
-        const int row = 4 * hh + (j >> 2);
-        const int chunk = 2 * g2 + ((j & 3) >> 1);
-        lo.v0 = (unsigned)(row * ROW_BYTES + ((chunk ^ swz(row)) << 4) + 8 * (j & 1));
-    }
+    const unsigned k_lane = lds_base + k_lane_offset(lane, 0), v_lane = lds_base + v_lane_offset(lane, 0);
 
     f32x16 acc[NDB];  // gradient^T tiles: channel 32 db + 8 (reg / 4) + 4 hh + reg % 4 of this lane's row
-    f32x16 acc_v[MODE == kBwdKV ? NDB : 1];  // fused mode: acc holds dK, acc_v holds dV
+    f32x16 acc_v[MODE == kBwdKV ? NDB : 1];  // keys: acc holds dK, acc_v holds dV
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -335,250 +308,119 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
         }
     const float c = p.scale_log2e;
 
-    // One 32-column block of a staged tile.
-    auto do_block = [&](auto mask_tag, unsigned tile_lds, int blk, const MaskArgs& ma, const float* tile_stats) __attribute__((always_inline)) {
-        constexpr int MASK = decltype(mask_tag)::value;
-        // C1 is read row-wise for the scores and (dQ, dK) transposed for the accumulation; C2, TILE_BYTES further on
-        // in the staged tile, through the same lane addresses and an immediate offset
-        const TileAddr ta = tile_addr(tile_lds, lo);
-        constexpr unsigned kTransposedHalf = MODE == kBwdV ? TILE_BYTES : 0;  // the tile read transposed for the accumulation
-        f32x16 s = qk_block(ta, blk, r1f);
-        apply_mask<MASK, CODE>(s, blk, ma);
-        bf16x8 xf[2];
-        if (MODE == kBwdV) {
+    // Both products that make P and dS start from what would be subtracted from them: S from -lse / scale and dP from -delta, so that
+    // P = 2^(S c) and dS = P dP with no subtraction per pair.  dQ: lse and delta are the lane's own; keys: four 16-byte reads each.
+    f32x16 s_init, dp_init;
+    if (!COLSTAT) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float l2 = COLSTAT ? tile_stats[32 * blk + 8 * (r >> 2) + 4 * hh + (r & 3)] : lse2_row;
-                xf[r >> 3][r & 7] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -l2));
-            }
-        } else if constexpr (MODE == kBwdKV && CLEAR_BWD_KV_EARLY_P) {
-            // The probabilities first, rounded to bf16 (they are the operand of the dV product anyway), so that the
-            // fp32 scores are dead before dP is formed: eight registers less at the block's peak.
-            bf16x8 pf[2];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float l2 = COLSTAT ? tile_stats[32 * blk + 8 * (r >> 2) + 4 * hh + (r & 3)] : lse2_row;
-                pf[r >> 3][r & 7] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -l2));
-            }
-            asm volatile("" : "+v"(pf[0]), "+v"(pf[1]));  // (keeps the conversion in front of the dP products)
-            const f32x16 dp = qk_block(ta, blk, r2f, TILE_BYTES);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float dl = COLSTAT ? tile_stats[TILE_KEYS + 32 * blk + 8 * (r >> 2) + 4 * hh + (r & 3)] : delta_row;
-                xf[r >> 3][r & 7] = (__bf16)((float)pf[r >> 3][r & 7] * (dp[r] - dl));
-            }
-            pv_block(acc_v, ta, blk, pf, TILE_BYTES);
-        } else {
-            const f32x16 dp = qk_block(ta, blk, r2f, TILE_BYTES);
-            bf16x8 pf[2];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int slot = 32 * blk + 8 * (r >> 2) + 4 * hh + (r & 3);
-                const float l2 = COLSTAT ? tile_stats[slot] : lse2_row;
-                const float dl = COLSTAT ? tile_stats[TILE_KEYS + slot] : delta_row;
-                const float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -l2));
-                if constexpr (MODE == kBwdKV) pf[r >> 3][r & 7] = (__bf16)pr;
-                xf[r >> 3][r & 7] = (__bf16)(pr * (dp[r] - dl));
-            }
-            if constexpr (MODE == kBwdKV) {
-                // dV += dO^T P from the same probabilities (the dO tile read transposed)
-                pv_block(acc_v, ta, blk, pf, TILE_BYTES);
-            }
+        for (int r = 0; r < 16; ++r) {
+            s_init[r] = lse_row * neg_inv_scale;
+            dp_init[r] = -delta_row;
         }
-        pv_block(acc, ta, blk, xf, kTransposedHalf);
+        asm volatile("" : "+v"(s_init), "+v"(dp_init));
+    }
+    struct Block {
+        unsigned kb[2], vb[2];   // operand addresses of its tile pair
+        const float* stats;      // of its tile
+        bool masked;             // kMaskTable: whether the lane masks admit less than everything
+        MaskArgs ma;
     };
 
-    // The same block for dQ (lse and delta are the lane's own scalars, 64 accumulator registers: there is room)
-    // as a hand-ordered pipeline in the manner of the forward kernel: 2 KS + 2 NDB matrix instructions in
-    // program order, each LDS operand read two slots ahead of the instruction that consumes it,
-    //   slots [0, KS)        S = K q^T
-    //   slots [KS, 2 KS)     dP = V dO^T            | mask, P = 2^(S c - lse) of the finished S
-    //   slots [2 KS, end)    dQ^T += K^T dS^T       | dS = P (dP - delta) first, in slot 2 KS
-    auto do_block_q = [&](auto mask_tag, unsigned tile_lds, int blk, const MaskArgs& ma) __attribute__((always_inline)) {
-        constexpr int MASK = decltype(mask_tag)::value;
-        const TileAddr ta = tile_addr(tile_lds, lo);
-        constexpr int S_END = KS, DP_END = 2 * KS, NSLOT = 2 * KS + 2 * NDB;
+    // One 32-column block as a hand-ordered pipeline in the manner of the forward kernel: matrix instructions in program order, each LDS
+    // operand read PD slots ahead of the instruction that takes it; two slots after a product's last instruction its results can be
+    // read without a wait, and from there the vector work is dealt out two scores at a time:
+    //   dQ:   slots [0, KS)    S = K q^T            keys:  slots [0, KS)    S = Q k^T
+    //         next KS          dP = V dO^T                 next KS          dP = dO v^T
+    //                                                      next 2 NDB       dV^T += dO^T P^T
+    //         last 2 NDB       dQ^T += K^T dS^T            last 2 NDB       dK^T += Q^T dS^T
+    // Keys at 128 channels: dS is taken from the probabilities as rounded to bf16 for the dV product, so that the fp32 ones need not live beside
+    // dP (255 of 256 registers as it is).
+    auto do_block = [&](auto mask_tag, auto blk_tag, const Block& b) __attribute__((always_inline)) {
+        constexpr int MASK = decltype(mask_tag)::value, blk = decltype(blk_tag)::value;
+        constexpr bool KV = MODE == kBwdKV, ROUNDED_P = KV && D == 128;
+        constexpr int S_END = KS, DP_END = 2 * KS, DV_END = DP_END + (KV ? 2 * NDB : 0), NSLOT = DV_END + 2 * NDB;
+        constexpr unsigned AT = blk * BLOCK_BYTES;
         auto operand = [&](int slot) {
-            if (slot < S_END) return read_k_operand(ta, blk, slot);
-            if (slot < DP_END) return read_k_operand(ta, blk, slot - S_END, TILE_BYTES);
-            const int i = slot - DP_END;  // s2-major, so that consecutive instructions write different accumulators
-            return read_v_operand(ta, blk, i / NDB, i % NDB);
+            if (slot < S_END) return read_k(b.kb, slot, AT);
+            if (slot < DP_END) return read_k(b.kb, slot - S_END, AT + TILE_BYTES);
+            if (slot < DV_END) return read_v(b.vb, (slot - DP_END) / NDB, (slot - DP_END) % NDB, AT + TILE_BYTES);  // (consecutive instructions write different accumulators)
+            return read_v(b.vb, (slot - DV_END) / NDB, (slot - DV_END) % NDB, AT);
         };
-        constexpr int PD = 2, RING = PD + 2;
+        constexpr int PD = 2, RING = KV && D == 128 ? PD + 1 : PD + 2;
         bf16x8 op[RING];
+        const float* const st = b.stats + 32 * blk + 4 * (fresh_lane_id() >> 5);  // statistics of this lane's 16 columns: 4 groups of 4
+        auto column_stats = [&](int offset) __attribute__((always_inline)) {
+            f32x16 v;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const f32x4 w = *(const f32x4*)(st + offset + 8 * g);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[4 * g + u] = w[u];
+            }
+            return v;
+        };
+        f32x16 sc = COLSTAT ? column_stats(0) : s_init, dp = dp_init;
 #pragma unroll
         for (int i = 0; i < PD; ++i) op[i] = operand(i);
-        const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        f32x16 sc = zero, dp = zero;
-        bf16x8 xf[2];
-        auto run_slot = [&](auto slot_tag) __attribute__((always_inline)) {
-            constexpr int slot = decltype(slot_tag)::value;
-            if (slot + PD < NSLOT) op[(slot + PD) % RING] = operand(slot + PD);
-            if (slot == DP_END) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) xf[r >> 3][r & 7] = (__bf16)(sc[r] * (dp[r] - delta_row));
-            }
-            if (slot < S_END)
-                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], r1f[slot], sc, 0, 0, 0);
-            else if (slot < DP_END)
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], r2f[slot - S_END], dp, 0, 0, 0);
-            else {
-                constexpr int i = slot >= DP_END ? slot - DP_END : 0;
-                acc[i % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], xf[i / NDB], acc[i % NDB], 0, 0, 0);
-            }
-            if (slot == S_END) apply_mask<MASK, CODE>(sc, blk, ma);
-            // the exponentials of the finished scores, 16 / KS per slot under the dP products
-            constexpr int EPS = 16 / KS;
-            if (slot >= S_END && slot < DP_END) {
-#pragma unroll
-                for (int e = 0; e < EPS; ++e) {
-                    const int r = (slot - S_END) * EPS + e;
-                    sc[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r], c, -lse2_row));
-                }
-            }
-            SCHED_FENCE();
-        };
-        static_for<NSLOT>(run_slot);
-    };
-
-    // The fused dK + dV block in the same manner, 2 KS + 4 NDB matrix instructions.  Used at head_dim 64; at 128
-    // channels fp32 scores, dP and an operand ring do not fit the registers together (see do_block_kv_early).
-    //   slots [0, KS)            S = Q k^T
-    //   slots [KS, 2 KS)         dP = dO v^T          | mask, P = 2^(S c - lse) of the finished S
-    //   next 2 NDB slots         dV^T += dO^T P^T     | dS = P (dP - delta)
-    //   last 2 NDB slots         dK^T += Q^T dS^T
-    auto do_block_kv = [&](auto mask_tag, unsigned tile_lds, int blk, const MaskArgs& ma, const float* tile_stats) __attribute__((always_inline)) {
-        constexpr int MASK = decltype(mask_tag)::value;
-        const TileAddr ta = tile_addr(tile_lds, lo);
-        constexpr int S_END = KS, DP_END = 2 * KS, DV_END = DP_END + 2 * NDB, NSLOT = DV_END + 2 * NDB;
-        auto operand = [&](int slot) {
-            if (slot < S_END) return read_k_operand(ta, blk, slot);
-            if (slot < DP_END) return read_k_operand(ta, blk, slot - S_END, TILE_BYTES);
-            if (slot < DV_END) return read_v_operand(ta, blk, (slot - DP_END) / NDB, (slot - DP_END) % NDB, TILE_BYTES);
-            return read_v_operand(ta, blk, (slot - DV_END) / NDB, (slot - DV_END) % NDB);
-        };
-        constexpr int PD = CLEAR_BWD_KV_OPERAND_PREFETCH, RING = PD + 2;
-        bf16x8 op[RING];
-#pragma unroll
-        for (int i = 0; i < PD; ++i) op[i] = operand(i);
-        const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        f32x16 sc = zero, dp = zero;
         bf16x8 pf[2], xf[2];
-        const float* const st = tile_stats + 32 * blk + 4 * hh;  // statistics of this lane's 16 columns: 4 groups of 4
-        constexpr int GS = KS / 4;  // slots per group of four columns under the dP products
-        static_assert(KS % 4 == 0 && 2 * NDB >= 4, "four column groups are spread over the dP slots and the first dV slots");
+        MaskWords mw;
+        auto p_pair = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+            for (int r = 2 * i; r < 2 * i + 2; ++r) {
+                sc[r] = __builtin_amdgcn_exp2f(sc[r] * c);
+                if (KV) pf[r >> 3][r & 7] = (__bf16)sc[r];
+            }
+        };
+        auto ds_pair = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+            for (int r = 2 * i; r < 2 * i + 2; ++r) {
+                float pr = sc[r];
+                if (ROUNDED_P) {  // back from the packed operand registers: an even element is the low half of its word
+                    const unsigned w = __builtin_bit_cast(u32x4, pf[r >> 3])[(r & 7) >> 1];
+                    pr = __builtin_bit_cast(float, (r & 1) ? (w & 0xffff0000u) : (w << 16));
+                }
+                xf[r >> 3][r & 7] = (__bf16)(pr * dp[r]);
+            }
+        };
         auto run_slot = [&](auto slot_tag) __attribute__((always_inline)) {
             constexpr int slot = decltype(slot_tag)::value;
             if (slot + PD < NSLOT) op[(slot + PD) % RING] = operand(slot + PD);
+            if (MASK == kMaskTable && slot == 0 && b.masked) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) mw.w[r] = b.ma.row[blk][r];
+            }
+            if (COLSTAT && slot == S_END - 2) dp = column_stats(TILE_KEYS);
+            if (!KV && slot == DP_END) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) ds_pair(i);
+            }
             if (slot < S_END)
                 sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], r1f[slot], sc, 0, 0, 0);
             else if (slot < DP_END)
                 dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], r2f[slot - S_END], dp, 0, 0, 0);
             else if (slot < DV_END) {
                 constexpr int i = slot >= DP_END && slot < DV_END ? slot - DP_END : 0;
-                acc_v[i % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], pf[i / NDB], acc_v[i % NDB], 0, 0, 0);
+                if constexpr (KV) acc_v[i % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], pf[i / NDB], acc_v[i % NDB], 0, 0, 0);
             } else {
                 constexpr int i = slot >= DV_END ? slot - DV_END : 0;
                 acc[i % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], xf[i / NDB], acc[i % NDB], 0, 0, 0);
             }
-            if (slot == S_END) apply_mask<MASK, CODE>(sc, blk, ma);
-            // P under the dP products: one group of four columns (one 16-byte read of their lse) every GS slots
-            if (slot >= S_END && slot < DP_END && (slot - S_END) % GS == 0) {
-                constexpr int g = slot >= S_END ? (slot - S_END) / GS : 0;
-                const f32x4 l2 = *(const f32x4*)(st + 8 * g);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) sc[4 * g + u] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[4 * g + u], c, -l2[u]));
-                if (g == 1 || g == 3) {
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) pf[g >> 1][u] = (__bf16)sc[8 * (g >> 1) + u];
+            constexpr int WAIT = KS == 8 ? 2 : 1;
+            if (slot == S_END + WAIT) {
+                if (MASK == kMaskTable) {
+                    if (b.masked) mask_scores(sc, mw);
+                } else {
+                    apply_mask<MASK, CODE>(sc, blk, b.ma);
                 }
             }
-            // dS under the dV products, a group of four columns per slot from the second one on
-            if (slot > DP_END && slot <= DP_END + 4) {
-                constexpr int g = slot > DP_END ? slot - DP_END - 1 : 0;
-                const f32x4 dl = *(const f32x4*)(st + TILE_KEYS + 8 * g);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) xf[g >> 1][4 * (g & 1) + u] = (__bf16)(sc[4 * g + u] * (dp[4 * g + u] - dl[u]));
+            for (int i = 0; i < 8; ++i) {
+                // (dQ: all of P is due before the dS products, so it is done KS / 8 slots earlier per pair)
+                if (slot == S_END + WAIT + (KV ? i * KS / 8 : i * (KS - WAIT) / 8)) p_pair(i);
+                if (KV && slot == DP_END + WAIT + (KS == 8 && i > 0 ? 1 : 0) + i * KS / 8) ds_pair(i);
             }
             SCHED_FENCE();
         };
-        static_for<NSLOT>(run_slot);
-    };
-
-    // The same products for 128 channels, where the registers do not hold fp32 scores and dP together with the
-    // operand ring: the probabilities are rounded to bf16 as soon as the scores are complete (see
-    // CLEAR_BWD_KV_EARLY_P), dV follows at once, and dS then takes the place of P in the same registers,
-    //   slots [0, KS)            S = Q k^T
-    //   next 2 NDB slots         dV^T += dO^T P^T     | first half of P before them, second half under the first NDB
-    //   next KS slots            dP = dO v^T
-    //   last 2 NDB slots         dK^T += Q^T dS^T     | dS = P (dP - delta) likewise, over P
-    auto do_block_kv_early = [&](auto mask_tag, unsigned tile_lds, int blk, const MaskArgs& ma, const float* tile_stats) __attribute__((always_inline)) {
-        constexpr int MASK = decltype(mask_tag)::value;
-        TileAddr ta = tile_addr(tile_lds, lo);
-        constexpr int S_END = KS, DV_END = S_END + 2 * NDB, DP_END = DV_END + KS, NSLOT = DP_END + 2 * NDB;
-        auto operand = [&](int slot) {
-            // the lane addresses of the 8 + 8 operand positions are formed again at every read (one XOR each) instead
-            // of living in sixteen registers through the loop
-            if (CLEAR_BWD_KV_FRESH_ADDR) asm volatile("" : "+v"(ta.kb), "+v"(ta.vb0), "+v"(ta.vb1));
-            if (slot < S_END) return read_k_operand(ta, blk, slot);
-            if (slot < DV_END) return read_v_operand(ta, blk, (slot - S_END) / NDB, (slot - S_END) % NDB, TILE_BYTES);
-            if (slot < DP_END) return read_k_operand(ta, blk, slot - DV_END, TILE_BYTES);
-            return read_v_operand(ta, blk, (slot - DP_END) / NDB, (slot - DP_END) % NDB);
-        };
-        constexpr int PD = CLEAR_BWD_KV_OPERAND_PREFETCH, RING = PD + CLEAR_BWD_KV_RING_SLACK;
-        bf16x8 op[RING];
-#pragma unroll
-        for (int i = 0; i < PD; ++i) op[i] = operand(i);
-        const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        f32x16 sc = zero, dp = zero;
-        bf16x8 pf[2];  // P, then dS
-        const float* const st = tile_stats + 32 * blk + 4 * (fresh_lane_id() >> 5);  // statistics of this lane's 16 columns: 4 groups of 4
-        auto p_group = [&](int g) __attribute__((always_inline)) {
-            const f32x4 l2 = *(const f32x4*)(st + 8 * g);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) pf[g >> 1][4 * (g & 1) + u] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[4 * g + u], c, -l2[u]));
-        };
-        auto ds_group = [&](int g) __attribute__((always_inline)) {
-            const f32x4 dl = *(const f32x4*)(st + TILE_KEYS + 8 * g);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                // P back from the packed operand registers: an even element is the low half of its word
-                const unsigned w = __builtin_bit_cast(u32x4, pf[g >> 1])[2 * (g & 1) + (u >> 1)];
-                const float pr = __builtin_bit_cast(float, (u & 1) ? (w & 0xffff0000u) : (w << 16));
-                pf[g >> 1][4 * (g & 1) + u] = (__bf16)(pr * (dp[4 * g + u] - dl[u]));
-            }
-        };
-        auto run_slot = [&](auto slot_tag) __attribute__((always_inline)) {
-            constexpr int slot = decltype(slot_tag)::value;
-            if (slot + PD < NSLOT) op[(slot + PD) % RING] = operand(slot + PD);
-            if (slot == S_END) {
-                apply_mask<MASK, CODE>(sc, blk, ma);
-                p_group(0);
-                p_group(1);
-            }
-            constexpr int LATE = NDB > 2 ? 2 : 1;  // the second half is due at slot NDB of its product
-            if (slot == S_END + 1) p_group(2);
-            if (slot == S_END + LATE) p_group(3);
-            if (slot == DP_END) {
-                ds_group(0);
-                ds_group(1);
-            }
-            if (slot == DP_END + 1) ds_group(2);
-            if (slot == DP_END + LATE) ds_group(3);
-            if (slot < S_END)
-                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], r1f[slot], sc, 0, 0, 0);
-            else if (slot < DV_END) {
-                constexpr int i = slot >= S_END && slot < DV_END ? slot - S_END : 0;
-                acc_v[i % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], pf[i / NDB], acc_v[i % NDB], 0, 0, 0);
-            } else if (slot < DP_END)
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], r2f[slot >= DV_END && slot < DP_END ? slot - DV_END : 0], dp, 0, 0, 0);
-            else {
-                constexpr int i = slot >= DP_END ? slot - DP_END : 0;
-                acc[i % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[slot % RING], pf[i / NDB], acc[i % NDB], 0, 0, 0);
-            }
-            SCHED_FENCE();
-        };
-        static_assert(NDB >= 2, "the second half of P and of dS is formed under the first NDB slots of its product");
         static_for<NSLOT>(run_slot);
     };
 
@@ -596,25 +438,20 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
         }
     };
     const const_int_ptr wave_desc = (const_int_ptr)p.wave_desc;
-    // Runs the reachable blocks of one staged tile (one code shape per block product, whichever mode).
-    auto run_blocks = [&](auto mask_tag, bool run0, bool run1, const MaskArgs& ma, int buf, int j) __attribute__((always_inline)) {
-        const unsigned tile_lds = lds_base + (unsigned)buf * STAGE_BYTES + (unsigned)j * (2 * TILE_BYTES);
-        const float* tile_stats = stats + ((buf * TPS + j) * 2) * TILE_KEYS;
-        if constexpr (MODE == kBwdQ && CLEAR_BWD_PIPELINED_Q) {
-            if (run0) do_block_q(mask_tag, tile_lds, 0, ma);
-            if (run1) do_block_q(mask_tag, tile_lds, 1, ma);
-        } else if constexpr (MODE == kBwdKV && CLEAR_BWD_PIPELINED_KV) {
-            if constexpr (CLEAR_BWD_PIPELINED_KV == 2) {
-                if (run0) do_block_kv_early(mask_tag, tile_lds, 0, ma, tile_stats);
-                if (run1) do_block_kv_early(mask_tag, tile_lds, 1, ma, tile_stats);
-            } else {
-                if (run0) do_block_kv(mask_tag, tile_lds, 0, ma, tile_stats);
-                if (run1) do_block_kv(mask_tag, tile_lds, 1, ma, tile_stats);
-            }
-        } else {
-            if (run0) do_block(mask_tag, tile_lds, 0, ma, tile_stats);
-            if (run1) do_block(mask_tag, tile_lds, 1, ma, tile_stats);
-        }
+    // Runs the reachable blocks of one staged tile.
+    auto run_blocks = [&](auto mask_tag, bool run0, bool run1, const MaskArgs& ma, bool masked0, bool masked1, int buf, int j) __attribute__((always_inline)) {
+        Block b;
+        const unsigned tile_at = (unsigned)buf * STAGE_BYTES + (unsigned)j * (2 * TILE_BYTES);
+        b.kb[0] = k_lane + tile_at;
+        b.vb[0] = v_lane + tile_at;
+        b.kb[1] = b.kb[0] ^ K_LANE_ODD;
+        b.vb[1] = b.vb[0] ^ V_LANE_ODD;
+        b.stats = stats + ((buf * TPS + j) * 2) * TILE_KEYS;
+        b.ma = ma;
+        b.masked = masked0;
+        if (run0) do_block(mask_tag, std::integral_constant<int, 0>{}, b);
+        b.masked = masked1;
+        if (run1) do_block(mask_tag, std::integral_constant<int, 1>{}, b);
     };
     auto run_tile = [&](auto mask_tag, int t, int buf, int j) __attribute__((always_inline)) {
         if constexpr (decltype(mask_tag)::value == kMaskTable) {
@@ -627,7 +464,7 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
             MaskArgs ma;
             ma.row[0] = mask_tbl + 16 * i0;
             ma.row[1] = mask_tbl + 16 * i1;
-            run_blocks(mask_tag, i0 != zeros, i1 != zeros, ma, buf, j);
+            run_blocks(mask_tag, i0 != zeros, i1 != zeros, ma, i0 != zeros - 1, i1 != zeros - 1, buf, j);
             return;
         }
         int ta, tb;
@@ -667,7 +504,7 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
             ma.row[0] = mask_tbl + 16 * i0;
             ma.row[1] = mask_tbl + 16 * i1;
         }
-        run_blocks(mask_tag, cls0 != kBlockSkip, cls1 != kBlockSkip, ma, buf, j);
+        run_blocks(mask_tag, cls0 != kBlockSkip, cls1 != kBlockSkip, ma, true, true, buf, j);
     };
     auto run_category = [&](auto mask_tag, int& t, int end, int& buf) __attribute__((always_inline)) {
         for (; t < end; t += TPS, buf ^= 1) {
@@ -698,10 +535,10 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
     const LaneRow out_row = lane_row();
     if (!out_row.valid) return;
     const int out_token = out_row.token, out_hh = out_row.hh;
-    const float out_scale = MODE == kBwdV ? 1.0f : p.scale;  // dQ and dK carry the 1 / sqrt(d) of the logits
+    const float out_scale = p.scale;  // dQ and dK carry the 1 / sqrt(d) of the logits
     if (LINROWS) {
         // partial sums of this column split: [mode][bh][split][row][d] fp32
-        constexpr int slot0 = MODE == kBwdKV ? (int)kBwdK : MODE;
+        constexpr int slot0 = MODE == kBwdKV ? kPartK : kPartQ;
         float* wo = p.ws + ((((long long)slot0 * p.B * p.H + bh) * p.n_splits + split) * p.n_text + out_token) * D;
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
@@ -711,7 +548,7 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
                 *(f32x4*)(wo + 32 * db + 8 * g + 4 * out_hh) = v;
             }
         if constexpr (MODE == kBwdKV) {
-            float* wv = p.ws + ((((long long)kBwdV * p.B * p.H + bh) * p.n_splits + split) * p.n_text + out_token) * D;
+            float* wv = p.ws + ((((long long)kPartV * p.B * p.H + bh) * p.n_splits + split) * p.n_text + out_token) * D;
 #pragma unroll
             for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -721,8 +558,8 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
                 }
         }
     } else {
-        const TensorStrides& outs = MODE == kBwdQ ? p.dqs : (MODE == kBwdV ? p.dvs : p.dks);
-        __bf16* orow = (__bf16*)(MODE == kBwdQ ? p.dQ : (MODE == kBwdV ? p.dV : p.dK)) + batch * outs.sb + head * outs.sh + (long long)out_token * outs.sn;
+        const TensorStrides& outs = MODE == kBwdQ ? p.dqs : p.dks;
+        __bf16* orow = (__bf16*)(MODE == kBwdQ ? p.dQ : p.dK) + batch * outs.sb + head * outs.sh + (long long)out_token * outs.sn;
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -837,8 +674,8 @@ __global__ void __launch_bounds__(256) clear_bwd_reduce_kernel(const BwdParams p
         s += v3;
     }
     for (; k < p.n_splits; ++k, part += pitch) s += *(const f32x4*)part;
-    __bf16* const out = (__bf16*)(mode == kBwdQ ? p.dQ : (mode == kBwdK ? p.dK : p.dV));
-    const TensorStrides& st = mode == kBwdQ ? p.dqs : (mode == kBwdK ? p.dks : p.dvs);
+    __bf16* const out = (__bf16*)(mode == kPartQ ? p.dQ : (mode == kPartK ? p.dK : p.dV));
+    const TensorStrides& st = mode == kPartQ ? p.dqs : (mode == kPartK ? p.dks : p.dvs);
     bf16x4 r;
 #pragma unroll
     for (int j = 0; j < 4; ++j) r[j] = (__bf16)s[j];
@@ -895,7 +732,6 @@ hipError_t launch_bf16_backward(const BwdParams& p, const void* O, float* delta,
         e = hipGetLastError();
     }
     const long long per_head = (long long)p.n_classes * p.n_q_tiles;
-#if CLEAR_BWD_FUSED_KV
     if (phase == kBwdPhaseFour) {
         const int nlin4 = p.n_text > 0 ? BH * p.n_tq_tiles * p.n_splits : 0, nimg = (int)(BH * per_head);  // (64 image workgroups per CU at most)
         const int code = mask_code_of(p.mask_kind);
@@ -903,7 +739,6 @@ hipError_t launch_bf16_backward(const BwdParams& p, const void* O, float* delta,
                : code == kCodeFull ? launch_bwd_all<kCodeFull>(p, nimg, nlin4, stream)
                                    : launch_bwd_all<kCodeGeneric>(p, nimg, nlin4, stream);
     }
-#endif
     const int nlin = p.n_text > 0 ? BH * p.n_tq_tiles * p.n_splits : 0;
     BwdParams pq = p;  // for the dQ kernels
     if (all) {
@@ -931,21 +766,11 @@ hipError_t launch_bf16_backward(const BwdParams& p, const void* O, float* delta,
     if (e == hipSuccess && (all || phase == kBwdPhaseImageQ)) e = launch_image(pq, std::integral_constant<int, kBwdQ>{});
     if (e == hipSuccess && nlin > 0 && (all || phase == kBwdPhaseTextQ)) e = launch_bwd<kBwdQ, true>(pq, nlin, stream);
     if (e == hipSuccess && (all || phase == kBwdPhaseImageKV)) {
-#if CLEAR_BWD_FUSED_KV
         e = launch_image(p, std::integral_constant<int, kBwdKV>{});
-#else
-        e = launch_image(p, std::integral_constant<int, kBwdK>{});
-        if (e == hipSuccess) e = launch_image(p, std::integral_constant<int, kBwdV>{});
-#endif
     }
     if (e != hipSuccess || p.n_text == 0) return e;
     if (e == hipSuccess && (all || phase == kBwdPhaseTextKV)) {
-#if CLEAR_BWD_FUSED_KV
         e = launch_bwd<kBwdKV, true>(p, nlin, stream);
-#else
-        e = launch_bwd<kBwdK, true>(p, nlin, stream);
-        if (e == hipSuccess) e = launch_bwd<kBwdV, true>(p, nlin, stream);
-#endif
     }
     if (e == hipSuccess && (all || phase == kBwdPhaseReduce)) {
         hipLaunchKernelGGL(clear_bwd_reduce_kernel, dim3((unsigned)((3LL * BH * p.n_text + kReduceRows - 1) / kReduceRows)), dim3(256), 0, stream, p);
