@@ -116,6 +116,8 @@ struct clear_attn_ctx {
     int bwd_BH = 0;
     float* d_bwd_delta = nullptr;  // [B*H][N]
     float* d_bwd_ws = nullptr;     // [3][B*H][max splits][n_text][head_dim]
+    int bwd_shape_BH = 0;          // bwd_shape is the launch shape of a backward pass of so many (batch, head) units
+    BackwardShape bwd_shape = {};
     // keys after the prologue (clear_attn_forward_prologue), grown on demand
     int kpro_BH = 0;
     void* d_kpro = nullptr;        // [B*H][N][head_dim] bf16
@@ -1141,15 +1143,28 @@ static int backward_impl(clear_attn_ctx* ctx, const void* Q, const void* K, cons
     if (n_text > 0) {
         const int per_block = bf16_text_queries_per_block();
         p.n_tq_tiles = (n_text + per_block - 1) / per_block;
-        choose_text_splits(N, BH, p.n_tq_tiles, ctx->num_cus, together, &p.n_splits, &p.split_keys);
+        if (together) {
+            if (ctx->bwd_shape_BH != BH) {
+                const double steps = ctx->t.fwd[0].steps, waves = (double)p.n_q_tiles * kBf16NWY * kBf16NWX;
+                const double with_rows = (double)((s.gridH + kWaveQH - 1) / kWaveQH) * ((s.gridW + kWaveQW - 1) / kWaveQW);
+                const BackwardProblem bp = {n_text, head_dim, BH, ctx->num_cus, N, (long long)BH * p.n_classes * p.n_q_tiles, ctx->t.fwd[0].stages, steps, steps * waves / with_rows};
+                ctx->bwd_shape = choose_backward_shape(bp);
+                ctx->bwd_shape_BH = BH;
+            }
+            p.n_splits = ctx->bwd_shape.n_splits;
+            p.split_keys = ctx->bwd_shape.split_keys;
+            p.text_first = ctx->bwd_shape.text_first;
+        } else {
+            choose_text_splits(N, BH, p.n_tq_tiles, ctx->num_cus, false, &p.n_splits, &p.split_keys);
+        }
         p.ws = ctx->d_bwd_ws;
     }
     auto run = [&](hipStream_t st, int phase) {
         return ctx->head_dim == 128 ? launch_bf16_d128_backward(p, O, ctx->d_bwd_delta, st, phase) : launch_bf16_d64_backward(p, O, ctx->d_bwd_delta, st, phase);
     };
     // After delta, the four kernels (dQ and dK/dV of the image rows and of the text rows) are independent.  Up to 64
-    // image workgroups per CU they go out as one launch, longest workgroups first, so that each kind fills the CUs the
-    // others leave idle (64 x 64 grid, the paper's training size: 0.59 -> 0.48 ms against one launch after the other,
+    // image workgroups per CU they go out as one launch, in the order that choose_backward_shape picks, so that each kind fills
+    // the CUs the others leave idle (64 x 64 grid, the paper's training size: 0.59 -> 0.48 ms against one launch after the other,
     // 0.54 with the kinds on two streams as an earlier version ran them; 128 x 128: 2.18 -> 1.89 ms; 256 x 256: 1 %);
     // the largest problems, where it gains nothing, keep one launch per kernel.
     hipError_t e = hipSuccess;

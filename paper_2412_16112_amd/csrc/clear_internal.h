@@ -223,13 +223,14 @@ struct BwdParams {
     int n_classes, stride, stride_rx, stride_ry;  // strided mask, as in FwdParams (otherwise 1, 1, 0, 0)
     float scale_log2e;  // log2(e) / sqrt(head_dim)
     float scale;        // 1 / sqrt(head_dim)
-    // text rows: sums over every token, split along the columns, partial sums added up afterwards
+    // text rows: sums over every token, split along the columns, partial sums added up afterwards (one split: stored as they are)
     int n_tq_tiles, n_splits, split_keys;
+    bool text_first;  // one launch for all rows (kBwdPhaseFour): see BackwardShape
     float* ws;  // [3 (dQ, dK, dV)][B*H][n_splits][n_text][head_dim]
 };
 // phase: kBwdPhaseAll (the dQ kernels, which form delta on their way, then the dK / dV kernels, then the reduction),
 // or one kernel of the pass: delta first; the image-row and text-row kernels are independent
-// of each other; the reduction of the text-row partial sums comes after the two text-row kernels.
+// of each other; the reduction of the text-row partial sums, if there are several, comes after the two text-row kernels.
 // kBwdPhaseFour: the four kernels between delta and the reduction in one launch.
 enum BwdPhase : int { kBwdPhaseAll = -1, kBwdPhaseDelta = 0, kBwdPhaseImageQ = 1, kBwdPhaseImageKV = 2, kBwdPhaseTextQ = 3, kBwdPhaseTextKV = 4, kBwdPhaseReduce = 5, kBwdPhaseFour = 6 };
 hipError_t launch_bf16_d128_backward(const BwdParams& p, const void* O, float* delta, hipStream_t stream, int phase);

@@ -15,7 +15,7 @@
 //   dK+dV  keys      Q | dO                   Q k^T         dO v^T         dK += Q^T dS, dV += dO^T P, from one S and one dP
 // lse and delta belong to the query: a per-lane scalar for dQ, a per-column vector (staged next to the tile)
 // for dK and dV.  Text rows sum over every token: they are split along the columns into partial sums that a
-// small kernel adds up, like the text-query rows of the forward pass.
+// small kernel adds up, like the text-query rows of the forward pass; with one range of columns they store their gradients themselves.
 // delta is formed by the dQ kernels on their way when they run before the dK / dV kernels (BwdParams::delta_out),
 // otherwise by clear_bwd_delta_kernel.
 //
@@ -536,8 +536,8 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
     if (!out_row.valid) return;
     const int out_token = out_row.token, out_hh = out_row.hh;
     const float out_scale = p.scale;  // dQ and dK carry the 1 / sqrt(d) of the logits
-    if (LINROWS) {
-        // partial sums of this column split: [mode][bh][split][row][d] fp32
+    if (LINROWS && p.n_splits > 1) {
+        // partial sums of this column split: [mode][bh][split][row][d] fp32 (one range of columns is the whole sum: stored below)
         constexpr int slot0 = MODE == kBwdKV ? kPartK : kPartQ;
         float* wo = p.ws + ((((long long)slot0 * p.B * p.H + bh) * p.n_splits + split) * p.n_text + out_token) * D;
 #pragma unroll
@@ -590,20 +590,35 @@ __global__ void __launch_bounds__(512, 1) clear_bwd_bf16_kernel(const BwdParams 
     clear_bwd_bf16_workgroup<MODE, LINROWS, CODE>(p, (int)blockIdx.x, (int)gridDim.x);
 }
 
-// The four independent kernels of a backward pass in one launch, longest workgroups first: [0, n_image) dK and dV of
-// the image keys, [n_image, 2 n_image) dQ of the image queries, then n_text_wgs workgroups for dK and dV of the text
-// keys and as many for dQ of the text queries.  For problems of a few rounds of workgroups, where four launches, one
-// after the other or on two streams, leave CUs idle between them.  (delta comes from clear_bwd_delta_kernel here.)
+// The four independent kernels of a backward pass in one launch of 2 n_image + 2 n_text_wgs workgroups, in one of two orders:
+//   image rows first   dK and dV of the image keys, dQ of the image queries, dK and dV of the text keys, dQ of the text queries
+//   p.text_first       dK and dV of the text keys, of the image keys, dQ of the text queries, of the image queries
+// For problems of a few rounds of workgroups, where four launches, one after the other or on two streams, leave CUs idle between them, and
+// where it is the kind that runs last that decides how evenly the CUs finish (choose_backward_shape, which states what that is
+// worth).  (delta comes from clear_bwd_delta_kernel here.)
 template <int CODE>
 __global__ void __launch_bounds__(512, 1) clear_bwd_bf16_all_kernel(const BwdParams p, const int n_image, const int n_text_wgs)
 {
     int bid = (int)blockIdx.x;
-    if (bid < n_image) return clear_bwd_bf16_workgroup<kBwdKV, false, CODE>(p, bid, n_image);
-    bid -= n_image;
-    if (bid < n_image) return clear_bwd_bf16_workgroup<kBwdQ, false, CODE>(p, bid, n_image);
-    bid -= n_image;
-    if (bid < n_text_wgs) return clear_bwd_bf16_workgroup<kBwdKV, true, kCodeDisc>(p, bid, n_text_wgs);
-    clear_bwd_bf16_workgroup<kBwdQ, true, kCodeDisc>(p, bid - n_text_wgs, n_text_wgs);
+    bool text, kv;
+    if (p.text_first) {
+        kv = bid < n_text_wgs + n_image;
+        if (!kv) bid -= n_text_wgs + n_image;
+        text = bid < n_text_wgs;
+        if (!text) bid -= n_text_wgs;
+    } else {
+        text = bid >= 2 * n_image;
+        if (text) bid -= 2 * n_image;
+        const int n = text ? n_text_wgs : n_image;
+        kv = bid < n;
+        if (!kv) bid -= n;
+    }
+    if (!text) {
+        if (kv) return clear_bwd_bf16_workgroup<kBwdKV, false, CODE>(p, bid, n_image);
+        return clear_bwd_bf16_workgroup<kBwdQ, false, CODE>(p, bid, n_image);
+    }
+    if (kv) return clear_bwd_bf16_workgroup<kBwdKV, true, kCodeDisc>(p, bid, n_text_wgs);
+    clear_bwd_bf16_workgroup<kBwdQ, true, kCodeDisc>(p, bid, n_text_wgs);
 }
 
 // delta_i = dO_i . O_i for every row: D / 8 lanes per row (8 channels = 16 bytes each).  A workgroup takes 256 / CHUNKS
@@ -772,7 +787,7 @@ hipError_t launch_bf16_backward(const BwdParams& p, const void* O, float* delta,
     if (e == hipSuccess && (all || phase == kBwdPhaseTextKV)) {
         e = launch_bwd<kBwdKV, true>(p, nlin, stream);
     }
-    if (e == hipSuccess && (all || phase == kBwdPhaseReduce)) {
+    if (e == hipSuccess && p.n_splits > 1 && (all || phase == kBwdPhaseReduce)) {
         hipLaunchKernelGGL(clear_bwd_reduce_kernel, dim3((unsigned)((3LL * BH * p.n_text + kReduceRows - 1) / kReduceRows)), dim3(256), 0, stream, p);
         e = hipGetLastError();
     }

@@ -156,4 +156,96 @@ ForwardShape choose_forward_shape(const ForwardProblem& fp)
     return best;
 }
 
+// When the last of num_cus CUs finishes, if every workgroup starts on the CU that is free first: n[i] workgroups of cost[i], in this order.
+static double finish_time(int num_cus, const double (&n)[4], const double (&cost)[4])
+{
+    struct Group {
+        double free_at, cus;
+    } g[6] = {{0.0, (double)num_cus}};  // by time; a kind adds one group at most
+    int ng = 1;
+    for (int i = 0; i < 4; ++i)
+        for (double left = n[i]; left > 0;) {
+            if (left >= num_cus && g[ng - 1].free_at - g[0].free_at <= cost[i]) {  // whole rounds: every CU takes one
+                const double rounds = std::floor(left / num_cus);
+                for (int k = 0; k < ng; ++k) g[k].free_at += rounds * cost[i];
+                left -= rounds * num_cus;
+                continue;
+            }
+            const double take = std::min(left, g[0].cus), at = g[0].free_at + cost[i];
+            left -= take;
+            g[0].cus -= take;
+            if (g[0].cus == 0) std::copy(g + 1, g + ng--, g);
+            int k = ng;
+            while (k > 0 && g[k - 1].free_at > at) --k;
+            if (k > 0 && g[k - 1].free_at == at) {
+                g[k - 1].cus += take;
+            } else {
+                std::copy_backward(g + k, g + ng, g + ng + 1);
+                g[k] = {at, take};
+                ++ng;
+            }
+        }
+    return g[ng - 1].free_at;
+}
+
+// Launch shape of a backward pass in one launch: column ranges of the text rows and the order of its four kinds of workgroups.
+//
+// As in the forward pass one workgroup fills a CU, and the time of a few rounds is how evenly they fill the CUs.  Long text rows go first, or
+// they are the last to run; short ones go last and fill the gaps that image rows of unequal length leave.  Each pair of a split count and an order
+// is priced with a cost per workgroup (a fixed part, one per stage, one per block of either of the two waves of a SIMD; a text workgroup of four
+// waves or fewer has one wave to a SIMD) and two times for the launch: that of finish_time with all image rows as long as those whose waves
+// all have rows, and the evenly spread work plus half a workgroup of the last kind.  Their mean is taken, 4 % more where image rows come last (they differ
+// in length, which finish_time does not see).  Several ranges cost the kernel that adds them up.  A range of over four times an image row's walk that takes more than
+// a quarter of the evenly spread work is not considered: the mean misses how such workgroups outlast the others (24 heads, 128 x 128, 333 text tokens: one
+// range 1 433 us, four 1 360).
+// (Fitted to 16 calls at 128 channels and 10 at 64, 1 to 8 ranges in both orders, on one card: the picks take 4 % less than image rows first with
+// choose_text_splits and are nowhere slower.  24 heads of 128 channels, 512 text tokens, r = 16, backward call: 64 x 64 393 -> 374 us, 32 x 32,
+// r = 8 104 -> 91, 24 x 64 169 -> 146; 5 heads, 110 x 90, r = 12 192 -> 160; 38 heads of 64, 64 x 64 332 -> 314.)
+// Beyond 16 image workgroups per CU the evenness takes care of itself: image rows first, and choose_text_splits.
+BackwardShape choose_backward_shape(const BackwardProblem& bp)
+{
+    const int per_block = bf16_text_queries_per_block(), n_tiles = (bp.n_text + per_block - 1) / per_block;
+    BackwardShape best = {1, kKeyTileKeys, false};
+    if (bp.n_text == 0) return best;
+    choose_text_splits(bp.N, bp.BH, n_tiles, bp.num_cus, true, &best.n_splits, &best.split_keys);
+    if (bp.image_wgs > 16LL * bp.num_cus) return best;
+    const bool d64 = bp.head_dim == 64;
+    // cycles
+    const double fixed = d64 ? 8e3 : 18e3, stage = d64 ? 1900 : 1200, block_kv = d64 ? 920 : 1140, block_q = d64 ? 720 : 1020, lone_wave = d64 ? 0.57 : 0.5;
+    const int stage_keys = bf16_tiles_per_stage(bp.head_dim) * kKeyTileKeys;
+    const double image = fixed + bp.stages * stage, image_kv = image + 2 * bp.steps * block_kv, image_q = image + 2 * bp.steps * block_q;
+    const double full_kv = image + 2 * bp.full_steps * block_kv, full_q = image + 2 * bp.full_steps * block_q;
+    const int last_rows = bp.n_text - (n_tiles - 1) * per_block;
+    const double waves = last_rows * 2 > per_block ? 1.0 : (n_tiles - 1 + lone_wave) / n_tiles;  // cost of a text block, mean of the tiles
+    const int most = std::min(max_text_splits(bp.N), 16);
+    const double units = (double)bp.BH * n_tiles;
+    double best_time = 1e300;
+    long long last_keys = -1;
+    for (int s = 1; s <= most; ++s) {
+        long long keys = (bp.N + s - 1) / s;
+        keys = (keys + kKeyTileKeys - 1) / kKeyTileKeys * kKeyTileKeys;
+        if (keys == last_keys) continue;
+        last_keys = keys;
+        const int real = (int)((bp.N + keys - 1) / keys);
+        const double n_text_wgs = units * real, n_image = (double)bp.image_wgs;
+        if (n_text_wgs > std::max(units, 64.0 * bp.num_cus)) break;
+        const double text = fixed + std::ceil((double)keys / stage_keys) * stage, blocks = 2 * (double)keys / 32 * waves;
+        const double text_kv = text + blocks * block_kv, text_q = text + blocks * block_q;
+        const double reduce = real == 1 ? 0 : 12e3 + 3e-4 * 2 * 3 * sizeof(float) * bp.BH * real * (double)bp.n_text * bp.head_dim;  // a kernel of its own; partial sums written and read back
+        const double even = (n_image * (image_kv + image_q) + n_text_wgs * (text_kv + text_q)) / bp.num_cus, longest = std::max(full_kv, text_kv);
+        if (keys > 4 * 32 * bp.steps && text_kv > 0.25 * even && s < most) continue;
+        for (int text_first = 0; text_first < 2; ++text_first) {
+            const double n[2][4] = {{n_image, n_image, n_text_wgs, n_text_wgs}, {n_text_wgs, n_image, n_text_wgs, n_image}};
+            const double c[2][4] = {{full_kv, full_q, text_kv, text_q}, {text_kv, full_kv, text_q, full_q}};
+            const double spread = std::max(longest, even + 0.5 * c[text_first][3]);
+            const double time = (0.5 * (finish_time(bp.num_cus, n[text_first], c[text_first]) + spread) + reduce) * (text_first ? 1.04 : 1.0);
+            if (time < best_time) {
+                best_time = time;
+                best = {real, (int)keys, text_first != 0};
+            }
+        }
+    }
+    return best;
+}
+
 }  // namespace clear

@@ -42,4 +42,16 @@ struct ForwardShape {
 };
 ForwardShape choose_forward_shape(const ForwardProblem& fp);
 
+struct BackwardProblem {  // of a backward pass whose four kinds of workgroups go out in one launch
+    int n_text, head_dim, BH, num_cus;
+    long long N, image_wgs;  // image row tiles, each once for dQ and once for dK and dV
+    double stages, steps;    // of an image row tile, on average: stages, blocks per wave
+    double full_steps;       // blocks per wave that has rows
+};
+struct BackwardShape {
+    int n_splits, split_keys;  // column ranges of the text rows
+    bool text_first;           // text rows before image rows, dK + dV of both before dQ; otherwise the image rows first
+};
+BackwardShape choose_backward_shape(const BackwardProblem& bp);
+
 }  // namespace clear

@@ -200,6 +200,13 @@ static void launch_shapes()
                             n_splits = sh.n_splits;
                             split_keys = sh.split_keys;
                         }
+                        if (!f32) {
+                            const BackwardProblem bp = {n_text, head_dim, BH, cus, NV, (long long)BH * n_q_tiles, 20.0, 25.0, 40.0};
+                            const BackwardShape bwd = choose_backward_shape(bp);
+                            check_ranges(NV, bwd.n_splits, bwd.split_keys);
+                            // every (workgroup) index of the one launch is 31 bits and its threads 32
+                            if ((long long)BH * n_q_tiles <= 64LL * cus) EXPECT(2LL * BH * (n_q_tiles + (long long)n_tq * bwd.n_splits) * 512 <= 0xffffffffLL);
+                        }
                         check_ranges(NV, n_splits, split_keys);
                         if (text_partial_bytes(BH, plain, n_text, head_dim) <= kScratchBytes) EXPECT(text_partial_bytes(BH, n_splits, n_text, head_dim) <= kScratchBytes);
                     }

@@ -90,6 +90,41 @@ def test_backward_small_passes(B, H, n_text, gridH, gridW):
         check_grad("dV", dV[b, h].float().cpu().numpy()[cols], rV)
 
 
+@pytest.mark.parametrize("d,H,n_text,gridH,gridW,r", [
+    (128, 24, 333, 96, 96, 8),   # the one launch with its text rows first, several ranges of columns
+    (128, 24, 441, 43, 80, 16),  # the same, one range (stored without partial sums); cut tiles
+    (64, 38, 333, 64, 64, 16),   # the same
+    (128, 38, 512, 36, 20, 16),  # image rows first, one range
+    (128, 24, 77, 48, 85, 16),   # image rows first, several ranges; cut tiles
+    (64, 13, 300, 96, 96, 32),
+])
+def test_backward_orders_of_the_one_launch(d, H, n_text, gridH, gridW, r):
+    """Either order of the four kinds of workgroups (choose_backward_shape): every row of every head is written, and the
+    first and last head are right in rows and columns of all kinds."""
+    Q, K, V = make_qkv_shape(1, H, n_text, gridH, gridW, d, "bf16", seed=91, device="cuda:0")
+    dO = torch.randn(Q.shape, generator=torch.Generator(device="cuda:0").manual_seed(92), device="cuda:0").to(torch.bfloat16)
+    ctx = ca.ClearAttn(n_text, gridH, gridW, d, r, ca.CLEAR_BF16)
+    try:
+        O, lse = ctx.forward_lse(Q, K, V)
+        poison = [torch.full_like(Q, float("nan")) for _ in range(3)]
+        del poison  # the allocator hands the same memory to the gradients
+        grads = ctx.backward(Q, K, V, O, dO, lse)
+        torch.cuda.synchronize()
+    finally:
+        ctx.destroy()
+    assert all(bool(torch.isfinite(g).all()) for g in grads)
+    N = n_text + gridH * gridW
+    rows = np.unique([0, 31, 32, 255, 256, n_text - 1, n_text, n_text + 16 * gridW + 16, n_text + gridW - 1, N - gridW, N - 1])
+    rows = rows[rows < N]
+    for h in (0, H - 1):
+        q, k, v, g = (t[0, h].float().cpu().numpy() for t in (Q, K, V, dO))
+        dQ, dK, dV = (t[0, h].float().cpu().numpy()[rows] for t in grads)
+        check_grad("dQ", dQ, orc.backward_dq_rows(q, k, v, g, rows, n_text, gridH, gridW, r))
+        rK, rV = orc.backward_dkv_cols(q, k, v, g, rows, n_text, gridH, gridW, r)
+        check_grad("dK", dK, rK)
+        check_grad("dV", dV, rV)
+
+
 def test_forward_lse_is_the_log_of_the_softmax_denominator():
     n_text, gridH, gridW, r = 37, 20, 24, 5
     Q, K, V, dO, O, lse, *_ = run_case(n_text, gridH, gridW, r, 1, seed=77, q_scale=2.0)
