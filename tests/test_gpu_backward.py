@@ -69,9 +69,9 @@ def test_backward_batch_of_two():
 
 
 @pytest.mark.parametrize("B,H,n_text,gridH,gridW", [
-    (1, 1, 1, 64, 33),     # one text row, one range of columns
-    (1, 5, 33, 80, 131),   # five ranges (four at a time and one more), rows no multiple of a workgroup's
-    (2, 3, 19, 100, 83),   # four ranges; a thread's four heads belong to two batch entries
+    (1, 1, 1, 64, 33),     # one text row
+    (1, 5, 33, 80, 131),   # several ranges, no multiple of four; rows no multiple of a workgroup's
+    (2, 3, 19, 100, 83),   # several ranges; a thread's four heads belong to two batch entries
 ])
 def test_backward_small_passes(B, H, n_text, gridH, gridW):
     """The passes beside the matrix kernels, at sizes around their groups: delta (4 heads of 16 tokens a workgroup) and
