@@ -76,9 +76,12 @@ __device__ __forceinline__ float wave_pair_sum(float x)
 // lds_addr (wave-uniform), lane i at lds_addr + 16 i; lane i reads gbase + voff.  Counted by vmcnt.
 // Written as asm so that the compiler does not serialise later LDS reads behind it; the kernel waits
 // with explicit s_waitcnt vmcnt before the barrier that publishes the tile.
+// The compiler puts no wait states into asm, so they are written out: the load needs one after the write of M0 and five
+// after a vector instruction that wrote its scalar base (v_readlane, where the base had been spilled), which may stand right in
+// front of the asm: the write of M0 and four more.
 __device__ __forceinline__ void load_to_lds_16B(const void* gbase, unsigned voff, unsigned lds_addr)
 {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(gbase) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(gbase) : "memory", "m0");
 }
 
 // This lane's index in its wave from the hardware's lane count (two instructions, no register kept live for it).

@@ -36,10 +36,10 @@ constexpr int kCell = 16;  // keys per cell, queries per wave
 __device__ __forceinline__ int f32_swz(int row) { return row & 15; }
 
 // 16 bytes per lane from global memory into LDS at lds_addr + 16 * lane (see load_to_lds_16B; 64-bit addresses, as a head
-// of an fp32 context may exceed 4 GB).
+// of an fp32 context may exceed 4 GB).  One wait state after the write of M0; there is no scalar base to wait for.
 __device__ __forceinline__ void load_to_lds_16B_far(const void* src, unsigned lds_addr)
 {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(src) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(src) : "memory", "m0");
 }
 
 // max / sum over the four lanes that share a query (lanes l, l ^ 16, l ^ 32, l ^ 48)
