@@ -83,6 +83,11 @@ __device__ __forceinline__ void load_to_lds_16B(const void* gbase, unsigned voff
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(gbase) : "memory", "m0");
 }
+// The same with 4 bytes per lane: 256 bytes starting at lds_addr.
+__device__ __forceinline__ void load_to_lds_4B(const void* gbase, unsigned voff, unsigned lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_addr), "v"(voff), "s"(gbase) : "memory", "m0");
+}
 
 // This lane's index in its wave from the hardware's lane count (two instructions, no register kept live for it).
 __device__ __forceinline__ int fresh_lane_id()

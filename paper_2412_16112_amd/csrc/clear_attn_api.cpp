@@ -114,7 +114,7 @@ struct clear_attn_ctx {
     float* d_ws_ml = nullptr;
     // backward workspace, grown on demand
     int bwd_BH = 0;
-    float* d_bwd_delta = nullptr;  // [B*H][N]
+    float* d_bwd_stats = nullptr;  // [2][B*H][N]: BwdParams::neg_lse, neg_delta
     float* d_bwd_ws = nullptr;     // [3][B*H][max splits][n_text][head_dim]
     int bwd_shape_BH = 0;          // bwd_shape is the launch shape of a backward pass of so many (batch, head) units
     BackwardShape bwd_shape = {};
@@ -1049,17 +1049,17 @@ int clear_attn_reserve_backward(clear_attn_ctx* ctx, int BH)
             return fail(ctx, e == hipErrorOutOfMemory ? CLEAR_ERR_ALLOC : CLEAR_ERR_HIP, std::string("HIP error building the backward tile lists: ") + hipGetErrorString(e));
         }
     }
-    if (ctx->d_bwd_delta) (void)hipFree(ctx->d_bwd_delta);
+    if (ctx->d_bwd_stats) (void)hipFree(ctx->d_bwd_stats);
     if (ctx->d_bwd_ws) (void)hipFree(ctx->d_bwd_ws);
-    ctx->d_bwd_delta = ctx->d_bwd_ws = nullptr;
+    ctx->d_bwd_stats = ctx->d_bwd_ws = nullptr;
     ctx->bwd_BH = 0;
     const long long N = (long long)ctx->n_text + (long long)ctx->gridH * ctx->gridW;
-    hipError_t e = hipMalloc((void**)&ctx->d_bwd_delta, (size_t)BH * N * sizeof(float));
+    hipError_t e = hipMalloc((void**)&ctx->d_bwd_stats, (size_t)2 * BH * N * sizeof(float));
     if (e == hipSuccess && ctx->n_text > 0)
         e = hipMalloc((void**)&ctx->d_bwd_ws, (size_t)3 * BH * max_text_splits(N) * ctx->n_text * ctx->head_dim * sizeof(float));
     if (e != hipSuccess) {
-        if (ctx->d_bwd_delta) (void)hipFree(ctx->d_bwd_delta);
-        ctx->d_bwd_delta = nullptr;
+        if (ctx->d_bwd_stats) (void)hipFree(ctx->d_bwd_stats);
+        ctx->d_bwd_stats = nullptr;
         (void)hipGetLastError();
         return fail(ctx, e == hipErrorOutOfMemory ? CLEAR_ERR_ALLOC : CLEAR_ERR_HIP, std::string("backward workspace allocation failed: ") + hipGetErrorString(e));
     }
@@ -1119,7 +1119,7 @@ static int backward_impl(clear_attn_ctx* ctx, const void* Q, const void* K, cons
     const Schedule& s = ctx->t.sched;
     BwdParams p;
     memset(&p, 0, sizeof(p));
-    p.Q = Q; p.K = K; p.V = V; p.dO = dO; p.lse = lse; p.delta = ctx->d_bwd_delta;
+    p.Q = Q; p.K = K; p.V = V; p.dO = dO; p.lse = lse; p.neg_lse = ctx->d_bwd_stats; p.neg_delta = ctx->d_bwd_stats + BH * N;
     p.dQ = dQ; p.dK = dK; p.dV = dV;
     p.qs = ts[0]; p.ks = ts[1]; p.vs = ts[2]; p.os = ts[3]; p.dos = ts[4]; p.dqs = ts[5]; p.dks = ts[6]; p.dvs = ts[7];
     p.B = B; p.H = H; p.n_text = n_text; p.gridH = gridH; p.gridW = gridW; p.r2 = r * r;
@@ -1138,6 +1138,7 @@ static int backward_impl(clear_attn_ctx* ctx, const void* Q, const void* K, cons
         if ((long long)p.n_q_tiles * B * H * p.n_classes > 0x7fffffffLL) return fail(ctx, CLEAR_ERR_INVALID_ARG, "too many workgroups: B*H*r*r*row tiles must fit in 31 bits");
     }
     p.scale = (float)(1.0 / std::sqrt((double)head_dim));
+    p.neg_inv_scale = -1.0f / p.scale;
     p.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)head_dim));
     const bool together = (long long)BH * p.n_classes * p.n_q_tiles <= 64LL * ctx->num_cus;  // one launch for the four kernels, see below
     if (n_text > 0) {
@@ -1160,7 +1161,7 @@ static int backward_impl(clear_attn_ctx* ctx, const void* Q, const void* K, cons
         p.ws = ctx->d_bwd_ws;
     }
     auto run = [&](hipStream_t st, int phase) {
-        return ctx->head_dim == 128 ? launch_bf16_d128_backward(p, O, ctx->d_bwd_delta, st, phase) : launch_bf16_d64_backward(p, O, ctx->d_bwd_delta, st, phase);
+        return ctx->head_dim == 128 ? launch_bf16_d128_backward(p, O, st, phase) : launch_bf16_d64_backward(p, O, st, phase);
     };
     // After delta, the four kernels (dQ and dK/dV of the image rows and of the text rows) are independent.  Up to 64
     // image workgroups per CU they go out as one launch, in the order that choose_backward_shape picks, so that each kind fills
@@ -1257,7 +1258,7 @@ void clear_attn_destroy(clear_attn_ctx* ctx)
         }
     if (ctx->d_ws_o) (void)hipFree(ctx->d_ws_o);
     if (ctx->d_ws_ml) (void)hipFree(ctx->d_ws_ml);
-    if (ctx->d_bwd_delta) (void)hipFree(ctx->d_bwd_delta);
+    if (ctx->d_bwd_stats) (void)hipFree(ctx->d_bwd_stats);
     if (ctx->d_bwd_ws) (void)hipFree(ctx->d_bwd_ws);
     if (ctx->d_kpro) (void)hipFree(ctx->d_kpro);
     delete ctx;

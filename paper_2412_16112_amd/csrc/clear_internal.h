@@ -199,14 +199,16 @@ struct BwdParams {
     const void* V;
     const void* dO;
     const float* lse;    // [B*H][N] natural log of the softmax denominators (from the forward pass)
-    const float* delta;  // [B*H][N] dO_i . O_i (in the context's workspace: from the delta kernel, or from the dQ kernels, see delta_out)
-    const void* O;       // the forward output, read where delta is formed inside the dQ kernels
-    float* delta_out;    // not null: the dQ kernels form delta of their own rows from O and dO, use it and store it here for
-                         // the dK / dV kernels launched after them (null: every kernel reads `delta`)
+    // What the columns of dK and dV start S and dP from, both [B*H][N] in the context's workspace: -lse / scale and -delta, with
+    // delta_i = dO_i . O_i.  Stored by the delta kernel, or, where O is given here, by the dQ kernels for the dK / dV kernels launched
+    // after them.
+    float* neg_lse;
+    float* neg_delta;
+    const void* O;  // the forward output: the dQ kernels form both for their own rows (null: every kernel reads them)
     void* dQ;
     void* dK;
     void* dV;
-    TensorStrides qs, ks, vs, os, dos, dqs, dks, dvs;  // lse and delta are plain [B*H][N]
+    TensorStrides qs, ks, vs, os, dos, dqs, dks, dvs;  // lse, neg_lse and neg_delta are plain [B*H][N]
     int B, H, n_text, gridH, gridW, r2;
     long long N;
     int n_q_tiles, n_qtx;
@@ -223,18 +225,19 @@ struct BwdParams {
     int n_classes, stride, stride_rx, stride_ry;  // strided mask, as in FwdParams (otherwise 1, 1, 0, 0)
     float scale_log2e;  // log2(e) / sqrt(head_dim)
     float scale;        // 1 / sqrt(head_dim)
+    float neg_inv_scale;  // -1 / scale
     // text rows: sums over every token, split along the columns, partial sums added up afterwards (one split: stored as they are)
     int n_tq_tiles, n_splits, split_keys;
     bool text_first;  // one launch for all rows (kBwdPhaseFour): see BackwardShape
     float* ws;  // [3 (dQ, dK, dV)][B*H][n_splits][n_text][head_dim]
 };
-// phase: kBwdPhaseAll (the dQ kernels, which form delta on their way, then the dK / dV kernels, then the reduction),
+// phase: kBwdPhaseAll (the dQ kernels, which form neg_lse and neg_delta on their way, then the dK / dV kernels, then the reduction),
 // or one kernel of the pass: delta first; the image-row and text-row kernels are independent
 // of each other; the reduction of the text-row partial sums, if there are several, comes after the two text-row kernels.
 // kBwdPhaseFour: the four kernels between delta and the reduction in one launch.
 enum BwdPhase : int { kBwdPhaseAll = -1, kBwdPhaseDelta = 0, kBwdPhaseImageQ = 1, kBwdPhaseImageKV = 2, kBwdPhaseTextQ = 3, kBwdPhaseTextKV = 4, kBwdPhaseReduce = 5, kBwdPhaseFour = 6 };
-hipError_t launch_bf16_d128_backward(const BwdParams& p, const void* O, float* delta, hipStream_t stream, int phase);
-hipError_t launch_bf16_d64_backward(const BwdParams& p, const void* O, float* delta, hipStream_t stream, int phase);
+hipError_t launch_bf16_d128_backward(const BwdParams& p, const void* O, hipStream_t stream, int phase);
+hipError_t launch_bf16_d64_backward(const BwdParams& p, const void* O, hipStream_t stream, int phase);
 
 // band_merge.hip: combination of the text-query outputs of several row bands.
 constexpr int kMaxMergeParts = 64;

@@ -13,10 +13,10 @@
 //   mode   rows      column tiles (C1 | C2)   S = C1 r1^T   dP = C2 r2^T   accumulators
 //   dQ     queries   K | V                    K q^T         V dO^T         dQ += K^T dS
 //   dK+dV  keys      Q | dO                   Q k^T         dO v^T         dK += Q^T dS, dV += dO^T P, from one S and one dP
-// lse and delta belong to the query: a per-lane scalar for dQ, a per-column vector (staged next to the tile)
-// for dK and dV.  Text rows sum over every token: they are split along the columns into partial sums that a
+// lse and delta belong to the query: a per-lane scalar for dQ, a per-column vector (staged next to the tile, by LDS-direct loads
+// like the tile, in the form in which S and dP start from it: neg_lse, neg_delta) for dK and dV.  Text rows sum over every token: they are split along the columns into partial sums that a
 // small kernel adds up, like the text-query rows of the forward pass; with one range of columns they store their gradients themselves.
-// delta is formed by the dQ kernels on their way when they run before the dK / dV kernels (BwdParams::delta_out),
+// Both are formed by the dQ kernels on their way when they run before the dK / dV kernels (BwdParams::O given),
 // otherwise by clear_bwd_delta_kernel.
 //
 // What bounds it: a 32 x 32 block is 24 (dQ) or 32 (dK + dV) matrix instructions of 32 cycles, each of which holds the SIMD's vector issue
@@ -54,7 +54,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 enum BwdMode : int { kBwdQ = 0, kBwdKV = 1 };
 enum BwdPart : int { kPartQ = 0, kPartK = 1, kPartV = 2 };  // partial sums of the text rows, in this order in the workspace
 
-constexpr int STATS_BYTES = TILE_KEYS * 2 * 4;                           // per staged tile: lse2 and delta of its 64 columns
+constexpr int STATS_BYTES = TILE_KEYS * 2 * 4;                           // per staged tile: neg_lse and neg_delta of its 64 columns
 constexpr int BWD_LDS_BYTES = NBUF * STAGE_BYTES + NBUF * TPS * STATS_BYTES;
 
 // One workgroup of a backward launch: workgroup `bid` of `nblk`.
@@ -123,8 +123,8 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
     const unsigned char* const C1 = (const unsigned char*)head_of(MODE == kBwdQ ? p.K : p.Q, c1s);
     const unsigned char* const C2 = (const unsigned char*)head_of(MODE == kBwdQ ? p.V : p.dO, c2s);
     const unsigned c1_pitch = (unsigned)c1s.sn * 2, c2_pitch = (unsigned)c2s.sn * 2;  // bytes from one token row to the next
-    const float* const lse = p.lse + (long long)bh * p.N;
-    const float* const delta = p.delta + (long long)bh * p.N;
+    float* const neg_lse = p.neg_lse + (long long)bh * p.N;
+    float* const neg_delta = p.neg_delta + (long long)bh * p.N;
 
     // ---- this wave's rows, and this lane's one among them.  What depends on the lane (row coordinates, token, validity,
     // the half of the wave) is worked out again from the hardware's lane count wherever it is needed (here, per masked
@@ -170,12 +170,10 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
         r1f[s] = *(const bf16x8*)(R1 + (long long)r_token * r1s.sn + 8 * hh + 16 * s);
         r2f[s] = *(const bf16x8*)(R2 + (long long)r_token * r2s.sn + 8 * hh + 16 * s);
     }
-    // dQ: lse and delta of this lane's query
-    const float neg_inv_scale = -1.0f / p.scale;
-    float lse_row = 0.f, delta_row = 0.f;
+    // dQ: what S and dP of this lane's query start from
+    float s_from = 0.f, dp_from = 0.f;
     if (!COLSTAT) {
-        lse_row = lse[r_token];
-        if (p.delta_out) {
+        if (p.O) {
             // delta of this lane's row from the dO fragments it holds and the matching pieces of its O row; the other half
             // of the row's channels sits 32 lanes away
             const __bf16* orow = head_of(p.O, p.os) + (long long)r_token * p.os.sn + 8 * (fresh_lane_id() >> 5);
@@ -186,11 +184,16 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
 #pragma unroll
                 for (int j = 0; j < 8; ++j) part += (float)o[j] * (float)r2f[s][j];
             }
-            delta_row = part + __shfl_xor(part, 32, 64);
+            dp_from = -(part + __shfl_xor(part, 32, 64));
+            s_from = p.lse[(long long)bh * p.N + r_token] * p.neg_inv_scale;
             const LaneRow own = lane_row();
-            if (own.valid && own.hh == 0 && split == 0) p.delta_out[(long long)bh * p.N + own.token] = delta_row;
+            if (own.valid && own.hh == 0 && split == 0) {
+                neg_lse[own.token] = s_from;
+                neg_delta[own.token] = dp_from;
+            }
         } else {
-            delta_row = delta[r_token];
+            s_from = neg_lse[r_token];
+            dp_from = neg_delta[r_token];
         }
     }
 #pragma unroll
@@ -198,7 +201,7 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
         asm volatile("" : "+v"(r1f[s]));
         asm volatile("" : "+v"(r2f[s]));
     }
-    asm volatile("" : "+v"(lse_row), "+v"(delta_row));
+    asm volatile("" : "+v"(s_from), "+v"(dp_from));
 
     const const_int_ptr row_ptr = (const_int_ptr)p.row_ptr, col_idx = (const_int_ptr)p.col_idx, n_plain = (const_int_ptr)p.n_plain;
     const const_u64_ptr mask_tbl = (const_u64_ptr)p.mask_tbl;
@@ -245,8 +248,8 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
     };
 
     // ---- staging: LDS-direct loads of the two column tiles (same layout and swizzle as K and V in the
-    // forward kernel), and for dK / dV the statistics of the tile's 64 queries (wave j of the first TPS waves
-    // fetches them for tile j of the stage and writes them to LDS before the next barrier)
+    // forward kernel), and for dK / dV neg_lse and neg_delta of the tile's 64 queries (wave j of the first TPS waves
+    // for tile j of the stage)
     // A staging wave takes 16 rows of both tiles, all their planes: one token address per tile (half of the rows in turn if the waves do not share).
     static_assert(NW / ISSUE_SHARE == TILE_KEYS / 16, "the waves that stage a tile cover its rows");
     auto issue_tile = [&](int i, unsigned lds_tile) {
@@ -267,7 +270,6 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
         };
         static_for<NPLANE>(load_plane);
     };
-    float st_lse = 0.f, st_delta = 0.f;  // in flight: statistics of slot `lane` of tile `wave` of the next stage
     // Half of the waves stage a whole stage, the other half the next one (each SIMD holds one wave of either half): while
     // one wave of a SIMD stands at its load instructions the other one is already at its matrix products.
     int issue_turn = 0;
@@ -278,24 +280,20 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
 #pragma unroll
         for (int j = 0; j < TPS; ++j)
             if (j < len && mine) issue_tile(t + j, lds_base + (unsigned)buf * STAGE_BYTES + (unsigned)j * (2 * TILE_BYTES));
+        // (Not through registers: a value in flight there is one more to hold through the blocks, and where the allocator spilled it, the store
+        // to scratch waited for the stage that had just been requested.)
         if (COLSTAT && wave < len) {
             int a, b;
             tile_origin(t + wave, a, b);
-            const int token = slot_token(a, b, fresh_lane_id());
-            st_lse = lse[token];  // (scaled when it is published: no wait for it here)
-            st_delta = delta[token];
-        }
-    };
-    auto publish_stats = [&](int buf, int len) {  // called before the barrier that opens stage buffer buf
-        if (COLSTAT && wave < len) {
-            float* dst = stats + ((buf * TPS + wave) * 2) * TILE_KEYS;
-            const int ln = fresh_lane_id();
-            dst[ln] = st_lse * neg_inv_scale;
-            dst[TILE_KEYS + ln] = -st_delta;
+            const unsigned offset = 4 * (unsigned)slot_token(a, b, fresh_lane_id());
+            const unsigned at = lds_base + NBUF * STAGE_BYTES + (unsigned)((buf * TPS + wave) * STATS_BYTES);
+            load_to_lds_4B(neg_lse, offset, at);
+            load_to_lds_4B(neg_delta, offset, at + TILE_KEYS * 4);
         }
     };
 
-    const unsigned k_lane = lds_base + k_lane_offset(lane, 0), v_lane = lds_base + v_lane_offset(lane, 0);
+    // Lane offsets of the two operand reads, both below 2 KB, in one register: the dK / dV kernel of the square and Swin masks has no second one.
+    const unsigned kv_lane = k_lane_offset(lane, 0) | v_lane_offset(lane, 0) << 16;
 
     f32x16 acc[NDB];  // gradient^T tiles: channel 32 db + 8 (reg / 4) + 4 hh + reg % 4 of this lane's row
     f32x16 acc_v[MODE == kBwdKV ? NDB : 1];  // keys: acc holds dK, acc_v holds dV
@@ -314,8 +312,8 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
     if (!COLSTAT) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            s_init[r] = lse_row * neg_inv_scale;
-            dp_init[r] = -delta_row;
+            s_init[r] = s_from;
+            dp_init[r] = dp_from;
         }
         asm volatile("" : "+v"(s_init), "+v"(dp_init));
     }
@@ -334,7 +332,7 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
     //                                                      next 2 NDB       dV^T += dO^T P^T
     //         last 2 NDB       dQ^T += K^T dS^T            last 2 NDB       dK^T += Q^T dS^T
     // Keys at 128 channels: dS is taken from the probabilities as rounded to bf16 for the dV product, so that the fp32 ones need not live beside
-    // dP (255 of 256 registers as it is).
+    // dP (251 to 256 of 256 registers as it is).
     auto do_block = [&](auto mask_tag, auto blk_tag, const Block& b) __attribute__((always_inline)) {
         constexpr int MASK = decltype(mask_tag)::value, blk = decltype(blk_tag)::value;
         constexpr bool KV = MODE == kBwdKV, ROUNDED_P = KV && D == 128;
@@ -425,25 +423,24 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
     };
 
     int pf_tile = 0;
-    int pend_len = 0;  // tiles of the stage whose statistics are in flight
     auto begin_stage = [&](int buf) {
-        publish_stats(buf, pend_len);
         wait_vmcnt<0>();
         __syncthreads();
-        pend_len = 0;
         if (pf_tile < n_tiles) {
-            pend_len = stage_len(pf_tile);
+            const int len = stage_len(pf_tile);
             issue_stage(pf_tile, buf ^ 1);
-            pf_tile += pend_len;
+            pf_tile += len;
         }
     };
     const const_int_ptr wave_desc = (const_int_ptr)p.wave_desc;
     // Runs the reachable blocks of one staged tile.
     auto run_blocks = [&](auto mask_tag, bool run0, bool run1, const MaskArgs& ma, bool masked0, bool masked1, int buf, int j) __attribute__((always_inline)) {
         Block b;
-        const unsigned tile_at = (unsigned)buf * STAGE_BYTES + (unsigned)j * (2 * TILE_BYTES);
-        b.kb[0] = k_lane + tile_at;
-        b.vb[0] = v_lane + tile_at;
+        const unsigned tile_at = lds_base + (unsigned)buf * STAGE_BYTES + (unsigned)j * (2 * TILE_BYTES);
+        unsigned kv = kv_lane;
+        asm volatile("" : "+v"(kv));  // (taken apart here, not in front of the loop)
+        b.kb[0] = tile_at + (kv & 0xffff);
+        b.vb[0] = tile_at + (kv >> 16);
         b.kb[1] = b.kb[0] ^ K_LANE_ODD;
         b.vb[1] = b.vb[0] ^ V_LANE_ODD;
         b.stats = stats + ((buf * TPS + j) * 2) * TILE_KEYS;
@@ -517,9 +514,8 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
 
     // prologue: the first stage is in flight
     if (n_tiles > 0) {
-        pend_len = stage_len(0);
+        pf_tile = stage_len(0);
         issue_stage(0, 0);
-        pf_tile = pend_len;
     }
     int buf = 0, t = 0;
     run_category(std::integral_constant<int, kMaskNone>{}, t, cb1, buf);
@@ -613,12 +609,20 @@ __global__ void __launch_bounds__(512, 1) clear_bwd_bf16_all_kernel(const BwdPar
         kv = bid < n;
         if (!kv) bid -= n;
     }
+    // Each kind reads its parameters for itself: read once for all four, they fill the scalar registers of every one of them (122 spilled
+    // for the disc at 128 channels, now 10), and what is spilled takes vector registers that dK and dV need.  (The kernel's first argument
+    // is at the start of its argument segment.)
+    auto params = []() -> const BwdParams& {
+        auto at = (const __attribute__((address_space(4))) BwdParams*)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(at));
+        return *(const BwdParams*)at;
+    };
     if (!text) {
-        if (kv) return clear_bwd_bf16_workgroup<kBwdKV, false, CODE>(p, bid, n_image);
-        return clear_bwd_bf16_workgroup<kBwdQ, false, CODE>(p, bid, n_image);
+        if (kv) return clear_bwd_bf16_workgroup<kBwdKV, false, CODE>(params(), bid, n_image);
+        return clear_bwd_bf16_workgroup<kBwdQ, false, CODE>(params(), bid, n_image);
     }
-    if (kv) return clear_bwd_bf16_workgroup<kBwdKV, true, kCodeDisc>(p, bid, n_text_wgs);
-    clear_bwd_bf16_workgroup<kBwdQ, true, kCodeDisc>(p, bid, n_text_wgs);
+    if (kv) return clear_bwd_bf16_workgroup<kBwdKV, true, kCodeDisc>(params(), bid, n_text_wgs);
+    clear_bwd_bf16_workgroup<kBwdQ, true, kCodeDisc>(params(), bid, n_text_wgs);
 }
 
 // delta_i = dO_i . O_i for every row: D / 8 lanes per row (8 channels = 16 bytes each).  A workgroup takes 256 / CHUNKS
@@ -627,7 +631,7 @@ __global__ void __launch_bounds__(512, 1) clear_bwd_bf16_all_kernel(const BwdPar
 // 4 608 tokens, head_dim 128: 11.8 us, 4.8 TB/s.  With the reduction below, a training step's call 576 -> 564 us.
 constexpr int kDeltaHeads = 4, kDeltaTokens = 256 / CHUNKS;
 __global__ void __launch_bounds__(256) clear_bwd_delta_kernel(const __bf16* O, TensorStrides os, const __bf16* dO, TensorStrides dos, int H, int BH,
-                                                              long long N, unsigned n_token_blocks, float* delta)
+                                                              long long N, unsigned n_token_blocks, const float* lse, float neg_inv_scale, float* neg_lse, float* neg_delta)
 {
     const long long t = (long long)(blockIdx.x % n_token_blocks) * kDeltaTokens + threadIdx.x / CHUNKS;
     const int bh0 = (int)(blockIdx.x / n_token_blocks) * kDeltaHeads;
@@ -635,12 +639,14 @@ __global__ void __launch_bounds__(256) clear_bwd_delta_kernel(const __bf16* O, T
     const long long tc = t < N ? t : N - 1;
     const int n_heads = imin(kDeltaHeads, BH - bh0);
     bf16x8 o[kDeltaHeads], g[kDeltaHeads];
+    float l[kDeltaHeads];
 #pragma unroll
     for (int i = 0; i < kDeltaHeads; ++i) {
         if (i < n_heads) {
             const int b = (bh0 + i) / H, h = (bh0 + i) % H;
             o[i] = *(const bf16x8*)(O + b * os.sb + h * os.sh + tc * os.sn + 8 * part);
             g[i] = *(const bf16x8*)(dO + b * dos.sb + h * dos.sh + tc * dos.sn + 8 * part);
+            l[i] = lse[(long long)(bh0 + i) * N + tc];
         }
     }
 #pragma unroll
@@ -651,7 +657,10 @@ __global__ void __launch_bounds__(256) clear_bwd_delta_kernel(const __bf16* O, T
             for (int j = 0; j < 8; ++j) s += (float)o[i][j] * (float)g[i][j];
 #pragma unroll
             for (int off = CHUNKS / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-            if (t < N && part == 0) delta[(long long)(bh0 + i) * N + t] = s;
+            if (t < N && part == 0) {
+                neg_lse[(long long)(bh0 + i) * N + t] = l[i] * neg_inv_scale;
+                neg_delta[(long long)(bh0 + i) * N + t] = -s;
+            }
         }
     }
 }
@@ -735,7 +744,7 @@ hipError_t launch_bwd(const BwdParams& p, int nblk, hipStream_t stream)
 
 }  // namespace
 
-hipError_t launch_bf16_backward(const BwdParams& p, const void* O, float* delta, hipStream_t stream, int phase)
+hipError_t launch_bf16_backward(const BwdParams& p, const void* O, hipStream_t stream, int phase)
 {
     const int BH = p.B * p.H;
     const bool all = phase == kBwdPhaseAll;
@@ -743,7 +752,7 @@ hipError_t launch_bf16_backward(const BwdParams& p, const void* O, float* delta,
     // (kBwdPhaseAll: no delta kernel; the dQ kernels form delta and run before the dK / dV kernels, which read it)
     if (phase == kBwdPhaseDelta) {
         const unsigned token_blocks = (unsigned)((p.N + kDeltaTokens - 1) / kDeltaTokens), head_blocks = (unsigned)((BH + kDeltaHeads - 1) / kDeltaHeads);
-        hipLaunchKernelGGL(clear_bwd_delta_kernel, dim3(token_blocks * head_blocks), dim3(256), 0, stream, (const __bf16*)O, p.os, (const __bf16*)p.dO, p.dos, p.H, BH, p.N, token_blocks, delta);
+        hipLaunchKernelGGL(clear_bwd_delta_kernel, dim3(token_blocks * head_blocks), dim3(256), 0, stream, (const __bf16*)O, p.os, (const __bf16*)p.dO, p.dos, p.H, BH, p.N, token_blocks, p.lse, p.neg_inv_scale, p.neg_lse, p.neg_delta);
         e = hipGetLastError();
     }
     const long long per_head = (long long)p.n_classes * p.n_q_tiles;
@@ -756,10 +765,7 @@ hipError_t launch_bf16_backward(const BwdParams& p, const void* O, float* delta,
     }
     const int nlin = p.n_text > 0 ? BH * p.n_tq_tiles * p.n_splits : 0;
     BwdParams pq = p;  // for the dQ kernels
-    if (all) {
-        pq.O = O;
-        pq.delta_out = delta;
-    }
+    if (all) pq.O = O;
     auto shift = [&](BwdParams* q, int b, int h) {
         auto at = [&](const void* t, const TensorStrides& st) { return (const __bf16*)t + b * st.sb + h * st.sh; };
         const long long row = ((long long)b * p.H + h) * p.N;
@@ -772,8 +778,8 @@ hipError_t launch_bf16_backward(const BwdParams& p, const void* O, float* delta,
         q->dV = (void*)at(p.dV, p.dvs);
         if (q->O) q->O = at(q->O, p.os);
         q->lse = p.lse + row;
-        q->delta = p.delta + row;
-        if (q->delta_out) q->delta_out += row;
+        q->neg_lse = p.neg_lse + row;
+        q->neg_delta = p.neg_delta + row;
     };
     auto launch_image = [&](const BwdParams& params, auto mode_tag) {
         return launch_by_heads(params, per_head, 0xffffffffLL / 512, shift, [&](const BwdParams& q, int n) { return launch_bwd<decltype(mode_tag)::value, false>(q, n, stream); });

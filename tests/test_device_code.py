@@ -87,3 +87,16 @@ def test_wait_states_of_lds_direct_loads(code_objects):
             loads += n
             assert not bad, "%s: %d of %d loads, the first %s" % (kernel, len(bad), n, bad[0])
     assert loads > 1000
+
+
+def test_backward_kernels_spill_no_vector_register(code_objects):
+    """A reload from scratch memory waits for every load issued before it, the staged tiles in front included."""
+    spills = {}
+    for path in code_objects:
+        notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", path], check=True, capture_output=True, text=True).stdout
+        for kernel in notes.split("- .agpr_count")[1:]:
+            name = re.search(r"\.name: +(_Z\w+)\n", kernel).group(1)
+            if "clear_bwd" in name:
+                spills[name] = int(re.search(r"\.vgpr_spill_count: +(\d+)", kernel).group(1))
+    assert len(spills) >= 22
+    assert not {k: n for k, n in spills.items() if n}
