@@ -250,7 +250,7 @@ int clear_attn_forward_lse(clear_attn_ctx* ctx, const void* Q, const void* K, co
 /* Backward pass.  Q, K, V as given to the forward pass, O and lse as it returned them, dO the gradient with
  * respect to O; writes dQ, dK, dV (device, [B, H, N, head_dim], the tensors' dtype; fp32 accumulation, one
  * rounding on output).  All tensors 16-byte aligned; dQ, dK, dV must not overlap each other or an input.
- * Enqueues on stream, never synchronises; allocates only if the context's backward workspace ([B*H][N] floats
+ * Enqueues on stream, never synchronises; allocates only if the context's backward workspace (two [B*H][N] of floats
  * plus the split sums of the text rows) has to grow: call clear_attn_reserve_backward beforehand to avoid
  * that.  Shape arguments as for clear_attn_forward (CLEAR_ERR_MISMATCH otherwise, nothing launched). */
 int clear_attn_backward(clear_attn_ctx* ctx, const void* Q, const void* K, const void* V, const void* O,

@@ -1161,7 +1161,7 @@ static int backward_impl(clear_attn_ctx* ctx, const void* Q, const void* K, cons
         p.ws = ctx->d_bwd_ws;
     }
     auto run = [&](hipStream_t st, int phase) {
-        return ctx->head_dim == 128 ? launch_bf16_d128_backward(p, O, st, phase) : launch_bf16_d64_backward(p, O, st, phase);
+        return ctx->head_dim == 128 ? launch_bf16_d128_backward(p, O, ctx->d_bwd_stats, st, phase) : launch_bf16_d64_backward(p, O, ctx->d_bwd_stats, st, phase);
     };
     // After delta, the four kernels (dQ and dK/dV of the image rows and of the text rows) are independent.  Up to 64
     // image workgroups per CU they go out as one launch, in the order that choose_backward_shape picks, so that each kind fills

@@ -235,9 +235,10 @@ struct BwdParams {
 // or one kernel of the pass: delta first; the image-row and text-row kernels are independent
 // of each other; the reduction of the text-row partial sums, if there are several, comes after the two text-row kernels.
 // kBwdPhaseFour: the four kernels between delta and the reduction in one launch.
+// O: the forward output; stats: [2][B*H][N], where the delta kernel stores neg_lse and neg_delta.
 enum BwdPhase : int { kBwdPhaseAll = -1, kBwdPhaseDelta = 0, kBwdPhaseImageQ = 1, kBwdPhaseImageKV = 2, kBwdPhaseTextQ = 3, kBwdPhaseTextKV = 4, kBwdPhaseReduce = 5, kBwdPhaseFour = 6 };
-hipError_t launch_bf16_d128_backward(const BwdParams& p, const void* O, hipStream_t stream, int phase);
-hipError_t launch_bf16_d64_backward(const BwdParams& p, const void* O, hipStream_t stream, int phase);
+hipError_t launch_bf16_d128_backward(const BwdParams& p, const void* O, float* stats, hipStream_t stream, int phase);
+hipError_t launch_bf16_d64_backward(const BwdParams& p, const void* O, float* stats, hipStream_t stream, int phase);
 
 // band_merge.hip: combination of the text-query outputs of several row bands.
 constexpr int kMaxMergeParts = 64;

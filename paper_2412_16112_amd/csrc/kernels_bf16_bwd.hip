@@ -744,7 +744,7 @@ hipError_t launch_bwd(const BwdParams& p, int nblk, hipStream_t stream)
 
 }  // namespace
 
-hipError_t launch_bf16_backward(const BwdParams& p, const void* O, hipStream_t stream, int phase)
+hipError_t launch_bf16_backward(const BwdParams& p, const void* O, float* stats, hipStream_t stream, int phase)
 {
     const int BH = p.B * p.H;
     const bool all = phase == kBwdPhaseAll;
@@ -752,7 +752,7 @@ hipError_t launch_bf16_backward(const BwdParams& p, const void* O, hipStream_t s
     // (kBwdPhaseAll: no delta kernel; the dQ kernels form delta and run before the dK / dV kernels, which read it)
     if (phase == kBwdPhaseDelta) {
         const unsigned token_blocks = (unsigned)((p.N + kDeltaTokens - 1) / kDeltaTokens), head_blocks = (unsigned)((BH + kDeltaHeads - 1) / kDeltaHeads);
-        hipLaunchKernelGGL(clear_bwd_delta_kernel, dim3(token_blocks * head_blocks), dim3(256), 0, stream, (const __bf16*)O, p.os, (const __bf16*)p.dO, p.dos, p.H, BH, p.N, token_blocks, p.lse, p.neg_inv_scale, p.neg_lse, p.neg_delta);
+        hipLaunchKernelGGL(clear_bwd_delta_kernel, dim3(token_blocks * head_blocks), dim3(256), 0, stream, (const __bf16*)O, p.os, (const __bf16*)p.dO, p.dos, p.H, BH, p.N, token_blocks, p.lse, p.neg_inv_scale, stats, stats + BH * p.N);
         e = hipGetLastError();
     }
     const long long per_head = (long long)p.n_classes * p.n_q_tiles;
