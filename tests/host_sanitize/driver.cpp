@@ -319,6 +319,36 @@ static void tile_orders()
     }
 }
 
+// The launch shapes that the cases of tests/test_gpu_backward.py are named for: how many column ranges the text rows take and whether they
+// go first.  A change of the cost model that moves one of them leaves an order or a kernel without its test.
+static void backward_orders()
+{
+    const struct {
+        int d, B, H, n_text, gh, gw, r, kind, shift, n_splits;
+        bool text_first;
+    } cases[] = {
+        // test_backward_orders_of_the_one_launch
+        {128, 1, 24, 333, 96, 96, 8, CLEAR_MASK_DISC, 0, 3, true},    {128, 1, 24, 441, 43, 80, 16, CLEAR_MASK_DISC, 0, 1, true},
+        {64, 1, 38, 333, 64, 64, 16, CLEAR_MASK_DISC, 0, 1, true},    {128, 1, 38, 512, 36, 20, 16, CLEAR_MASK_DISC, 0, 1, false},
+        {128, 1, 24, 77, 48, 85, 16, CLEAR_MASK_DISC, 0, 3, false},   {64, 1, 13, 300, 96, 96, 32, CLEAR_MASK_DISC, 0, 10, false},
+        {64, 1, 38, 333, 64, 64, 16, CLEAR_MASK_SWIN, 8, 2, true},    {128, 1, 24, 512, 43, 80, 8, CLEAR_MASK_SWIN, 4, 2, true},
+        {64, 1, 24, 512, 43, 80, 8, CLEAR_MASK_SQUARE, 0, 2, true},   {128, 1, 24, 512, 43, 80, 8, CLEAR_MASK_SQUARE, 0, 3, false},
+        {64, 1, 24, 333, 32, 32, 3, CLEAR_MASK_STRIDED, 1, 1, true},  {128, 1, 24, 333, 43, 80, 4, CLEAR_MASK_STRIDED, 5, 2, false},
+        // test_backward_small_passes
+        {128, 1, 1, 1, 64, 33, 4, CLEAR_MASK_DISC, 0, 4, false},      {128, 1, 5, 33, 80, 131, 4, CLEAR_MASK_DISC, 0, 15, false},
+        {128, 2, 3, 19, 100, 83, 4, CLEAR_MASK_DISC, 0, 15, false},
+    };
+    for (const auto& c : cases) {
+        clear_attn_ctx* ctx = nullptr;
+        EXPECT(clear_attn_create_masked(&ctx, c.n_text, c.gh, c.gw, c.d, c.r, CLEAR_BF16, c.kind, c.shift) == CLEAR_OK);
+        const size_t bytes = (size_t)(c.n_text + c.gh * c.gw) * c.d * 2 * c.B * c.H;
+        auto at = [&](int i) { return (void*)(uintptr_t)((i + 1) * ((bytes + 4095) & ~(size_t)4095)); };  // (never read: the launchers are stand-ins)
+        EXPECT(clear_attn_backward(ctx, at(0), at(1), at(2), at(3), at(4), (const float*)at(8), at(5), at(6), at(7), c.B, c.H, c.n_text, c.gh, c.gw, c.d, c.r, nullptr) == CLEAR_OK);
+        EXPECT(fake::backward.n_splits == c.n_splits && fake::backward.text_first == c.text_first);
+        clear_attn_destroy(ctx);
+    }
+}
+
 int main()
 {
     schedules();
@@ -327,6 +357,7 @@ int main()
     wave_descriptors();
     failures += check_block_programs();
     launch_shapes();
+    backward_orders();
     bands_and_argument_checks();
     contexts();
     tile_orders();

@@ -69,9 +69,9 @@ def test_backward_batch_of_two():
 
 
 @pytest.mark.parametrize("B,H,n_text,gridH,gridW", [
-    (1, 1, 1, 64, 33),     # one text row
-    (1, 5, 33, 80, 131),   # several ranges, no multiple of four; rows no multiple of a workgroup's
-    (2, 3, 19, 100, 83),   # several ranges; a thread's four heads belong to two batch entries
+    (1, 1, 1, 64, 33),     # one text row, 4 ranges of columns (tests/host_sanitize/driver.cpp checks the numbers of ranges)
+    (1, 5, 33, 80, 131),   # 15 ranges (three times four at a time and three more); rows no multiple of a workgroup's
+    (2, 3, 19, 100, 83),   # 15 ranges; a thread's four heads belong to two batch entries
 ])
 def test_backward_small_passes(B, H, n_text, gridH, gridW):
     """The passes beside the matrix kernels, at sizes around their groups: delta (4 heads of 16 tokens a workgroup) and
@@ -90,25 +90,32 @@ def test_backward_small_passes(B, H, n_text, gridH, gridW):
         check_grad("dV", dV[b, h].float().cpu().numpy()[cols], rV)
 
 
-@pytest.mark.parametrize("d,H,n_text,gridH,gridW,r", [
-    (128, 24, 333, 96, 96, 8),   # the one launch with its text rows first, several ranges of columns
-    (128, 24, 441, 43, 80, 16),  # the same, one range (stored without partial sums); cut tiles
-    (64, 38, 333, 64, 64, 16),   # the same
-    (128, 38, 512, 36, 20, 16),  # image rows first, one range
-    (128, 24, 77, 48, 85, 16),   # image rows first, several ranges; cut tiles
-    (64, 13, 300, 96, 96, 32),
+@pytest.mark.parametrize("d,H,n_text,gridH,gridW,r,kind,shift", [
+    # (tests/host_sanitize/driver.cpp checks that each case takes the launch shape named here)
+    (128, 24, 333, 96, 96, 8, orc.MASK_DISC, 0),    # the one launch with its text rows first, several ranges of columns
+    (128, 24, 441, 43, 80, 16, orc.MASK_DISC, 0),   # the same, one range (stored without partial sums); cut tiles
+    (64, 38, 333, 64, 64, 16, orc.MASK_DISC, 0),    # the same
+    (128, 38, 512, 36, 20, 16, orc.MASK_DISC, 0),   # image rows first, one range
+    (128, 24, 77, 48, 85, 16, orc.MASK_DISC, 0),    # image rows first, several ranges; cut tiles
+    (64, 13, 300, 96, 96, 32, orc.MASK_DISC, 0),
+    (64, 38, 333, 64, 64, 16, orc.MASK_SWIN, 8),    # the kernels of the other masks, text rows first, several ranges
+    (128, 24, 512, 43, 80, 8, orc.MASK_SWIN, 4),
+    (64, 24, 512, 43, 80, 8, orc.MASK_SQUARE, 0),
+    (128, 24, 512, 43, 80, 8, orc.MASK_SQUARE, 0),  # image rows first, several ranges
+    (64, 24, 333, 32, 32, 3, orc.MASK_STRIDED, 1),  # text rows first, one range; classes of unequal size
+    (128, 24, 333, 43, 80, 4, orc.MASK_STRIDED, 5), # image rows first, several ranges
 ])
-def test_backward_orders_of_the_one_launch(d, H, n_text, gridH, gridW, r):
+def test_backward_orders_of_the_one_launch(d, H, n_text, gridH, gridW, r, kind, shift, monkeypatch):
     """Either order of the four kinds of workgroups (choose_backward_shape): every row of every head is written, and the
     first and last head are right in rows and columns of all kinds."""
     Q, K, V = make_qkv_shape(1, H, n_text, gridH, gridW, d, "bf16", seed=91, device="cuda:0")
     dO = torch.randn(Q.shape, generator=torch.Generator(device="cuda:0").manual_seed(92), device="cuda:0").to(torch.bfloat16)
-    ctx = ca.ClearAttn(n_text, gridH, gridW, d, r, ca.CLEAR_BF16)
+    ctx = ca.ClearAttn(n_text, gridH, gridW, d, r, ca.CLEAR_BF16, kind, shift)  # (the two sides number the mask kinds alike)
     try:
         O, lse = ctx.forward_lse(Q, K, V)
-        poison = [torch.full_like(Q, float("nan")) for _ in range(3)]
-        del poison  # the allocator hands the same memory to the gradients
-        grads = ctx.backward(Q, K, V, O, dO, lse)
+        with monkeypatch.context() as m:  # the gradients are handed over full of NaN
+            m.setattr(torch, "empty_like", lambda t: torch.full_like(t, float("nan")))
+            grads = ctx.backward(Q, K, V, O, dO, lse)
         torch.cuda.synchronize()
     finally:
         ctx.destroy()
@@ -119,8 +126,10 @@ def test_backward_orders_of_the_one_launch(d, H, n_text, gridH, gridW, r):
     for h in (0, H - 1):
         q, k, v, g = (t[0, h].float().cpu().numpy() for t in (Q, K, V, dO))
         dQ, dK, dV = (t[0, h].float().cpu().numpy()[rows] for t in grads)
-        check_grad("dQ", dQ, orc.backward_dq_rows(q, k, v, g, rows, n_text, gridH, gridW, r))
-        rK, rV = orc.backward_dkv_cols(q, k, v, g, rows, n_text, gridH, gridW, r)
+        with orc.mask_kind(kind, shift):
+            rQ = orc.backward_dq_rows(q, k, v, g, rows, n_text, gridH, gridW, r)
+            rK, rV = orc.backward_dkv_cols(q, k, v, g, rows, n_text, gridH, gridW, r)
+        check_grad("dQ", dQ, rQ)
         check_grad("dK", dK, rK)
         check_grad("dV", dV, rV)
 
