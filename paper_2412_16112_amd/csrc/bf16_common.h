@@ -1,8 +1,7 @@
 // Device-side building blocks shared by the bf16 kernels (forward and backward) for gfx950, head_dim
 // CLEAR_HEAD_DIM (128 unless the including file sets 64):
-// vector types, the LDS layout of a staged 64-token tile and its swizzle, LDS-direct staging loads, MFMA
-// operand reads from a staged tile (row-wise and transposed), the element masks of Eq. 3, and the two
-// 32 x 32 block products every kernel is made of.
+// vector types, LDS-direct staging loads, the element masks of Eq. 3, the LDS layout of a staged 64-token tile and the MFMA
+// operand reads from it (row-wise and transposed).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -33,7 +32,7 @@ constexpr int KS = D / 16;           // contraction steps of Q K^T (16 channels 
 constexpr int NDB = D / 32;          // 32-channel slices of O
 constexpr int CHUNKS = D / 8;        // 16-byte chunks per token row
 constexpr int ROW_BYTES = D * 2;     // one token row of K or V
-constexpr int ROWS_PER_LOAD = 1024 / ROW_BYTES;  // token rows one LDS-direct wave load covers
+constexpr int ROWS_PER_STORE = 1024 / ROW_BYTES;  // token rows a wave stores with 16 bytes per lane
 constexpr int TILE_KEYS = kKeyTileKeys;
 constexpr int TILE_BYTES = TILE_KEYS * ROW_BYTES;  // 16 KB for K, same for V
 // How many matrix instructions ahead the forward block pipeline reads its LDS operands.  At 128 channels the image-query
@@ -161,6 +160,7 @@ struct MaskArgs {
     int hh, qy, qx, gridH, gridW, r2;
     int kind, r, shift;    // MaskKind; for kinds other than the disc: radius / window size and Swin shift
     const_u64_ptr row[2];  // kMaskTable: 16 lane masks per key block (one per score register)
+    bool masked[2];        // kMaskTable: whether they admit less than everything
 };
 
 // Lane masks of a block: 16 words, one per score register, kept in scalar registers from the block's S product to its

@@ -678,10 +678,10 @@ __device__ __forceinline__ void clear_fwd_bf16_workgroup(const FwdParams& p, con
             for (int t = 0; t < 4; ++t) v[t] = (__bf16)(oacc[db][4 * g + t] * inv);
             *(bf16x4*)(wbase + qi * OROW + (32 * db + 8 * g + 4 * hh) * 2) = v;
         }
-    // CHUNKS lanes per row, ROWS_PER_LOAD rows per store instruction
+    // CHUNKS lanes per row, ROWS_PER_STORE rows per store instruction
 #pragma unroll
-    for (int i = 0; i < 32 / ROWS_PER_LOAD; ++i) {
-        const int row = ROWS_PER_LOAD * i + lane / CHUNKS;  // query slot of the patch
+    for (int i = 0; i < 32 / ROWS_PER_STORE; ++i) {
+        const int row = ROWS_PER_STORE * i + lane / CHUNKS;  // query slot of the patch
         const f32x4 chunk = *(const f32x4*)(wbase + row * OROW + (lane % CHUNKS) * 16);
         long long token;
         bool store;

@@ -32,9 +32,6 @@
 #include "block_class.h"
 #include "clear_internal.h"
 
-#ifndef CLEAR_BWD_ISSUE_SHARE
-#define CLEAR_BWD_ISSUE_SHARE 2  // 2: the waves stage whole stages in turns, half of them each time; 1: every wave its share of every stage
-#endif
 #if CLEAR_HEAD_DIM == 64
 // second compilation of this file: its own kernel and launcher names
 #define clear_bwd_bf16_kernel clear_bwd_bf16_d64_kernel
@@ -62,7 +59,7 @@ template <int MODE, bool LINROWS, int CODE>
 __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, const int bid, const int nblk)
 {
     constexpr int NWY = kBf16NWY, NWX = kBf16NWX, NW = NWY * NWX;
-    constexpr int ISSUE_SHARE = CLEAR_BWD_ISSUE_SHARE;  // 2: the waves take turns, half of them staging a whole stage
+    constexpr int STAGERS = NW / 2;  // the waves take turns, half of them staging a whole stage
     constexpr bool COLSTAT = MODE != kBwdQ;  // lse / delta indexed by column
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];  // [NBUF][TPS][C1 tile | C2 tile], then the column statistics
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
@@ -250,8 +247,8 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
     // ---- staging: LDS-direct loads of the two column tiles (same layout and swizzle as K and V in the
     // forward kernel), and for dK / dV neg_lse and neg_delta of the tile's 64 queries (wave j of the first TPS waves
     // for tile j of the stage)
-    // A staging wave takes 16 rows of both tiles, all their planes: one token address per tile (half of the rows in turn if the waves do not share).
-    static_assert(NW / ISSUE_SHARE == TILE_KEYS / 16, "the waves that stage a tile cover its rows");
+    // A staging wave takes 16 rows of both tiles, all their planes: one token address per tile.
+    static_assert(STAGERS == TILE_KEYS / 16, "the waves that stage a tile cover its rows");
     auto issue_tile = [&](int i, unsigned lds_tile) {
         int a, b;
         tile_origin(i, a, b);
@@ -259,7 +256,7 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
         // since the kernel's start get spilled in the fused dK / dV kernel, and their reload from scratch memory would
         // wait for every load issued before it, the staged tile in front included.
         const int ln = fresh_lane_id();
-        const int part = wave % (NW / ISSUE_SHARE), row = 16 * part + (ln >> 2);
+        const int part = wave % STAGERS, row = 16 * part + (ln >> 2);
         const unsigned token = (unsigned)slot_token(a, b, row);
         const unsigned chunk_off = (unsigned)(((ln & 3) ^ plane_swz(row)) << 4);
         const unsigned o1 = token * c1_pitch + chunk_off, o2 = token * c2_pitch + chunk_off;
@@ -275,7 +272,7 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
     int issue_turn = 0;
     auto issue_stage = [&](int t, int buf) {
         const int len = stage_len(t);
-        const bool mine = ISSUE_SHARE == 1 || (wave / (NW / ISSUE_SHARE)) == (issue_turn & (ISSUE_SHARE - 1));
+        const bool mine = wave / STAGERS == (issue_turn & 1);
         ++issue_turn;
 #pragma unroll
         for (int j = 0; j < TPS; ++j)
@@ -320,7 +317,6 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
     struct Block {
         unsigned kb[2], vb[2];   // operand addresses of its tile pair
         const float* stats;      // of its tile
-        bool masked;             // kMaskTable: whether the lane masks admit less than everything
         MaskArgs ma;
     };
 
@@ -383,7 +379,7 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
         auto run_slot = [&](auto slot_tag) __attribute__((always_inline)) {
             constexpr int slot = decltype(slot_tag)::value;
             if (slot + PD < NSLOT) op[(slot + PD) % RING] = operand(slot + PD);
-            if (MASK == kMaskTable && slot == 0 && b.masked) {
+            if (MASK == kMaskTable && slot == 0 && b.ma.masked[blk]) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) mw.w[r] = b.ma.row[blk][r];
             }
@@ -406,7 +402,7 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
             constexpr int WAIT = KS == 8 ? 2 : 1;
             if (slot == S_END + WAIT) {
                 if (MASK == kMaskTable) {
-                    if (b.masked) mask_scores(sc, mw);
+                    if (b.ma.masked[blk]) mask_scores(sc, mw);
                 } else {
                     apply_mask<MASK, CODE>(sc, blk, b.ma);
                 }
@@ -434,7 +430,7 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
     };
     const const_int_ptr wave_desc = (const_int_ptr)p.wave_desc;
     // Runs the reachable blocks of one staged tile.
-    auto run_blocks = [&](auto mask_tag, bool run0, bool run1, const MaskArgs& ma, bool masked0, bool masked1, int buf, int j) __attribute__((always_inline)) {
+    auto run_blocks = [&](auto mask_tag, bool run0, bool run1, const MaskArgs& ma, int buf, int j) __attribute__((always_inline)) {
         Block b;
         const unsigned tile_at = lds_base + (unsigned)buf * STAGE_BYTES + (unsigned)j * (2 * TILE_BYTES);
         unsigned kv = kv_lane;
@@ -445,9 +441,7 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
         b.vb[1] = b.vb[0] ^ V_LANE_ODD;
         b.stats = stats + ((buf * TPS + j) * 2) * TILE_KEYS;
         b.ma = ma;
-        b.masked = masked0;
         if (run0) do_block(mask_tag, std::integral_constant<int, 0>{}, b);
-        b.masked = masked1;
         if (run1) do_block(mask_tag, std::integral_constant<int, 1>{}, b);
     };
     auto run_tile = [&](auto mask_tag, int t, int buf, int j) __attribute__((always_inline)) {
@@ -461,7 +455,9 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
             MaskArgs ma;
             ma.row[0] = mask_tbl + 16 * i0;
             ma.row[1] = mask_tbl + 16 * i1;
-            run_blocks(mask_tag, i0 != zeros, i1 != zeros, ma, i0 != zeros - 1, i1 != zeros - 1, buf, j);
+            ma.masked[0] = i0 != zeros - 1;  // (the entry in front of the all-zeros one is all ones)
+            ma.masked[1] = i1 != zeros - 1;
+            run_blocks(mask_tag, i0 != zeros, i1 != zeros, ma, buf, j);
             return;
         }
         int ta, tb;
@@ -491,17 +487,7 @@ __device__ __forceinline__ void clear_bwd_bf16_workgroup(const BwdParams& p, con
         ma.b = linear ? lin_limit : tb;
         ma.qy = tile_row.ry; ma.qx = tile_row.rx; ma.gridH = cH; ma.gridW = cW; ma.r2 = p.r2;
         ma.kind = p.mask_kind; ma.r = p.mask_r; ma.shift = p.mask_shift;
-        ma.row[0] = ma.row[1] = mask_tbl;
-        if (!LINROWS && !linear && p.mask_tbl) {
-            const int ncol = 2 * p.mask_rx + 1;
-            const int ones = (2 * p.mask_ry + 1) * ncol, zeros = ones + 1;
-            const int dbx = (tb - wx0) >> 3, dby = (ta - wy0) >> 2;
-            const int i0 = (cls0 == kBlockPartial) ? (dby + p.mask_ry) * ncol + dbx + p.mask_rx : (cls0 == kBlockFull ? ones : zeros);
-            const int i1 = (cls1 == kBlockPartial) ? (dby + 1 + p.mask_ry) * ncol + dbx + p.mask_rx : (cls1 == kBlockFull ? ones : zeros);
-            ma.row[0] = mask_tbl + 16 * i0;
-            ma.row[1] = mask_tbl + 16 * i1;
-        }
-        run_blocks(mask_tag, cls0 != kBlockSkip, cls1 != kBlockSkip, ma, true, true, buf, j);
+        run_blocks(mask_tag, cls0 != kBlockSkip, cls1 != kBlockSkip, ma, buf, j);
     };
     auto run_category = [&](auto mask_tag, int& t, int end, int& buf) __attribute__((always_inline)) {
         for (; t < end; t += TPS, buf ^= 1) {
