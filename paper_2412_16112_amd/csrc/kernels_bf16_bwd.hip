@@ -25,7 +25,7 @@
 // 256 bytes took an XOR per operand), lse and delta go in as the initial accumulators of S and dP (16 subtractions of delta less; lse was the
 // addend of a multiply-add that is a multiplication now), blocks that are admitted whole take no mask, and P and dS are formed under the matrix
 // instructions of the products between.
-// 24 heads of 128 channels, 512 text tokens, 64 x 64 grid, r = 16, forward and backward, one box: 557 -> 518 us; 128 x 128, 333 text tokens:
+// 24 heads of 128 channels, 512 text tokens, 64 x 64 grid, r = 16, forward and backward, on one card: 557 -> 518 us; 128 x 128, 333 text tokens:
 // 1 991 -> 1 858 us; 38 heads of 64 channels, 64 x 64: 489 -> 455 us.
 // (S rounds at the size of lse from its first product on, where it used to grow to it.  Error of P from its exponent, emulated in fp32 at 128 channels:
 // 3.1e-7 -> 6.2e-7 of itself for logits of deviation 1, 4.9e-7 -> 5.1e-7 for 2, 2.7e-6 -> 2.1e-6 for 12; P's rounding to bf16 is 1.7e-3, and the error of dQ, dK and

@@ -199,7 +199,7 @@ static double finish_time(int num_cus, const double (&n)[4], const double (&cost
 // a quarter of the evenly spread work is not considered: the mean misses how such workgroups outlast the others (24 heads, 128 x 128, 333 text tokens: one
 // range 1 433 us, four 1 360).
 // (Fitted to 16 calls at 128 channels and 10 at 64, 1 to 8 ranges in both orders.  Training steps against image rows first with choose_text_splits and a
-// reduction always, forward included, one box: 24 heads of 128 channels, 512 text tokens, 64 x 64, r = 16 518 -> 500 us, 32 x 32, r = 8 151 -> 141; 43 x 80, 441 text
+// reduction always, forward included, on one card: 24 heads of 128 channels, 512 text tokens, 64 x 64, r = 16 518 -> 500 us, 32 x 32, r = 8 151 -> 141; 43 x 80, 441 text
 // tokens 468 -> 440; 48 x 85, 77 text tokens 369 -> 365; 128 x 128, 333 text tokens 1 865 -> 1 873, its runs 0.8 % apart; 38 heads, 36 x 20 214 -> 204; 38 heads of 64,
 // 333 text tokens, 64 x 64 455 -> 442; 4 x 28 heads of 64, 104 x 72, r = 8 1 869 -> 1 815.)
 // Beyond 16 image workgroups per CU the evenness takes care of itself: image rows first, and choose_text_splits.
